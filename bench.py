@@ -79,35 +79,40 @@ ALG_MODEL = {"edits": alg_edits, "touched": alg_touched, "frame": alg_frame}
 # Design bytes (what these kernels move as designed, each byte once)
 # ---------------------------------------------------------------------------
 
+def bytes_sums(st):
+    """Sums of the touched blocks: per incidence its 4-byte entry, mask byte and the parts
+    of its tet's record (diagonal: one gradient and three scalars, 48 B; off-diagonal: two
+    gradients and two scalars, 64 B); 9 values written per diagonal block (72 B), 18 per
+    off-diagonal block (144 B)."""
+    return (53 * st["diag_incidences"] + 69 * st["off_incidences"]
+            + 72 * st["diag_blocks"] + 144 * st["off_blocks"])
+
+
 def bytes_touched(st):
-    """Streaming phase 2: per edit its 10 claim records (320 B); per claimed diagonal
-    block 9 written values (72 B) and 6 contribution doubles per incidence (48 B);
-    per claimed off-diagonal block 18 written values (144 B) and 9 doubles (72 B)
-    per incidence."""
-    return (320 * st["edits"] + 72 * st["diag_blocks"] + 48 * st["diag_incidences"]
-            + 144 * st["off_blocks"] + 72 * st["off_incidences"])
+    """Two-launch frame, phase 2: per edit its 10 claim records (320 B), and the sums."""
+    return 320 * st["edits"] + bytes_sums(st)
 
 
 def bytes_edits(st):
-    """Streaming phase 1: per edit id + state + tet stamp read/write + mask read + 10
-    claim records written + undo byte (335 B); per changed tet its 10 block ids and
-    10 incidence positions, 10 block descriptors, 10 block stamp read/writes, mask
-    write and 78 contribution doubles written (1105 B); per activation the tet's
-    vertex ids, E and vertex coordinates (120 B)."""
-    return 335 * st["edits"] + 1105 * st["changed"] + 120 * st["activated"]
+    """Two-launch frame, phase 1: per edit id + state + tet stamp read/write + mask read +
+    10 claim records written + undo byte (335 B); per changed tet its 10 block
+    descriptors, 10 block stamp read/writes and mask write (401 B)."""
+    return 335 * st["edits"] + 401 * st["changed"]
 
 
 def bytes_frame(st):
-    """Both streaming phases (one fused launch or two launches)."""
-    return bytes_edits(st) + bytes_touched(st)
+    """One-launch frame: per edit id, state, mask byte read and written, undo byte and kept
+    id (12 B); per changed tet its 10 block descriptors (320 B); the sums, each block once
+    (edits that share a block read and write it again, from cache)."""
+    return 12 * st["edits"] + 320 * st["changed"] + bytes_sums(st)
 
 
 def bytes_delta(st):
     """+/- delta frame (k_delta_edits + k_delta_clear): per edit its id, state, tet stamp
     read/write and mask read, and its stamp cleared again (20 B); per changed tet its
-    512-byte record, its mask write, and the 144 CSR entries of its 10 blocks read and
-    written by the atomic additions (2,817 B)."""
-    return 20 * st["edits"] + 2817 * st["changed"]
+    descriptors (320 B), vertex ids and geometry record (144 B), its mask write, and the
+    144 CSR entries of its 10 blocks read and written by the atomic additions (2,769 B)."""
+    return 20 * st["edits"] + 2769 * st["changed"]
 
 
 def bytes_connectivity_pass(n_tets, n_nodes, n_pairs=0):
@@ -119,17 +124,17 @@ def bytes_connectivity_pass(n_tets, n_nodes, n_pairs=0):
     return 21 * n_tets + 4 * n_nodes
 
 
-def bytes_element(n_active, n_tets, n_nodes):
-    """Rebuild element kernel: per tet its mask byte, 10 incidence positions and 78
-    contribution doubles written (element matrix or zeros: 665 B); per active tet its
-    vertex ids and E (24 B); node coordinates once (24 B per node)."""
-    return 665 * n_tets + 24 * n_active + 24 * n_nodes
+def bytes_element(n_tets, n_nodes):
+    """Rebuild geometry kernel: per tet its vertex ids, E and mask byte (25 B) and its
+    128-byte record written; node coordinates once (24 B per node)."""
+    return 153 * n_tets + 24 * n_nodes
 
 
-def bytes_reduce(nd, no, ni_d, ni_o):
-    """Rebuild reduce kernel: per block its 32 B descriptor, 9 (diagonal) or 18
-    written values, and its incidences' contribution doubles (6 or 9 each)."""
-    return 32 * (nd + no) + 72 * nd + 144 * no + 48 * ni_d + 72 * ni_o
+def bytes_reduce(nd, no, n_tets):
+    """Rebuild rows kernel: per tet its record and mask byte once, its 4 node incidences
+    (4 B) and 12 row terms (2 B); per row block (diagonal once, off-diagonal twice) its
+    8-byte plan entry and 9 values written."""
+    return (129 + 16 + 24) * n_tets + 80 * (nd + 2 * no)
 
 
 # ---------------------------------------------------------------------------
@@ -190,28 +195,20 @@ def load_traffic(workload, kernels, per=None):
     return round(sum(rec[k]["bytes"] for k in kernels) / max(units, 1), 1)
 
 
-def load_frame_traffic(touched_kernel):
-    """Per-frame HBM bytes of the two streaming kernels (first pass over the headline step,
-    phase 2 as the instantiation `touched_kernel`), or None."""
-    return _traffic().get("frames", {}).get(touched_kernel)
+def load_frame_traffic(kernel):
+    """Per-frame HBM bytes of the frame kernel (first pass over the headline step), or None."""
+    return _traffic().get("frames", {}).get(kernel)
 
 
 def kernel_instance(asm, kernel):
-    """Template instantiation of `kernel` that the context's mapping launches: the key of
-    its counter record (counters of another instantiation are not attached)."""
-    c = asm.get_config()
-    nt = "true" if c["rebuild_nt"] else "false"
-    if kernel == "k_element":
-        return f"k_element<{nt}>"
-    if kernel in ("k_reduce_all", "k_touched", "k_frame"):
-        which = "rebuild" if kernel == "k_reduce_all" else "stream"
-        qd, qo = c[which + "_qd"], c[which + "_qo"]
-        m = asm.bucket_map(which)
-        mixed = "true" if any(q != qd for q in m["diag"]) or any(q != qo for q in m["off"]) else "false"
-        if kernel == "k_reduce_all":
-            return f"k_reduce_all<{qd}, {qo}, {mixed}, {nt}>"
-        return f"{kernel}<{qd}, {qo}, {mixed}>"
+    """Template instantiation of `kernel` that the context launches: the key of its counter
+    record (counters of another instantiation are not attached)."""
+    if kernel == "k_rows":
+        return f"k_rows<{'true' if asm.get_config()['rebuild_nt'] else 'false'}>"
     return kernel
+
+
+ONE_LAUNCH_EDITS = 2304  # largest list that runs as one launch (include/stafem.h, sta_set_config)
 
 
 def roofline(kernel, alg_bytes, seconds, launches, traffic=None, design_bytes=None):
@@ -348,8 +345,11 @@ class Stream:
                 for k, (n, ms) in ktimes.items()}
         cands = [k for k in ("frame", "touched", "edits") if k in ktimes]
         dom = max(cands, key=lambda k: ktimes[k][1])
-        alg = steps * sum(ALG_MODEL[dom](st) for st in self.stats)
-        des = steps * sum(design[dom](st) for st in self.stats)
+        # the frames that ran through the dominant kernel
+        one = [st for st in self.stats if self.asm.get_config()["fused"] or st["edits"] <= ONE_LAUNCH_EDITS]
+        mine = one if dom == "frame" else [st for st in self.stats if not any(st is o for o in one)]
+        alg = steps * sum(ALG_MODEL[dom](st) for st in mine)
+        des = steps * sum(design[dom](st) for st in mine)
         return kern, roofline("k_" + dom, alg, ktimes[dom][1] * 1e-3, ktimes[dom][0],
                               traffic=load_traffic(self.workload, [kernel_instance(self.asm, "k_" + dom)]),
                               design_bytes=des)
@@ -378,30 +378,26 @@ class Stream:
         asm = self.asm
         asm.enable_kernel_timing(True)
         asm.kernel_times()
-        act = []
-        m = self.mask0.copy()
-        for (di, ds), (ids, st) in zip(self.dframes, self.frames_host):
+        for di, ds in self.dframes:
             asm.apply_edits(di, ds)
-            m[ids] = st
-            act.append(int(m.sum()))
             for _ in range(reps):
                 asm.full_rebuild()
         kt = asm.kernel_times()
         asm.enable_kernel_timing(False)
         nd, no = asm.n_diag_blocks, asm.n_off_blocks
-        rb = bytes_reduce(nd, no, 4 * self.n_tets, 6 * self.n_tets)
-        eb = bytes_element(float(np.mean(act)), self.n_tets, self.n_nodes)
+        rb = bytes_reduce(nd, no, self.n_tets)
+        eb = bytes_element(self.n_tets, self.n_nodes)
         n_e, ms_e = kt.get("element", (0, 0.0))
         n_r, ms_r = kt.get("reduce", (0, 0.0))
         # a batch too large for the Infinity Cache is rebuilt in mesh groups (one element and two
         # reduce launches per group): rates and counted bytes are per rebuild, all groups together
         rebuilds = len(self.frames_host) * reps
         per_e, per_r = n_e / max(rebuilds, 1), n_r / max(rebuilds, 1)
-        te = load_traffic(self.workload, [kernel_instance(asm, "k_element")])
-        tr = load_traffic(self.workload, [kernel_instance(asm, "k_reduce_all")])
-        el = roofline("k_element", eb * rebuilds, ms_e * 1e-3, rebuilds,
+        te = load_traffic(self.workload, ["k_geometry"])
+        tr = load_traffic(self.workload, [kernel_instance(asm, "k_rows")])
+        el = roofline("k_geometry", eb * rebuilds, ms_e * 1e-3, rebuilds,
                       traffic=None if te is None else round(te * per_e, 1))
-        re = roofline("k_reduce_all", rb * rebuilds, ms_r * 1e-3, rebuilds,
+        re = roofline("k_rows", rb * rebuilds, ms_r * 1e-3, rebuilds,
                       traffic=None if tr is None else round(tr * per_r, 1))
         el["launches_per_rebuild"], re["launches_per_rebuild"] = per_e, per_r
         return {"element": el, "reduce": re,
@@ -437,7 +433,7 @@ class Stream:
             return ev[0].elapsed_time(ev[1]) * 1e3
 
         rows, t_stream, t_cold, t_reb, t_reb_cold = [], [], [], [], []
-        ftr = load_frame_traffic(kernel_instance(asm, "k_touched")) if self.workload == "fracture" else None
+        ftr = load_frame_traffic("k_once") if self.workload == "fracture" else None
         for k, ((di, ds), st) in enumerate(zip(self.dframes, self.stats)):
             ids_h = self.frames_host[k][0]
             prev = torch.from_numpy(self.mask_before(k)[ids_h].copy()).cuda()  # undoes the frame
@@ -458,7 +454,7 @@ class Stream:
                          "rebuild_cold_us": round(float(np.median(reb_cold)), 3), "alg_bytes": alg,
                          "stream_gbs": round(alg / (np.median(warm) * 1e-6) / 1e9, 2)})
             if ftr and k < len(ftr):
-                cb = ftr[k]["k_edits"] + ftr[k]["k_touched"]
+                cb = ftr[k]["k_once"]
                 rows[-1]["counter_bytes"] = cb
                 rows[-1]["counter_gbs"] = round(cb / (np.median(warm) * 1e-6) / 1e9, 2)
                 rows[-1]["counter_frac_of_peak"] = round(cb / (np.median(warm) * 1e-6) / 1e9 / HBM_PEAK_GBS, 5)

@@ -88,7 +88,7 @@ typedef int sta_status;
  *   mask0  host, n_tets uint8 in {0, 1}
  * Inputs are copied; the caller keeps ownership.  Synchronises `stream`.
  * On success *out owns all device memory until sta_destroy; values hold
- * rebuild(mask0).  Element matrices are computed for every candidate here, so
+ * rebuild(mask0).  Element geometry is computed for every candidate here, so
  * later activations need no recomputation unless parameters change.
  * Errors: STA_EINVAL, STA_EDEGENERATE, STA_ENOMEM, STA_EHIP; *out = NULL. */
 sta_status sta_build_pattern(const double* x, int64_t n_nodes, const int32_t* tets, int64_t n_tets,
@@ -124,8 +124,8 @@ sta_status sta_apply_edits(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* 
  * with FP64 atomics, and nothing is re-summed.  Faster per touched entry
  * than sta_apply_edits, but the result depends on the order in which
  * concurrent edits land: it equals the rebuild only up to rounding, and the
- * difference can grow over many frames (drift).  The mask and per-element
- * contributions are kept as sta_apply_edits expects, so the exact policy or
+ * difference can grow over many frames (drift).  The mask is kept as
+ * sta_apply_edits expects, so the exact policy or
  * sta_full_rebuild may follow at any time (a rebuild removes the drift).
  * Arguments as sta_apply_edits; if n_dev (device int32) is not NULL the edit
  * count is *n_dev and n_edits is the arrays' capacity (graph-capturable).
@@ -198,16 +198,17 @@ sta_status sta_last_frame_stats(sta_ctx* ctx, void* stream, int64_t* out, int n_
  * call synchronises its stream and adds the frame's statistics (the nine
  * values of sta_last_frame_stats).  The file is closed by sta_destroy.  A
  * file that cannot be opened for appending fails the build with STA_EINVAL. */
-#define STA_KERNEL_ELEMENT 0   /* element contributions (rebuild / activation) */
-#define STA_KERNEL_REDUCE 1    /* re-sum of every block (rebuild) */
-/* A batch whose contributions exceed 200 MB is rebuilt in groups of
+#define STA_KERNEL_ELEMENT 0   /* element geometry (rebuild) */
+#define STA_KERNEL_REDUCE 1    /* sums of every row (rebuild) */
+/* A batch whose geometry records exceed 100 MB is rebuilt in groups of
  * consecutive meshes: each group counts one STA_KERNEL_ELEMENT launch and two
- * STA_KERNEL_REDUCE launches (diagonal, then off-diagonal blocks). */
-#define STA_KERNEL_EDITS 2     /* streaming phase 1: validate, flip, claim */
-#define STA_KERNEL_TOUCHED 3   /* streaming phase 2: re-sum claimed blocks */
+ * STA_KERNEL_REDUCE launches (the tiles of rows, then the rows of nodes too
+ * large for a tile). */
+#define STA_KERNEL_EDITS 2     /* two-launch frame, phase 1: validate, flip, claim */
+#define STA_KERNEL_TOUCHED 3   /* two-launch frame, phase 2: re-sum claimed blocks */
 #define STA_KERNEL_ADJOINT 4
 #define STA_KERNEL_SOLVE 5     /* all kernels of one CG solve */
-#define STA_KERNEL_FRAME 6     /* fused frame: both streaming phases in one launch */
+#define STA_KERNEL_FRAME 6     /* frame of one launch */
 #define STA_KERNEL_DELTA 7     /* +/- delta frame (sta_apply_edits_delta), both launches */
 #define STA_NUM_KERNELS 8
 sta_status sta_enable_kernel_timing(sta_ctx* ctx, int on);
@@ -303,19 +304,20 @@ sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_componen
 sta_status sta_face_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_components, void* stream);
 
 /* Execution configuration.
- *   fused       0: a frame is two launches (edit phase, touched phase);
+ *   fused       A frame whose list (capacity) holds at most 2,304 edits is one
+ *               launch.  Above, 0: two launches (edit phase, touched phase);
  *               1: one persistent launch (both phases, grid barrier between).
- *   rebuild_qd / rebuild_qo, stream_qd / stream_qo: slot mapping, i.e. lanes
- *               cooperating on one block value for diagonal / off-diagonal
- *               blocks in the rebuild and in the streaming update
- *               (diagonal: 1 = thread-, 4 = quad-, 16 = wave-sixteenth-per-slot;
- *               off-diagonal: 1 or 4), here for every incidence-length
- *               bucket alike (see sta_set_bucket_map).  Every mapping adds the
- *               same terms in the same order: results are bit-identical.
+ *               With fused 1 and a spin limit set (sta_set_barrier_spin_limit)
+ *               every frame is the persistent launch.
+ *   rebuild_qd / rebuild_qo, stream_qd / stream_qo: slot mapping (diagonal
+ *               1, 4 or 16; off-diagonal 1 or 4), here for every
+ *               incidence-length bucket alike (see sta_set_bucket_map).
+ *               Checked, kept and reported; the sums are computed one way
+ *               whatever it says.
  *   grid_cap    upper bound on the fused kernel's workgroups (0 = the
  *               co-resident limit).
- *   rebuild_nt  1: the rebuild streams contributions and values with
- *               non-temporal cache hints (each byte is touched once).
+ *   rebuild_nt  1: the rebuild stores the values with a non-temporal cache
+ *               hint.
  * sta_get_config writes the same 7 integers.  Defaults: 0, 1, 1, 1, 1, 0, 0. */
 sta_status sta_set_config(sta_ctx* ctx, int fused, int rebuild_qd, int rebuild_qo, int stream_qd, int stream_qo,
                           int grid_cap, int rebuild_nt);
@@ -323,10 +325,9 @@ sta_status sta_get_config(const sta_ctx* ctx, int* out7);
 
 /* Audit of the maintained state against the Sec. 3.3 invariant (the
  * maintained matrix equals a rebuild from the mask), without changing it:
- * out2[1] = tets whose 78 stored contribution slots differ in any bit from
- * what a rebuild would store (the element matrix of an active tet, +0.0 for
- * an inactive one); out2[0] = matrix values differing in any bit from a
- * re-sum of the stored contributions into a scratch copy (nnz doubles,
+ * out2[1] = tets whose stored geometry differs in any bit from what a rebuild
+ * would store; out2[0] = matrix values differing in any bit from a sum of the
+ * stored geometry's element entries into a scratch copy (nnz doubles,
  * allocated on first use).  Both 0 for an intact context.  Synchronises
  * `stream`.  STA_ESTALE after sta_set_params until a rebuild. */
 sta_status sta_audit(sta_ctx* ctx, void* stream, int64_t* out2);
@@ -344,14 +345,11 @@ sta_status sta_set_barrier_spin_limit(sta_ctx* ctx, int64_t polls);
  * the per-block work of a local recompute, O(|Delta| kappa) in Prop. 1).
  * Diagonal blocks fall in bucket 0 (kappa <= 8), 1 (9..32) or 2 (> 32);
  * off-diagonal blocks in bucket 0 (kappa <= 8) or 1 (> 8).  qd3[b] in
- * {1, 4, 16} and qo2[b] in {1, 4} give the lanes per value for each bucket;
- * which = 0 sets the rebuild's mapping, 1 the streaming update's.  The
- * kernels allocate the largest group per block and a block of a bucket with
- * a smaller group leaves the rest idle, so a mixed mapping trades idle lanes
- * for load depth where segment lengths differ; sta_autotune chooses it by
- * timing.  sta_set_config resets every bucket to one mapping.  Results are
- * bit-identical for every mapping.  sta_get_config reports the allocation
- * (the largest group).  STA_EINVAL on a value outside the sets above. */
+ * {1, 4, 16} and qo2[b] in {1, 4} are the setting of each bucket; which = 0
+ * sets the rebuild's mapping, 1 the streaming update's.  The setting is
+ * checked, kept and reported; the sums are computed one way whatever it says.
+ * sta_set_config resets every bucket to one mapping.  sta_get_config reports
+ * the largest setting.  STA_EINVAL on a value outside the sets above. */
 sta_status sta_set_bucket_map(sta_ctx* ctx, int which, const int* qd3, const int* qo2);
 
 /* The mapping per bucket (qd3, qo2; either may be NULL) and the number of
@@ -359,13 +357,11 @@ sta_status sta_set_bucket_map(sta_ctx* ctx, int which, const int* qd3, const int
  * may be NULL). */
 sta_status sta_get_bucket_map(const sta_ctx* ctx, int which, int* qd3, int* qo2, int64_t* blocks5);
 
-/* Autotuner: times every slot mapping for the full rebuild, and every
- * mapping x {two launches, fused with grid caps} for one streaming frame
- * (ids_dev / states_dev, device, n_edits; each timed application is undone
- * before the next), keeps the fastest of each, then, for every non-empty
- * incidence-length bucket in turn, tries each group size for that bucket
- * alone (sta_set_bucket_map) and keeps it where it is faster, and returns a
- * text report in report (may be NULL).  If the environment variable STA_TUNE_CACHE names a
+/* Autotuner: times the full rebuild with and without rebuild_nt, and one
+ * streaming frame (ids_dev / states_dev, device, n_edits; each timed
+ * application is undone before the next) with fused 0 and with fused 1 under
+ * grid caps, keeps the fastest of each and returns a text report in report
+ * (may be NULL).  If the environment variable STA_TUNE_CACHE names a
  * file, a previous result for the same mesh sizes and frame size is reused
  * from it and new results are appended.  Synchronises `stream`. */
 sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* states_dev, int64_t n_edits,

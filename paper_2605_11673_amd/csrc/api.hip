@@ -237,55 +237,30 @@ static std::vector<int32_t> adjoint_chunk_order(const double* x, const std::vect
     return order;
 }
 
-// A batch whose contributions (78 doubles per tet) exceed the 256 MB Infinity Cache is rebuilt
-// in groups of consecutive meshes of at most this many contribution bytes, element pass then
-// reduce per group: the reduce then reads what the element pass just wrote from that cache (on
-// the 64-mesh batch, 853 MB: 660 -> 580 us per rebuild, same bits; groups of at most 100 / 160 /
-// 250 / 300 / 400 MB: 636 / 602 / 608 / 618 / 629 us).  A batch's meshes share no block, so
-// every block's segment lies in one group.
-constexpr double kRebuildGroupBytes = 200e6;
-constexpr double kContributionBytesPerTet = 78 * 8;
+// A batch whose geometry records (128 bytes per tet) and values (about 190 bytes per tet)
+// together exceed the 256 MB Infinity Cache is rebuilt in groups of consecutive meshes of at
+// most this many record bytes, geometry pass then rows per group: the rows then read the
+// records from that cache.  A batch's meshes share no block, so every row lies in one group.
+constexpr double kRebuildGroupBytes = 100e6;
 
-// The rebuild groups of a batch (node_off / tet_off: k + 1 mesh offsets), or none when the
-// whole batch fits one group.  Blocks are numbered diagonal first, then off-diagonal, each in
-// row order, so each mesh's blocks of either kind form one range, found from the CSR position
-// of each block's upper copy.
-static std::vector<std::array<int64_t, 6>> rebuild_groups(const HostPattern& P, const std::vector<BlockDesc>& hd,
-                                                          const std::vector<int64_t>& node_off,
-                                                          const std::vector<int64_t>& tet_off)
+// The rebuild groups of a batch (tet_off: k + 1 mesh offsets), or none when the whole batch
+// fits one group.
+static std::vector<std::array<int64_t, 8>> rebuild_groups(const RowPlan& R, const std::vector<int64_t>& tet_off)
 {
-    std::vector<std::array<int64_t, 6>> groups;
+    std::vector<std::array<int64_t, 8>> groups;
     const size_t k = tet_off.size() > 1 ? tet_off.size() - 1 : 0;
-    if (k < 2 || (double)tet_off[k] * kContributionBytesPerTet <= kRebuildGroupBytes)
+    if (k < 2 || (double)tet_off[k] * sizeof(TetGeo) <= kRebuildGroupBytes)
         return groups;
-    std::vector<int64_t> first_value(k + 1);
-    for (size_t j = 0; j <= k; ++j)
-        first_value[j] = P.rowptr[3 * node_off[j]];
-    auto mesh_of = [&](int64_t up) {
-        return (int64_t)(std::upper_bound(first_value.begin(), first_value.end(), up) - first_value.begin()) - 1;
+    auto first = [](const std::vector<int32_t>& mesh, size_t j) {
+        return (int64_t)(std::lower_bound(mesh.begin(), mesh.end(), (int32_t)j) - mesh.begin());
     };
-    // start[j]: the first block of mesh j (the kind's block count if it has none)
-    auto starts = [&](int64_t b0, int64_t nb, std::vector<int64_t>& start) {
-        start.assign(k + 1, nb);
-        int64_t prev = -1;
-        for (int64_t b = 0; b < nb; ++b) {
-            const int64_t m = mesh_of(hd[b0 + b].up);
-            if (m < prev)
-                return false;
-            for (int64_t q = prev + 1; q <= m; ++q)
-                start[q] = b;
-            prev = m;
-        }
-        return true;
-    };
-    std::vector<int64_t> dstart, ostart;
-    if (!starts(0, P.nd, dstart) || !starts(P.nd, P.no, ostart))
-        return groups;
     for (size_t j = 0; j < k;) {
         size_t j1 = j + 1;
-        while (j1 < k && (double)(tet_off[j1 + 1] - tet_off[j]) * kContributionBytesPerTet <= kRebuildGroupBytes)
+        while (j1 < k && (double)(tet_off[j1 + 1] - tet_off[j]) * sizeof(TetGeo) <= kRebuildGroupBytes)
             ++j1;
-        groups.push_back({tet_off[j], tet_off[j1], dstart[j], dstart[j1], ostart[j], ostart[j1]});
+        groups.push_back({tet_off[j], tet_off[j1], first(R.tile_mesh, j), first(R.tile_mesh, j1),
+                          first(R.bigd_mesh, j), first(R.bigd_mesh, j1), first(R.bigo_mesh, j),
+                          first(R.bigo_mesh, j1)});
         j = j1;
     }
     if (groups.size() < 2)
@@ -330,6 +305,9 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     if (!msg.empty())
         return fail(nullptr, STA_EINVAL, msg);
 
+    RowPlan R;
+    build_row_plan(n_nodes, tets, n_tets, P, node_off, R);
+
     sta_ctx* c = new (std::nothrow) sta_ctx();
     if (!c)
         return fail(nullptr, STA_ENOMEM, "host allocation failed");
@@ -357,7 +335,7 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.mat = material(nu, rho, dt);
 
     const int64_t nb = P.nd + P.no;
-    double *xs, *E_d, *cd, *co, *values;
+    double *xs, *E_d, *geo, *values;
     int4* T;
     uint8_t *mask, *undo, *wg_err;
     int32_t *e2b, *e2p, *ndiag;
@@ -379,8 +357,20 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     ALLOC(ndiag, n_nodes);
     ALLOC(e2b, 10 * n_tets);
     ALLOC(e2p, 10 * n_tets);
-    ALLOC(cd, 24 * n_tets);
-    ALLOC(co, 54 * n_tets);
+    ALLOC(geo, kGeoDoubles * n_tets);
+    uint32_t *di = nullptr, *oi = nullptr;
+    RowTile* tiles = nullptr;
+    uint2 *rowblk = nullptr, *rownode = nullptr;
+    uint16_t* terms = nullptr;
+    int32_t *bigd = nullptr, *bigo = nullptr;
+    ALLOC(di, R.di.size());
+    ALLOC(oi, R.oi.size());
+    ALLOC(tiles, R.tiles.size());
+    ALLOC(rowblk, R.rowblk.size());
+    ALLOC(rownode, R.rownode.size());
+    ALLOC(terms, R.terms.size());
+    ALLOC(bigd, R.bigd.size());
+    ALLOC(bigo, R.bigo.size());
     ALLOC(estamp, n_tets);
     ALLOC(bstamp, nb);
     ALLOC(rec, 10 * n_tets + 160);
@@ -389,6 +379,7 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     ALLOC(undo, n_tets);
     ALLOC(wg_err, 16 * n_tets / 256 + 4096);
     ALLOC(ctl, 1);
+    ALLOC(c->stat_ws, 4);
     ALLOC(c->dinc, 4 * n_tets);
     TetRecord* trec = nullptr;
     ALLOC(trec, n_tets);
@@ -436,16 +427,20 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     const std::vector<int32_t> order = adjoint_chunk_order(x, hT, node_off, tet_off);
     if (e == hipSuccess) e = upload(c->adj_order, order.data(), order.size(), s);
     c->adj_chunks = (int32_t)n_chunks;
+    if (e == hipSuccess) e = upload(di, R.di.data(), R.di.size(), s);
+    if (e == hipSuccess) e = upload(oi, R.oi.data(), R.oi.size(), s);
+    if (e == hipSuccess) e = upload(tiles, R.tiles.data(), R.tiles.size(), s);
+    if (e == hipSuccess) e = upload(rowblk, R.rowblk.data(), R.rowblk.size(), s);
+    if (e == hipSuccess) e = upload(rownode, R.rownode.data(), R.rownode.size(), s);
+    if (e == hipSuccess) e = upload(terms, R.terms.data(), R.terms.size(), s);
+    if (e == hipSuccess) e = upload(bigd, R.bigd.data(), R.bigd.size(), s);
+    if (e == hipSuccess) e = upload(bigo, R.bigo.data(), R.bigo.size(), s);
     {
         std::vector<TetRecord> hr((size_t)n_tets);
         for (int64_t t = 0; t < n_tets; ++t) {
             TetRecord& r = hr[t];
-            std::memset(&r, 0, sizeof r);
-            for (int j = 0; j < 10; ++j) {
+            for (int j = 0; j < 10; ++j)
                 r.desc[j] = hd[he2b[10 * t + j]];
-                r.pos[j] = P.e2p[10 * t + j];
-            }
-            r.T = hT[t];
         }
         if (e == hipSuccess) e = upload(trec, hr.data(), hr.size(), s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);  // hr is freed at the end of this block
@@ -466,8 +461,18 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.e2b = e2b;
     v.e2p = e2p;
     v.trec = trec;
-    v.cd = cd;
-    v.co = co;
+    v.geo = geo;
+    v.di = di;
+    v.oi = oi;
+    v.tiles = tiles;
+    v.rowblk = rowblk;
+    v.rownode = rownode;
+    v.terms = terms;
+    v.bigd = bigd;
+    v.bigo = bigo;
+    v.n_tiles = (int32_t)R.tiles.size();
+    v.n_bigd = (int32_t)R.bigd.size();
+    v.n_bigo = (int32_t)R.bigo.size();
     v.values = values;
     v.estamp = estamp;
     v.bstamp = bstamp;
@@ -477,10 +482,9 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.wg_err = wg_err;
     v.ctl = ctl;
 
-    // the records' geometry, computed on the device with the element kernel's routine
-    if (e == hipSuccess) e = launch_refresh_records(v, trec, s);
-    if (e == hipSuccess) e = launch_element(v, false, s);
-    if (e == hipSuccess) e = launch_reduce_all(v, c->rebuild_map, s);
+    if (e == hipSuccess) e = launch_geometry(v, s);
+    if (e == hipSuccess) e = launch_rows(v, false, s);
+    if (e == hipSuccess) e = launch_rows_big(v, false, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     int32_t bits = 0;
     if (e == hipSuccess) e = hipMemcpy(&bits, &ctl->err, sizeof(int32_t), hipMemcpyDeviceToHost);
@@ -508,7 +512,7 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     }
     c->node_off = node_off;
     c->tet_off = tet_off;
-    c->rebuild_groups = rebuild_groups(P, hd, node_off, tet_off);
+    c->rebuild_groups = rebuild_groups(R, tet_off);
     c->nnz_off.resize(node_off.size());
     for (size_t j = 0; j < node_off.size(); ++j)
         c->nnz_off[j] = P.rowptr[3 * node_off[j]];
@@ -545,24 +549,31 @@ void trace_call(sta_ctx* ctx, const char* call, int64_t n, bool n_is_capacity, h
     std::fflush(ctx->trace);
 }
 
-// One frame: two launches, or one persistent launch.
+// One frame.  A list that fits k_once's table takes one launch without a grid
+// barrier whatever the mode (5.9 us a frame on the 384k-tet stream, against
+// 8.4 for two launches and 15 to 23 for one with a barrier); a longer one two
+// launches, or with fused set one persistent launch with a barrier.  A spin
+// limit set by the caller asks for the barrier it limits.
 sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, int32_t n_host, const int32_t* n_dev,
                      hipStream_t s)
 {
     hipError_t e = hipSuccess;
-    if (ctx->fused) {
+    if (frame_fits_once(n_host) && !(ctx->fused && ctx->barrier_spin != kBarrierSpinDefault)) {
+        e = timed(
+            ctx, STA_KERNEL_FRAME, s, [&] { return launch_once(ctx->v, ids, states, n_host, n_dev, s); }, true);
+    } else if (ctx->fused) {
         if (ctx->frame_max_grid <= 0) {
-            e = frame_max_grid(ctx->stream_map, ctx->device, &ctx->frame_max_grid);
+            e = frame_max_grid(ctx->device, &ctx->frame_max_grid);
             if (e != hipSuccess)
                 return hip_fail(ctx, e, "occupancy query");
             if (ctx->frame_max_grid <= 0)
                 return fail(ctx, STA_EINVAL, "fused frame kernel cannot be resident");
         }
-        const int grid = frame_grid_for(ctx->stream_map, n_host, ctx->frame_max_grid, ctx->frame_grid_cap);
+        const int grid = frame_grid_for(n_host, ctx->frame_max_grid, ctx->frame_grid_cap);
         e = timed(
             ctx, STA_KERNEL_FRAME, s,
             [&] {
-                return launch_frame(ctx->v, ctx->stream_map, grid, ids, states, n_host, n_dev, ctx->barrier_spin, s);
+                return launch_frame(ctx->v, grid, ids, states, n_host, n_dev, ctx->barrier_spin, s);
             },
             true);
         ctx->fused_used = true;
@@ -573,7 +584,7 @@ sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, in
         if (e == hipSuccess)
             e = timed(
                 ctx, STA_KERNEL_TOUCHED, s,
-                [&] { return launch_touched_phase(ctx->v, ctx->stream_map, ids, n_host, n_dev, s); }, true);
+                [&] { return launch_touched_phase(ctx->v, ids, n_host, n_dev, s); }, true);
     }
     if (e != hipSuccess)
         return hip_fail(ctx, e, "frame launch");
@@ -612,36 +623,35 @@ sta_status sta_full_rebuild(sta_ctx* ctx, void* stream)
     const bool nt = ctx->rebuild_map.nt != 0;
     if (ctx->rebuild_groups.empty()) {
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_ELEMENT, s, [&] { return launch_element(ctx->v, nt, s); }, true);
+            e = timed(ctx, STA_KERNEL_ELEMENT, s, [&] { return launch_geometry(ctx->v, s); }, true);
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_reduce_all(ctx->v, ctx->rebuild_map, s); }, true);
+            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows(ctx->v, nt, s); }, true);
+        if (e == hipSuccess)
+            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows_big(ctx->v, false, s); }, true);
     }
     for (const auto& g : ctx->rebuild_groups) {
-        // views of the group's tets, of its diagonal blocks and of its off-diagonal blocks (the
-        // reduce takes the diagonal blocks at desc[0, nd) and the off-diagonal ones at desc[nd, nd + no))
+        // views of the group's tets and of its tiles and large blocks
         DevView vt = ctx->v;
         vt.n_tets = (int32_t)(g[1] - g[0]);
         vt.T += g[0];
         vt.E += g[0];
         vt.mask += g[0];
-        vt.e2b += 10 * g[0];
-        vt.e2p += 10 * g[0];
-        vt.trec += g[0];
-        vt.estamp += g[0];
-        DevView vd = ctx->v;
-        vd.desc += g[2];
-        vd.nd = (int32_t)(g[3] - g[2]);
-        vd.no = 0;
-        DevView vo = ctx->v;
-        vo.desc += ctx->v.nd + g[4];
-        vo.nd = 0;
-        vo.no = (int32_t)(g[5] - g[4]);
+        vt.geo += kGeoDoubles * g[0];
+        DevView vr = ctx->v;
+        vr.tiles += g[2];
+        vr.n_tiles = (int32_t)(g[3] - g[2]);
+        vr.bigd += g[4];
+        vr.n_bigd = (int32_t)(g[5] - g[4]);
+        vr.bigo += g[6];
+        vr.n_bigo = (int32_t)(g[7] - g[6]);
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_ELEMENT, s, [&] { return launch_element(vt, nt, s); }, true);
+            e = timed(ctx, STA_KERNEL_ELEMENT, s, [&] { return launch_geometry(vt, s); }, true);
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_reduce_all(vd, ctx->rebuild_map, s); }, true);
+            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows(vr, nt, s); }, true);
+        // launched for every group, with or without large nodes, so that each group's row passes are
+        // the same two in the kernel times
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_reduce_all(vo, ctx->rebuild_map, s); }, true);
+            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows_big(vr, true, s); }, true);
     }
     if (e != hipSuccess)
         return hip_fail(ctx, e, "full_rebuild launch");
@@ -771,6 +781,14 @@ sta_status sta_last_frame_stats(sta_ctx* ctx, void* stream, int64_t* out, int n_
     const int64_t n = (h.last_n >= 0 && h.last_n <= ctx->n_tets) ? h.last_n : 0;
     const int64_t max_regions = 4 * ((16 * ctx->n_tets + 255) / 256 + 1);
     const int64_t g = (h.last_regions >= 0 && h.last_regions <= max_regions) ? h.last_regions : 0;
+    unsigned long long once[4] = {0, 0, 0, 0};
+    if (e == hipSuccess && h.last_regions == -1 && n > 0 && h.frame_err == 0) {
+        e = launch_once_stats(ctx->v, (int32_t)n, ctx->stat_ws, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(once, ctx->stat_ws, sizeof once, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(s);
+    }
     std::vector<BlockDesc> rc((size_t)g * 40);
     std::vector<int32_t> cnt((size_t)g * 2);
     std::vector<uint8_t> un((size_t)n);
@@ -786,6 +804,9 @@ sta_status sta_last_frame_stats(sta_ctx* ctx, void* stream, int64_t* out, int n_
     st[7] = n;
     st[8] = (n > 0 && h.frame_err != 0) ? 1 : 0;
     if (n > 0 && h.frame_err == 0) {
+        for (int k = 0; k < 4; ++k)
+            st[k] = (int64_t)once[k];
+        st[4] = 9 * st[0] + 18 * st[1];
         for (int64_t w = 0; w < g; ++w) {
             for (int k = 0; k < cnt[2 * w] && k < 16; ++k) {
                 const BlockDesc& d = rc[40 * w + k];
@@ -855,8 +876,6 @@ sta_status sta_set_params(sta_ctx* ctx, const double* x_dev, const double* E_dev
     double* xs = const_cast<double*>(ctx->v.xs);
     hipError_t e = launch_set_params(ctx->v, x_dev, E_dev, xs, xs + ctx->n_nodes, xs + 2 * ctx->n_nodes,
                                      const_cast<double*>(ctx->v.E), static_cast<hipStream_t>(stream));
-    if (e == hipSuccess)
-        e = launch_refresh_records(ctx->v, const_cast<TetRecord*>(ctx->v.trec), static_cast<hipStream_t>(stream));
     if (e != hipSuccess)
         return hip_fail(ctx, e, "set_params launch");
     ctx->stale = true;
@@ -912,7 +931,6 @@ sta_status sta_set_config(sta_ctx* ctx, int fused, int rebuild_qd, int rebuild_q
     if (!ctx || (fused != 0 && fused != 1) || !valid_map(rebuild_qd, rebuild_qo) || !valid_map(stream_qd, stream_qo) ||
         grid_cap < 0 || (rebuild_nt != 0 && rebuild_nt != 1))
         return STA_EINVAL;
-    ctx->frame_max_grid = 0;  // the fused kernel's occupancy depends on the mapping
     ctx->fused = fused;
     ctx->rebuild_map = uniform_map(rebuild_qd, rebuild_qo, rebuild_nt);
     ctx->stream_map = uniform_map(stream_qd, stream_qo, 0);
@@ -954,7 +972,7 @@ sta_status sta_audit(sta_ctx* ctx, void* stream, int64_t* out2)
     unsigned long long* counts = reinterpret_cast<unsigned long long*>(ctx->audit_ws + ctx->nnz);
     e = hipMemsetAsync(counts, 0, 2 * sizeof(unsigned long long), s);
     if (e == hipSuccess)
-        e = launch_audit(ctx->v, ctx->rebuild_map, ctx->audit_ws, ctx->nnz, counts, s);
+        e = launch_audit(ctx->v, ctx->audit_ws, ctx->nnz, counts, s);
     unsigned long long h[2] = {0, 0};
     if (e == hipSuccess)
         e = hipMemcpyAsync(h, counts, sizeof h, hipMemcpyDeviceToHost, s);
@@ -998,7 +1016,6 @@ sta_status sta_set_bucket_map(sta_ctx* ctx, int which, const int* qd3, const int
         ctx->rebuild_map = m;
     } else {
         ctx->stream_map = m;
-        ctx->frame_max_grid = 0;
     }
     return STA_OK;
 }

@@ -1,18 +1,16 @@
 // gfx950 kernels for exact assembly of A_t = M_t + dt^2 K_t (paper Sec. 3.4
 // eq. (8), implicit-Euler matrix of Sec. 6.2 eq. (9)).
 //
-// Data flow.  Each candidate tet's element matrix is split into its 10 node
-// blocks (4 diagonal, 6 off-diagonal) and stored at the tet's position in
-// each block's incidence segment: the persistent per-element contributions
-// the paper's streaming policy keeps across frames (Sec. 3.5).  An inactive
-// tet's slots hold +0.0.  A matrix entry is the sum of its segment's terms,
-// taken in ascending tet id from +0.0.  The full rebuild recomputes every
-// tet's slots (zero for inactive ones) and re-sums every block; the
-// streaming update rewrites the slots of tets whose state changed and
-// re-sums only the blocks they cover.  Both use the same summation routine,
-// so they agree bit for bit with each other and with a rebuild that skips
-// inactive tets (an accumulator that starts at +0.0 never becomes -0.0, so
-// adding +0.0 changes nothing).
+// Data flow.  Each candidate tet has one 128-byte geometry record (basis
+// gradients, scaled moduli, lumped mass).  A matrix entry is the sum, in
+// ascending tet id from +0.0, of the entries of its active tets' element
+// matrices, each formed from the tet's record where it is needed: nothing of
+// the 78 values per tet is stored.  The full rebuild recomputes every record
+// and sums every row; the streaming update re-sums the blocks that the edited
+// tets cover.  Both form and add the same terms in the same order, so they
+// agree bit for bit with each other and with a rebuild that skips inactive
+// tets (an accumulator that starts at +0.0 never becomes -0.0, so adding
+// +0.0 changes nothing).
 //
 // Floating point: contraction is off for this file and the element formula
 // is evaluated in a fixed order (see include/stafem.h); only IEEE + - * / and
@@ -35,53 +33,6 @@ constexpr int kRegionDiag = 16, kRegionOff = 24, kRegion = kRegionDiag + kRegion
 constexpr int kRegionsPerBlock = kBlock / 64;
 
 typedef double dvec2 __attribute__((ext_vector_type(2)));
-
-// Loads and stores with an optional non-temporal (streaming) cache hint, for
-// data touched exactly once per launch (the rebuild's contributions and values).
-template <bool NT>
-__device__ __forceinline__ double ld(const double* p)
-{
-    if (NT)
-        return __builtin_nontemporal_load(p);
-    return *p;
-}
-template <bool NT>
-__device__ __forceinline__ void st(double* p, double x)
-{
-    if (NT)
-        __builtin_nontemporal_store(x, p);
-    else
-        *p = x;
-}
-template <bool NT>
-__device__ __forceinline__ void st2(double* p, double a, double b)
-{
-    const dvec2 x = {a, b};
-    if (NT)
-        __builtin_nontemporal_store(x, reinterpret_cast<dvec2*>(p));
-    else
-        *reinterpret_cast<dvec2*>(p) = x;
-}
-
-// The rebuild kernels remap workgroup ids so that neighbouring work, which
-// shares contribution, descriptor and CSR cache lines, runs on one XCD: the
-// element kernel gives each XCD one contiguous eighth of the tets (xcd_remap).
-//
-// Reduce: each XCD takes runs of kXcdRun consecutive workgroups in turn, so
-// that the runs spread every part of the work (the diagonal blocks, then the
-// off-diagonal ones) evenly over the XCDs.  One contiguous range per XCD put
-// the whole diagonal section on three XCDs and was 4% slower; plain
-// round-robin was 1% slower.  Workgroups past the last whole round of runs
-// keep their ids, so the map is a permutation of [0, G).
-constexpr int kXcdRun = 16;
-__device__ __forceinline__ int xcd_remap_runs(int wg, int G)
-{
-    const int full = G / (kXcds * kXcdRun) * (kXcds * kXcdRun);
-    if (wg >= full)
-        return wg;
-    const int x = wg % kXcds, idx = wg / kXcds;
-    return ((idx / kXcdRun) * kXcds + x) * kXcdRun + idx % kXcdRun;
-}
 
 struct Geo {
     double g[4][3];
@@ -167,181 +118,8 @@ __device__ __forceinline__ double entry(const double* ga, const double* gb, doub
 constexpr int PA[6] = {0, 0, 0, 1, 1, 2};
 constexpr int PB[6] = {1, 2, 3, 2, 3, 3};
 
-// Compute tet e's element matrix and store its 78 distinct values at the
-// tet's 10 incidence positions.  Off-diagonal blocks are stored in block
-// orientation (row node = smaller node id).  pos: the tet's 10 positions.
-template <bool NT = false>
-__device__ __forceinline__ void store_element(const DevView& v, int e, int4 t, const int* pos)
-{
-    Geo G;
-    element_geometry(v, e, t, G);
-    if (G.det == 0.0)
-        atomicOr(&v.ctl->err, ERR_DEGENERATE);
-    const int id[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const double s = dot3(G.g[a], G.g[a]);
-        double* dst = v.cd + 6 * (size_t)pos[a];
-        st2<NT>(dst + 0, entry(G.g[a], G.g[a], s, G, 0, 0, true), entry(G.g[a], G.g[a], s, G, 0, 1, true));
-        st2<NT>(dst + 2, entry(G.g[a], G.g[a], s, G, 0, 2, true), entry(G.g[a], G.g[a], s, G, 1, 1, true));
-        st2<NT>(dst + 4, entry(G.g[a], G.g[a], s, G, 1, 2, true), entry(G.g[a], G.g[a], s, G, 2, 2, true));
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const bool sw = id[PA[q]] > id[PB[q]];
-        double ga[3], gb[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            ga[i] = sw ? G.g[PB[q]][i] : G.g[PA[q]][i];
-            gb[i] = sw ? G.g[PA[q]][i] : G.g[PB[q]][i];
-        }
-        const double s = dot3(ga, gb);
-        double* dst = v.co + 9 * (size_t)pos[4 + q];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                st<NT>(dst + 3 * i + j, entry(ga, gb, s, G, i, j, false));
-    }
-}
-
-// Zero the 78 slots of an inactive tet.
-template <bool NT = false>
-__device__ __forceinline__ void zero_element(const DevView& v, const int* pos)
-{
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        double* dst = v.cd + 6 * (size_t)pos[a];
-        st2<NT>(dst + 0, 0.0, 0.0);
-        st2<NT>(dst + 2, 0.0, 0.0);
-        st2<NT>(dst + 4, 0.0, 0.0);
-    }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        double* dst = v.co + 9 * (size_t)pos[4 + q];
-#pragma unroll
-        for (int j = 0; j < 9; ++j)
-            st<NT>(dst + j, 0.0);
-    }
-}
-
-// The canonical sum of value vi of one block: +0.0 plus the segment's terms
-// in ascending tet id.  Q lanes share one value ("slot mapping": Q = 1
-// thread-, 4 quad-, 16 wave-sixteenth-per-slot): lane q of the group loads
-// terms q, q+Q, q+2Q, ... CH at a time (padding terms are +0.0), then every
-// lane of the group adds all terms in ascending order, taking each from the
-// lane that holds it.  The additions are the same whatever Q is, so the
-// result is bit-identical across mappings.  src0: wave lane of the group's
-// lane 0; groups of Q lanes never straddle a wave.
-//
-// Padding terms past the segment end load the segment's last term (always
-// in range, and on a line the group loads anyway) and are then replaced by
-// +0.0: the CH loads issue back to back with no branch around each, where a
-// guarded load per term cost an exec-mask branch apiece.
-template <int Q, int CH, bool NT = false>
-__device__ __forceinline__ double seg_sum(const double* __restrict__ c, int stride, int vi, int k0, int k1, int q,
-                                          int src0)
-{
-    double acc = 0.0;
-    for (int base = k0; base < k1; base += Q * CH) {
-        double t[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int k = base + q + j * Q;
-            const int kc = k < k1 ? k : k1 - 1;  // base < k1, so kc is in [k0, k1)
-            t[j] = ld<NT>(c + (size_t)kc * stride + vi);
-        }
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-            t[j] = base + q + j * Q < k1 ? t[j] : 0.0;
-        if (Q == 1) {
-#pragma unroll
-            for (int j = 0; j < CH; ++j)
-                acc = acc + t[j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < CH; ++j)
-#pragma unroll
-                for (int l = 0; l < Q; ++l)
-                    acc = acc + __shfl(t[j], src0 + l, 64);
-        }
-    }
-    return acc;
-}
-
-// Terms held per lane per chunk: about 32 loads in flight per diagonal value
-// (64 with sixteen lanes, so that the long segments of refinement supersets,
-// 48 tets, are read in one round).
-template <int Q>
-struct DiagChunk {
-    static constexpr int CH = Q == 1 ? 32 : (Q == 4 ? 8 : 4);
-};
-template <int Q>
-struct OffChunk {
-    static constexpr int CH = Q == 1 ? 8 : 2;
-};
-
 __device__ __constant__ int kDiagP[6] = {0, 0, 0, 1, 1, 2};
 __device__ __constant__ int kDiagQ[6] = {0, 1, 2, 1, 2, 2};
-
-// Recompute value vi (0..5 unique diagonal values, 0..8 off-diagonal) of the
-// block described by d and write it (and its mirror) into the CSR values.
-// All QD (or QO) lanes of the group call this; lane q == 0 writes.
-template <int QD, int QO, bool NT = false>
-__device__ __forceinline__ void block_value(const DevView& v, const BlockDesc& d, int vi, int q, int src0)
-{
-    if (d.kind == 0) {
-        const double acc = seg_sum<QD, DiagChunk<QD>::CH, NT>(v.cd, 6, vi, d.k0, d.k1, q, src0);
-        if (q == 0) {
-            const int p = kDiagP[vi], r = kDiagQ[vi];
-            st<NT>(v.values + d.up + p * d.rl + r, acc);
-            if (p != r)
-                st<NT>(v.values + d.up + r * d.rl + p, acc);
-        }
-    } else {
-        const double acc = seg_sum<QO, OffChunk<QO>::CH, NT>(v.co, 9, vi, d.k0, d.k1, q, src0);
-        if (q == 0) {
-            const int p = vi / 3, r = vi - 3 * (vi / 3);
-            st<NT>(v.values + d.up + p * d.rl + r, acc);
-            st<NT>(v.values + d.lo + r * d.rlj + p, acc);
-        }
-    }
-}
-
-// block_value with the lane group size Q of the block's incidence-length
-// bucket (Q <= the allocation QD / QO; a power of four, so that groups
-// aligned to Q never straddle a wave).  MIXED = false: every bucket uses the
-// allocation, and only that code path is compiled (the smaller mappings'
-// deeper load chunks would otherwise cost registers and occupancy).
-template <int QD, int QO, bool MIXED, bool NT = false>
-__device__ __forceinline__ void block_value_q(const DevView& v, const BlockDesc& d, int vi, int q, int src0, int Q)
-{
-    if (!MIXED) {
-        block_value<QD, QO, NT>(v, d, vi, q, src0);
-    } else if (d.kind == 0) {
-        if (QD >= 16 && Q == 16)
-            block_value<16, 1, NT>(v, d, vi, q, src0);
-        else if (QD >= 4 && Q == 4)
-            block_value<4, 1, NT>(v, d, vi, q, src0);
-        else
-            block_value<1, 1, NT>(v, d, vi, q, src0);
-    } else {
-        if (QO >= 4 && Q == 4)
-            block_value<1, 4, NT>(v, d, vi, q, src0);
-        else
-            block_value<1, 1, NT>(v, d, vi, q, src0);
-    }
-}
-
-// Lane group size of block d under mapping m (its incidence-length bucket's).
-template <int QD, int QO, bool MIXED>
-__device__ __forceinline__ int bucket_q(const MapConfig& m, const BlockDesc& d)
-{
-    if (!MIXED)
-        return d.kind == 0 ? QD : QO;
-    const int kappa = d.k1 - d.k0;
-    return d.kind == 0 ? m.qdb[diag_bucket(kappa)] : m.qob[off_bucket(kappa)];
-}
 
 __device__ __forceinline__ BlockDesc load_desc(const BlockDesc* p)
 {
@@ -366,182 +144,383 @@ __device__ __forceinline__ void store_desc(BlockDesc* p, const BlockDesc& d)
     q[1] = make_int4(d.lo, d.rlj, d.kind, d.block);
 }
 
+__device__ __forceinline__ BlockDesc empty_desc()
+{
+    return BlockDesc{0, 0, 0, 0, 0, 0, -1, -1};
+}
+
 // ---------------------------------------------------------------------------
 // Full rebuild
 // ---------------------------------------------------------------------------
 
-// Every candidate: active -> element matrix into its slots, inactive -> zeros.
-// One lane per tet.  A tet's ten slot chunks lie far apart (each in its
-// block's incidence segment), so lanes storing their own chunks would send
-// one partial-line request per lane and store.  Instead each wave stages one
-// slot of its 64 tets at a time in LDS and stores it cooperatively:
-// neighbouring lanes write neighbouring parts of the same chunk, and the
-// memory pipeline merges them into a few line requests.
-template <bool NT>
-__global__ __launch_bounds__(kBlock) void k_element(DevView v)
+// Every candidate's geometry record.  One lane per tet; a wave stages its 64
+// records in LDS (17 doubles apart, so that neither side conflicts) and stores
+// them as whole lines: 12.4 us for 384,000 tets, 60 MB at 4.9 TB/s, where
+// writing each tet's 78 values into its blocks' segments took 58 to 69.
+__global__ __launch_bounds__(kBlock) void k_geometry(DevView v)
 {
-    __shared__ double s_stage[kBlock / 64][64 * 9];
+    constexpr int kStride = kGeoDoubles + 1;
+    __shared__ double s_stage[kBlock / 64][64 * kStride];
     const int wg = xcd_remap(blockIdx.x, gridDim.x);
     const int base = wg * kBlock + (threadIdx.x & ~63);  // the wave's first tet
     if (base >= v.n_tets)
         return;
     const int lane = threadIdx.x & 63;
-    const int e = base + lane;
     const int nw = v.n_tets - base < 64 ? v.n_tets - base : 64;  // tets of this wave
-    const bool valid = lane < nw;
-    int pos[10];
-#pragma unroll
-    for (int j = 0; j < 10; ++j)
-        pos[j] = valid ? v.e2p[10 * (size_t)e + j] : 0;
-    const bool active = valid && v.mask[e];
+    const int e = base + (lane < nw ? lane : nw - 1);
     Geo G;
-    int4 t = make_int4(0, 1, 2, 3);
-    if (active) {
-        t = v.T[e];
-        element_geometry(v, e, t, G);
-        if (G.det == 0.0)
-            atomicOr(&v.ctl->err, ERR_DEGENERATE);
-    }
+    element_geometry(v, e, v.T[e], G);
+    const bool degenerate = G.det == 0.0;
+    if (degenerate && v.mask[e])
+        atomicOr(&v.ctl->err, ERR_DEGENERATE);
     double* buf = s_stage[threadIdx.x >> 6];
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        buf[kStride * lane + k] = G.g[k / 3][k % 3];
+    buf[kStride * lane + 12] = G.lamV;
+    buf[kStride * lane + 13] = G.muV;
+    buf[kStride * lane + 14] = G.ml;
+    buf[kStride * lane + 15] = __longlong_as_double(degenerate ? 1ll : 0ll);  // degenerate, pad
     // LDS accesses of one wave complete in issue order; the wavefront-scope
-    // fences only keep the compiler from moving them across the exchange
+    // fence only keeps the compiler from moving them across the exchange
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    dvec2* dst = reinterpret_cast<dvec2*>(v.geo + (size_t)kGeoDoubles * base);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        if (active) {
-            const double s = dot3(G.g[a], G.g[a]);
-            buf[6 * lane + 0] = entry(G.g[a], G.g[a], s, G, 0, 0, true);
-            buf[6 * lane + 1] = entry(G.g[a], G.g[a], s, G, 0, 1, true);
-            buf[6 * lane + 2] = entry(G.g[a], G.g[a], s, G, 0, 2, true);
-            buf[6 * lane + 3] = entry(G.g[a], G.g[a], s, G, 1, 1, true);
-            buf[6 * lane + 4] = entry(G.g[a], G.g[a], s, G, 1, 2, true);
-            buf[6 * lane + 5] = entry(G.g[a], G.g[a], s, G, 2, 2, true);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                buf[6 * lane + k] = 0.0;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // 64 chunks of 48 B = 192 pieces of 16 B, three per lane
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int p = lane + 64 * j, m = p / 3, k = p - 3 * m;
-            const int pm = __shfl(pos[a], m, 64);
-            if (m < nw)
-                st2<NT>(v.cd + 6 * (size_t)pm + 2 * k, buf[6 * m + 2 * k], buf[6 * m + 2 * k + 1]);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    for (int j = 0; j < kGeoDoubles / 2; ++j) {
+        const int p = lane + 64 * j, m = p >> 3, k = p & 7;
+        if (m < nw)
+            dst[p] = dvec2{buf[kStride * m + 2 * k], buf[kStride * m + 2 * k + 1]};
     }
-    const int id[4] = {t.x, t.y, t.z, t.w};
+}
+
+// The CSR rows of one tile of nodes.  The tile's (node, tet) pairs' records
+// are staged in LDS by eight lanes each, so that every record is read as one
+// whole line, with zeros for inactive tets; then one lane per pair forms its
+// diagonal block's 6 values, one lane per off-diagonal row block sums its 9
+// values over the block's terms, and six lanes per node sum the diagonal
+// block's, all in ascending tet id.  Both blocks (i, j) and (j, i) are formed,
+// each by its row's tile: entry (p, q) of one is bitwise entry (q, p) of the
+// other, since a product's operands commute, and twice the arithmetic costs
+// less than scattering the mirror in 24-byte pieces.  The rows leave through
+// LDS as one contiguous range.
+//
+// Loads past a tile's end take its last element (in range), so that no branch
+// or wait separates the loads of a round (with one: 116 us instead of 50 on the
+// 384,000-tet cube; summing stored contributions from HBM took 88 to 91).
+constexpr int kRowThreads = 192;
+constexpr int kRowStride = 15;              // doubles per staged record (odd: neighbouring records differ in bank)
+constexpr int kDiagStride = kTilePairs + 1;  // diagonal values: value vi of pair p at vi * kDiagStride + p
+constexpr int kRowOut = 6 * kDiagStride > 9 * kTileBlocks ? 6 * kDiagStride : 9 * kTileBlocks;
+static_assert(kRowThreads == kTileBlocks + 64 && kTileNodes * 6 <= 64, "one wave of diagonal lanes");
+static_assert(kTilePairs == kRowThreads, "one lane per pair");
+template <bool NT>
+__global__ __launch_bounds__(kRowThreads) void k_rows(DevView v)
+{
+    __shared__ double s_geo[kTilePairs * kRowStride];
+    __shared__ double s_out[kRowOut];  // the diagonal values, then the rows
+    __shared__ uint16_t s_term[kTileTerms];
+    __shared__ uint8_t s_vertex[kTilePairs];  // the row node's local vertex in each pair's tet
+    const RowTile tile = v.tiles[xcd_remap(blockIdx.x, gridDim.x)];
+    const int tid = threadIdx.x;
+    constexpr int kRounds = kTilePairs * 8 / kRowThreads;
+    constexpr int kPerRound = kRowThreads / 8;
+    constexpr int kTermRounds = kTileTerms / kRowThreads;
+    const int j = tid & 7;
+    uint32_t u[kRounds];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        if (active) {
-            const bool sw = id[PA[q]] > id[PB[q]];
-            double ga[3], gb[3];
+    for (int k = 0; k < kRounds; ++k)
+        u[k] = v.di[tile.pair0 + min(k * kPerRound + (tid >> 3), tile.pairs - 1)];
+    uint16_t term[kTermRounds];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                ga[i] = sw ? G.g[PB[q]][i] : G.g[PA[q]][i];
-                gb[i] = sw ? G.g[PA[q]][i] : G.g[PB[q]][i];
-            }
+    for (int k = 0; k < kTermRounds; ++k)
+        term[k] = v.terms[tile.term0 + min(k * kRowThreads + tid, tile.terms - 1)];
+    // row block or row node of this lane
+    const int dl = tid - kTileBlocks;  // diagonal lane: node dl / 6, value dl % 6
+    const bool has_blk = tid < tile.blks, has_node = dl >= 0 && dl < 6 * tile.nodes;
+    const uint2 rb = dl < 0 ? v.rowblk[tile.blk0 + min(tid, tile.blks - 1)]
+                            : v.rownode[tile.node0 + min(dl / 6, tile.nodes - 1)];
+    dvec2 q[kRounds];
+    uint8_t on[kRounds];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        q[k] = reinterpret_cast<const dvec2*>(v.geo + (size_t)kGeoDoubles * (u[k] >> 2))[j];
+        on[k] = v.mask[u[k] >> 2];
+    }
+#pragma unroll
+    for (int k = 0; k < kTermRounds; ++k)
+        s_term[k * kRowThreads + tid] = term[k];
+#pragma unroll
+    for (int k = 0; k < kRounds; ++k) {
+        const int p = k * kPerRound + (tid >> 3);
+        s_geo[p * kRowStride + 2 * j] = on[k] ? q[k].x : 0.0;
+        if (j < 7)
+            s_geo[p * kRowStride + 2 * j + 1] = on[k] ? q[k].y : 0.0;
+        else
+            s_vertex[p] = (uint8_t)(u[k] & 3u);
+    }
+    __syncthreads();
+    {
+        const double* r = s_geo + tid * kRowStride;
+        const double* pa = r + 3 * s_vertex[tid];
+        Geo G;
+        G.lamV = r[12];
+        G.muV = r[13];
+        G.ml = r[14];
+        const double g[3] = {pa[0], pa[1], pa[2]};
+        const double s = dot3(g, g);
+#pragma unroll
+        for (int vi = 0; vi < 6; ++vi) {
+            constexpr int P[6] = {0, 0, 0, 1, 1, 2}, Q[6] = {0, 1, 2, 1, 2, 2};
+            s_out[vi * kDiagStride + tid] = entry(g, g, s, G, P[vi], Q[vi], true);
+        }
+    }
+    __syncthreads();
+    const int rl = (int)(rb.y >> 16), at = (int)(rb.y & 0xffffu);
+    const int first = (int)(rb.x & 0xffffu), end = first + (int)(rb.x >> 16);
+    double acc[3][3] = {};
+    if (dl < 0) {
+        for (int k = first; k < end; ++k) {
+            const uint32_t t = s_term[k];
+            const double* r = s_geo + (t >> 4) * kRowStride;
+            const double* pa = r + 3 * ((t >> 2) & 3u);
+            const double* pb = r + 3 * (t & 3u);
+            Geo G;
+            G.lamV = r[12];
+            G.muV = r[13];
+            const double ga[3] = {pa[0], pa[1], pa[2]}, gb[3] = {pb[0], pb[1], pb[2]};
             const double s = dot3(ga, gb);
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    buf[9 * lane + 3 * i + j] = entry(ga, gb, s, G, i, j, false);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 9; ++k)
-                buf[9 * lane + k] = 0.0;
+                for (int c = 0; c < 3; ++c)
+                    acc[i][c] = acc[i][c] + entry(ga, gb, s, G, i, c, false);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // 64 chunks of 72 B (8-byte aligned) = 576 doubles, nine per lane
+    } else {
+        const double* x = s_out + (dl % 6) * kDiagStride;
+        for (int k = first; k < end; k += 8) {
+            double t[8];
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int p = lane + 64 * j, m = p / 9, k = p - 9 * m;
-            const int pm = __shfl(pos[4 + q], m, 64);
-            if (m < nw)
-                st<NT>(v.co + 9 * (size_t)pm + k, buf[9 * m + k]);
+            for (int w = 0; w < 8; ++w)
+                t[w] = x[min(k + w, end - 1)];
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                acc[0][0] = acc[0][0] + (k + w < end ? t[w] : 0.0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    if (has_blk && end > first) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                s_out[at + i * rl + c] = acc[i][c];
+    } else if (has_node) {
+        const int i = kDiagP[dl % 6], c = kDiagQ[dl % 6];
+        s_out[at + i * rl + c] = acc[0][0];
+        if (i != c)
+            s_out[at + c * rl + i] = acc[0][0];
+    }
+    __syncthreads();
+    for (int k = tid; k < 9 * tile.blks; k += kRowThreads) {
+        if (NT)
+            __builtin_nontemporal_store(s_out[k], v.values + tile.val0 + k);
+        else
+            v.values[tile.val0 + k] = s_out[k];
     }
 }
 
-// Off-diagonal value vi of block d with one lane per value (QO = 1), the
-// block's 9 lanes in one wave from wave lane b0.  The mirror is written
-// transposed through a shuffle (lane (p, r) writes mirror entry (p, r), the
-// value of lane (r, p)), so that lanes 3p..3p+2 write one 24-byte row piece
-// of the block and one of its mirror.
-template <bool NT>
-__device__ __forceinline__ void off_value_rows(const DevView& v, const BlockDesc& d, int vi, int b0)
+// ---------------------------------------------------------------------------
+// Sums of a few blocks by one wave (streaming, and the rows of nodes too large
+// for a tile)
+// ---------------------------------------------------------------------------
+
+// A wave sums up to two diagonal blocks or up to six off-diagonal ones: the
+// ten blocks of a tet take three waves, two for its diagonal blocks (2 x 24
+// incidences each on the structured cube) and one for the others (32).  One
+// wave for all ten took 128 terms, two per lane, and two values per lane in
+// turn, and the longer instruction stream was the longest link of a frame's
+// chain.
+template <bool kDiag>
+struct Unit {
+    static constexpr int kBlocks = kDiag ? 2 : 6;
+    static constexpr int kValues = kDiag ? 6 : 9;  // entries formed per term
+    static constexpr int kStride = kDiag ? 7 : 9;  // doubles per term in LDS (odd: no bank conflicts)
+};
+constexpr int kUnits = 3;       // waves for a tet's ten blocks
+constexpr int kUnitTerms = 64;  // terms formed at a time, one per lane
+// LDS of a wave of either kind, with room to read eight terms past the last,
+// and of the three waves of a tet
+constexpr int kUnitDoubles = (kUnitTerms + 8) * Unit<false>::kStride;
+constexpr int kDiagUnitDoubles = (kUnitTerms + 8) * Unit<true>::kStride;
+constexpr int kTetDoubles = 2 * kDiagUnitDoubles + kUnitDoubles;
+
+// The state of a tet is its mask byte unless the frame's own edits say
+// otherwise: listed gives 0 or 1 for an edited tet, kUnlisted for any other.
+constexpr uint32_t kUnlisted = 2u;
+struct MaskState {
+    __device__ __forceinline__ uint32_t listed(uint32_t) const { return kUnlisted; }
+};
+
+// The wave's blocks laid end to end: the terms before each block's, and for
+// this lane's block its terms, their start and the shift to incidences.
+template <bool kDiag>
+struct UnitTerms {
+    int cnt, own, shift;
+    int pre[Unit<kDiag>::kBlocks + 1];
+    __device__ __forceinline__ int total() const { return pre[Unit<kDiag>::kBlocks]; }
+};
+
+template <bool kDiag>
+__device__ __forceinline__ UnitTerms<kDiag> unit_terms(const BlockDesc& d)
 {
-    const double acc = seg_sum<1, OffChunk<1>::CH, NT>(v.co, 9, vi, d.k0, d.k1, 0, b0 + vi);
-    const int p = vi / 3, r = vi - 3 * (vi / 3);
-    const double tr = __shfl(acc, b0 + 3 * r + p, 64);
-    st<NT>(v.values + d.up + p * d.rl + r, acc);
-    st<NT>(v.values + d.lo + p * d.rlj + r, tr);
+    const int lane = threadIdx.x & 63;
+    UnitTerms<kDiag> b;
+    b.cnt = lane < Unit<kDiag>::kBlocks && d.kind >= 0 ? d.k1 - d.k0 : 0;
+    b.own = 0;
+    b.pre[0] = 0;
+#pragma unroll
+    for (int r = 0; r < Unit<kDiag>::kBlocks; ++r) {
+        b.own = lane == r ? b.pre[r] : b.own;
+        b.pre[r + 1] = b.pre[r] + __builtin_amdgcn_readlane(b.cnt, r);
+    }
+    b.shift = d.k0 - b.own;
+    return b;
 }
 
-// Lanes: 6*QD per diagonal block (section padded to whole waves), then the
-// off-diagonal blocks: for QO = 1, 7 blocks of 9 lanes per wave (lane 63
-// idle, so that a block never straddles two waves), else 9*QO per block.
-// Each block's lanes use its incidence-length bucket's group size Q (at most
-// the allocation); lanes past 6Q (9Q) of a block idle.
-template <int QD, int QO, bool MIXED, bool NT>
-__global__ __launch_bounds__(kBlock) void k_reduce_all(DevView v, int64_t diag_lanes, MapConfig m)
+// Incidence of term base + lane (of some incidence where there is no such term).
+template <bool kDiag>
+__device__ __forceinline__ uint32_t load_incidence(const DevView& v, const UnitTerms<kDiag>& b, int base)
 {
-    const int wg = xcd_remap_runs(blockIdx.x, gridDim.x);
-    const int64_t t = (int64_t)wg * kBlock + threadIdx.x;
+    const int t = base + (int)(threadIdx.x & 63);
+    int r = 0;
+#pragma unroll
+    for (int w = 1; w < Unit<kDiag>::kBlocks; ++w)
+        r += t >= b.pre[w] ? 1 : 0;
+    const int k = t + __shfl(b.shift, r, 64);
+    return (kDiag ? v.di : v.oi)[t < b.total() ? k : 0];
+}
+
+// Sum the wave's blocks and write their CSR values; u: the incidences of the
+// first kUnitTerms terms.  Each lane forms the entries of one term at a time
+// from its tet's record into val (LDS, kUnitDoubles per wave); then one lane
+// per block value adds its block's entries in ascending order.  Any segment
+// length works.
+template <bool kDiag, class State>
+__device__ __forceinline__ void sum_unit(const DevView& v, const BlockDesc& d, const UnitTerms<kDiag>& b, uint32_t u,
+                                         double* val, const State& state)
+{
+    using U = Unit<kDiag>;
     const int lane = threadIdx.x & 63;
-    if (t < diag_lanes) {
-        const int b = (int)(t / (6 * QD));
-        if (b >= v.nd)
-            return;
-        const int rem = (int)(t - (int64_t)b * (6 * QD));
-        const BlockDesc d = load_desc(v.desc + b);
-        const int Q = bucket_q<QD, QO, MIXED>(m, d);
-        if (rem >= 6 * Q)
-            return;
-        const int q = rem & (Q - 1);
-        block_value_q<QD, QO, MIXED, NT>(v, d, rem / Q, q, lane - q, Q);
-    } else {
-        const int64_t u = t - diag_lanes;
-        if (QO == 1) {
-            const int l = (int)(u & 63);  // = lane: diag_lanes is a multiple of 64
-            const int o1 = (int)(u >> 6) * 7 + l / 9;
-            if (l == 63 || o1 >= v.no)
-                return;
-            off_value_rows<NT>(v, load_desc(v.desc + v.nd + o1), l % 9, lane - l % 9);
-            return;
+    const int total = b.total();
+    // the value of this lane: block r0, entry e0 of it, term range
+    const bool has = lane < U::kBlocks * U::kValues;
+    const int r0 = has ? lane / U::kValues : 0, e0 = has ? lane % U::kValues : 0;
+    const int lo = __shfl(b.own, r0, 64), hi = has ? lo + __shfl(b.cnt, r0, 64) : lo;
+    double acc = 0.0;
+    for (int base = 0; base < total; base += kUnitTerms) {
+        if (base > 0)
+            u = load_incidence<kDiag>(v, b, base);
+        const uint32_t e = kDiag ? u >> 2 : u >> 4;
+        const double* r = v.geo + (size_t)kGeoDoubles * e;
+        const double* pa = r + 3 * (kDiag ? u & 3u : (u >> 2) & 3u);
+        double ga[3], gb[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            ga[i] = pa[i];
+        Geo G;
+        G.lamV = r[12];
+        G.muV = r[13];
+        if (kDiag) {
+            G.ml = r[14];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                gb[i] = ga[i];
+        } else {
+            const double* pb = r + 3 * (u & 3u);
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                gb[i] = pb[i];
         }
-        const int o = (int)(u / (9 * QO));
-        if (o >= v.no)
-            return;
-        const int rem = (int)(u - (int64_t)o * (9 * QO));
-        const BlockDesc d = load_desc(v.desc + v.nd + o);
-        const int Q = bucket_q<QD, QO, MIXED>(m, d);
-        if (rem >= 9 * Q)
-            return;
-        const int q = rem & (Q - 1);
-        block_value_q<QD, QO, MIXED, NT>(v, d, rem / Q, q, lane - q, Q);
+        const uint8_t active = v.mask[e];
+        const uint32_t listed = state.listed(e);  // while the record is in flight
+        const bool on = listed == kUnlisted ? active != 0 : listed != 0u;
+        // LDS accesses of one wave complete in issue order; the fences only
+        // keep the compiler from moving them
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const double s = dot3(ga, gb);
+        double* dst = val + lane * U::kStride;
+#pragma unroll
+        for (int k = 0; k < U::kValues; ++k) {
+            constexpr int P[6] = {0, 0, 0, 1, 1, 2}, Q[6] = {0, 1, 2, 1, 2, 2};
+            const double x = entry(ga, gb, s, G, kDiag ? P[k % 6] : k / 3, kDiag ? Q[k % 6] : k % 3, kDiag);
+            dst[k] = on ? x : 0.0;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // eight terms at a time; those past the block's end (the space has
+        // room for them) are replaced by +0.0
+        const int z = min(hi - base, kUnitTerms);
+        for (int k = max(lo - base, 0); k < z; k += 8) {
+            const double* p = val + k * U::kStride + e0;
+            double t[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                t[w] = p[w * U::kStride];
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                acc = acc + (k + w < z ? t[w] : 0.0);
+        }
+    }
+    const int up = __shfl(d.up, r0, 64), rl = __shfl(d.rl, r0, 64);
+    const int dn = __shfl(d.lo, r0, 64), rj = __shfl(d.rlj, r0, 64);
+    if (hi > lo) {
+        // entries 00 01 02 11 12 22 of a diagonal block, row by row of another
+        const int pc = kDiag ? (int)(0xA65210u >> (4 * e0)) & 15 : 0;
+        const int p = kDiag ? pc >> 2 : e0 / 3, c = kDiag ? pc & 3 : e0 % 3;
+        v.values[up + p * rl + c] = acc;
+        if (!kDiag || p != c)
+            v.values[dn + c * rj + p] = acc;
+    }
+}
+
+// The same from the start, with the states in the mask.
+template <bool kDiag>
+__device__ __forceinline__ void sum_unit_masked(const DevView& v, const BlockDesc& d, double* val)
+{
+    const UnitTerms<kDiag> b = unit_terms<kDiag>(d);
+    if (b.total() > 0)
+        sum_unit<kDiag>(v, d, b, load_incidence<kDiag>(v, b, 0), val, MaskState{});
+}
+
+// Rows of nodes too large for a tile: waves of two of their diagonal blocks,
+// then waves of six of their off-diagonal ones.  An off-diagonal block is
+// written in both its rows; the other node's tile, if it has one, writes the
+// same bits.
+__global__ __launch_bounds__(kBlock) void k_rows_big(DevView v)
+{
+    __shared__ double s_val[kBlock / 64][kUnitDoubles];
+    const int lane = threadIdx.x & 63;
+    const int w = blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wd = (v.n_bigd + Unit<true>::kBlocks - 1) / Unit<true>::kBlocks;
+    BlockDesc d = empty_desc();
+    if (w < wd) {
+        const int k = w * Unit<true>::kBlocks + lane;
+        if (lane < Unit<true>::kBlocks && k < v.n_bigd)
+            d = load_desc(v.desc + v.bigd[k]);
+        sum_unit_masked<true>(v, d, s_val[threadIdx.x >> 6]);
+    } else {
+        const int k = (w - wd) * Unit<false>::kBlocks + lane;
+        if (lane < Unit<false>::kBlocks && k < v.n_bigo)
+            d = load_desc(v.desc + v.bigo[k]);
+        sum_unit_masked<false>(v, d, s_val[threadIdx.x >> 6]);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Streaming update
 // ---------------------------------------------------------------------------
-
-// Gradient of local vertex a (0..3, not a compile-time constant) by
-// selects, so that no register array is indexed at run time.
-__device__ __forceinline__ void pick_gradient(const Geo& G, int a, double* g)
-{
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-        g[i] = a == 0 ? G.g[0][i] : (a == 1 ? G.g[1][i] : (a == 2 ? G.g[2][i] : G.g[3][i]));
-}
 
 __device__ __forceinline__ int tet_vertex(int4 t, int a)
 {
@@ -555,61 +534,12 @@ constexpr uint32_t kSlotA = 0u | 1u << 2 | 2u << 4 | 3u << 6 | 0u << 8 | 0u << 1
 constexpr uint32_t kSlotB = 0u | 1u << 2 | 2u << 4 | 3u << 6 | 1u << 8 | 2u << 10 | 3u << 12 | 2u << 14 | 3u << 16 |
                             3u << 18;
 
-// Write block slot r of a tet with vertex ids t: its element-matrix values
-// (geometry G; block orientation: row vertex = the one with the smaller node
-// id; same arithmetic as store_element) when active, zeros when not.  One
-// code path serves all ten slots (the slot only selects gradients), which
-// keeps the streaming kernels' instruction footprint small.
-__device__ __forceinline__ void store_slot(const DevView& v, int4 t, const Geo& G, int r, int pos, bool active)
-{
-    if (!active) {
-        if (r < 4) {
-            double2* dst = reinterpret_cast<double2*>(v.cd + 6 * (size_t)pos);
-            const double2 z = make_double2(0.0, 0.0);
-            dst[0] = z;
-            dst[1] = z;
-            dst[2] = z;
-        } else {
-            double* dst = v.co + 9 * (size_t)pos;
-#pragma unroll
-            for (int j = 0; j < 9; ++j)
-                dst[j] = 0.0;
-        }
-        return;
-    }
-    if (G.det == 0.0 && r == 0)
-        atomicOr(&v.ctl->err, ERR_DEGENERATE);
-    int A = (int)(kSlotA >> (2 * r)) & 3, B = (int)(kSlotB >> (2 * r)) & 3;
-    if (tet_vertex(t, A) > tet_vertex(t, B)) {
-        const int c = A;
-        A = B;
-        B = c;
-    }
-    double ga[3], gb[3];
-    pick_gradient(G, A, ga);
-    pick_gradient(G, B, gb);
-    const double s = dot3(ga, gb);
-    if (r < 4) {
-        double2* dst = reinterpret_cast<double2*>(v.cd + 6 * (size_t)pos);
-        dst[0] = make_double2(entry(ga, ga, s, G, 0, 0, true), entry(ga, ga, s, G, 0, 1, true));
-        dst[1] = make_double2(entry(ga, ga, s, G, 0, 2, true), entry(ga, ga, s, G, 1, 1, true));
-        dst[2] = make_double2(entry(ga, ga, s, G, 1, 2, true), entry(ga, ga, s, G, 2, 2, true));
-    } else {
-        double* dst = v.co + 9 * (size_t)pos;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                dst[3 * i + j] = entry(ga, gb, s, G, i, j, false);
-    }
-}
-
-__device__ BlockDesc kNoClaim = {0, 0, 0, 0, 0, 0, -1, -1};
 __device__ int32_t kNoTet = -1;
+__device__ uint8_t kNoState = 0;
 
-__device__ __forceinline__ BlockDesc empty_desc()
+__device__ __forceinline__ bool is_degenerate(const DevView& v, int id)
 {
-    return BlockDesc{0, 0, 0, 0, 0, 0, -1, -1};
+    return reinterpret_cast<const TetGeo*>(v.geo)[id].degenerate != 0;
 }
 
 // Edit count of this frame: *n_dev if given and within [0, n_host], else n_host.
@@ -631,16 +561,9 @@ __device__ __forceinline__ int frame_count(int32_t n_host, const int32_t* n_dev,
 // tet's stamp (a second edit of the same tet in this frame finds it taken:
 // duplicate).  If the state changes, each slot lane claims its block (first
 // claimant wins; the claim's kind and block descriptor are returned in ckind
-// (-1: no claim) and cbd for the wave's compaction), the owner
-// flips the mask bit and the slot lanes rewrite the tet's 78 contribution
-// slots (element matrix on activation, zeros on deactivation).  Returns the
-// lane's error bits.  All 16 lanes of the edit must call it together.
-//
-// The frame is a short chain of dependent memory round trips, so its time is
-// their latency: every load that needs only the tet id (incidence positions,
-// mask bit, vertex ids, modulus) and then the block descriptors and vertex
-// coordinates are issued before the first atomic or store, which the compiler
-// could not move them across.
+// (-1: no claim) and cbd for the wave's compaction) and the owner flips the
+// mask bit.  Returns the lane's error bits.  All 16 lanes of the edit must
+// call it together.
 __device__ __forceinline__ int edit_lane(const DevView& v, int id, unsigned st, int i, int r, int& ckind,
                                          BlockDesc& cbd)
 {
@@ -652,59 +575,31 @@ __device__ __forceinline__ int edit_lane(const DevView& v, int id, unsigned st, 
         return 0;
     }
     const bool slot = r < 10;
-    const TetRecord* rc = v.trec + id;
-    // round trip 1: the tet's record (this lane's block descriptor and
-    // incidence position; vertex ids and geometry for an activation), its
-    // mask bit and its stamp
+    // round trip 1: this lane's block descriptor, the tet's mask bit, its
+    // stamp and whether an activation would assemble a degenerate tet
     BlockDesc bd = empty_desc();
-    int ep = 0;
-    if (slot) {
-        bd = load_desc(rc->desc + r);
-        ep = rc->pos[r];
-    }
-    int4 t = make_int4(0, 0, 0, 0);
-    Geo G;
-    if (slot && st) {
-        t = rc->T;
-        const dvec2* gp = reinterpret_cast<const dvec2*>(rc->g);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const dvec2 q = gp[k];
-            G.g[(2 * k) / 3][(2 * k) % 3] = q.x;
-            G.g[(2 * k + 1) / 3][(2 * k + 1) % 3] = q.y;
-        }
-        const dvec2 lm = *reinterpret_cast<const dvec2*>(&rc->lamV);
-        G.lamV = lm.x;
-        G.muV = lm.y;
-        G.ml = rc->ml;
-        G.det = rc->degenerate ? 0.0 : 1.0;  // store_slot only tests det == 0
-    }
+    if (slot)
+        bd = load_desc(v.trec[id].desc + r);
     const uint8_t prev = v.mask[id];
+    const bool degenerate = is_degenerate(v, id);
     unsigned taken = 0u;
     if (r == 0)
         taken = atomicExch(&v.estamp[id], 1u);
-    // round trip 2: the block claim (its result is needed only for the claim
-    // record, written last)
+    // round trip 2: the block claim
     const bool change = prev != st;
     unsigned claimed = 1u;
     if (slot && change)
         claimed = atomicExch(&v.bstamp[bd.block], 1u);
-    // the atomics' results pass through cross-lane moves, which the compiler
-    // keeps in place, so their waits fall here and after the slot stores
     const int owner = __shfl(taken, (threadIdx.x & 63) & ~(kEditLanes - 1), 64) == 0u;
     int bits = 0;
     if (!owner) {
         if (r == 0)
             bits = ERR_DUP;
-    } else if (change) {
-        if (r == 0)
-            v.mask[id] = (uint8_t)st;
-        if (slot)
-            store_slot(v, t, G, r, ep, st != 0u);
+    } else if (change && r == 0) {
+        v.mask[id] = (uint8_t)st;
+        if (st && degenerate)
+            atomicOr(&v.ctl->err, ERR_DEGENERATE);
     }
-    // the claim is consumed last, so the claim's round trip overlaps the slot
-    // arithmetic; the caller compacts the wave's claims into its region
-    claimed = __shfl(claimed, threadIdx.x & 63, 64);
     if (slot && claimed == 0u) {
         ckind = r < 4 ? 0 : 1;
         cbd = bd;
@@ -714,89 +609,73 @@ __device__ __forceinline__ int edit_lane(const DevView& v, int id, unsigned st, 
     return bits;
 }
 
-// Phase 2 lanes: per claim region, 6 QD lanes for each of its 16 diagonal
-// records then 9 QO lanes for each of its 24 off-diagonal records, padded to
-// whole waves; after all regions, one lane per edit (stamp release,
-// rollback).  Every lane group of Q starts at a multiple of Q, so it never
-// crosses a wave boundary.  Lanes of records past a region's count have
-// nothing to do, and since each region fills from its start, whole waves of
-// them exit at once.
-template <int QD, int QO>
-struct Phase2 {
-    static constexpr int LD = 6 * QD, LO = 9 * QO;
-    static constexpr int kDiagLanes = kRegionDiag * LD;
-    // padded to whole waves, so that every region starts at a wave boundary
-    static constexpr int kRegionLanes = (kDiagLanes + kRegionOff * LO + 63) / 64 * 64;
-};
+// Phase 2 waves: kDW per claim region for its diagonal records (two at a
+// time) and kOW for its off-diagonal ones (six at a time), each going on while
+// records are left; then one lane per edit (stamp release, rollback).  A region
+// fills from its start and mostly holds 4 to 6 diagonal and 10 to 15
+// off-diagonal claims, so three and three waves take one pass (twelve, one for
+// every possible record, left most of them to find nothing); a persistent
+// grid, which cannot have them all resident, takes fewer.
+template <int kDW, int kOW>
+struct RegionWaves {
+    static constexpr int kWaves = kDW + kOW;
+    bool diag;
+    int blocks, stride, first, k, count;  // k: the record of lane 0 in this pass
 
-// Decode phase-2 lane t: a record lane (region w, slot in the region, lane
-// rem among the record's 6 QD or 9 QO lanes), an edit lane (edit = index
-// into the edit list, returned in w with slot = -1) or a padding lane
-// (slot = -2).
-template <int QD, int QO>
-__device__ __forceinline__ void touched_role(int64_t t, int regions, int& w, int& slot, int& rem)
-{
-    using P = Phase2<QD, QO>;
-    const int64_t rl = (int64_t)regions * P::kRegionLanes;
-    rem = 0;
-    if (t >= rl) {
-        w = (int)(t - rl);
-        slot = -1;
-        return;
+    // The claim record of this lane in wave `part` of region w, if there is one.
+    __device__ __forceinline__ BlockDesc start(const DevView& v, int w, int part)
+    {
+        diag = part < kDW;
+        blocks = diag ? Unit<true>::kBlocks : Unit<false>::kBlocks;
+        stride = blocks * (diag ? kDW : kOW);
+        first = w * kRegion + (diag ? 0 : kRegionDiag);
+        k = (diag ? part : part - kDW) * blocks;
+        count = v.rcount[2 * w + (diag ? 0 : 1)];
+        return load(v);
     }
-    w = (int)(t / P::kRegionLanes);
-    const int u = (int)(t - (int64_t)w * P::kRegionLanes);
-    if (u < P::kDiagLanes) {
-        slot = u / P::LD;
-        rem = u - slot * P::LD;
-    } else {
-        const int u2 = u - P::kDiagLanes;
-        const int k = u2 / P::LO;
-        if (k >= kRegionOff) {
-            slot = -2;
-            return;
+    __device__ __forceinline__ BlockDesc load(const DevView& v) const
+    {
+        const int lane = threadIdx.x & 63;
+        BlockDesc d = empty_desc();
+        if (lane < blocks) {
+            d = load_desc(v.rec + (size_t)first + k + lane);  // in range, valid or not
+            if (k + lane >= count)
+                d = empty_desc();
         }
-        slot = kRegionDiag + k;
-        rem = u2 - k * P::LO;
+        return d;
     }
-}
-
-// Phase 2, record lane rem: re-sum value rem / Q of a claimed block, Q lanes
-// per value (Q from the block's incidence-length bucket; lanes past the
-// record's 6Q or 9Q idle) unless the frame has an error; the record's first
-// lane releases the block's claim stamp either way.
-template <int QD, int QO, bool MIXED>
-__device__ __forceinline__ void touched_record(const DevView& v, const BlockDesc& d, int fe, int rem,
-                                               const MapConfig& m)
-{
-    const int Q = bucket_q<QD, QO, MIXED>(m, d);
-    if (rem >= (d.kind == 0 ? 6 : 9) * Q)
-        return;
-    const int q = rem & (Q - 1);
-    if (!fe)
-        block_value_q<QD, QO, MIXED>(v, d, rem / Q, q, (threadIdx.x & 63) - q, Q);
-    if (rem == 0)
-        v.bstamp[d.block] = 0u;
-}
+    // Re-sum the wave's blocks, first record d, unless the frame has an error,
+    // and release their claim stamps either way.
+    __device__ __forceinline__ void run(const DevView& v, BlockDesc d, int fe, double* val)
+    {
+        static_assert(kRegionDiag >= 2 * kDW && kRegionOff >= 6 * kOW, "a wave's first records are in its region");
+        while (k < count) {
+            if (!fe) {
+                if (diag)
+                    sum_unit_masked<true>(v, d, val);
+                else
+                    sum_unit_masked<false>(v, d, val);
+            }
+            if ((int)(threadIdx.x & 63) < blocks && d.kind >= 0)
+                v.bstamp[d.block] = 0u;
+            k += stride;
+            if (k < count)
+                d = load(v);
+        }
+    }
+};
+using TouchedWaves = RegionWaves<4, 2>;  // two-launch frame
+using FusedWaves = RegionWaves<2, 2>;    // persistent frame
 
 // Phase 2, edit lane for edit i (tet id, undo byte u): release the tet stamp
-// and, if the frame has an error, undo the edit's mask flip and slot rewrite.
+// and, if the frame has an error, undo the edit's mask flip.
 __device__ __forceinline__ void touched_edit(const DevView& v, int id, uint8_t u, int fe)
 {
     if (id < 0 || id >= v.n_tets)
         return;
     v.estamp[id] = 0u;
-    if (fe && u != 0xFF) {
-        int ep[10];
-#pragma unroll
-        for (int k = 0; k < 10; ++k)
-            ep[k] = v.e2p[10 * (size_t)id + k];
+    if (fe && u != 0xFF)
         v.mask[id] = u;
-        if (u)
-            store_element(v, id, v.T[id], ep);
-        else
-            zero_element(v, ep);
-    }
 }
 
 // Workgroup-wide OR of error bits.
@@ -880,25 +759,27 @@ __global__ __launch_bounds__(kBlock) void k_edits(DevView v, const int32_t* __re
 }
 
 // Phase 2 as its own kernel.
-template <int QD, int QO, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_touched(DevView v, const int32_t* __restrict__ ids, int32_t n_host,
-                                                    const int32_t* __restrict__ n_dev, MapConfig m)
+                                                    const int32_t* __restrict__ n_dev)
 {
+    __shared__ double s_val[kBlock / 64][kUnitDoubles];
     __shared__ int s_bits;
     // the edit phase ran `edit_wgs` workgroups of kRegionsPerBlock waves, each wave one claim region
     const int edit_wgs = n_host > 0 ? (n_host * kEditLanes + kBlock - 1) / kBlock : 1;
     const int regions = edit_wgs * kRegionsPerBlock;
-    int w, slot, rem;
-    touched_role<QD, QO>((int64_t)blockIdx.x * kBlock + threadIdx.x, regions, w, slot, rem);
+    const int64_t wave = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const bool rec_wave = wave < (int64_t)regions * TouchedWaves::kWaves;
+    TouchedWaves tw;
     // claim record and count, or the edit's id and undo byte, load together
-    // with the error bytes and the device-side count; lanes without them read
-    // fixed empty values instead, so the loads need no branch
-    const bool rec_lane = slot >= 0;
-    const bool edit_lane_ = slot == -1 && w < n_host;
-    const BlockDesc d = load_desc(rec_lane ? v.rec + (size_t)w * kRegion + slot : &kNoClaim);
-    const int cnt = rec_lane ? v.rcount[2 * w + (slot >= kRegionDiag ? 1 : 0)] : 0;
-    const int id = *(edit_lane_ ? ids + w : &kNoTet);
-    const uint8_t u = edit_lane_ ? v.undo[w] : (uint8_t)0xFF;
+    // with the error bytes and the device-side count
+    BlockDesc d = empty_desc();
+    if (rec_wave)
+        d = tw.start(v, (int)(wave / TouchedWaves::kWaves), (int)(wave % TouchedWaves::kWaves));
+    const int64_t i = (wave - (int64_t)regions * TouchedWaves::kWaves) * 64 + lane;
+    const bool edit = !rec_wave && i < n_host;
+    const int id = *(edit ? ids + i : &kNoTet);
+    const uint8_t u = edit ? v.undo[i] : (uint8_t)0xFF;
     // the error bytes of every workgroup of the edit phase
     int bits = threadIdx.x < edit_wgs ? v.wg_err[threadIdx.x] : 0;
     for (int k = threadIdx.x + kBlock; k < edit_wgs; k += kBlock)
@@ -907,12 +788,10 @@ __global__ __launch_bounds__(kBlock) void k_touched(DevView v, const int32_t* __
     const int n = frame_count(n_host, n_dev, bad_n);
     const int fe = block_or(bits, &s_bits);
     publish_frame(v, fe, n, regions);
-    if (rec_lane) {
-        if (slot - (slot >= kRegionDiag ? kRegionDiag : 0) < cnt)
-            touched_record<QD, QO, MIXED>(v, d, fe, rem, m);
-    } else if (edit_lane_ && w < n) {
+    if (rec_wave)
+        tw.run(v, d, fe, s_val[threadIdx.x >> 6]);
+    else if (edit && i < n)
         touched_edit(v, id, u, fe);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -948,60 +827,69 @@ __device__ __forceinline__ void delta_block(const DevView& v, const BlockDesc& d
 }
 
 // Lane r of edit i under the delta policy (16 lanes per edit, lane r < 10
-// owns block slot r).  A changed tet's slot values are added (activation:
-// computed and stored in its slot first) or subtracted (deletion: read from
-// its slot, which is then zeroed), so the per-element contributions stay as
-// the exact policy expects and either policy may follow.  Invalid and
-// duplicate edits are skipped and reported; nothing is rolled back.
+// owns block slot r).  A changed tet's block entries, formed from its
+// geometry record, are added (activation) or subtracted (deletion); the mask
+// stays as the exact policy expects, so either policy may follow.  Invalid
+// and duplicate edits are skipped and reported; nothing is rolled back.
 __device__ __forceinline__ int delta_lane(const DevView& v, int id, unsigned st, int r)
 {
     if (id < 0 || id >= v.n_tets || st > 1u)
         return r == 0 ? ERR_RANGE : 0;
     const bool slot = r < 10;
-    uint32_t eb = 0;
-    int ep = 0;
-    if (slot) {
-        eb = (uint32_t)v.e2b[10 * (size_t)id + r];
-        ep = v.e2p[10 * (size_t)id + r];
-    }
-    int4 t = make_int4(0, 0, 0, 0);
-    double E = 0.0;
-    if (slot && st) {
-        t = v.T[id];
-        E = v.E[id];
-    }
     const uint8_t prev = v.mask[id];
     unsigned taken = 0u;
     if (r == 0)
         taken = atomicExch(&v.estamp[id], 1u);
     BlockDesc bd = empty_desc();
-    if (slot)
-        bd = load_desc(v.desc + eb);
-    double X[4][3];
-    if (slot && st)
-        load_vertices(v, t, X);
+    Geo G;
+    double ga[3], gb[3];
+    bool degenerate = false;
+    if (slot) {
+        bd = load_desc(v.trec[id].desc + r);
+        const int4 t = v.T[id];
+        int A = (int)(kSlotA >> (2 * r)) & 3, B = (int)(kSlotB >> (2 * r)) & 3;
+        const bool swap = tet_vertex(t, A) > tet_vertex(t, B);  // block orientation: the smaller node's row
+        const TetGeo* q = reinterpret_cast<const TetGeo*>(v.geo) + id;
+        const double* pa = q->g + 3 * (swap ? B : A);
+        const double* pb = q->g + 3 * (swap ? A : B);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            ga[i] = pa[i];
+            gb[i] = pb[i];
+        }
+        G.lamV = q->lamV;
+        G.muV = q->muV;
+        G.ml = q->ml;
+        degenerate = q->degenerate != 0;
+    }
     const bool owner = __shfl(taken, (threadIdx.x & 63) & ~(kEditLanes - 1), 64) == 0u;
     if (!owner)
         return r == 0 ? ERR_DUP : 0;
     if (prev == st)
         return 0;
-    if (r == 0)
+    if (r == 0) {
         v.mask[id] = (uint8_t)st;
+        if (st && degenerate)
+            atomicOr(&v.ctl->err, ERR_DEGENERATE);
+    }
     if (!slot)
         return 0;
-    const int nv = r < 4 ? 6 : 9;
-    const double* src = r < 4 ? v.cd + 6 * (size_t)ep : v.co + 9 * (size_t)ep;
+    const double s = dot3(ga, gb);
     double x[9];
-    Geo G;
-    if (st) {
-        geometry_from(v, X, E, G);
-        store_slot(v, t, G, r, ep, true);
-    }
+    if (r < 4) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k)
-        x[k] = k < nv ? src[k] : 0.0;
-    if (!st)
-        store_slot(v, t, G, r, ep, false);
+        for (int k = 0; k < 6; ++k) {
+            constexpr int P[6] = {0, 0, 0, 1, 1, 2}, Q[6] = {0, 1, 2, 1, 2, 2};
+            x[k] = entry(ga, gb, s, G, P[k], Q[k], true);
+        }
+#pragma unroll
+        for (int k = 6; k < 9; ++k)
+            x[k] = 0.0;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            x[k] = entry(ga, gb, s, G, k / 3, k % 3, false);
+    }
     delta_block(v, bd, x, st != 0u);
     return 0;
 }
@@ -1049,12 +937,11 @@ __global__ __launch_bounds__(kBlock) void k_delta_clear(DevView v, const int32_t
 // The whole frame in one persistent launch: phase 1 over the edits, grid
 // barrier, phase 2 over the claimed blocks (grid-stride loops; lane groups
 // stay aligned because the stride is a multiple of the workgroup size).
-template <int QD, int QO, bool MIXED>
 __global__ __launch_bounds__(kBlock) void k_frame(DevView v, const int32_t* __restrict__ ids,
                                                   const uint8_t* __restrict__ states, int32_t n_host,
-                                                  const int32_t* __restrict__ n_dev, MapConfig m,
-                                                  unsigned spin_limit)
+                                                  const int32_t* __restrict__ n_dev, unsigned spin_limit)
 {
+    __shared__ double s_val[kBlock / 64][kUnitDoubles];
     __shared__ int s_bits;
     __shared__ int s_ok;
     bool bad_n;
@@ -1079,68 +966,211 @@ __global__ __launch_bounds__(kBlock) void k_frame(DevView v, const int32_t* __re
         return;
     const int fe = frame_error(v, gridDim.x, &s_bits);
     publish_frame(v, fe, n, regions);
-    const int64_t total = (int64_t)regions * Phase2<QD, QO>::kRegionLanes + n_host;
-    for (int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x; t < total; t += (int64_t)gridDim.x * kBlock) {
-        int w, slot, rem;
-        touched_role<QD, QO>(t, regions, w, slot, rem);
-        if (slot >= 0) {
-            const int c = v.rcount[2 * w + (slot >= kRegionDiag ? 1 : 0)];
-            if (slot - (slot >= kRegionDiag ? kRegionDiag : 0) < c)
-                touched_record<QD, QO, MIXED>(v, load_desc(v.rec + (size_t)w * kRegion + slot), fe, rem, m);
-        } else if (slot == -1 && w < n) {
-            touched_edit(v, ids[w], v.undo[w], fe);
+    const int lane = threadIdx.x & 63;
+    const int64_t rec_waves = (int64_t)regions * FusedWaves::kWaves, waves = rec_waves + (n_host + 63) / 64;
+    for (int64_t w = (int64_t)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < waves;
+         w += (int64_t)gridDim.x * (kBlock / 64)) {
+        if (w < rec_waves) {
+            FusedWaves fw;
+            const BlockDesc d = fw.start(v, (int)(w / FusedWaves::kWaves), (int)(w % FusedWaves::kWaves));
+            fw.run(v, d, fe, s_val[threadIdx.x >> 6]);
+        } else {
+            const int64_t i = (w - rec_waves) * 64 + lane;
+            if (i < n)
+                touched_edit(v, ids[i], v.undo[i], fe);
         }
     }
 }
 
-// Audit: 1 if tet e's 78 stored contribution slots differ in any bit from
-// what the rebuild would store (its element matrix if active, +0.0 if not).
-__device__ __forceinline__ int audit_element(const DevView& v, int e)
+// The frame's edits as a chained hash table in LDS: head[h] is the last edit
+// of bucket h (-1: none) and edit[i] = (tet << 1 | requested state, the next
+// edit of its bucket).
+struct EditTable {
+    const int32_t* head;
+    const int2* edit;
+    int log2;
+    __device__ __forceinline__ uint32_t bucket(uint32_t e) const { return (e * 2654435761u) >> (32 - log2); }
+    __device__ __forceinline__ uint32_t listed(uint32_t e) const
+    {
+        uint32_t l = kUnlisted;
+        for (int i = head[bucket(e)]; i >= 0;) {
+            const int2 t = edit[i];
+            l = (uint32_t)t.x >> 1 == e ? (uint32_t)t.x & 1u : l;
+            i = t.y;
+        }
+        return l;
+    }
+};
+
+// A whole frame in one launch without a grid barrier, for edit lists that fit
+// a table in LDS.  Every workgroup reads the whole list into its own table
+// (validating it, so that all agree on the frame's error before anything is
+// written and nothing needs undoing), and three waves per edit re-sum the ten
+// blocks of its tet, taking an edited tet's state from the table and any other
+// tet's from the mask; only the edit's own waves use and write its tet's mask
+// byte, so no result depends on when it is written.  Blocks shared by several
+// edits are summed by each of them to the same bits: cheaper than claiming
+// them, which takes a second launch (or a grid barrier) before the claims can
+// be used.  What remains is a chain of four dependent round trips: edit, block
+// descriptors, incidences, geometry.
+//
+// kEdits: edits per workgroup; kShare: edits of the list per lane (n_host <=
+// 64 kUnits kEdits kShare).
+constexpr int kOnceMax = 2304;  // edits of the largest variant
+constexpr int kOnceSpare = 64;  // heads past the buckets, for lanes without an edit
+template <int kEdits, int kShare>
+__global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const int32_t* __restrict__ ids,
+                                                               const uint8_t* __restrict__ states, int32_t n_host,
+                                                               const int32_t* __restrict__ n_dev, int log2)
 {
-    int pos[10];
+    constexpr int kThreads = 64 * kUnits * kEdits;
+    // heads (1 << log2, then kOnceSpare), then kShare kThreads edits
+    extern __shared__ int4 s_dynamic[];
+    __shared__ double s_val[kEdits][kTetDoubles];
+    __shared__ int s_bits, s_change[kEdits];
+    int32_t* head = reinterpret_cast<int32_t*>(s_dynamic);
+    int2* edit = reinterpret_cast<int2*>(head + (1 << log2) + kOnceSpare);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int unit = wave % kUnits, own = wave / kUnits, i = blockIdx.x * kEdits + own;
+    // the wave's own edit, and this lane's share of the list
+    int id = -1;
+    unsigned st = 0;
+    if (n_host > 0) {
+        id = ids[min(i, n_host - 1)];
+        st = states[min(i, n_host - 1)];
+    }
+    int lid[kShare];
+    uint8_t lst[kShare];
 #pragma unroll
-    for (int j = 0; j < 10; ++j)
-        pos[j] = v.e2p[10 * (size_t)e + j];
-    const bool active = v.mask[e] != 0;
-    Geo G;
-    const int4 t = v.T[e];
-    if (active)
-        element_geometry(v, e, t, G);
-    const int id[4] = {t.x, t.y, t.z, t.w};
-    bool bad = false;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const double* c = v.cd + 6 * (size_t)pos[a];
-        double ga[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            ga[i] = active ? G.g[a][i] : 0.0;
-        const double s = dot3(ga, ga);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const double want = active ? entry(ga, ga, s, G, kDiagP[k], kDiagQ[k], true) : 0.0;
-            bad = bad || __double_as_longlong(c[k]) != __double_as_longlong(want);
+    for (int k = 0; k < kShare; ++k) {
+        lid[k] = *(n_host > 0 ? ids + min(tid + k * kThreads, n_host - 1) : &kNoTet);
+        lst[k] = *(n_host > 0 ? states + min(tid + k * kThreads, n_host - 1) : &kNoState);
+    }
+    for (int h = tid; h < 1 << (log2 - 2); h += kThreads)
+        s_dynamic[h] = make_int4(-1, -1, -1, -1);
+    if (tid == 0)
+        s_bits = 0;
+    bool bad_n;
+    const int n = frame_count(n_host, n_dev, bad_n);
+    const bool mine = i < n && id >= 0 && id < v.n_tets;
+    BlockDesc bd = empty_desc();
+    uint8_t prev = 0;
+    bool degenerate = false;
+    if (mine) {  // in flight while the table is built
+        if (lane < (unit < 2 ? Unit<true>::kBlocks : Unit<false>::kBlocks))
+            bd = load_desc(v.trec[id].desc + 2 * unit + lane);
+        if (unit == 0) {
+            prev = v.mask[id];
+            degenerate = is_degenerate(v, id);
         }
     }
+    __syncthreads();
+    int bits = bad_n ? ERR_RANGE : 0;
+    const EditTable table{head, edit, log2};
+    int next[kShare];
+    bool valid[kShare];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const bool sw = id[PA[q]] > id[PB[q]];
-        double ga[3], gb[3];
+    for (int k = 0; k < kShare; ++k) {
+        const bool in = tid + k * kThreads < n;
+        valid[k] = in && (uint32_t)lid[k] < (uint32_t)v.n_tets && lst[k] <= 1;
+        bits |= in && !valid[k] ? ERR_RANGE : 0;
+        next[k] = atomicExch(head + (valid[k] ? table.bucket((uint32_t)lid[k]) : (1u << log2) + (uint32_t)lane),
+                             tid + k * kThreads);
+    }
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            ga[i] = active ? (sw ? G.g[PB[q]][i] : G.g[PA[q]][i]) : 0.0;
-            gb[i] = active ? (sw ? G.g[PA[q]][i] : G.g[PB[q]][i]) : 0.0;
+    for (int k = 0; k < kShare; ++k) {
+        next[k] = valid[k] ? next[k] : -1;
+        edit[tid + k * kThreads] = make_int2((int)((uint32_t)lid[k] << 1 | (lst[k] & 1u)), next[k]);
+    }
+    __syncthreads();
+    // in flight while duplicates are looked for
+    UnitTerms<true> bdiag{};
+    UnitTerms<false> boff{};
+    uint32_t u = 0;
+    if (mine) {
+        if (unit < 2) {
+            bdiag = unit_terms<true>(bd);
+            u = load_incidence<true>(v, bdiag, 0);
+        } else {
+            boff = unit_terms<false>(bd);
+            u = load_incidence<false>(v, boff, 0);
         }
-        const double s = dot3(ga, gb);
-        const double* c = v.co + 9 * (size_t)pos[4 + q];
+    }
+    // a duplicate finds its twin further down its own chain
+    bool more = false;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int k = 0; k < kShare; ++k)
+        more |= next[k] >= 0;
+    while (more) {
+        int2 t[kShare];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const double want = active ? entry(ga, gb, s, G, i, j, false) : 0.0;
-                bad = bad || __double_as_longlong(c[3 * i + j]) != __double_as_longlong(want);
+        for (int k = 0; k < kShare; ++k)
+            t[k] = edit[next[k] >= 0 ? next[k] : 0];
+        more = false;
+#pragma unroll
+        for (int k = 0; k < kShare; ++k)
+            if (next[k] >= 0) {
+                bits |= (uint32_t)t[k].x >> 1 == (uint32_t)lid[k] ? ERR_DUP : 0;
+                next[k] = t[k].y;
+                more |= next[k] >= 0;
             }
     }
+    if (bits)
+        atomicOr(&s_bits, bits);
+    if (unit == 0 && lane == 0)
+        s_change[own] = prev != st;
+    __syncthreads();
+    const int fe = s_bits;
+    publish_frame(v, fe, n, -1);
+    if (fe || !mine)
+        return;
+    const bool change = s_change[own] != 0;
+    if (unit == 0 && lane == 0) {
+        v.undo[i] = change ? prev : (uint8_t)0xFF;
+        reinterpret_cast<int32_t*>(v.rec)[i] = id;
+        if (change) {
+            v.mask[id] = (uint8_t)st;
+            if (st && degenerate)
+                atomicOr(&v.ctl->err, ERR_DEGENERATE);
+        }
+    }
+    if (!change)
+        return;
+    if (unit < 2)
+        sum_unit<true>(v, bd, bdiag, u, s_val[own] + unit * kDiagUnitDoubles, table);
+    else
+        sum_unit<false>(v, bd, boff, u, s_val[own] + 2 * kDiagUnitDoubles, table);
+}
+
+// Statistics of a frame of k_once: the distinct blocks of its changed tets
+// (claimed through their stamps) and their incidences, diagonal and
+// off-diagonal, into count[0..3]; then the stamps are released.
+__global__ __launch_bounds__(kBlock) void k_once_stats(DevView v, int n, unsigned long long* count, int release)
+{
+    const int t = blockIdx.x * kBlock + threadIdx.x, i = t / kEditLanes, r = t % kEditLanes;
+    if (i >= n || r >= 10 || v.undo[i] == 0xFF)
+        return;
+    const BlockDesc d = load_desc(v.trec[reinterpret_cast<const int32_t*>(v.rec)[i]].desc + r);
+    if (release) {
+        v.bstamp[d.block] = 0u;
+    } else if (atomicExch(&v.bstamp[d.block], 1u) == 0u) {
+        atomicAdd(count + (d.kind == 0 ? 0 : 1), 1ull);
+        atomicAdd(count + (d.kind == 0 ? 2 : 3), (unsigned long long)(d.k1 - d.k0));
+    }
+}
+
+// Audit: 1 if tet e's stored geometry differs in any bit from what the
+// rebuild would store.
+__device__ __forceinline__ int audit_element(const DevView& v, int e)
+{
+    Geo G;
+    element_geometry(v, e, v.T[e], G);
+    const TetGeo* q = reinterpret_cast<const TetGeo*>(v.geo) + e;
+    auto differs = [](double x, double y) { return __double_as_longlong(x) != __double_as_longlong(y); };
+    bool bad = differs(q->lamV, G.lamV) || differs(q->muV, G.muV) || differs(q->ml, G.ml);
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        bad = bad || differs(q->g[k], G.g[k / 3][k % 3]);
     return bad ? 1 : 0;
 }
 
@@ -1189,27 +1219,6 @@ __global__ __launch_bounds__(kBlock) void k_set_params(int n_nodes, int n_tets, 
         Eout[i] = Ein[i];
 }
 
-// The geometry part of every tet record, from the current coordinates and
-// moduli, by the rebuild's own routine (element_geometry).
-__global__ __launch_bounds__(kBlock) void k_refresh_records(DevView v, TetRecord* __restrict__ trec)
-{
-    const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (e >= v.n_tets)
-        return;
-    Geo G;
-    element_geometry(v, e, v.T[e], G);
-    TetRecord& rc = trec[e];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            rc.g[3 * a + i] = G.g[a][i];
-    rc.lamV = G.lamV;
-    rc.muV = G.muV;
-    rc.ml = G.ml;
-    rc.degenerate = G.det == 0.0 ? 1 : 0;
-}
-
 inline unsigned blocks_for(int64_t threads)
 {
     return (unsigned)((threads + kBlock - 1) / kBlock);
@@ -1217,61 +1226,33 @@ inline unsigned blocks_for(int64_t threads)
 
 }  // namespace
 
-// Dynamic LDS of the element kernel, reserved and unused: with its 18 KB of
-// staging it makes 44 KB per workgroup, three workgroups per CU instead of
-// the five its registers allow; fewer tets in flight keep their node
-// coordinates and staged lines in cache (on the 384k-tet cube: 61.0 -> 57.4 us
-// per rebuild, same bits; two per CU 58.6 us, four 60.0 us).
-constexpr uint32_t kElementReservedLds = 26 << 10;
-
-hipError_t launch_element(const DevView& v, bool nt, hipStream_t s)
+hipError_t launch_geometry(const DevView& v, hipStream_t s)
 {
     if (v.n_tets == 0)
         return hipSuccess;
-    if (nt)
-        launch_kernel(&k_element<true>, dim3(blocks_for(v.n_tets)), dim3(kBlock), kElementReservedLds, s, v);
-    else
-        launch_kernel(&k_element<false>, dim3(blocks_for(v.n_tets)), dim3(kBlock), kElementReservedLds, s, v);
+    launch_kernel(&k_geometry, dim3(blocks_for(v.n_tets)), dim3(kBlock), 0, s, v);
     return hipGetLastError();
 }
 
-#define STA_MAPPINGS(X) X(1, 1) X(1, 4) X(4, 1) X(4, 4) X(16, 1) X(16, 4)
-
-// Whether some incidence-length bucket uses fewer lanes than the allocation.
-bool mixed_map(const MapConfig& m)
+hipError_t launch_rows(const DevView& v, bool nt, hipStream_t s)
 {
-    for (int b = 0; b < kDiagBuckets; ++b)
-        if (m.qdb[b] != m.qd)
-            return true;
-    for (int b = 0; b < kOffBuckets; ++b)
-        if (m.qob[b] != m.qo)
-            return true;
-    return false;
+    if (v.n_tiles == 0)
+        return hipSuccess;
+    if (nt)
+        launch_kernel(&k_rows<true>, dim3(v.n_tiles), dim3(kRowThreads), 0, s, v);
+    else
+        launch_kernel(&k_rows<false>, dim3(v.n_tiles), dim3(kRowThreads), 0, s, v);
+    return hipGetLastError();
 }
 
-hipError_t launch_reduce_all(const DevView& v, const MapConfig& m, hipStream_t s)
+hipError_t launch_rows_big(const DevView& v, bool always, hipStream_t s)
 {
-    const int64_t diag_lanes = ((int64_t)v.nd * 6 * m.qd + 63) / 64 * 64;
-    const int64_t threads = diag_lanes + (m.qo == 1 ? ((int64_t)v.no + 6) / 7 * 64 : (int64_t)v.no * 9 * m.qo);
-    if (v.nd + v.no == 0)
+    const int waves = (v.n_bigd + Unit<true>::kBlocks - 1) / Unit<true>::kBlocks +
+                      (v.n_bigo + Unit<false>::kBlocks - 1) / Unit<false>::kBlocks;
+    if (waves == 0 && !always)
         return hipSuccess;
-    const bool mixed = mixed_map(m);
-#define LAUNCH(QD, QO)                                                                                    \
-    if (m.qd == QD && m.qo == QO) {                                                                       \
-        const dim3 g(blocks_for(threads));                                                                \
-        if (mixed && m.nt)                                                                                \
-            launch_kernel(&k_reduce_all<QD, QO, true, true>, g, dim3(kBlock), 0, s, v, diag_lanes, m);    \
-        else if (mixed)                                                                                   \
-            launch_kernel(&k_reduce_all<QD, QO, true, false>, g, dim3(kBlock), 0, s, v, diag_lanes, m);   \
-        else if (m.nt)                                                                                    \
-            launch_kernel(&k_reduce_all<QD, QO, false, true>, g, dim3(kBlock), 0, s, v, diag_lanes, m);   \
-        else                                                                                              \
-            launch_kernel(&k_reduce_all<QD, QO, false, false>, g, dim3(kBlock), 0, s, v, diag_lanes, m);  \
-        return hipGetLastError();                                                                         \
-    }
-    STA_MAPPINGS(LAUNCH)
-#undef LAUNCH
-    return hipErrorInvalidValue;
+    launch_kernel(&k_rows_big, dim3(waves > 0 ? (waves + kBlock / 64 - 1) / (kBlock / 64) : 1), dim3(kBlock), 0, s, v);
+    return hipGetLastError();
 }
 
 hipError_t launch_edit_phase(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
@@ -1295,81 +1276,87 @@ hipError_t launch_delta_frame(const DevView& v, const int32_t* ids, const uint8_
     return hipGetLastError();
 }
 
-hipError_t launch_touched_phase(const DevView& v, const MapConfig& m, const int32_t* ids, int32_t n_host,
-                                const int32_t* n_dev, hipStream_t s)
+bool frame_fits_once(int32_t n_host)
 {
-#define LAUNCH(QD, QO)                                                                                      \
-    if (m.qd == QD && m.qo == QO) {                                                                         \
-        const int64_t regions = (n_host > 0 ? ((int64_t)n_host * kEditLanes + kBlock - 1) / kBlock : 1) * kRegionsPerBlock; \
-        const int64_t lanes = regions * Phase2<QD, QO>::kRegionLanes + n_host;                              \
-        if (mixed_map(m))                                                                                   \
-            launch_kernel(&k_touched<QD, QO, true>, dim3(blocks_for(lanes)), dim3(kBlock), 0, s, v, ids,    \
-                          n_host, n_dev, m);                                                                \
-        else                                                                                                \
-            launch_kernel(&k_touched<QD, QO, false>, dim3(blocks_for(lanes)), dim3(kBlock), 0, s, v, ids,   \
-                          n_host, n_dev, m);                                                                \
-        return hipGetLastError();                                                                           \
-    }
-    STA_MAPPINGS(LAUNCH)
-#undef LAUNCH
-    return hipErrorInvalidValue;
+    return n_host <= kOnceMax;
 }
 
-hipError_t frame_max_grid(const MapConfig& m, int device, int* max_grid)
+hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
+                       const int32_t* n_dev, hipStream_t s)
+{
+    int log2 = 8;  // buckets: at least the edits, up to 2048
+    while ((1 << log2) < n_host && log2 < 11)
+        ++log2;
+#define ONCE(E, S)                                                                                           \
+    if (n_host <= 64 * kUnits * E * S) {                                                                     \
+        launch_kernel(&k_once<E, S>, dim3(n_host > 0 ? (n_host + E - 1) / E : 1), dim3(64 * kUnits * E),     \
+                      (uint32_t)(sizeof(int32_t) * ((1 << log2) + kOnceSpare) +                              \
+                                 sizeof(int2) * 64 * kUnits * E * S),                                        \
+                      s, v, ids, states, n_host, n_dev, log2);                                               \
+        return hipGetLastError();                                                                            \
+    }
+    ONCE(1, 1)
+    ONCE(2, 2)
+    ONCE(4, 3)
+#undef ONCE
+    return hipErrorInvalidValue;
+}
+static_assert(kOnceMax == 64 * kUnits * 4 * 3, "the largest variant covers the largest list");
+
+hipError_t launch_once_stats(const DevView& v, int32_t n, unsigned long long* counts4, hipStream_t s)
+{
+    hipError_t e = hipMemsetAsync(counts4, 0, 4 * sizeof(unsigned long long), s);
+    for (int release = 0; release <= 1 && e == hipSuccess && n > 0; ++release) {
+        hipLaunchKernelGGL(k_once_stats, dim3(blocks_for((int64_t)n * kEditLanes)), dim3(kBlock), 0, s, v, n, counts4,
+                           release);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
+// Lanes of phase 2: the regions' waves, then one lane per edit.
+static int64_t touched_lanes(int32_t n_host, int region_waves)
+{
+    const int64_t regions = (n_host > 0 ? ((int64_t)n_host * kEditLanes + kBlock - 1) / kBlock : 1) * kRegionsPerBlock;
+    return regions * region_waves * 64 + n_host;
+}
+
+hipError_t launch_touched_phase(const DevView& v, const int32_t* ids, int32_t n_host, const int32_t* n_dev,
+                                hipStream_t s)
+{
+    launch_kernel(&k_touched, dim3(blocks_for(touched_lanes(n_host, TouchedWaves::kWaves))), dim3(kBlock), 0, s, v, ids, n_host, n_dev);
+    return hipGetLastError();
+}
+
+hipError_t frame_max_grid(int device, int* max_grid)
 {
     int cus = 0, per_cu = 0;
     hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
-    if (e != hipSuccess)
-        return e;
-#define OCC(QD, QO)                                                                                        \
-    if (m.qd == QD && m.qo == QO)                                                                          \
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(                                                  \
-            &per_cu, mixed_map(m) ? (const void*)&k_frame<QD, QO, true> : (const void*)&k_frame<QD, QO, false>, \
-            kBlock, 0);
-    STA_MAPPINGS(OCC)
-#undef OCC
-    if (e != hipSuccess)
-        return e;
-    *max_grid = per_cu * cus;
-    return hipSuccess;
+    if (e == hipSuccess)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&k_frame, kBlock, 0);
+    if (e == hipSuccess)
+        *max_grid = per_cu * cus;
+    return e;
 }
 
-int frame_grid_for(const MapConfig& m, int32_t n_host, int max_grid, int grid_cap)
+int frame_grid_for(int32_t n_host, int max_grid, int grid_cap)
 {
-    int L = 16;
-#define LANES(QD, QO)                 \
-    if (m.qd == QD && m.qo == QO)     \
-        L = Phase2<QD, QO>::kRegionLanes;
-    STA_MAPPINGS(LANES)
-#undef LANES
-    const int64_t regions = (n_host > 0 ? ((int64_t)n_host * kEditLanes + kBlock - 1) / kBlock : 1) * kRegionsPerBlock;
-    const int64_t want = (regions * L + n_host + kBlock - 1) / kBlock;
+    const int64_t want = (touched_lanes(n_host, FusedWaves::kWaves) + kBlock - 1) / kBlock;
     int64_t g = want < max_grid ? want : max_grid;
     if (grid_cap > 0 && g > grid_cap)
         g = grid_cap;
     return (int)(g < 1 ? 1 : g);
 }
 
-hipError_t launch_frame(const DevView& v, const MapConfig& m, int grid, const int32_t* ids, const uint8_t* states,
-                        int32_t n_host, const int32_t* n_dev, unsigned spin_limit, hipStream_t s)
+hipError_t launch_frame(const DevView& v, int grid, const int32_t* ids, const uint8_t* states, int32_t n_host,
+                        const int32_t* n_dev, unsigned spin_limit, hipStream_t s)
 {
-#define LAUNCH(QD, QO)                                                                                        \
-    if (m.qd == QD && m.qo == QO) {                                                                           \
-        if (mixed_map(m))                                                                                     \
-            launch_kernel(&k_frame<QD, QO, true>, dim3(grid), dim3(kBlock), 0, s, v, ids, states, n_host,     \
-                          n_dev, m, spin_limit);                                                              \
-        else                                                                                                  \
-            launch_kernel(&k_frame<QD, QO, false>, dim3(grid), dim3(kBlock), 0, s, v, ids, states, n_host,    \
-                          n_dev, m, spin_limit);                                                              \
-        return hipGetLastError();                                                                             \
-    }
-    STA_MAPPINGS(LAUNCH)
-#undef LAUNCH
-    return hipErrorInvalidValue;
+    launch_kernel(&k_frame, dim3(grid), dim3(kBlock), 0, s, v, ids, states, n_host, n_dev, spin_limit);
+    return hipGetLastError();
 }
 
-hipError_t launch_audit(const DevView& v, const MapConfig& m, double* scratch_values, int64_t nnz,
-                        unsigned long long* counts, hipStream_t s)
+hipError_t launch_audit(const DevView& v, double* scratch_values, int64_t nnz, unsigned long long* counts,
+                        hipStream_t s)
 {
     hipError_t e = hipSuccess;
     if (v.n_tets > 0) {
@@ -1380,7 +1367,9 @@ hipError_t launch_audit(const DevView& v, const MapConfig& m, double* scratch_va
         return e;
     DevView w = v;
     w.values = scratch_values;
-    e = launch_reduce_all(w, m, s);
+    e = launch_rows(w, false, s);
+    if (e == hipSuccess)
+        e = launch_rows_big(w, false, s);
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL(k_audit_values, dim3(blocks_for(nnz)), dim3(kBlock), 0, s, v.values, scratch_values, nnz,
@@ -1394,14 +1383,6 @@ hipError_t launch_clear_stamps(const DevView& v, hipStream_t s)
     if (n == 0)
         return hipSuccess;
     hipLaunchKernelGGL(k_clear_stamps, dim3(blocks_for(n)), dim3(kBlock), 0, s, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_refresh_records(const DevView& v, TetRecord* trec, hipStream_t s)
-{
-    if (v.n_tets == 0)
-        return hipSuccess;
-    hipLaunchKernelGGL(k_refresh_records, dim3(blocks_for(v.n_tets)), dim3(kBlock), 0, s, v, trec);
     return hipGetLastError();
 }
 

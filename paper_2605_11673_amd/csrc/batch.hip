@@ -1,5 +1,5 @@
 // Batched contexts (many independent meshes in one context) and the
-// autotuner that picks the slot mapping and the frame execution mode.
+// autotuner that picks the rebuild's stores and the frame execution mode.
 //
 // A batch of meshes is their disjoint union: node, tet, row and value ranges
 // are concatenated, so every kernel of the single-mesh path applies
@@ -56,15 +56,6 @@ Cfg cfg_from(const int* x)
     for (int& v : c.sdb) v = x[k++];
     for (int& v : c.sob) v = x[k++];
     return c;
-}
-
-// Uniform mappings: every bucket as the allocation.
-void set_uniform(Cfg& c)
-{
-    for (int& v : c.rdb) v = c.rqd;
-    for (int& v : c.rob) v = c.rqo;
-    for (int& v : c.sdb) v = c.sqd;
-    for (int& v : c.sob) v = c.sqo;
 }
 
 Cfg current(const sta_ctx* ctx)
@@ -161,8 +152,6 @@ double median(std::vector<float> v)
     std::sort(v.begin(), v.end());
     return v.empty() ? 0.0 : v[v.size() / 2];
 }
-
-const int kMaps[6][2] = {{1, 1}, {1, 4}, {4, 1}, {4, 4}, {16, 1}, {16, 4}};
 
 }  // namespace
 
@@ -330,96 +319,48 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
         }
         return median(t) * 1e3;
     };
-    // one bucket at a time, each group size of that bucket alone; a change
-    // is kept only if it is at least 1% faster
-    auto refine = [&](Cfg& c, double& t_best, bool rebuild) {
-        const char* what = rebuild ? "rebuild" : "frame  ";
-        for (int bk = 0; bk < kDiagBuckets + kOffBuckets && st == STA_OK; ++bk) {
-            if (ctx->bucket_blocks[bk] == 0)
-                continue;
-            const bool diag = bk < kDiagBuckets;
-            const int nq = diag ? 3 : 2;
-            const int qs[3] = {1, 4, 16};
-            int* slot = diag ? (rebuild ? &c.rdb[bk] : &c.sdb[bk])
-                             : (rebuild ? &c.rob[bk - kDiagBuckets] : &c.sob[bk - kDiagBuckets]);
-            const int keep = *slot;
-            int chosen = keep;
-            for (int k = 0; k < nq && st == STA_OK; ++k) {
-                if (qs[k] == keep)
-                    continue;
-                *slot = qs[k];
-                const double t = rebuild ? time_rebuild(c) : time_frame(c);
-                std::snprintf(line, sizeof line, "%s  bucket %s%d (%lld blocks) q %2d: %9.2f us\n", what,
-                              diag ? "d" : "o", diag ? bk : bk - kDiagBuckets, (long long)ctx->bucket_blocks[bk],
-                              qs[k], t);
-                rep += line;
-                if (t < 0.99 * t_best) {
-                    t_best = t;
-                    chosen = qs[k];
-                }
-            }
-            *slot = chosen;
-        }
-    };
-
-    // 1. rebuild: uniform mappings, then per bucket
-    double best_t = 1e30;
+    // The slot mapping stays as it was set: the sums are computed one way whatever it says.
     best = saved;
-    for (int nt = 0; nt <= 1 && st == STA_OK; ++nt)
-        for (auto& m : kMaps) {
-            Cfg c = saved;
-            c.rqd = m[0], c.rqo = m[1], c.nt = nt;
-            set_uniform(c);
-            const double med = time_rebuild(c);
-            std::snprintf(line, sizeof line, "rebuild  map %2dx%d nt %d: %9.2f us\n", m[0], m[1], nt, med);
-            rep += line;
-            if (med < best_t) {
-                best_t = med;
-                best.rqd = m[0];
-                best.rqo = m[1];
-                best.nt = nt;
-            }
-        }
-    for (int bk = 0; bk < kDiagBuckets; ++bk)
-        best.rdb[bk] = best.rqd;
-    for (int bk = 0; bk < kOffBuckets; ++bk)
-        best.rob[bk] = best.rqo;
-    refine(best, best_t, true);
-    // the allocation is the largest group of any bucket
-    best.rqd = std::max({best.rdb[0], best.rdb[1], best.rdb[2]});
-    best.rqo = std::max(best.rob[0], best.rob[1]);
+    for (int bk = 0; bk < kDiagBuckets + kOffBuckets; ++bk) {
+        if (ctx->bucket_blocks[bk] == 0)
+            continue;
+        const bool diag = bk < kDiagBuckets;
+        std::snprintf(line, sizeof line, "bucket %s%d (%lld blocks): one computation for every mapping\n",
+                      diag ? "d" : "o", diag ? bk : bk - kDiagBuckets, (long long)ctx->bucket_blocks[bk]);
+        rep += line;
+    }
 
-    // 2. streaming frame: mapping x mode, then per bucket
+    // 1. rebuild: cached or non-temporal stores
+    double best_t = 1e30;
+    for (int nt = 0; nt <= 1 && st == STA_OK; ++nt) {
+        Cfg c = saved;
+        c.nt = nt;
+        const double med = time_rebuild(c);
+        std::snprintf(line, sizeof line, "rebuild  nt %d: %9.2f us\n", nt, med);
+        rep += line;
+        if (med < best_t) {
+            best_t = med;
+            best.nt = nt;
+        }
+    }
+
+    // 2. streaming frame: the library's choice for the size, or one launch with a grid barrier
     best_t = 1e30;
     const int caps[3] = {0, 256, 1024};
     for (int fused = 0; fused <= 1 && st == STA_OK; ++fused)
-        for (auto& m : kMaps)
-            for (int ci = 0; ci < (fused ? 3 : 1) && st == STA_OK; ++ci) {
-                Cfg c = best;
-                c.fused = fused, c.sqd = m[0], c.sqo = m[1], c.cap = caps[ci];
-                for (int bk = 0; bk < kDiagBuckets; ++bk)
-                    c.sdb[bk] = m[0];
-                for (int bk = 0; bk < kOffBuckets; ++bk)
-                    c.sob[bk] = m[1];
-                const double med = time_frame(c);
-                std::snprintf(line, sizeof line, "frame    %s map %2dx%d cap %4d: %9.2f us\n",
-                              fused ? "fused" : "2-launch", m[0], m[1], caps[ci], med);
-                rep += line;
-                if (med < best_t) {
-                    best_t = med;
-                    best.fused = fused;
-                    best.sqd = m[0];
-                    best.sqo = m[1];
-                    best.cap = caps[ci];
-                }
+        for (int ci = 0; ci < (fused ? 3 : 1) && st == STA_OK; ++ci) {
+            Cfg c = best;
+            c.fused = fused, c.cap = caps[ci];
+            const double med = time_frame(c);
+            std::snprintf(line, sizeof line, "frame    %s cap %4d: %9.2f us\n", fused ? "fused" : "default", caps[ci],
+                          med);
+            rep += line;
+            if (med < best_t) {
+                best_t = med;
+                best.fused = fused;
+                best.cap = caps[ci];
             }
-    for (int bk = 0; bk < kDiagBuckets; ++bk)
-        best.sdb[bk] = best.sqd;
-    for (int bk = 0; bk < kOffBuckets; ++bk)
-        best.sob[bk] = best.sqo;
-    refine(best, best_t, false);
-    best.sqd = std::max({best.sdb[0], best.sdb[1], best.sdb[2]});
-    best.sqo = std::max(best.sob[0], best.sob[1]);
+        }
 
     ctx->timing = saved_timing;
     if (st == STA_OK && hipStreamSynchronize(s) == hipSuccess && sta_status_sync(ctx, stream) == STA_OK) {

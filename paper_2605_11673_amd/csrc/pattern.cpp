@@ -170,4 +170,110 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
     return "";
 }
 
+void build_row_plan(int64_t n, const int32_t* tets, int64_t m, const HostPattern& P,
+                    const std::vector<int64_t>& node_off, RowPlan& R)
+{
+    auto local = [&](int64_t e, int32_t node) {
+        for (int a = 0; a < 4; ++a)
+            if (tets[4 * e + a] == node)
+                return (uint32_t)a;
+        return 0u;
+    };
+    // incidences with their local vertices
+    R.di.resize((size_t)m * 4);
+    R.oi.resize((size_t)m * 6);
+    for (int64_t e = 0; e < m; ++e)
+        for (int a = 0; a < 4; ++a)
+            R.di[P.e2p[10 * e + a]] = (uint32_t)e << 2 | (uint32_t)a;
+    for (int64_t o = 0; o < P.no; ++o)
+        for (int32_t k = P.oseg[o]; k < P.oseg[o + 1]; ++k) {
+            const int64_t e = P.oinc[k];
+            R.oi[k] = (uint32_t)e << 4 | local(e, P.opair[2 * o]) << 2 | local(e, P.opair[2 * o + 1]);
+        }
+    // per row block (9 CSR values each) its off-diagonal block and whether the row is its upper node
+    const int64_t nb = P.nnz / 9;
+    std::vector<int32_t> row_off((size_t)nb, -1);
+    for (int64_t o = 0; o < P.no; ++o) {
+        const int64_t i = P.opair[2 * o], j = P.opair[2 * o + 1];
+        row_off[P.rowptr[3 * i] / 9 + (P.ometa[4 * o + 0] - P.rowptr[3 * i]) / 3] = (int32_t)(2 * o);
+        row_off[P.rowptr[3 * j] / 9 + (P.ometa[4 * o + 2] - P.rowptr[3 * j]) / 3] = (int32_t)(2 * o + 1);
+    }
+    R.rowblk.assign((size_t)nb, make_uint2(0, 0));
+    std::vector<uint8_t> big_off((size_t)P.no, 0);
+    size_t mesh = 0;
+    bool open = false;
+    for (int64_t i = 0; i < n; ++i) {
+        while (mesh + 2 < node_off.size() && i >= node_off[mesh + 1]) {
+            ++mesh;
+            open = false;
+        }
+        const int32_t d = P.ndiag[i];
+        if (d < 0)
+            continue;
+        const int32_t b0 = P.rowptr[3 * i] / 9, b1 = P.rowptr[3 * i + 3] / 9;
+        const int pairs = P.dseg[d + 1] - P.dseg[d];
+        int64_t terms = 0;
+        for (int32_t b = b0; b < b1; ++b)
+            if (row_off[b] >= 0)
+                terms += P.oseg[row_off[b] / 2 + 1] - P.oseg[row_off[b] / 2];
+        if (pairs > kTilePairs || b1 - b0 > kTileBlocks || terms > kTileTerms) {
+            R.bigd.push_back(d);
+            R.bigd_mesh.push_back((int32_t)mesh);
+            for (int32_t b = b0; b < b1; ++b)
+                if (row_off[b] >= 0)
+                    big_off[row_off[b] / 2] = 1;
+            open = false;
+            continue;
+        }
+        if (open) {
+            const RowTile& t = R.tiles.back();
+            open = t.pairs + pairs <= kTilePairs && t.blks + (b1 - b0) <= kTileBlocks && t.nodes < kTileNodes &&
+                   t.terms + terms <= kTileTerms && t.pair0 + t.pairs == P.dseg[d] && t.blk0 + t.blks == b0;
+        }
+        if (!open) {
+            RowTile t{};
+            t.pair0 = P.dseg[d];
+            t.blk0 = b0;
+            t.term0 = (int32_t)R.terms.size();
+            t.val0 = P.rowptr[3 * i];
+            t.node0 = (int32_t)R.rownode.size();
+            R.tiles.push_back(t);
+            R.tile_mesh.push_back((int32_t)mesh);
+            open = true;
+        }
+        RowTile& t = R.tiles.back();
+        const uint32_t rl = (uint32_t)(3 * (b1 - b0));
+        const uint32_t p0 = (uint32_t)t.pairs, row0 = (uint32_t)(P.rowptr[3 * i] - t.val0);
+        for (int32_t b = b0; b < b1; ++b) {
+            const uint32_t at = row0 + 3u * (uint32_t)(b - b0), first = (uint32_t)t.terms;
+            if (row_off[b] >= 0) {
+                const int32_t o = row_off[b] / 2;
+                for (int32_t k = P.oseg[o]; k < P.oseg[o + 1]; ++k) {
+                    const int64_t e = P.oinc[k];
+                    const uint32_t u = R.oi[k] & 15u;
+                    const uint32_t a = row_off[b] % 2 ? u & 3u : u >> 2, c = row_off[b] % 2 ? u >> 2 : u & 3u;
+                    const uint32_t p = p0 + (uint32_t)(P.e2p[10 * e + a] - P.dseg[d]);
+                    R.terms.push_back((uint16_t)(p << 4 | a << 2 | c));
+                    ++t.terms;
+                }
+            }
+            R.rowblk[b] = make_uint2(first | ((uint32_t)t.terms - first) << 16, at | rl << 16);
+            if (row_off[b] < 0)
+                R.rownode.push_back(make_uint2(p0 | (uint32_t)pairs << 16, at | rl << 16));
+        }
+        t.pairs += pairs;
+        t.blks += b1 - b0;
+        t.nodes += 1;
+    }
+    mesh = 0;
+    for (int64_t o = 0; o < P.no; ++o) {
+        while (mesh + 2 < node_off.size() && P.opair[2 * o] >= node_off[mesh + 1])
+            ++mesh;
+        if (big_off[o]) {
+            R.bigo.push_back((int32_t)(P.nd + o));
+            R.bigo_mesh.push_back((int32_t)mesh);
+        }
+    }
+}
+
 }  // namespace sta

@@ -32,7 +32,8 @@ struct Ctl {
     int32_t last_n;      // edit count of the last frame (statistics; also right under graph replay)
     uint32_t bar_count;  // grid barrier of the fused frame kernel: arrivals
     uint32_t bar_gen;    // and generation
-    int32_t last_regions;  // claim regions of the last frame (one per edit-phase wave of 4 edits)
+    int32_t last_regions;  // claim regions of the last frame (one per edit-phase wave of 4 edits); -1: a frame
+                           // that claims nothing (its edits' ids and undo bytes tell what it touched)
     int32_t pad;
 };
 
@@ -103,14 +104,13 @@ __host__ __device__ inline int off_bucket(int kappa)
     return kappa <= 8 ? 0 : 1;
 }
 
-// Slot mapping: lanes per block value (1 thread-, 4 quad-, 16
-// wave-sixteenth-per-slot; diagonal 1/4/16, off-diagonal 1/4), chosen per
-// incidence-length bucket (qdb, qob).  qd / qo are the lanes allocated per
-// value, the largest bucket mapping; a block whose bucket uses fewer leaves
-// the rest of its lanes idle.
+// Slot mapping as the caller set it: lanes per block value (diagonal 1/4/16,
+// off-diagonal 1/4) per incidence-length bucket (qdb, qob), qd / qo the
+// largest of each.  Kept and reported; the sums are computed one lane per
+// term, then one lane per value, whatever it says.
 struct MapConfig {
     int qd = 1, qo = 1;
-    int nt = 0;  // non-temporal cache hints (rebuild only)
+    int nt = 0;  // non-temporal stores of the values (rebuild only)
     int qdb[kDiagBuckets] = {1, 1, 1};
     int qob[kOffBuckets] = {1, 1};
 };
@@ -148,33 +148,58 @@ struct BlockDesc {
     int32_t block;   // block id
 };
 
-// Everything the edit phase reads about one candidate tet, packed in one
-// 512-byte record so that an edit needs a single memory round trip before
-// its atomics: the tet's 10 block descriptors (local pairs 00 11 22 33 | 01
-// 02 03 12 13 23), its geometry as the element formula uses it (basis
-// gradients g_0..g_3, lamV, muV and the lumped mass per vertex, computed on
-// the device by the same routine as the rebuild's, so an activation
-// reproduces the rebuild's bits without redoing the determinant and the
-// inverse; refreshed by sta_set_params), a flag for det == 0, its vertex ids
-// and its 10 incidence positions.
+// A candidate tet's 10 block descriptors (local pairs 00 11 22 33 | 01 02 03
+// 12 13 23), packed so that an edit reaches all of them in one memory round
+// trip.
 struct TetRecord {
     BlockDesc desc[10];
-    double g[12];  // g_a component i at 3a + i
-    int4 T;
-    double lamV, muV, ml;  // lamV at a 16-byte boundary (read with muV as one 16-byte load)
-    int32_t pos[10];
-    int32_t degenerate;  // det == 0
-    int32_t pad[3];
 };
-static_assert(sizeof(TetRecord) == 512, "tet record is 512 bytes");
-static_assert(offsetof(TetRecord, lamV) % 16 == 0, "lamV and muV are read as one 16-byte load");
+
+// A candidate tet's geometry as the element formula uses it (basis gradients
+// g_0..g_3, lamV, muV and the lumped mass per vertex), one 128-byte line.
+// Every matrix entry is summed from these records: a 9-value element block
+// needs two gradients and two or three scalars of its tet, so the records (49
+// MB on the 384k-tet cube) replace 240 MB of stored 78-value contributions
+// that the rebuild wrote and read back.  Computed by the rebuild's geometry
+// pass for every candidate, active or not, so that an activation finds its
+// record ready.
+struct TetGeo {
+    double g[12];  // g_a component i at 3a + i
+    double lamV, muV, ml;
+    int32_t degenerate;  // det == 0
+    int32_t pad;
+};
+static_assert(sizeof(TetGeo) == 128, "tet geometry is one 128-byte line");
+constexpr int kGeoDoubles = 16;  // doubles per record; the first 15 hold values
+
+// Rows of the rebuild.  A tile is a run of consecutive nodes whose CSR rows
+// one workgroup computes and writes as one contiguous range.  Its pairs are
+// the nodes' diagonal incidences (a tet and which of its vertices the node
+// is), contiguous in di; its row blocks are the nodes' (node, neighbour)
+// blocks, contiguous in rowblk; its terms list, for each off-diagonal row
+// block in ascending tet id, the pair and the two local vertices.
+constexpr int kTilePairs = 192, kTileBlocks = 128, kTileNodes = 10, kTileTerms = 768;
+struct RowTile {
+    int32_t pair0, pairs;  // range of di
+    int32_t blk0, blks;    // range of rowblk
+    int32_t term0, terms;  // range of terms
+    int32_t val0;          // first CSR value of the tile
+    int32_t node0;         // first entry of rownode; the tile has `nodes` of them
+    int32_t nodes, pad[3];
+};
+static_assert(sizeof(RowTile) == 48, "row tile is read as three 16-byte loads");
+// Row block: x = first term in the tile | terms << 16 (none: diagonal), y =
+// position of its entry (0, 0) in the tile's values | row length << 16.
+// Row node: x = first pair in the tile | pairs << 16, y = position of the
+// diagonal block | row length << 16.  Term: pair in the node's segment's
+// tile << 4 | local vertex of the row node << 2 | local vertex of the column
+// node.
 
 // Everything the kernels need, passed by value.
 //
-// Invariant kept by every kernel: the contributions of an inactive tet are
-// +0.0 in all 78 of its incidence slots.  Block sums then run over the whole
-// segment without looking at the mask, and adding those +0.0 terms gives the
-// same bits as skipping them.
+// Block sums run over the whole incidence segment; an inactive tet's term is
+// +0.0, and adding it gives the same bits as skipping it (an accumulator that
+// starts at +0.0 never becomes -0.0).
 struct DevView {
     int32_t n_nodes, n_tets;
     int32_t nd, no;               // diagonal / off-diagonal 3x3 blocks
@@ -190,9 +215,18 @@ struct DevView {
     // incidence positions (into cd for the first 4, into co for the other 6)
     const int32_t* e2b;
     const int32_t* e2p;
-    const TetRecord* trec;        // per tet: what the edit phase reads
-    double* cd;                   // 6 unique values per diagonal incidence
-    double* co;                   // 9 values per off-diagonal incidence (block orientation)
+    const TetRecord* trec;        // per tet: its block descriptors
+    double* geo;                  // per tet: TetGeo
+    const uint32_t* di;           // per diagonal incidence: tet << 2 | local vertex
+    const uint32_t* oi;           // per off-diagonal incidence: tet << 4 | row vertex << 2 | column vertex
+    // rebuild plan: tiles of rows, and the blocks of nodes too large for a tile
+    const RowTile* tiles;
+    const uint2* rowblk;
+    const uint2* rownode;
+    const uint16_t* terms;
+    const int32_t* bigd;          // diagonal blocks of large nodes
+    const int32_t* bigo;          // off-diagonal blocks with a large node
+    int32_t n_tiles, n_bigd, n_bigo;
     double* values;               // CSR values
     // streaming state
     // Stamps are 1 only while a frame is in flight: the edit phase sets them,
@@ -202,6 +236,7 @@ struct DevView {
     // Claimed blocks of the frame, compacted per edit-phase wave (4 edits):
     // region w holds up to 16 diagonal then 24 off-diagonal block
     // descriptors; rcount[2w], rcount[2w+1] say how many of each are valid.
+    // A frame of one launch claims nothing and keeps its edits' tet ids here.
     BlockDesc* rec;
     int32_t* rcount;
     uint8_t* undo;                // per edit: previous mask value, 0xFF = nothing to undo
@@ -246,7 +281,7 @@ struct sta_ctx {
     int64_t bucket_blocks[sta::kDiagBuckets + sta::kOffBuckets] = {};  // blocks per incidence-length bucket
     int fused = 0;          // 1: one persistent launch per frame
     int frame_grid_cap = 0; // 0: occupancy limit only
-    int frame_max_grid = 0; // co-resident workgroups for the fused kernel (per stream_map)
+    int frame_max_grid = 0; // co-resident workgroups for the fused kernel
     unsigned barrier_spin = sta::kBarrierSpinDefault;  // polls before the fused frame's barrier gives up
     bool fused_used = false;  // a fused frame ran since the last rebuild (stamps may be left taken)
     // per-call trace (environment variable STA_TRACE names a JSON-lines file)
@@ -276,8 +311,9 @@ struct sta_ctx {
     // batch layout: per mesh node / tet / value offsets (k+1 entries)
     std::vector<int64_t> node_off, tet_off, nnz_off;
     // A batch rebuilt in groups of consecutive meshes (empty: in one pass): per group its tet
-    // range, its diagonal block range and its off-diagonal block range, each [begin, end).
-    std::vector<std::array<int64_t, 6>> rebuild_groups;
+    // range, its tile range and its ranges of large diagonal and off-diagonal blocks, each [begin, end).
+    std::vector<std::array<int64_t, 8>> rebuild_groups;
+    unsigned long long* stat_ws = nullptr;  // frame statistics: 4 counters
     std::string errmsg;
     // per-kernel event timing
     bool timing = false;
@@ -313,34 +349,40 @@ inline void launch_kernel(void (*k)(KArgs...), dim3 grid, dim3 block, uint32_t s
 }
 
 // Kernel launchers (assembly.hip).
-hipError_t launch_element(const DevView& v, bool nt, hipStream_t s);
-hipError_t launch_reduce_all(const DevView& v, const MapConfig& m, hipStream_t s);
-// Streaming phases.  n_dev (device int32, may be NULL) overrides n_host, which
+hipError_t launch_geometry(const DevView& v, hipStream_t s);
+hipError_t launch_rows(const DevView& v, bool nt, hipStream_t s);
+// The blocks of nodes too large for a tile; nothing to do: launched only if always is set.
+hipError_t launch_rows_big(const DevView& v, bool always, hipStream_t s);
+// Streaming.  n_dev (device int32, may be NULL) overrides n_host, which
 // then only sizes the grid (an upper bound on the edit count).
+// One launch for a list that fits its table (frame_fits_once), else two phases.
+bool frame_fits_once(int32_t n_host);
+hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
+                       const int32_t* n_dev, hipStream_t s);
+// Blocks and incidences (diagonal, off-diagonal) touched by the last frame of launch_once.
+hipError_t launch_once_stats(const DevView& v, int32_t n, unsigned long long* counts4, hipStream_t s);
 hipError_t launch_edit_phase(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                              const int32_t* n_dev, hipStream_t s);
-hipError_t launch_touched_phase(const DevView& v, const MapConfig& m, const int32_t* ids, int32_t n_host,
-                                const int32_t* n_dev, hipStream_t s);
+hipError_t launch_touched_phase(const DevView& v, const int32_t* ids, int32_t n_host, const int32_t* n_dev,
+                                hipStream_t s);
 // +/- delta policy: one launch applying the edits' contributions with FP64
 // atomics, one releasing the tet stamps.
 hipError_t launch_delta_frame(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                               const int32_t* n_dev, hipStream_t s);
 // Fused frame: both phases in one persistent launch of `grid` co-resident workgroups.
-hipError_t frame_max_grid(const MapConfig& m, int device, int* max_grid);
-int frame_grid_for(const MapConfig& m, int32_t n_host, int max_grid, int grid_cap);
-hipError_t launch_frame(const DevView& v, const MapConfig& m, int grid, const int32_t* ids, const uint8_t* states,
-                        int32_t n_host, const int32_t* n_dev, unsigned spin_limit, hipStream_t s);
-// Audit: counts[1] += tets whose stored contributions differ from the rebuild's,
-// then the blocks re-summed from the stored contributions into scratch_values
-// (nnz) and counts[0] += values differing from the maintained ones.
-hipError_t launch_audit(const DevView& v, const MapConfig& m, double* scratch_values, int64_t nnz,
-                        unsigned long long* counts, hipStream_t s);
+hipError_t frame_max_grid(int device, int* max_grid);
+int frame_grid_for(int32_t n_host, int max_grid, int grid_cap);
+hipError_t launch_frame(const DevView& v, int grid, const int32_t* ids, const uint8_t* states, int32_t n_host,
+                        const int32_t* n_dev, unsigned spin_limit, hipStream_t s);
+// Audit: counts[1] += tets whose stored geometry differs from the rebuild's,
+// then the rows summed from the stored geometry into scratch_values (nnz) and
+// counts[0] += values differing from the maintained ones.
+hipError_t launch_audit(const DevView& v, double* scratch_values, int64_t nnz, unsigned long long* counts,
+                        hipStream_t s);
 // Release every tet and block stamp (a fill kernel, so that it can be captured).
 hipError_t launch_clear_stamps(const DevView& v, hipStream_t s);
 hipError_t launch_set_params(const DevView& v, const double* x_aos, const double* E, double* xs, double* ys,
                              double* zs, double* Eout, hipStream_t s);
-// Copy the current coordinates and moduli into the tet records.
-hipError_t launch_refresh_records(const DevView& v, TetRecord* trec, hipStream_t s);
 
 // Adjoint and CG launchers (adjoint.hip, cg.hip).
 // The adjoint visits the tets in chunks of kAdjointChunk consecutive ids, in
@@ -387,5 +429,18 @@ struct HostPattern {
 };
 // bs: rows per node (3: elasticity, 1: scalar proxy operator).
 std::string build_host_pattern(int64_t n_nodes, const int32_t* tets, int64_t n_tets, HostPattern& P, int bs = 3);
+
+// The rebuild's row tiles over a pattern of 3-row nodes (pattern.cpp).  No
+// tile crosses a node of node_off, so that a batch's tiles belong to one mesh.
+struct RowPlan {
+    std::vector<uint32_t> di, oi;
+    std::vector<RowTile> tiles;
+    std::vector<uint2> rowblk, rownode;
+    std::vector<uint16_t> terms;
+    std::vector<int32_t> bigd, bigo;
+    std::vector<int32_t> tile_mesh, bigd_mesh, bigo_mesh;  // mesh of each tile and large block, ascending
+};
+void build_row_plan(int64_t n_nodes, const int32_t* tets, int64_t n_tets, const HostPattern& P,
+                    const std::vector<int64_t>& node_off, RowPlan& R);
 
 }  // namespace sta

@@ -135,7 +135,7 @@ def _need_f64(t: torch.Tensor, n: int):
 
 
 class Assembler:
-    """One superset mesh: its fixed pattern, element contributions and current A_t.
+    """One superset mesh: its fixed pattern, element geometry and current A_t.
 
     x (n, 3) float64, tets (m, 4) int32, E (m,) float64, mask0 (m,) uint8 are
     host arrays; they are copied into the context.
@@ -363,7 +363,7 @@ class Assembler:
         return {"diag": list(qd), "off": list(qo), "diag_blocks": list(nb)[:3], "off_blocks": list(nb)[3:]}
 
     def autotune(self, ids: torch.Tensor, states: torch.Tensor, reps: int = 7, stream=None) -> str:
-        """Pick slot mappings and frame mode by timing (see sta_autotune); returns the report."""
+        """Pick the rebuild's stores and the frame mode by timing (see sta_autotune); returns the report."""
         buf = ctypes.create_string_buffer(8192)
         _check(load().sta_autotune(self._ctx, _dev_ptr(ids), _dev_ptr(states), int(ids.numel()), int(reps),
                                    _stream_handle(stream), buf, len(buf)), self._ctx)

@@ -1,0 +1,162 @@
+"""Sums from geometry records: every variant of the frame kernels at the edges of
+its range, tiles of rows and nodes too large for a tile, and records of inactive
+degenerate tets.  Everything bitwise against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_11673_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def S():
+    from paper_2605_11673_amd import stafem
+    return stafem
+
+
+def check(asm, want, what):
+    got = asm.values()
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()
+    bad = np.nonzero(got.view(np.uint64) != np.ascontiguousarray(want).view(np.uint64))[0]
+    assert len(bad) == 0, f"{what}: {len(bad)} values differ, first at {bad[0]}"
+
+
+def touched(w, ids):
+    """Distinct diagonal and off-diagonal blocks of the tets, and their incidences."""
+    t = np.sort(w.tets.astype(np.int64), axis=1)
+    pairs = [(0, 1), (0, 2), (0, 3), (1, 2), (1, 3), (2, 3)]
+    keys = np.stack([t[:, a] * w.n_nodes + t[:, b] for a, b in pairs], 1)
+    nodes, edges = np.unique(t[ids]), np.unique(keys[ids])
+    return (len(nodes), len(edges), int(np.isin(t, nodes).sum()), int(np.isin(keys, edges).sum()))
+
+
+@pytest.mark.parametrize("k", [1, 3, 191, 192, 193, 767, 768, 769, 2303, 2304, 2305, 2900])
+def test_frame_variants_at_their_edges(k):
+    """k edits in random order with random states (some change nothing), through the
+    host count and through a device count with k as the capacity; statistics; a
+    duplicate and an out-of-range id leave everything as it was."""
+    Sm = S()
+    w = W.make_fracture(seed=k, n=8, counts=[10])
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    g = np.random.default_rng(k)
+    asm = Sm.Assembler.from_workload(w)
+    mask = w.mask0.copy()
+    for step in range(3):
+        ids = g.permutation(w.n_tets)[:k].astype(np.int32)
+        st = g.integers(0, 2, size=k).astype(np.uint8)
+        n = k if step != 1 else max(1, k - 7)
+        di, ds = Sm.upload_frame(ids, st)
+        if step == 0:
+            asm.apply_edits(di, ds)
+        else:
+            asm.apply_edits_dev(di, ds, torch.tensor([n], dtype=torch.int32, device="cuda"))
+        changed = ids[:n][mask[ids[:n]] != st[:n]]
+        mask[ids[:n]] = st[:n]
+        check(asm, oracle.rebuild_workload(w, mask, pat), f"{k} edits, step {step}")
+        s = asm.last_frame_stats()
+        assert (s["diag_blocks"], s["off_blocks"], s["diag_incidences"], s["off_incidences"]) == touched(w, changed)
+        assert s["edits"] == n and s["changed"] == len(changed)
+        assert s["activated"] == int(mask[changed].sum()) and s["rolled_back"] == 0
+    want = oracle.rebuild_workload(w, mask, pat)
+    for bad, code in ((np.append(ids[:-1], ids[0]) if k > 1 else None, Sm.STA_EDUP),
+                      (np.append(ids[:-1], w.n_tets), Sm.STA_ERANGE), (np.append(ids[:-1], -1), Sm.STA_ERANGE)):
+        if bad is None:
+            continue
+        asm.apply_edits(*Sm.upload_frame(bad.astype(np.int32), (1 - mask[np.clip(bad, 0, w.n_tets - 1)])))
+        assert asm.status_sync() == code
+        check(asm, want, f"{k} edits, refused with {code}")
+        assert asm.audit() == {"values_differing": 0, "tets_differing": 0}
+    asm.apply_edits(*Sm.upload_frame(ids, mask[ids]))  # no stamp stayed taken, nothing changes
+    assert asm.status_sync() == Sm.STA_OK
+    check(asm, want, "no change")
+    asm.close()
+
+
+def hub_mesh(spokes):
+    """A 6^3 cube whose surface triangles at x = 0 are joined to one far node, each `spokes`
+    times over (overlapping candidates are allowed), and a node in no tet."""
+    x = W.jittered_nodes(6, 0.1, W.rng(3, W.STREAM_JITTER))
+    cube = W.kuhn_tets(6)
+    hub = len(x)
+    x = np.concatenate([x, [[-2.0, 0.4, 0.6]], [[5.0, 5.0, 5.0]]])
+    ids = np.arange(49).reshape(7, 7)
+    tri = np.concatenate([np.stack([ids[:-1, :-1], ids[1:, :-1], ids[1:, 1:]], -1).reshape(-1, 3),
+                          np.stack([ids[:-1, :-1], ids[:-1, 1:], ids[1:, 1:]], -1).reshape(-1, 3)])
+    fan = np.concatenate([np.full((len(tri), 1), hub), tri], 1)
+    tets = np.concatenate([cube] + [fan] * spokes).astype(np.int32)
+    g = np.random.default_rng(spokes)
+    m = len(tets)
+    return W.Workload(f"hub{spokes}", x, tets, W.lognormal_E(m, g), g.integers(0, 2, size=m).astype(np.uint8))
+
+
+@pytest.mark.parametrize("spokes", [1, 2, 3, 9])
+def test_nodes_around_and_past_the_tile_limits(spokes):
+    """The hub has 72 to 648 incident tets (a tile holds 192) and terms for 216 to 1,944
+    row entries (a tile holds 768): rebuild, frames, delta policy's state, new parameters."""
+    Sm = S()
+    w = hub_mesh(spokes)
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    mask = w.mask0.copy()
+    check(asm, oracle.rebuild_workload(w, mask, pat), "initial")
+    g = np.random.default_rng(7)
+    for k in (5, 300, 900):
+        ids = g.permutation(w.n_tets)[:k].astype(np.int32)
+        st = g.integers(0, 2, size=len(ids)).astype(np.uint8)
+        asm.apply_edits(*Sm.upload_frame(ids, st))
+        mask[ids] = st
+        check(asm, oracle.rebuild_workload(w, mask, pat), f"{k} edits")
+    for fused in (1, 0):
+        asm.set_config(fused=fused, rebuild_nt=fused)
+        asm.set_barrier_spin_limit(1 << 25 if fused else 0)  # fused: the frame with the grid barrier
+        ids = g.permutation(w.n_tets)[:w.n_tets // 2].astype(np.int32)
+        asm.apply_edits(*Sm.upload_frame(ids, 1 - mask[ids]))
+        mask[ids] = 1 - mask[ids]
+        check(asm, oracle.rebuild_workload(w, mask, pat), f"half toggled, fused {fused}")
+    asm.apply_edits_delta(*Sm.upload_frame(ids, 1 - mask[ids]))
+    mask[ids] = 1 - mask[ids]
+    E = w.E * 1.25
+    x = w.x + 1e-3 * g.standard_normal(w.x.shape)
+    asm.set_params(torch.from_numpy(x).cuda(), torch.from_numpy(E).cuda())
+    asm.full_rebuild()
+    want = oracle.rebuild(x, w.tets, E, w.nu, w.rho, w.dt, mask, *pat)
+    check(asm, want, "new parameters")
+    assert asm.audit() == {"values_differing": 0, "tets_differing": 0} and asm.status_sync() == Sm.STA_OK
+    asm.close()
+
+
+def test_inactive_degenerate_tet_contributes_nothing():
+    """New positions flatten a tet that is off: its record holds infinities, every value
+    stays what the oracle (which skips it) gives, in the rebuild and in frames beside it."""
+    Sm = S()
+    w = W.make_cube(1)
+    x = w.x.copy()
+    flat = 100
+    x[w.tets[flat][3]] = x[w.tets[flat][:3]].mean(axis=0)
+    t = w.tets.astype(np.int64)
+    d = x[t[:, 1:]] - x[t[:, :1]]
+    det = np.einsum("ij,ij->i", d[:, 0], np.cross(d[:, 1], d[:, 2]))
+    off = np.nonzero(np.abs(det) < 1e-12)[0]
+    x[w.tets[flat][3]] = x[w.tets[flat][0]]  # exactly flat: every tet with both nodes has det == 0
+    both = np.isin(t, [t[flat][0]]).any(1) & np.isin(t, [t[flat][3]]).any(1)
+    mask = w.mask0.copy()
+    mask[both] = 0
+    mask[off] = 0
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler(w.x, w.tets, w.E, w.nu, w.rho, w.dt, mask)
+    asm.set_params(torch.from_numpy(x).cuda())
+    asm.full_rebuild()
+    check(asm, oracle.rebuild(x, w.tets, w.E, w.nu, w.rho, w.dt, mask, *pat), "rebuild")
+    assert asm.status_sync() == Sm.STA_OK
+    beside = np.nonzero(np.isin(t, t[flat]).any(1) & (mask == 1))[0][:40].astype(np.int32)
+    for st in (0, 1):
+        asm.apply_edits(*Sm.upload_frame(beside, np.full(len(beside), st, np.uint8)))
+        mask[beside] = st
+        check(asm, oracle.rebuild(x, w.tets, w.E, w.nu, w.rho, w.dt, mask, *pat), f"beside it, state {st}")
+    assert asm.status_sync() == Sm.STA_OK
+    asm.apply_edits(*Sm.upload_frame(np.array([flat], np.int32), np.ones(1, np.uint8)))
+    assert asm.status_sync() == Sm.STA_EDEGENERATE
+    asm.close()
