@@ -591,6 +591,19 @@ sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, in
     return STA_OK;
 }
 
+// Iterations to launch before the next look at the residual: what is left at
+// the mean rate of the `launched` iterations so far, at least 4 and at most
+// twice as many as have run (the rate changes on the way).
+int cg_chunk(const CgScalars& h, int launched)
+{
+    const double rate = std::log(h.rr / h.bnorm2) / launched;  // per iteration, negative
+    const double left = std::log(h.tol2 / h.rr) / rate;
+    const int most = 2 * launched < 256 ? 2 * launched : 256;
+    if (!(left < most))  // not a number, infinite or growing residual included
+        return rate < 0.0 ? most : 16;
+    return left > 4.0 ? (int)std::ceil(left) : 4;
+}
+
 bool valid_map(int qd, int qo)
 {
     return (qd == 1 || qd == 4 || qd == 16) && (qo == 1 || qo == 4);
@@ -1101,15 +1114,19 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
     const int nparts = cg_partials(n);
     hipError_t e = hipSuccess;
     if (!ctx->cg_ws) {
-        e = dalloc(ctx, &ctx->cg_ws, (size_t)7 * n + nparts);
+        e = dalloc(ctx, &ctx->cg_ws, (size_t)8 * n + nparts);
         if (e == hipSuccess)
             e = dalloc(ctx, &ctx->cg_dpos, (size_t)n);
+        if (e == hipSuccess)
+            e = dalloc(ctx, &ctx->cg_adj, (size_t)kCgNeighbours * ctx->n_nodes);
         if (e == hipSuccess)
             e = dalloc(ctx, &ctx->cg_s, 1);
         if (e == hipSuccess)
             e = hipHostMalloc((void**)&ctx->cg_host, sizeof(CgScalars), hipHostMallocDefault);
         if (e == hipSuccess)
             e = launch_diag_positions(ctx->v, ctx->cg_dpos, s);
+        if (e == hipSuccess)
+            e = launch_cg_adjacency(ctx->v, ctx->rowptr, ctx->colidx, ctx->cg_adj, s);
         if (e != hipSuccess) {
             ctx->cg_ws = nullptr;
             return fail(ctx, STA_ENOMEM, "CG workspace allocation failed");
@@ -1124,19 +1141,19 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
     c.colidx = ctx->colidx;
     c.vals = values_dev ? values_dev : ctx->v.values;
     c.dpos = ctx->cg_dpos;
-    c.x = ctx->cg_ws;
+    c.adj = ctx->cg_adj;
+    c.zp = ctx->cg_ws;  // first: its records are read 16 bytes at a time
+    c.x = c.zp + 4 * (size_t)n;
     c.r = c.x + n;
-    c.z = c.r + n;
-    c.p = c.z + n;
-    c.q = c.p + 2 * n;
+    c.q = c.r + n;
     c.dinv = c.q + n;
     c.part = c.dinv + n;
     c.s = ctx->cg_s;
     e = launch_cg_init(c, b_dev, rtol, s);
     // iterations k = 0 .. max_iter (the last one only records the residual),
-    // 16 at a time between host checks
-    const int chunk = 16;
-    int next = 0;
+    // cg_chunk of them between host checks (a check costs about 18 us of idle GPU, a launch
+    // pair past convergence about 3)
+    int next = 0, chunk = 16;
     while (e == hipSuccess) {
         const int count = max_iter + 1 - next < chunk ? max_iter + 1 - next : chunk;
         if (count > 0)
@@ -1148,6 +1165,7 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
             e = hipStreamSynchronize(s);
         if (e != hipSuccess || ctx->cg_host->done || next > max_iter)
             break;
+        chunk = cg_chunk(*ctx->cg_host, next);
     }
     if (e == hipSuccess)
         e = launch_cg_output(c, x_dev, s);

@@ -9,16 +9,26 @@
 // over the workgroups' partials in index order): results are reproducible
 // run to run.
 //
-// One iteration is two launches.  The matrix-vector product first sums the
-// previous update's partials of r.z and r.r (every workgroup the same way,
-// so all get the same bits), checks convergence, forms beta, and builds the
-// new search direction p = z + beta p on the fly from a second copy of p.
-// The update then sums the product's partials of p.Ap into alpha and
-// updates x, r, z with partials of r.z and r.r.  The product works per node:
-// the three rows of a node share one column list (3x3 blocks), so a group of
-// lanes walks the node's neighbours once, reading one column index and one
-// 3-vector of p per neighbour for all three rows.  Both grids are capped, so
-// that the partials every workgroup sums stay few.
+// One iteration is two launches.  The matrix-vector product sums the previous
+// update's partials of r.z and r.r (every workgroup the same way, so all get
+// the same bits), checks convergence, forms beta, and builds the new search
+// direction p = z + beta p on the fly.  The update then sums the product's
+// partials of p.Ap into alpha and updates x, r, z with partials of r.z and
+// r.r.  The product works per node: the three rows of a node share one column
+// list (3x3 blocks), so a group of lanes walks the node's neighbours once,
+// reading one neighbour and one record of its z and p for all three rows.
+//
+// Both kernels are bound by latency (their data, 72 MB of values and 2 MB a
+// vector on the 207k-row fracture system, come from the Infinity Cache): every
+// load that does not need the scalars is issued before the partials are
+// summed, z and p of a node are one 48-byte record (two copies, written in
+// turn), and each node's first 16 neighbours stand at a fixed place, so that
+// the product is two round trips deep.  Sums over a workgroup go through
+// cross-lane moves and one barrier.  Per iteration of the 207k-row system 20.6
+// + 6.4 -> 15.4 + 5.8 us (the product at 5.3 TB/s), of a 5k-row one 6.5 + 4.5
+// -> 4.6 + 3.3 us.  Loading a round's neighbours a round ahead, and product
+// grids of 768 to 4,320 workgroups, gave 5.0 to 5.9 ms for a solve that takes
+// 5.1 at 2,048.
 #include <hip/hip_runtime.h>
 
 #include "sta_internal.h"
@@ -27,8 +37,11 @@ namespace sta {
 
 namespace {
 
+typedef double dvec2 __attribute__((ext_vector_type(2)));
+
 constexpr int kBlock = 256;
-constexpr int kNodeLanes = 16;  // lanes per node (three CSR rows) in the matrix-vector product
+constexpr int kNodeLanes = kCgNeighbours;  // lanes per node (three CSR rows) in the matrix-vector product
+constexpr int kGroups = kBlock / kNodeLanes;
 #ifndef STA_CG_SPMV_GRID
 #define STA_CG_SPMV_GRID 2048
 #endif
@@ -37,88 +50,82 @@ constexpr int kNodeLanes = 16;  // lanes per node (three CSR rows) in the matrix
 #endif
 constexpr int kSpmvGridMax = STA_CG_SPMV_GRID;
 constexpr int kUpdateGridMax = STA_CG_UPDATE_GRID;
+static_assert(kUpdateGridMax <= kBlock, "one lane holds one partial of the update");
 
-// Workgroup sum of one value per thread, fixed tree; result valid in thread 0.
-__device__ __forceinline__ double block_sum(double x, double* sh)
+// x plus the x of the lane that a DPP control names.
+template <int kCtrl>
+__device__ __forceinline__ double add_dpp(double x)
 {
-    sh[threadIdx.x] = x;
-    __syncthreads();
-#pragma unroll
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    return sh[0];
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, kCtrl, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, 0xf, 0xf, false);
+    return x + __longlong_as_double((long long)hi << 32 | (unsigned)lo);
 }
 
-// Sum of partials[0..n) by one workgroup: thread t adds t, t+256, ... in order, then a tree.
-// Eight loads are issued before their additions (same order of additions).
-__device__ __forceinline__ double reduce_partials(const double* __restrict__ p, int n, double* sh)
+// Sum over each aligned group of 16 lanes, the same bits in all of them: lanes
+// 1 and 2 apart (quad permutations), then the mirrored half row and row (all
+// lanes of a quad, then of a half row, hold the same sum by then).
+__device__ __forceinline__ double sum16(double x)
+{
+    x = add_dpp<0xB1>(x);   // quad_perm 1 0 3 2
+    x = add_dpp<0x4E>(x);   // quad_perm 2 3 0 1
+    x = add_dpp<0x141>(x);  // row_half_mirror
+    return add_dpp<0x140>(x);  // row_mirror
+}
+
+__device__ __forceinline__ double sum64(double x)
+{
+    x = sum16(x);
+    x = x + __shfl_xor(x, 16, 64);
+    return x + __shfl_xor(x, 32, 64);
+}
+
+constexpr int kWaves = kBlock / 64;
+
+// Workgroup sums of one or two values per thread, valid in every thread; sh
+// (kWaves doubles per value) must not be in use.
+__device__ __forceinline__ double block_sum(double x, double* sh)
+{
+    x = sum64(x);
+    if ((threadIdx.x & 63) == 0)
+        sh[threadIdx.x >> 6] = x;
+    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+__device__ __forceinline__ void block_sum2(double x, double y, double* sh, double& sx, double& sy)
+{
+    x = sum64(x);
+    y = sum64(y);
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = x;
+        sh[kWaves + (threadIdx.x >> 6)] = y;
+    }
+    __syncthreads();
+    sx = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    sy = (sh[4] + sh[5]) + (sh[6] + sh[7]);
+}
+
+// This thread's share of partials[0..n): t, t + 256, ... in order, eight loads
+// at a time before their additions.
+__device__ __forceinline__ double share_of_partials(const double* __restrict__ p, int n)
 {
     double acc = 0.0;
-    int i = threadIdx.x;
-    for (; i + 7 * kBlock < n; i += 8 * kBlock) {
+    for (int i = threadIdx.x; i < n; i += 8 * kBlock) {
         double t[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k)
-            t[k] = p[i + k * kBlock];
+            t[k] = i + k * kBlock < n ? p[i + k * kBlock] : 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             acc = acc + t[k];
     }
-    for (; i < n; i += kBlock)
-        acc = acc + p[i];
-    return block_sum(acc, sh);
-}
-
-// Workgroup sums of two values per thread, fixed trees; results valid in every thread.
-__device__ __forceinline__ void block_sum2(double x, double y, double* sh, double& sx, double& sy)
-{
-    sh[threadIdx.x] = x;
-    sh[kBlock + threadIdx.x] = y;
-    __syncthreads();
-#pragma unroll
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + s];
-            sh[kBlock + threadIdx.x] = sh[kBlock + threadIdx.x] + sh[kBlock + threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    sx = sh[0];
-    sy = sh[kBlock];
-}
-
-// Sums of p[0..n) and q[0..n) in one pass, each in the order of reduce_partials.
-__device__ __forceinline__ void reduce_partials2(const double* __restrict__ p, const double* __restrict__ q, int n,
-                                                 double* sh, double& sp, double& sq)
-{
-    double a = 0.0, b = 0.0;
-    int i = threadIdx.x;
-    for (; i + 7 * kBlock < n; i += 8 * kBlock) {
-        double t[8], u[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            t[k] = p[i + k * kBlock];
-            u[k] = q[i + k * kBlock];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            a = a + t[k];
-            b = b + u[k];
-        }
-    }
-    for (; i < n; i += kBlock) {
-        a = a + p[i];
-        b = b + q[i];
-    }
-    block_sum2(a, b, sh, sp, sq);
+    return acc;
 }
 
 __global__ __launch_bounds__(kBlock) void k_cg_init(CgView c, const double* __restrict__ b)
 {
-    __shared__ double sh[kBlock];
+    __shared__ double sh[2 * kWaves];
     const int r = blockIdx.x * kBlock + threadIdx.x;
     double rz = 0.0, bb = 0.0;
     if (r < c.n) {
@@ -130,15 +137,14 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgView c, const double* __re
         c.x[r] = 0.0;
         c.r[r] = br;
         const double z = br * di;
-        c.z[r] = z;
-        c.p[r] = 0.0;  // p_0 = z_0 + 0 * 0, formed by the first product
-        c.p[c.n + r] = 0.0;
+        double* zp = c.zp + 6 * (size_t)(r / 3) + r % 3;
+        zp[0] = z;
+        zp[3] = 0.0;  // p_0 = z_0 + 0 * 0, formed by the first product
         rz = br * z;
         bb = br * br;
     }
-    const double s1 = block_sum(rz, sh);
-    __syncthreads();
-    const double s2 = block_sum(bb, sh);
+    double s1, s2;
+    block_sum2(rz, bb, sh, s1, s2);
     if (threadIdx.x == 0) {
         c.part[blockIdx.x] = s1;
         c.part[c.nparts + blockIdx.x] = s2;
@@ -147,10 +153,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(CgView c, const double* __re
 
 __global__ __launch_bounds__(kBlock) void k_cg_init_finish(CgView c, double rtol)
 {
-    __shared__ double sh[kBlock];
-    const double rz = reduce_partials(c.part, c.nparts, sh);
-    __syncthreads();
-    const double bb = reduce_partials(c.part + c.nparts, c.nparts, sh);
+    __shared__ double sh[2 * kWaves];
+    double rz, bb;
+    block_sum2(share_of_partials(c.part, c.nparts), share_of_partials(c.part + c.nparts, c.nparts), sh, rz, bb);
     if (threadIdx.x == 0) {
         c.s->rz = rz;
         c.s->rzk[0] = rz;
@@ -167,47 +172,18 @@ __global__ __launch_bounds__(kBlock) void k_cg_init_finish(CgView c, double rtol
 // partials; stop if converged or k reaches max_iter; beta = (r_k.z_k) /
 // (r_{k-1}.z_{k-1}).  Then p_new = z + beta p_old and q = A p_new, with the
 // partials of p_new . q.  kNodeLanes lanes per node; lane l takes neighbours
-// l, l + kNodeLanes, ...; the three row sums are combined by a fixed shuffle
-// tree.  p_old is read, p_new written only for the node's own rows, so the two
-// never alias.
+// l, l + kNodeLanes, ...; the three row sums are combined by a fixed tree.  The
+// records of copy cur are read, p_new goes into the other copy.
+//
+// Node groups of kGroups nodes: with at least kXcds workgroups each XCD walks
+// one contiguous share of them (its workgroups in turn), so that neighbouring
+// nodes, which gather the same records, stay in one L2; otherwise a plain
+// grid-stride.  All groups of a workgroup run the same number of rounds.
 __global__ __launch_bounds__(kBlock) void k_cg_spmv(CgView c, int k, int cur, int max_iter)
 {
-    __shared__ double sh[2 * kBlock];
-    if (c.s->done)
-        return;
-    double beta = 0.0;
-    {
-        double rz = c.s->rzk[0], rr = c.s->rr;
-        if (k > 0)
-            reduce_partials2(c.part + c.nparts_s, c.part + c.nparts_s + c.nparts_u, c.nparts_u, sh, rz, rr);
-        if ((k > 0 && rr <= c.s->tol2) || k >= max_iter) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
-                c.s->rr = rr;
-                c.s->iters = k;
-                c.s->done = 1;
-            }
-            return;
-        }
-        if (k > 0) {
-            beta = rz / c.s->rzk[(k - 1) & 1];
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
-                c.s->rzk[k & 1] = rz;
-                c.s->rr = rr;
-                c.s->iters = k;
-            }
-        }
-    }
-    const double* __restrict__ pold = c.p + (cur ? c.n : 0);
-    double* __restrict__ pnew = c.p + (cur ? 0 : c.n);
+    __shared__ double sh[2 * kWaves], sh2[kWaves];
     const int nn = c.n / 3;
     const int group = threadIdx.x / kNodeLanes, l = threadIdx.x & (kNodeLanes - 1);
-    constexpr int kGroups = kBlock / kNodeLanes;
-    double pq = 0.0;
-    // Node groups of kGroups nodes: with at least kXcds workgroups each XCD walks one
-    // contiguous share of them (its workgroups in turn), so that neighbouring
-    // nodes, which gather the same entries of z and p, stay in one L2 (29.8 ->
-    // 28.3 us per iteration on the 207k-row fracture system); otherwise a plain
-    // grid-stride.  All groups of a workgroup run the same number of rounds.
     const int ngroups = (nn + kGroups - 1) / kGroups;
     int g0 = blockIdx.x, g1 = ngroups, gstep = gridDim.x;
     if ((int)gridDim.x >= kXcds) {
@@ -216,81 +192,158 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(CgView c, int k, int cur, in
         g1 = (int)((int64_t)ngroups * (xcd + 1) / kXcds);
         gstep = G / kXcds + (xcd < G % kXcds ? 1 : 0);  // workgroups on this XCD
     }
-    for (int gi = g0; gi < g1; gi += gstep) {
+    const double* __restrict__ zp = c.zp + (cur ? 2 * (size_t)c.n : 0);
+    double* __restrict__ zp_new = c.zp + (cur ? 0 : 2 * (size_t)c.n);
+    // what this lane needs of node group gi before the scalars are known
+    struct Lane {
+        int i, base, rl, j;         // node, its rows' start and length, neighbour (-1: none)
+        dvec2 n[3];                 // the neighbour's z and p
+        double v[3][3];             // the block
+        double z, p, di;            // lanes 0..2: the node's own row
+    };
+    auto first_trip = [&](int gi, Lane& a) {
         const int i = gi * kGroups + group;
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-        if (i < nn) {
-            const int base = c.rowptr[3 * i];
-            const int rl = c.rowptr[3 * i + 1] - base;
-            const int deg = rl / 3;
-            for (int kk = l; kk < deg; kk += kNodeLanes) {
-                const int j = c.colidx[base + 3 * kk] / 3;
-                const double* v = c.vals + base + 3 * kk;
-                double pj[3];
+        a.i = i < nn && gi < g1 ? i : -1;
+        const int ii = a.i >= 0 ? i : 0;
+        a.base = c.rowptr[3 * ii];
+        a.rl = c.rowptr[3 * ii + 1] - a.base;
+        a.j = c.adj[kNodeLanes * (size_t)ii + l];
+        const int own = l < 3 ? l : 0;
+        a.z = zp[6 * (size_t)ii + own];
+        a.p = zp[6 * (size_t)ii + 3 + own];
+        a.di = c.dinv[3 * (size_t)ii + own];
+    };
+    auto second_trip = [&](Lane& a) {
+        if (a.j >= 0 && a.i >= 0) {
+            const dvec2* r = reinterpret_cast<const dvec2*>(zp + 6 * (size_t)a.j);
+            const double* v = c.vals + a.base + 3 * l;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    pj[q] = c.z[3 * j + q] + beta * pold[3 * j + q];
+            for (int q = 0; q < 3; ++q) {
+                a.n[q] = r[q];
+#pragma unroll
+                for (int w = 0; w < 3; ++w)
+                    a.v[q][w] = v[q * a.rl + w];
+            }
+        }
+    };
+    Lane a;
+    first_trip(g0 < g1 ? g0 : 0, a);
+    double rz = 0.0, rr = 0.0;
+    if (k > 0 && (int)threadIdx.x < c.nparts_u) {
+        rz = c.part[c.nparts_s + threadIdx.x];
+        rr = c.part[c.nparts_s + c.nparts_u + threadIdx.x];
+    }
+    const int done = c.s->done;
+    const double tol2 = c.s->tol2, rz_old = c.s->rzk[(k - 1) & 1], rz0 = c.s->rzk[0], rr0 = c.s->rr;
+    if (g0 >= g1)
+        a.i = -1;
+    second_trip(a);
+    if (done)
+        return;
+    double beta = 0.0;
+    if (k > 0) {
+        block_sum2(rz, rr, sh, rz, rr);
+    } else {
+        rz = rz0;
+        rr = rr0;
+    }
+    if ((k > 0 && rr <= tol2) || k >= max_iter) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            c.s->rr = rr;
+            c.s->iters = k;
+            c.s->done = 1;
+        }
+        return;
+    }
+    if (k > 0) {
+        beta = rz / rz_old;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            c.s->rzk[k & 1] = rz;
+            c.s->rr = rr;
+            c.s->iters = k;
+        }
+    }
+    double pq = 0.0;
+    for (int gi = g0; gi < g1; gi += gstep) {
+        if (gi != g0) {
+            first_trip(gi, a);
+            second_trip(a);
+        }
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+        if (a.i >= 0) {
+            if (a.j >= 0) {
+                const double pj[3] = {a.n[0].x + beta * a.n[1].y, a.n[0].y + beta * a.n[2].x,
+                                      a.n[1].x + beta * a.n[2].y};
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    a0 = a0 + v[q] * pj[q];
-                    a1 = a1 + v[rl + q] * pj[q];
-                    a2 = a2 + v[2 * rl + q] * pj[q];
+                    s0 = s0 + a.v[0][q] * pj[q];
+                    s1 = s1 + a.v[1][q] * pj[q];
+                    s2 = s2 + a.v[2][q] * pj[q];
+                }
+            }
+            for (int kk = l + kNodeLanes; 3 * kk < a.rl; kk += kNodeLanes) {  // past the first 16 neighbours
+                const double* r = zp + 6 * (size_t)(c.colidx[a.base + 3 * kk] / 3);
+                const double* v = c.vals + a.base + 3 * kk;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const double pj = r[q] + beta * r[3 + q];
+                    s0 = s0 + v[q] * pj;
+                    s1 = s1 + v[a.rl + q] * pj;
+                    s2 = s2 + v[2 * a.rl + q] * pj;
                 }
             }
         }
-#pragma unroll
-        for (int o = kNodeLanes / 2; o > 0; o >>= 1) {
-            a0 = a0 + __shfl_xor(a0, o, kNodeLanes);
-            a1 = a1 + __shfl_xor(a1, o, kNodeLanes);
-            a2 = a2 + __shfl_xor(a2, o, kNodeLanes);
-        }
-        if (i < nn && l < 3) {
-            const int r = 3 * i + l;
-            const double acc = l == 0 ? a0 : (l == 1 ? a1 : a2);
-            const double q = c.dinv[r] != 0.0 ? acc : 0.0;
-            const double pr = c.z[r] + beta * pold[r];
-            pnew[r] = pr;
-            c.q[r] = q;
+        s0 = sum16(s0);
+        s1 = sum16(s1);
+        s2 = sum16(s2);
+        if (a.i >= 0 && l < 3) {
+            const double acc = l == 0 ? s0 : (l == 1 ? s1 : s2);
+            const double q = a.di != 0.0 ? acc : 0.0;
+            const double pr = a.z + beta * a.p;
+            zp_new[6 * (size_t)a.i + 3 + l] = pr;
+            c.q[3 * a.i + l] = q;
             pq = pq + pr * q;
         }
     }
-    __syncthreads();  // sh is reused
-    const double s = block_sum(pq, sh);
+    const double s = block_sum(pq, sh2);
     if (threadIdx.x == 0)
         c.part[blockIdx.x] = s;
 }
 
 // Iteration k, second launch: alpha = (r_k.z_k) / (p.Ap) from the product's
-// partials; x += alpha p_new, r -= alpha q, z = Dinv r; partials of r.z and r.r
-// (grid-stride, each thread in ascending row order).  Each thread loads up to
-// kUpdateRows of its rows before it updates any of them, so that their loads
-// are in flight together (the vectors are distinct buffers, but the compiler
-// cannot know it and would not hoist a row's loads above the previous row's
-// stores): 29.8 instead of 31.5 us per iteration on the 207k-row fracture
-// system, same bits.
+// partials; x += alpha p_new, r -= alpha q, z = Dinv r (into p_new's copy);
+// partials of r.z and r.r (grid-stride, each thread in ascending row order).
+// Each thread loads its first kUpdateRows rows before the partials are summed,
+// and further ones four at a time before it updates any of them.
 constexpr int kUpdateRows = 4;
 __global__ __launch_bounds__(kBlock) void k_cg_update(CgView c, int k, int cur)
 {
-    __shared__ double sh[2 * kBlock];
-    if (c.s->done)
-        return;
-    const double pq = reduce_partials(c.part, c.nparts_s, sh);
-    const double alpha = c.s->rzk[k & 1] / pq;
-    const double* __restrict__ pnew = c.p + (cur ? 0 : c.n);
-    double rz = 0.0, rr = 0.0;
-    const int stride = gridDim.x * kBlock;
-    for (int i0 = blockIdx.x * kBlock + threadIdx.x; i0 < c.n; i0 += kUpdateRows * stride) {
-        double xs[kUpdateRows], ps[kUpdateRows], rs[kUpdateRows], qs[kUpdateRows], ds[kUpdateRows];
+    __shared__ double sh[2 * kWaves], sh2[kWaves];
+    double* __restrict__ zp_new = c.zp + (cur ? 0 : 2 * (size_t)c.n);
+    const int stride = gridDim.x * kBlock, i_first = blockIdx.x * kBlock + threadIdx.x;
+    double xs[kUpdateRows], ps[kUpdateRows], rs[kUpdateRows], qs[kUpdateRows], ds[kUpdateRows];
+    auto load_rows = [&](int i0) {
 #pragma unroll
         for (int u = 0; u < kUpdateRows; ++u) {
-            const int i = i0 + u * stride;
-            const bool on = i < c.n;
-            xs[u] = on ? c.x[i] : 0.0;
-            ps[u] = on ? pnew[i] : 0.0;
-            rs[u] = on ? c.r[i] : 0.0;
-            qs[u] = on ? c.q[i] : 0.0;
-            ds[u] = on ? c.dinv[i] : 0.0;
+            const int i = i0 + u * stride, ii = i < c.n ? i : 0;
+            xs[u] = c.x[ii];
+            ps[u] = zp_new[6 * (size_t)(ii / 3) + 3 + ii % 3];
+            rs[u] = c.r[ii];
+            qs[u] = c.q[ii];
+            ds[u] = c.dinv[ii];
         }
+    };
+    const int done = c.s->done;
+    const double rz_k = c.s->rzk[k & 1];
+    const double share = share_of_partials(c.part, c.nparts_s);
+    load_rows(i_first);
+    if (done)
+        return;
+    const double alpha = rz_k / block_sum(share, sh2);
+    double rz = 0.0, rr = 0.0;
+    for (int i0 = i_first; i0 < c.n; i0 += kUpdateRows * stride) {
+        if (i0 != i_first)
+            load_rows(i0);
 #pragma unroll
         for (int u = 0; u < kUpdateRows; ++u) {
             const int i = i0 + u * stride;
@@ -299,13 +352,12 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(CgView c, int k, int cur)
                 const double r = rs[u] - alpha * qs[u];
                 c.r[i] = r;
                 const double z = r * ds[u];
-                c.z[i] = z;
+                zp_new[6 * (size_t)(i / 3) + i % 3] = z;
                 rz = rz + r * z;
                 rr = rr + r * r;
             }
         }
     }
-    __syncthreads();  // sh is reused
     double s1, s2;
     block_sum2(rz, rr, sh, s1, s2);
     if (threadIdx.x == 0) {
@@ -332,6 +384,18 @@ __global__ __launch_bounds__(kBlock) void k_diag_positions(DevView v, int32_t* _
     dpos[r] = b >= 0 ? v.desc[b].up + p * v.desc[b].rl + p : -1;
 }
 
+// Each node's first kNodeLanes neighbours (itself included), -1 past the last.
+__global__ __launch_bounds__(kBlock) void k_cg_adjacency(int n_nodes, const int32_t* __restrict__ rowptr,
+                                                         const int32_t* __restrict__ colidx, int32_t* __restrict__ adj)
+{
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t i = t / kNodeLanes;
+    if (i >= n_nodes)
+        return;
+    const int l = (int)(t % kNodeLanes), base = rowptr[3 * i], rl = rowptr[3 * i + 1] - base;
+    adj[t] = 3 * l < rl ? colidx[base + 3 * l] / 3 : -1;
+}
+
 inline unsigned blocks(int64_t n, int per)
 {
     return (unsigned)((n + per - 1) / per);
@@ -344,6 +408,16 @@ hipError_t launch_diag_positions(const DevView& v, int32_t* dpos, hipStream_t s)
     if (v.n_nodes == 0)
         return hipSuccess;
     hipLaunchKernelGGL(k_diag_positions, dim3(blocks(3 * (int64_t)v.n_nodes, kBlock)), dim3(kBlock), 0, s, v, dpos);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_adjacency(const DevView& v, const int32_t* rowptr, const int32_t* colidx, int32_t* adj,
+                               hipStream_t s)
+{
+    if (v.n_nodes == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_cg_adjacency, dim3(blocks((int64_t)v.n_nodes * kNodeLanes, kBlock)), dim3(kBlock), 0, s,
+                       v.n_nodes, rowptr, colidx, adj);
     return hipGetLastError();
 }
 

@@ -252,6 +252,7 @@ struct CgScalars {
     double rzk[2];  // r_k . z_k by iteration parity (the product of iteration k reads k-1's, writes k's)
 };
 
+constexpr int kCgNeighbours = 16;
 struct CgView {
     int32_t n;        // rows
     int32_t nparts;   // partial sums of the start kernels (one per 256 rows)
@@ -261,7 +262,9 @@ struct CgView {
     const int32_t* colidx;
     const double* vals;
     const int32_t* dpos;  // diagonal position per row, -1 if none
-    double *x, *r, *z, *p, *q, *dinv, *part;  // p: two copies of n (previous / new direction)
+    const int32_t* adj;   // per node: its first kCgNeighbours neighbours, -1 past the last
+    double *x, *r, *q, *dinv, *part;
+    double* zp;           // two copies (previous / new direction) of a record per node: its z, then its p
     CgScalars* s;
 };
 
@@ -290,8 +293,9 @@ struct sta_ctx {
     int64_t trace_seq = 0;
     double trace_t0 = 0.0;     // host seconds at context build
     // lazily allocated workspaces
-    double* cg_ws = nullptr;        // 7 vectors of n_rows (two copies of p) + partials
+    double* cg_ws = nullptr;        // 8 vectors of n_rows (two copies of z and p) + partials
     int32_t* cg_dpos = nullptr;
+    int32_t* cg_adj = nullptr;
     sta::CgScalars* cg_s = nullptr;
     sta::CgScalars* cg_host = nullptr;  // pinned
     double* adj_xbar = nullptr;     // 3 doubles per diagonal incidence
@@ -395,6 +399,8 @@ hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chun
 hipError_t launch_slot_outer(int n_rows, const int32_t* rowptr, const int32_t* colidx, const double* a,
                              const double* b, double alpha, double* out, hipStream_t s);
 hipError_t launch_diag_positions(const DevView& v, int32_t* dpos, hipStream_t s);
+hipError_t launch_cg_adjacency(const DevView& v, const int32_t* rowptr, const int32_t* colidx, int32_t* adj,
+                               hipStream_t s);
 int cg_partials(int n);
 int spmv_grid(int n);
 int update_grid(int n);
