@@ -76,56 +76,253 @@ __device__ __forceinline__ void geometry(const DevView& v, int4 t, Geo& G)
     G.V = fabs(det) / 6.0;
 }
 
-// Gather the 3x3 cotangent block Abar_ab (rows: vertex a dofs, columns: vertex b dofs).
-__device__ __forceinline__ void gather_block(const DevView& v, const double* __restrict__ gA, const int* id, int a,
-                                             int b, int blk, double out[3][3])
+// Everything above depends on the cotangents through B_ab = Abar_ab + Abar_ba^T
+// alone: P_lam = sum_{a<b} g_a^T B_ab g_b + 1/2 sum_a g_a^T B_aa g_a,
+// P_mu = sum_{a<b} (g_b^T B_ab g_a + tr(B_ab) g_a.g_b) + 1/2 sum_a (...),
+// P_m = 1/2 sum_a tr(B_aa).  A brick of kAdjointBrick tets that are near in space
+// (kBrickChunks chunks of the Morton order) shares most of its blocks: 128
+// tets name 1,280 blocks, about 330 of them different.  So the brick's
+// different blocks are formed once, in LDS, and each tet reads its ten from
+// there.
+//
+// Per brick the plan lists the row blocks to read (one per diagonal block, two
+// per other block) in the order of their place in the values, so that lanes
+// side by side read runs of the rows, as (position, row length, block number |
+// kind), the blocks numbered in ascending id; and per tet slot ten references,
+// block number | transpose << 15.  (Two lists, upper copies and mirrors, read
+// every line of the rows twice: 78 instead of 72 us a call.)
+constexpr int kBrickChunks = kAdjointBrick / kAdjointChunk;
+constexpr int kBrickBlocks = 10 * kAdjointBrick, kBrickReads = 2 * kBrickBlocks;  // most a brick can have
+constexpr int kBrickTable = 4096;  // hash slots while a brick's blocks are found
+constexpr int kEntryWords = 3;
+constexpr int kMirror = 1 << 15, kDiagonal = 1 << 14;
+static_assert(kBrickBlocks < kBrickTable && kBrickBlocks < kDiagonal, "every block finds a place and a number");
+
+// Tet of slot t of a brick, or -1.
+__device__ __forceinline__ int brick_tet(const DevView& v, const int32_t* __restrict__ order, int n_chunks, int brick,
+                                         int t)
 {
-    const BlockDesc d = v.desc[blk];
-    if (a == b) {
+    const int c = brick * kBrickChunks + t / kAdjointChunk;
+    if (c >= n_chunks)
+        return -1;
+    const int e = order[c] * kAdjointChunk + t % kAdjointChunk;
+    return e < v.n_tets ? e : -1;
+}
+
+// Ranks of kMine values per thread among the n different values of list.
+template <int kMine>
+__device__ __forceinline__ void rank_among(const int* list, int n, const int (&v)[kMine], int (&r)[kMine])
+{
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+    for (int u = 0; u < kMine; ++u)
+        r[u] = 0;
+    for (int i = 0; i < n; ++i) {
+        const int x = list[i];
 #pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.up + i * d.rl + j];
-    } else if (id[a] < id[b]) {  // row node of the stored block is vertex a
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.up + i * d.rl + j];
-    } else {  // row node is vertex b: entry (3a+i, 3b+j) is the mirror part
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.lo + i * d.rlj + j];
+        for (int u = 0; u < kMine; ++u)
+            r[u] += x < v[u] ? 1 : 0;
     }
 }
 
-// The element pass's dynamic LDS, reserved and unused: it caps the pass at two
-// workgroups per CU.  More resident waves gather more cotangent rows at once
-// than the caches hold (on the 384k-tet fracture state: 81 us at two
-// workgroups per CU, 86 us at three, 97 us at four).
-constexpr size_t kAdjointReservedLds = 56 << 10;
-
-__global__ __launch_bounds__(kBlock) void k_adjoint_element(DevView v, const int32_t* __restrict__ order,
-                                                            int32_t n_chunks, const double* __restrict__ gA,
-                                                            double* __restrict__ g_logE, double* __restrict__ xbar)
+// Plan of one brick per workgroup.  fill = false: only how many row blocks it
+// reads, into starts, and how many blocks it has, into refs (as a word); true:
+// its entries, starts being the running sum by then, and its references.
+template <bool kFill>
+__global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const int32_t* __restrict__ order,
+                                                                int32_t n_chunks, AdjointPlan plan)
 {
-    // each XCD takes one contiguous share of the chunk order, chunks that are
-    // near in space: neighbouring tets share node blocks, so their cotangent
-    // rows stay in one L2 (132 -> 85 us for contiguous eighths of the tet ids
-    // on the 384k-tet fracture state; 81 -> 79 us for the Morton chunk order
-    // over the id order, both at two workgroups per CU; same bits throughout)
-    constexpr int kPer = kBlock / kAdjointChunk;
-    const int slot = xcd_remap(blockIdx.x, gridDim.x) * kPer + threadIdx.x / kAdjointChunk;
-    if (slot >= n_chunks)
+    __shared__ int s_key[kBrickTable];      // block of each hash slot, -1: free
+    __shared__ uint16_t s_at[kBrickTable];  // its place in s_list
+    __shared__ int s_list[kBrickBlocks], s_pos[kBrickReads];
+    __shared__ uint16_t s_rank[kBrickBlocks], s_src[kBrickReads];
+    __shared__ int s_n, s_m;
+    constexpr int kMine = kBrickBlocks / kAdjointBrick;
+    const int t = threadIdx.x, brick = blockIdx.x;
+    for (int k = t; k < kBrickTable; k += kAdjointBrick)
+        s_key[k] = -1;
+    if (t == 0)
+        s_n = s_m = 0;
+    __syncthreads();
+    const int e = brick_tet(v, order, n_chunks, brick, t);
+    int slot[10];
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        slot[q] = 0;
+        if (e >= 0) {
+            const int key = v.e2b[10 * (size_t)e + q];
+            unsigned h = ((unsigned)key * 2654435761u) >> 20;
+            for (;; h = (h + 1) & (kBrickTable - 1)) {  // ends: the table holds more than all references
+                const int old = atomicCAS(&s_key[h], -1, key);
+                if (old == -1) {
+                    const int at = atomicAdd(&s_n, 1);
+                    s_list[at] = key;
+                    s_at[h] = (uint16_t)at;
+                    atomicAdd(&s_m, key < v.nd ? 1 : 2);
+                }
+                if (old == -1 || old == key)
+                    break;
+            }
+            slot[q] = (int)h;
+        }
+    }
+    __syncthreads();
+    const int n = s_n, m = s_m;
+    if (!kFill) {
+        if (t == 0) {
+            plan.starts[brick] = m;
+            *reinterpret_cast<int32_t*>(plan.refs + (size_t)brick * 10 * kAdjointBrick) = n;
+        }
         return;
-    const int e = order[slot] * kAdjointChunk + (threadIdx.x % kAdjointChunk);
-    if (e >= v.n_tets)
+    }
+    int key[kMine], rank[kMine];
+#pragma unroll
+    for (int u = 0; u < kMine; ++u)
+        key[u] = t + u * kAdjointBrick < n ? s_list[t + u * kAdjointBrick] : -1;
+    rank_among<kMine>(s_list, n, key, rank);
+    __syncthreads();
+    if (t == 0)
+        s_m = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kMine; ++u) {
+        if (key[u] < 0)
+            continue;
+        const int i = t + u * kAdjointBrick;
+        s_rank[i] = (uint16_t)rank[u];
+        const BlockDesc d = v.desc[key[u]];
+        const int at = atomicAdd(&s_m, d.kind == 0 ? 1 : 2);
+        s_pos[at] = d.up;
+        s_src[at] = (uint16_t)i;
+        if (d.kind != 0) {
+            s_pos[at + 1] = d.lo;
+            s_src[at + 1] = (uint16_t)(i | kMirror);
+        }
+    }
+    __syncthreads();
+    constexpr int kPass = 5;  // row blocks ranked per thread and pass: a typical brick takes one
+    for (int k0 = t; k0 - t < m; k0 += kPass * kAdjointBrick) {
+        int pos[kPass], at[kPass];
+#pragma unroll
+        for (int u = 0; u < kPass; ++u)
+            pos[u] = k0 + u * kAdjointBrick < m ? s_pos[k0 + u * kAdjointBrick] : -1;
+        rank_among<kPass>(s_pos, m, pos, at);
+#pragma unroll
+        for (int u = 0; u < kPass; ++u) {
+            if (pos[u] < 0)
+                continue;
+            const int src = s_src[k0 + u * kAdjointBrick], mirror = src & kMirror;
+            const BlockDesc d = v.desc[s_list[src & ~kMirror]];
+            int32_t* o = plan.entries + kEntryWords * ((size_t)plan.starts[brick] + at[u]);
+            o[0] = pos[u];
+            o[1] = mirror ? d.rlj : d.rl;
+            o[2] = s_rank[src & ~kMirror] | (d.kind == 0 ? kDiagonal : mirror);
+        }
+    }
+    const int4 T = e >= 0 ? v.T[e] : make_int4(0, 0, 0, 0);
+    const int id[4] = {T.x, T.y, T.z, T.w};
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        constexpr int A[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2}, B[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
+        const unsigned swap = id[A[q]] > id[B[q]] ? 1u << 15 : 0u;
+        plan.refs[((size_t)brick * 10 + q) * kAdjointBrick + t] =
+            e >= 0 ? (uint16_t)(s_rank[s_at[slot[q]]] | swap) : (uint16_t)0;
+    }
+}
+
+// One brick per workgroup, one tet per lane; s_blocks: the brick's blocks, 9
+// doubles each, row node = the smaller node.  Bound by latency and by the
+// address units at about 10 waves a CU: staging 20 k clocks, of which the
+// reads are most, the tets' sums 8 k, the first chain 5 k.  At the fracture
+// mesh of resolution 40 (384,000 tets) 50 us (64 with every tet gathering its
+// 144 cotangents), the whole adjoint 72 (97).  Bricks of 64 tets, 8 rounds in
+// flight, whole rows per lane and atomic adds in LDS measured 71 to 82.
+__global__ __launch_bounds__(kAdjointBrick) void k_adjoint_element(DevView v, const int32_t* __restrict__ order,
+                                                                   int32_t n_chunks, AdjointPlan plan,
+                                                                   const double* __restrict__ gA,
+                                                                   double* __restrict__ g_logE,
+                                                                   double* __restrict__ xbar)
+{
+    extern __shared__ double s_blocks[];
+    // each XCD takes one contiguous share of the bricks: neighbouring bricks share rows in its L2
+    const int brick = xcd_remap(blockIdx.x, gridDim.x), t = threadIdx.x;
+    const int e = brick_tet(v, order, n_chunks, brick, t);
+    const int start = plan.starts[brick], m = plan.starts[brick + 1] - start;
+    const int32_t* __restrict__ entries = plan.entries + (size_t)kEntryWords * start;
+    // the tet's own data, in flight while the blocks are formed
+    const int ee = e >= 0 ? e : 0;
+    const uint8_t active = v.mask[ee];
+    const int4 T = v.T[ee];
+    const double E = v.E[ee];
+    int pos[4];
+    unsigned ref[10];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+        pos[a] = v.e2p[10 * (size_t)ee + a];
+#pragma unroll
+    for (int q = 0; q < 10; ++q)
+        ref[q] = plan.refs[((size_t)brick * 10 + q) * kAdjointBrick + t];
+    // three lanes per row block (its columns), 21 row blocks per wave and round,
+    // kAhead rounds in flight: a typical brick's 600 row blocks at once.  The
+    // upper copies are stored, then the mirrors added transposed (a diagonal
+    // block's copy is both).  Loads past the last row block take its data.
+    constexpr int kWaveBlocks = 21, kRound = kAdjointBrick / 64 * kWaveBlocks, kAhead = 15, kBatch = kAhead * kRound;
+    const int j = (t & 63) % 3, first = (t & 63) < 63 ? (t >> 6) * kWaveBlocks + (t & 63) / 3 : 1 << 20;
+    double x[kAhead][3];
+    int what[kAhead];
+    auto load_rows = [&](int b0) {
+        int pos[kAhead], rl[kAhead];
+#pragma unroll
+        for (int w = 0; w < kAhead; ++w) {
+            const int k = b0 + first + w * kRound;
+            const int32_t* o = entries + kEntryWords * min(k, m - 1);
+            pos[w] = o[0];
+            rl[w] = o[1];
+            what[w] = o[2] | ((m - 1 - k) >> 31);  // -1 past the end
+        }
+#pragma unroll
+        for (int w = 0; w < kAhead; ++w)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                x[w][i] = gA[pos[w] + i * rl[w] + j];
+    };
+    auto store_uppers = [&]() {
+#pragma unroll
+        for (int w = 0; w < kAhead; ++w)
+            if (what[w] >= 0 && !(what[w] & kMirror)) {
+                double* dst = s_blocks + 9 * (what[w] & (kDiagonal - 1)) + j;
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    dst[3 * i] = x[w][i];
+            }
+    };
+    auto add_mirrors = [&]() {
+#pragma unroll
+        for (int w = 0; w < kAhead; ++w)
+            if (what[w] >= 0 && (what[w] & (kMirror | kDiagonal))) {
+                double* dst = s_blocks + 9 * (what[w] & (kDiagonal - 1)) + 3 * j;
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    dst[i] = dst[i] + x[w][i];
+            }
+    };
+    for (int b0 = kBatch; b0 < m; b0 += kBatch) {  // rows past the first batch are read twice
+        load_rows(b0);
+        store_uppers();
+    }
+    load_rows(0);
+    store_uppers();
+    __syncthreads();
+    add_mirrors();
+    for (int b0 = kBatch; b0 < m; b0 += kBatch) {
+        load_rows(b0);
+        add_mirrors();
+    }
+    Geo G;
+    geometry(v, T, G);
+    __syncthreads();
+    if (e < 0)
         return;
-    const int* pos = v.e2p + 10 * (size_t)e;
-    if (!v.mask[e]) {
+    if (!active) {
         g_logE[e] = 0.0;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -136,93 +333,57 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_element(DevView v, const int
         }
         return;
     }
-    const int4 t = v.T[e];
-    const int id[4] = {t.x, t.y, t.z, t.w};
-    const int* eb = v.e2b + 10 * (size_t)e;
-    Geo G;
-    geometry(v, t, G);
-    const double E = v.E[e];
     const double lam_dt = (E * v.mat.clam) * v.mat.cdt;  // lambda dt^2
     const double mu_dt = (E * v.mat.cmu) * v.mat.cdt;    // mu dt^2
     const double lamV = lam_dt * G.V, muV = mu_dt * G.V;
 
+    // gbar_a = lamV U_a + muV W_a, U_a = sum_b B_ab g_b, W_a = sum_b (B_ab^T + tr(B_ab) I) g_b
     double Plam = 0.0, Pmu = 0.0, Pm = 0.0;
+    double U[4][3] = {}, W[4][3] = {};
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        constexpr int PA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2}, PB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
+        const int a = PA[q], b = PB[q];
+        const double* r = s_blocks + 9 * (ref[q] & 0x7fffu);
+        const int x = ref[q] >> 15 ? 2 : 0;  // transposed: entries 1 3, 2 6 and 5 7 change places
+        const double B[3][3] = {{r[0], r[1 + x], r[2 + 2 * x]},
+                                {r[3 - x], r[4], r[5 + x]},
+                                {r[6 - 2 * x], r[7 - x], r[8]}};
+        const double* ga = G.g[a];
+        const double* gb = G.g[b];
+        const double tr = (B[0][0] + B[1][1]) + B[2][2];
+        const double sab = (ga[0] * gb[0] + ga[1] * gb[1]) + ga[2] * gb[2];
+        double Bg[3], Btg[3];  // B g_b, B^T g_b
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            Bg[i] = (B[i][0] * gb[0] + B[i][1] * gb[1]) + B[i][2] * gb[2];
+            Btg[i] = (B[0][i] * gb[0] + B[1][i] * gb[1]) + B[2][i] * gb[2];
+            U[a][i] += Bg[i];
+            W[a][i] += Btg[i] + tr * gb[i];
+        }
+        const double plam = (ga[0] * Bg[0] + ga[1] * Bg[1]) + ga[2] * Bg[2];
+        const double pmu = ((ga[0] * Btg[0] + ga[1] * Btg[1]) + ga[2] * Btg[2]) + tr * sab;
+        if (a == b) {
+            Plam += 0.5 * plam;
+            Pmu += 0.5 * pmu;
+            Pm += 0.5 * tr;
+        } else {
+            Plam += plam;
+            Pmu += pmu;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {  // B_ba = B_ab^T
+                U[b][i] += (B[0][i] * ga[0] + B[1][i] * ga[1]) + B[2][i] * ga[2];
+                W[b][i] += ((B[i][0] * ga[0] + B[i][1] * ga[1]) + B[i][2] * ga[2]) + tr * ga[i];
+            }
+        }
+    }
+    g_logE[e] = lamV * Plam + muV * Pmu;
     double gbar[4][3];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int i = 0; i < 3; ++i)
-            gbar[a][i] = 0.0;
-
-    // pairs (a, b) with a <= b; B_ab = Abar_ab + Abar_ba^T, B_ba = B_ab^T
-    constexpr int PA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2};
-    constexpr int PB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
-#pragma unroll
-    for (int q = 0; q < 10; ++q) {
-        const int a = PA[q], b = PB[q];
-        double Aab[3][3], Aba[3][3];
-        gather_block(v, gA, id, a, b, eb[q], Aab);
-        if (a == b) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    Aba[i][j] = Aab[i][j];
-        } else {
-            gather_block(v, gA, id, b, a, eb[q], Aba);
-        }
-        // P terms over (a,b) and, for a != b, (b,a)
-        const double* ga = G.g[a];
-        const double* gb = G.g[b];
-        const double sab = (ga[0] * gb[0] + ga[1] * gb[1]) + ga[2] * gb[2];
-        double t_ab = 0.0, t_ba = 0.0, plam = 0.0, pmu = 0.0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                plam += ga[i] * Aab[i][j] * gb[j];
-                pmu += gb[i] * Aab[i][j] * ga[j];
-                if (a != b) {
-                    plam += gb[i] * Aba[i][j] * ga[j];
-                    pmu += ga[i] * Aba[i][j] * gb[j];
-                }
-            }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            t_ab += Aab[i][i];
-            t_ba += Aba[i][i];
-        }
-        if (a == b) {
-            Plam += plam;
-            Pmu += pmu + t_ab * sab;
-            Pm += t_ab;
-        } else {
-            Plam += plam;
-            Pmu += pmu + (t_ab + t_ba) * sab;
-        }
-        // gbar: B_ab = Aab + Aba^T drives gbar_a (with g_b); B_ba = B_ab^T drives gbar_b (with g_a)
-        double B[3][3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                B[i][j] = Aab[i][j] + Aba[j][i];
-        const double trB = (B[0][0] + B[1][1]) + B[2][2];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            double ua = 0.0, ub = 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                ua += (lamV * B[i][j] + muV * B[j][i]) * gb[j];
-                if (a != b)
-                    ub += (lamV * B[j][i] + muV * B[i][j]) * ga[j];
-            }
-            gbar[a][i] += ua + muV * trB * gb[i];
-            if (a != b)
-                gbar[b][i] += ub + muV * trB * ga[i];
-        }
-    }
-    g_logE[e] = lamV * Plam + muV * Pmu;
+            gbar[a][i] = lamV * U[a][i] + muV * W[a][i];
 
     const double Vbar = lam_dt * Plam + mu_dt * Pmu + 0.25 * v.mat.rho * Pm;
     const double detbar = Vbar * (G.det < 0.0 ? -1.0 : 1.0) / 6.0;
@@ -312,14 +473,30 @@ __global__ __launch_bounds__(kBlock) void k_slot_outer(int n_rows, const int32_t
 
 }  // namespace
 
-hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const double* gA, double* g_logE,
-                          double* g_x, double* xbar, hipStream_t s)
+int adjoint_bricks(int n_chunks)
 {
-    // kBlock / kAdjointChunk chunks per workgroup, so the grid covers n_chunks
-    const unsigned grid = (unsigned)((n_chunks + kBlock / kAdjointChunk - 1) / (kBlock / kAdjointChunk));
+    return (n_chunks + kBrickChunks - 1) / kBrickChunks;
+}
+
+hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
+                               bool fill, hipStream_t s)
+{
+    if (n_chunks == 0)
+        return hipSuccess;
+    const dim3 grid(adjoint_bricks(n_chunks));
+    if (fill)
+        hipLaunchKernelGGL(k_adjoint_plan<true>, grid, dim3(kAdjointBrick), 0, s, v, order, n_chunks, plan);
+    else
+        hipLaunchKernelGGL(k_adjoint_plan<false>, grid, dim3(kAdjointBrick), 0, s, v, order, n_chunks, plan);
+    return hipGetLastError();
+}
+
+hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
+                          const double* gA, double* g_logE, double* g_x, double* xbar, hipStream_t s)
+{
     if (v.n_tets > 0)
-        hipLaunchKernelGGL(k_adjoint_element, dim3(grid), dim3(kBlock), kAdjointReservedLds, s, v, order, n_chunks,
-                           gA, g_logE, xbar);
+        hipLaunchKernelGGL(k_adjoint_element, dim3(adjoint_bricks(n_chunks)), dim3(kAdjointBrick),
+                           9 * sizeof(double) * plan.most, s, v, order, n_chunks, plan, gA, g_logE, xbar);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || v.n_nodes == 0)
         return e;
@@ -408,7 +585,7 @@ extern "C" sta_status sta_adjoint_noalloc(sta_ctx* ctx, const double* gA_dev, do
     }
     // every diagonal incidence's three entries are written by the element pass
     // before the node pass reads them, so nothing needs clearing
-    e = sta::launch_adjoint(ctx->v, ctx->adj_order, ctx->adj_chunks, gA_dev, g_logE_dev, g_x_dev, xbar,
+    e = sta::launch_adjoint(ctx->v, ctx->adj_order, ctx->adj_chunks, ctx->adj_plan, gA_dev, g_logE_dev, g_x_dev, xbar,
                             static_cast<hipStream_t>(stream));
     if (e != hipSuccess) {
         ctx->errmsg = std::string("sta_adjoint_noalloc launch: ") + hipGetErrorString(e);

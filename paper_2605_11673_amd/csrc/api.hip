@@ -385,6 +385,9 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     ALLOC(trec, n_tets);
     const int64_t n_chunks = (n_tets + kAdjointChunk - 1) / kAdjointChunk;
     ALLOC(c->adj_order, n_chunks);
+    const int64_t bricks = adjoint_bricks((int)n_chunks);
+    ALLOC(c->adj_plan.refs, bricks * 10 * kAdjointBrick);
+    ALLOC(c->adj_plan.starts, bricks + 1);
 #undef ALLOC
     if (e != hipSuccess) {
         free_all(c);
@@ -482,6 +485,28 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.wg_err = wg_err;
     v.ctl = ctl;
 
+    // the adjoint's bricks: count, running sums, fill
+    if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, false, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess && bricks > 0) {
+        std::vector<int32_t> starts((size_t)bricks + 1), blocks((size_t)bricks);
+        e = hipMemcpy(starts.data(), c->adj_plan.starts, sizeof(int32_t) * bricks, hipMemcpyDeviceToHost);
+        if (e == hipSuccess)
+            e = hipMemcpy2D(blocks.data(), sizeof(int32_t), c->adj_plan.refs, 20 * kAdjointBrick, sizeof(int32_t),
+                            (size_t)bricks, hipMemcpyDeviceToHost);
+        int32_t sum = 0;  // at most 16 per tet slot: a tet reads 4 + 2 * 6 row blocks
+        for (int64_t k = 0; k < bricks; ++k) {
+            const int32_t m = starts[k];
+            starts[k] = sum;
+            sum += m;
+            c->adj_plan.most = std::max(c->adj_plan.most, blocks[k]);
+        }
+        starts[bricks] = sum;
+        if (e == hipSuccess) e = dalloc(c, &c->adj_plan.entries, (size_t)3 * sum);
+        if (e == hipSuccess)
+            e = hipMemcpy(c->adj_plan.starts, starts.data(), sizeof(int32_t) * (bricks + 1), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, true, s);
+    }
     if (e == hipSuccess) e = launch_geometry(v, s);
     if (e == hipSuccess) e = launch_rows(v, false, s);
     if (e == hipSuccess) e = launch_rows_big(v, false, s);
@@ -491,7 +516,8 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     if (e != hipSuccess) {
         free_all(c);
         delete c;
-        return fail(nullptr, STA_EHIP, std::string("build: ") + hipGetErrorString(e));
+        return fail(nullptr, e == hipErrorOutOfMemory ? STA_ENOMEM : STA_EHIP,
+                    std::string("build: ") + hipGetErrorString(e));
     }
     if (bits & ERR_DEGENERATE) {
         free_all(c);
@@ -1079,7 +1105,7 @@ sta_status sta_adjoint(sta_ctx* ctx, const double* gA_dev, double* g_logE_dev, d
     hipStream_t s = static_cast<hipStream_t>(stream);
     e = timed(ctx, STA_KERNEL_ADJOINT, s,
               [&] {
-                  return launch_adjoint(ctx->v, ctx->adj_order, ctx->adj_chunks, gA_dev, g_logE_dev, g_x_dev,
+                  return launch_adjoint(ctx->v, ctx->adj_order, ctx->adj_chunks, ctx->adj_plan, gA_dev, g_logE_dev, g_x_dev,
                                         ctx->adj_xbar, s);
               });
     if (e != hipSuccess)

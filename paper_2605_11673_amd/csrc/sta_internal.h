@@ -245,6 +245,17 @@ struct DevView {
     Material mat;
 };
 
+// The adjoint's bricks (adjoint.hip): three words for each row block that each
+// reads, where each brick's begin (one past the last at the end), and 10
+// references per tet slot.
+constexpr int kAdjointChunk = 16, kAdjointBrick = 128;
+struct AdjointPlan {
+    int32_t* entries = nullptr;
+    int32_t* starts = nullptr;
+    uint16_t* refs = nullptr;
+    int32_t most = 0;  // blocks of the brick that has most
+};
+
 // Conjugate-gradient workspace (cg.hip).
 struct CgScalars {
     double rz, alpha, beta, rr, bnorm2, tol2;
@@ -301,6 +312,7 @@ struct sta_ctx {
     double* adj_xbar = nullptr;     // 3 doubles per diagonal incidence
     int32_t* adj_order = nullptr;   // adjoint visiting order of the kAdjointChunk-tet chunks
     int32_t adj_chunks = 0;
+    sta::AdjointPlan adj_plan;
     int32_t* dinc = nullptr;        // per diagonal incidence: its tet (segments in ascending tet id)
     double* tet_ml = nullptr;       // per tet: lumped mass per vertex dof, (rho V) / 4
     bool tet_ml_stale = true;
@@ -391,11 +403,16 @@ hipError_t launch_set_params(const DevView& v, const double* x_aos, const double
 // Adjoint and CG launchers (adjoint.hip, cg.hip).
 // The adjoint visits the tets in chunks of kAdjointChunk consecutive ids, in
 // an order fixed at context build (each mesh's chunks by the Morton code of
-// their centroid), so that the chunks in flight together are near in space
-// and their cotangent rows shared in cache.  Any order gives the same bits.
-constexpr int kAdjointChunk = 16;
-hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const double* gA, double* g_logE,
-                          double* g_x, double* xbar, hipStream_t s);
+// their centroid), bricks of kAdjointBrick tets at a time.  Any order gives
+// the same bits.  The plan is found on the device at context build.
+// fill = false: the bricks' numbers of row blocks into starts, and of blocks as
+// the first word of each brick's references; then, with starts their running
+// sum and entries allocated, fill = true.
+hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
+                               bool fill, hipStream_t s);
+int adjoint_bricks(int n_chunks);
+hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
+                          const double* gA, double* g_logE, double* g_x, double* xbar, hipStream_t s);
 hipError_t launch_slot_outer(int n_rows, const int32_t* rowptr, const int32_t* colidx, const double* a,
                              const double* b, double alpha, double* out, hipStream_t s);
 hipError_t launch_diag_positions(const DevView& v, int32_t* dpos, hipStream_t s);

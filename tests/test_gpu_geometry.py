@@ -160,3 +160,32 @@ def test_inactive_degenerate_tet_contributes_nothing():
     asm.apply_edits(*Sm.upload_frame(np.array([flat], np.int32), np.ones(1, np.uint8)))
     assert asm.status_sync() == Sm.STA_EDEGENERATE
     asm.close()
+
+
+def scattered_mesh(n_nodes, m, seed):
+    """Tets of random far-apart nodes: no two of a brick of the adjoint share many blocks."""
+    g = np.random.default_rng(seed)
+    x = g.uniform(0.0, 1.0, size=(n_nodes, 3))
+    tets = np.argsort(g.uniform(size=(m, n_nodes)), axis=1)[:, :4].astype(np.int32)
+    return W.Workload("scattered", x, tets, W.lognormal_E(m, g), g.integers(0, 2, size=m).astype(np.uint8))
+
+
+@pytest.mark.parametrize("mesh", [lambda: scattered_mesh(400, 300, 1), lambda: scattered_mesh(30, 700, 2),
+                                  lambda: hub_mesh(9), lambda: W.make_cube(0, n=1, frames=0),
+                                  lambda: W.make_refinement(seed=2, n=3, frames=1)])
+def test_adjoint_bricks(mesh):
+    """Bricks with 1,280 different blocks (the most there can be), with few, with a node of
+    648 tets, with a single short chunk: every tet and coordinate within its rounding bound."""
+    from tests.bounds import adjoint_tolerances
+    Sm = S()
+    w = mesh()
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    g = np.random.default_rng(6).standard_normal(asm.nnz)
+    gl, gx = (t.cpu().numpy() for t in asm.adjoint(torch.from_numpy(g).cuda()))
+    args = (w.x, w.tets, w.E, w.nu, w.rho, w.dt, w.mask0, *pat, g)
+    ol, ox = oracle.adjoint(*args)
+    tl, tx = adjoint_tolerances(w, w.mask0, pat[0], pat[1], g)
+    assert np.all(np.abs(gl - ol) <= tl) and np.all(np.abs(gx - ox) <= tx)
+    assert np.all(gl[w.mask0 == 0] == 0.0)
+    asm.close()
