@@ -137,3 +137,16 @@ def test_trace_writes_one_line_per_call_with_frame_stats(tmp_path):
         assert ex.value.code == Sm.STA_EINVAL
     finally:
         os.environ.pop("STA_TRACE")
+
+
+def test_calls_take_the_current_stream():
+    assert S()._stream_handle() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    assert S()._stream_handle(side) == side.cuda_stream
+    with torch.cuda.stream(side):
+        assert S()._stream_handle() == side.cuda_stream
+    g = torch.cuda.CUDAGraph()
+    x = torch.zeros(1, device="cuda")
+    with torch.cuda.graph(g):
+        assert S()._stream_handle() == torch.cuda.current_stream().cuda_stream
+        x.add_(1.0)
