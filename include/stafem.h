@@ -286,8 +286,7 @@ sta_status sta_euler_step(sta_ctx* ctx, double* u_dev, double* v_dev, const doub
  * int32) receives, per tet, its component's smallest vertex id, or -1 for an
  * inactive tet; labels do not depend on execution order.  *n_components
  * (may be NULL) receives the number of components.  Synchronises `stream`
- * (the host reads the convergence flags and the count once per batch of
- * passes, normally once per call). */
+ * once, for the count. */
 sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_components, void* stream);
 
 /* Connectivity over shared faces (Sec. 3.6 leaves the adjacency open; this
@@ -299,7 +298,7 @@ sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_componen
  * *n_components (may be NULL) the number of components.  The candidate
  * pairs with a common face are found on the first call (a host sort of the
  * 4 n_tets vertex triples) and kept on the device with the context (8 B per
- * pair, 4 B per tet).  Synchronises `stream`.  Errors: STA_EINVAL,
+ * pair, 12 B per tet).  Synchronises `stream`.  Errors: STA_EINVAL,
  * STA_ENOMEM, STA_EHIP. */
 sta_status sta_face_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_components, void* stream);
 

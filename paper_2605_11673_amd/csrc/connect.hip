@@ -8,25 +8,27 @@
 // the component's smallest tet; the candidate pairs with a common vertex
 // triple are found once on the host and kept on the device.
 //
-// Vertex adjacency: components are found over the vertices by
-// hooking roots and shortcutting (a Shiloach-Vishkin style iteration): every
-// vertex keeps a parent pointer f, initially the smallest vertex of its
-// active tets (itself if smaller or isolated); in a hooking pass each
-// active tet climbs from its four vertices to their roots and lowers the
-// larger roots (and the vertices) to the smallest one with atomic minimum; a
-// shortcut pass points every vertex at the root it reaches.  Pointers only
-// decrease and stay inside the component, so when a hooking pass changes no
-// root, every component is one tree whose root is its smallest vertex.  A
-// tet's label is that vertex, independent of execution order.
+// Both are a union-find over parent pointers f.  Each workgroup first merges
+// one window of consecutive tets in LDS and keeps one root per set it finds.
+// Vertex: every vertex of the window then takes its set's root as its own,
+// exchanging it for that of another window that holds the vertex: those two
+// roots are to be united.  Face: the pairs that cross windows name two roots
+// each.  Of a workgroup's many pairs of roots few are different, and only those
+// are united.  Then every vertex (tet) climbs to its root, every
+// window's root lowers that root's smallest id by its own, and the labels read
+// that.  One wait per call, for the count, which the last launch writes to pinned
+// memory.
 //
-// Each pass is its own launch: within a pass, loads may see another XCD's
-// stale copy of a pointer, which only delays convergence (every update is a
-// monotone atomic minimum); the launch boundary makes all updates visible to
-// the next pass.  Passes are queued a few at a time, each returning at once
-// unless the pass before it changed something; after the batch the labels
-// (each climbing to its root) and the component count follow, and the host
-// reads the flags and the count back once.  If the batch's last pass still
-// changed something, another batch follows.
+// A union hooks one of two roots under the other with a compare and swap, and
+// climbs on from what it finds there if that was no root any more, so one pass
+// is complete.  Which one is hooked follows a fixed scattered order of the ids
+// (priority): trees stay shallow, where hooking the larger id under the smaller
+// makes chains as long as the row of windows.  Plain loads may see
+// another XCD's stale copy of a pointer: that is an older ancestor, and only
+// costs the swap that fails on it.  Climbing shortens paths with stores that
+// race; they only replace a pointer of a vertex that is no root by one to
+// another of its ancestors, and no swap takes such a vertex, so no union is
+// lost.  Launch boundaries make all of it visible to what follows.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -45,226 +47,310 @@ unsigned blocks(int64_t n)
     return (unsigned)((n + kBlock - 1) / kBlock);
 }
 
-// Hooking passes per batch: the vertex rebuild mostly converges in two, the
-// face rebuild in three (on the 384k-tet fracture stream: vertex 77 / 78 / 81
-// / 91 us per rebuild at 2 / 3 / 4 / 6 passes per batch, face 147 / 117 /
-// 122 / 126 us).  Flag words: [0, batch) set by hooking pass p when it
-// changes a pointer; kMaxBatch: a climb of the labelling pass stopped short
-// of a root; kMaxBatch + 1: the number of components.
-constexpr int kVertexBatch = 2, kFaceBatch = 3;
-constexpr int kMaxBatch = 3;
-constexpr int kTruncWord = kMaxBatch, kCountWord = kMaxBatch + 1;
-constexpr int kFlagWords = kMaxBatch + 2;
+// Tets per workgroup of the first merge.  Larger windows leave fewer roots to
+// unite: both adjacencies of a fracture mesh of 196,608 tets take 130, 107, 99
+// us a call at 256, 512, 1,024 tets.
+constexpr int kWindow = 1024;
+constexpr int kSlots = 8192;  // hash slots of a window's vertices
+static_assert(4 * kWindow < kSlots && kSlots == 1 << 13, "every vertex of a window finds a slot");
 
-// Pass p > 0 of a batch runs only if pass p - 1 changed something (gate
-// NULL: always).  The word is the same for every thread of the launch.
-__device__ __forceinline__ bool gated_off(const uint32_t* gate)
+// Pointers go to ids of smaller priority only, so every climb and union ends.
+__device__ __forceinline__ uint32_t priority(int x)
 {
-    return gate && *gate == 0u;
+    return (uint32_t)x * 2654435761u;
 }
 
-// Seed (replaces the identity start): every vertex points at the smallest
-// vertex of its active tets, or at itself if that is smaller or it has none,
-// read from its diagonal incidence segment (dinc: the tet of each incidence).
-// That vertex shares a tet with it, so the pointer stays inside the component
-// and only decreases, as every later update does; the hooking passes then
-// start from local minima and contend far less on their atomics.
-__global__ __launch_bounds__(kBlock) void k_cc_seed(DevView v, const int32_t* __restrict__ dinc, int* f,
-                                                    uint32_t* mark, uint32_t* flag)
+// The root above x as far as this thread sees; paths are shortened on the way.
+__device__ __forceinline__ int climb(int* f, int x)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < kFlagWords)
-        flag[i] = 0u;  // the first batch's flags
-    if (i >= v.n_nodes)
-        return;
-    int m = i;
-    bool any = false;
-    const int b = v.ndiag[i];
-    if (b >= 0) {
-        const BlockDesc d = v.desc[b];
-        constexpr int kChunk = 8;
-        for (int k0 = d.k0; k0 < d.k1; k0 += kChunk) {
-            int e[kChunk];
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j)
-                e[j] = k0 + j < d.k1 ? dinc[k0 + j] : -1;
-            bool on[kChunk];
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j)
-                on[j] = e[j] >= 0 && v.mask[e[j]];
-#pragma unroll
-            for (int j = 0; j < kChunk; ++j)
-                if (on[j]) {
-                    const int4 t = v.T[e[j]];
-                    const int lo = min(min(t.x, t.y), min(t.z, t.w));
-                    m = lo < m ? lo : m;
-                    any = true;
-                }
-        }
+    int prev = x, cur = f[x];
+    if (cur == x)
+        return x;
+    for (int next = f[cur]; next != cur; next = f[cur]) {
+        f[prev] = next;
+        prev = cur;
+        cur = next;
     }
-    f[i] = m;
-    mark[i] = any ? 1u : 0u;  // a vertex of an active tet
+    return cur;
 }
 
-// Follow parent pointers from x towards its root (at most kMaxSteps hops:
-// any vertex reached is an ancestor, which is all the passes need).
-constexpr int kMaxSteps = 1 << 16;
-
-__device__ __forceinline__ int climb(const int* f, int x)
+__device__ __forceinline__ void unite(int* f, int a, int b)
 {
-    for (int s = 0; s < kMaxSteps; ++s) {
-        const int p = f[x];
-        if (p == x)
+    a = climb(f, a);
+    b = climb(f, b);
+    while (a != b) {
+        if (priority(a) < priority(b)) {
+            const int c = a;
+            a = b;
+            b = c;
+        }
+        const int old = atomicCAS(f + a, a, b);
+        if (old == a)
             break;
-        x = p;
+        a = climb(f, old);
+        b = climb(f, b);
     }
-    return x;
 }
 
-// Hooking pass: each active tet lowers the roots of its four vertices (and
-// the vertices themselves) to the smallest of those roots.
-__global__ __launch_bounds__(kBlock) void k_cc_hook(DevView v, int* f, const uint32_t* gate, uint32_t* changed_out)
+// The same in LDS.
+__device__ __forceinline__ int climb_lds(volatile int* f, int x)
 {
-    const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (gated_off(gate) || e >= v.n_tets || !v.mask[e])
-        return;
-    const int4 t = v.T[e];
-    const int x[4] = {t.x, t.y, t.z, t.w};
-    int r[4], m = INT32_MAX;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        r[k] = climb(f, x[k]);
-        m = r[k] < m ? r[k] : m;
+    int cur = f[x];
+    if (cur == x)
+        return x;
+    for (int next = f[cur]; next != cur; next = f[cur]) {
+        f[x] = next;
+        x = cur;
+        cur = next;
     }
-    bool changed = false;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (r[k] > m) {
-            changed |= atomicMin(f + r[k], m) > m;
-            changed |= atomicMin(f + x[k], m) > m;
-        }
-    }
-    if (changed)
-        changed_out[0] = 1u;
+    return cur;
 }
 
-// Shortcut pass: every pointer to the root it reaches (only thread i writes f[i]).
-__global__ __launch_bounds__(kBlock) void k_cc_shortcut(int n, int* f, const uint32_t* gate)
+__device__ __forceinline__ void unite_lds(int* f, int a, int b)
+{
+    a = climb_lds(f, a);
+    b = climb_lds(f, b);
+    while (a != b) {
+        if (priority(a) < priority(b)) {
+            const int c = a;
+            a = b;
+            b = c;
+        }
+        const int old = atomicCAS(f + a, a, b);
+        if (old == a)
+            break;
+        a = climb_lds(f, old);
+    }
+}
+
+// A pair of roots that this workgroup has not just united.  The table keeps
+// the last pair of each place, so a pair may be new twice, but never unseen.
+constexpr int kPairSlots = 1024;
+__device__ __forceinline__ bool new_pair(unsigned long long* table, int a, int b)
+{
+    const unsigned long long key = (unsigned long long)(uint32_t)min(a, b) << 32 | (uint32_t)max(a, b);
+    const uint32_t h = (priority(a) + priority(b)) >> 22;
+    return atomicExch(table + h, key) != key;
+}
+static_assert(kPairSlots == 1 << (32 - 22), "the hash covers the table");
+
+// own[i] = -1: vertex i is in no active tet.
+__global__ __launch_bounds__(kBlock) void k_cc_init(int n, int* __restrict__ f, int* __restrict__ least,
+                                                    int* __restrict__ own, uint32_t* __restrict__ count)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (gated_off(gate) || i >= n)
-        return;
-    const int p = f[i];
-    const int r = climb(f, p);
-    if (r < p)
-        f[i] = r;
+    if (i == 0)
+        *count = 0u;
+    if (i < n) {
+        f[i] = i;
+        least[i] = INT32_MAX;
+        own[i] = -1;
+    }
 }
 
-// After the hooking passes have converged (roots fixed): thread e < n_tets
-// labels tet e with the root of its first vertex (-1 if inactive), climbing
-// there itself; thread i < n_nodes counts vertex i if it is a root and a
-// vertex of an active tet (each component's root is its smallest vertex,
-// which belongs to an active tet).  A climb that stops at the step limit
-// leaves a non-root, reported in *truncated (then another batch follows).
-__global__ __launch_bounds__(kBlock) void k_cc_finish(DevView v, const int* __restrict__ f,
-                                                      const uint32_t* __restrict__ mark, int32_t* __restrict__ label,
-                                                      uint32_t* count, uint32_t* truncated)
+// One window of tets: the vertices of its active tets in a hash table, merged
+// there; then its roots with those of other windows.  Bound by latency: chains
+// of LDS atomics, then of pointers to global roots.  22 us at 196,608 tets,
+// where seeding every vertex from its tets and two to four hooking passes, each
+// with a shortcut pass, took 13 + 62; the whole call 54 us at 384,000 tets, all
+// active or half of them (54, 464 before), 366 with scattered ids (5,554).
+__global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, int* f, int* __restrict__ own, int* least)
+{
+    __shared__ int s_key[kSlots], s_f[kSlots], s_least[kSlots];
+    __shared__ unsigned long long s_pair[kPairSlots];
+    const int e = blockIdx.x * kWindow + threadIdx.x;
+    const int4 t = v.T[min(e, v.n_tets - 1)];
+    const bool on = e < v.n_tets && v.mask[min(e, v.n_tets - 1)];
+    for (int h = threadIdx.x; h < kSlots; h += kWindow) {
+        s_key[h] = -1;
+        s_f[h] = h;
+        s_least[h] = INT32_MAX;
+    }
+    for (int h = threadIdx.x; h < kPairSlots; h += kWindow)
+        s_pair[h] = ~0ull;
+    __syncthreads();
+    if (on) {
+        const int x[4] = {t.x, t.y, t.z, t.w};
+        int slot[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            unsigned h = priority(x[k]) >> (32 - 13);
+            for (;; h = (h + 1) & (kSlots - 1)) {  // ends: there are more slots than vertices
+                const int old = atomicCAS(&s_key[h], -1, x[k]);
+                if (old == -1 || old == x[k])
+                    break;
+            }
+            slot[k] = (int)h;
+        }
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+            unite_lds(s_f, slot[0], slot[k]);
+    }
+    __syncthreads();
+    constexpr int kMine = kSlots / kWindow;
+    int root[kMine], other[kMine];
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int h = threadIdx.x + k * kWindow, x = s_key[h];
+        root[k] = other[k] = -1;
+        if (x >= 0) {
+            const int r = climb_lds(s_f, h);
+            atomicMin(s_least + r, x);
+            root[k] = s_key[r];
+            other[k] = atomicExch(own + x, root[k]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kMine; ++k) {
+        const int h = threadIdx.x + k * kWindow;
+        if (s_least[h] != INT32_MAX)  // h is a root
+            atomicMin(least + s_key[h], s_least[h]);
+    }
+#pragma unroll
+    for (int k = 0; k < kMine; ++k)
+        if (other[k] >= 0 && other[k] != root[k] && new_pair(s_pair, root[k], other[k]))
+            unite(f, root[k], other[k]);
+}
+
+// After the unions: of every id i the root, into own[i] (a root of i's window
+// before; -1: not in an active tet, not an active tet), and of every root the
+// smallest id and the count.  least[i] is set where i is a root of a window, to
+// the smallest id of its set there.
+__global__ __launch_bounds__(kBlock) void k_cc_roots(int n, int* __restrict__ own, const int* __restrict__ f,
+                                                     int* least, uint32_t* count)
 {
     __shared__ uint32_t s_count;
     if (threadIdx.x == 0)
         s_count = 0u;
     __syncthreads();
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t < v.n_tets) {
-        int32_t l = -1;
-        if (v.mask[t]) {
-            l = climb(f, v.T[t].x);
-            if (f[l] != l)
-                truncated[0] = 1u;
-        }
-        label[t] = l;
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    int r = -1, m = INT32_MAX;
+    if (i < n) {
+        r = own[i];
+        m = least[i];
     }
-    if (t < v.n_nodes && mark[t] && f[t] == t)
+    if (r >= 0) {
+        for (int p = f[r]; p != r; p = f[r])
+            r = p;
+        own[i] = r;
+    }
+    // A root hears from all its windows' roots: in a wave one lane speaks for
+    // the lanes with the same root (of two roots; lanes with further ones speak
+    // for themselves), and only if its id can lower what it sees there.  (Where
+    // tet ids are scattered and nearly every tet is a window's root, an atomic
+    // each took 4.6 ms of a call.)
+    bool speaks = m != INT32_MAX && r != i;  // least[i] is no root's, and stays
+    for (int k = 0; k < 2; ++k) {
+        const unsigned long long left = __ballot(speaks);
+        if (left == 0)
+            break;
+        const int lead = __ffsll(left) - 1, lr = __shfl(r, lead, 64);
+        const bool same = speaks && r == lr;
+        int least_id = same ? m : INT32_MAX;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1)
+            least_id = min(least_id, __shfl_xor(least_id, d, 64));
+        if ((int)(threadIdx.x & 63) == lead && least[lr] > least_id)
+            atomicMin(least + lr, least_id);
+        speaks = speaks && !same;
+    }
+    if (speaks && least[r] > m)
+        atomicMin(least + r, m);
+    if (m != INT32_MAX && r == i)
         atomicAdd(&s_count, 1u);
     __syncthreads();
     if (threadIdx.x == 0 && s_count)
         atomicAdd(count, s_count);
 }
 
-// Face adjacency: parent pointers over tets, each starting at itself.
-__global__ __launch_bounds__(kBlock) void k_ccf_init(int n_tets, int* f, uint32_t* flag)
+// Tet e's label: the smallest id at the root of its first vertex (-1 if
+// inactive); and the count, to the host.
+__global__ __launch_bounds__(kBlock) void k_cc_label(DevView v, const int* __restrict__ own,
+                                                     const int* __restrict__ least, int32_t* __restrict__ label,
+                                                     const uint32_t* __restrict__ count, uint32_t* host)
 {
     const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (e < kFlagWords)
-        flag[e] = 0u;  // the first batch's flags
-    if (e < n_tets)
-        f[e] = e;
+    if (e == 0)
+        __hip_atomic_store(host, *count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (e < v.n_tets)
+        label[e] = v.mask[e] ? least[own[v.T[e].x]] : -1;
 }
 
-// Face adjacency, seed: across each active face pair inside one aligned group
-// of 16 tet ids, the larger tet points at the smaller (atomic minimum).  Chains
-// stay inside a group (at most 15 hops) and every pointer still goes to a tet
-// of the same component with a smaller id; the hooking passes then start with
-// most of each group merged.  (Seeding from every face neighbour instead made
-// chains as long as the mesh and the first hooking pass slower.)
-__global__ __launch_bounds__(kBlock) void k_ccf_seed(const uint8_t* __restrict__ mask, const int2* __restrict__ pairs,
-                                                     int64_t n_pairs, int* f)
+// Face adjacency, one window of tets: the pairs inside it (pairs are sorted by
+// their smaller tet; start: the first pair of each window).
+__global__ __launch_bounds__(kWindow) void k_ccf_windows(int n_tets, const uint8_t* __restrict__ mask,
+                                                         const int2* __restrict__ pairs,
+                                                         const int64_t* __restrict__ start, int* __restrict__ own,
+                                                         int* __restrict__ f, int* __restrict__ least,
+                                                         uint32_t* __restrict__ count)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= n_pairs)
-        return;
-    const int2 p = pairs[k];  // p.x < p.y
-    if ((p.x >> 4) != (p.y >> 4) || !mask[p.x] || !mask[p.y])
-        return;
-    atomicMin(f + p.y, p.x);
-}
-
-// Hooking pass over the face pairs whose two tets are both active.
-__global__ __launch_bounds__(kBlock) void k_ccf_hook(const uint8_t* __restrict__ mask, const int2* __restrict__ pairs,
-                                                     int64_t n_pairs, int* f, const uint32_t* gate,
-                                                     uint32_t* changed_out)
-{
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (gated_off(gate) || k >= n_pairs)
-        return;
-    const int2 p = pairs[k];
-    if (!mask[p.x] || !mask[p.y])
-        return;
-    const int ra = climb(f, p.x), rb = climb(f, p.y);
-    if (ra == rb)
-        return;
-    const int lo = ra < rb ? ra : rb, hi = ra < rb ? rb : ra;
-    bool changed = atomicMin(f + hi, lo) > lo;
-    changed |= atomicMin(f + p.x, lo) > lo;
-    changed |= atomicMin(f + p.y, lo) > lo;
-    if (changed)
-        changed_out[0] = 1u;
-}
-
-// After the hooking passes have converged: label every tet with its root
-// (-1 if inactive), climbing there itself; count the active roots; report a
-// climb stopped at the step limit in *truncated.
-__global__ __launch_bounds__(kBlock) void k_ccf_label(int n_tets, const uint8_t* __restrict__ mask,
-                                                      const int* __restrict__ f, int32_t* __restrict__ label,
-                                                      uint32_t* count, uint32_t* truncated)
-{
-    __shared__ uint32_t s_count;
-    if (threadIdx.x == 0)
-        s_count = 0u;
+    __shared__ int s_f[kWindow], s_least[kWindow];
+    __shared__ uint8_t s_on[kWindow];
+    const int base = blockIdx.x * kWindow, e = base + threadIdx.x;
+    if (e == 0)
+        *count = 0u;
+    s_f[threadIdx.x] = threadIdx.x;
+    s_least[threadIdx.x] = INT32_MAX;
+    s_on[threadIdx.x] = e < n_tets ? mask[e] : (uint8_t)0;
+    const int64_t k1 = start[blockIdx.x + 1];
     __syncthreads();
-    const int e = blockIdx.x * kBlock + threadIdx.x;
-    if (e < n_tets) {
-        const bool on = mask[e] != 0;
-        const int r = on ? climb(f, e) : -1;
-        if (on && f[r] != r)
-            truncated[0] = 1u;
-        label[e] = r;
-        if (on && r == e)
-            atomicAdd(&s_count, 1u);
+    for (int64_t k = start[blockIdx.x] + threadIdx.x; k < k1; k += kWindow) {
+        const int a = pairs[k].x - base, b = pairs[k].y - base;
+        if (b < kWindow && s_on[a] && s_on[b])
+            unite_lds(s_f, a, b);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && s_count)
-        atomicAdd(count, s_count);
+    const int r = s_on[threadIdx.x] ? climb_lds(s_f, threadIdx.x) : -1;
+    if (r >= 0)
+        atomicMin(s_least + r, e);
+    __syncthreads();
+    if (e < n_tets) {
+        own[e] = r >= 0 ? base + r : -1;
+        f[e] = e;
+        least[e] = s_least[threadIdx.x];
+    }
+}
+
+// The pairs that cross windows, kCross per workgroup.  12 us at 196,608 tets
+// (three to six hooking passes over all pairs took 62 before); the whole call
+// 43 us at 384,000 tets, 70 with half of them active, 286 with scattered ids
+// (101, 160, 939 before).
+constexpr int kCrossLane = 4, kCross = kBlock * kCrossLane;
+__global__ __launch_bounds__(kBlock) void k_ccf_cross(const int2* __restrict__ pairs, int64_t n_pairs,
+                                                      const int* __restrict__ own, int* f)
+{
+    __shared__ unsigned long long s_pair[kPairSlots];
+    for (int h = threadIdx.x; h < kPairSlots; h += kBlock)
+        s_pair[h] = ~0ull;
+    int2 p[kCrossLane];
+    int a[kCrossLane], b[kCrossLane];
+#pragma unroll
+    for (int k = 0; k < kCrossLane; ++k)
+        p[k] = pairs[min((int64_t)blockIdx.x * kCross + k * kBlock + threadIdx.x, n_pairs - 1)];
+#pragma unroll
+    for (int k = 0; k < kCrossLane; ++k) {
+        a[k] = own[p[k].x];
+        b[k] = own[p[k].y];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kCrossLane; ++k)
+        if (a[k] >= 0 && b[k] >= 0 && a[k] != b[k] && new_pair(s_pair, a[k], b[k]))
+            unite(f, a[k], b[k]);
+}
+
+__global__ __launch_bounds__(kBlock) void k_ccf_label(int n_tets, const int* __restrict__ own,
+                                                      const int* __restrict__ least, int32_t* __restrict__ label,
+                                                      const uint32_t* __restrict__ count, uint32_t* host)
+{
+    const int e = blockIdx.x * kBlock + threadIdx.x;
+    if (e == 0)
+        __hip_atomic_store(host, *count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (e < n_tets) {
+        const int r = own[e];
+        label[e] = r >= 0 ? least[r] : -1;
+    }
 }
 
 }  // namespace
@@ -313,117 +399,52 @@ std::vector<int2> host_face_pairs(const std::vector<int4>& T)
     return pairs;
 }
 
-// One read-back per batch: the flags and the component count; *passes
-// counts the hooking passes that ran.  converged: the batch's last pass
-// changed nothing and no labelling climb stopped short.
-static hipError_t finish_batch(uint32_t* flag, uint32_t* host, int batch, int* passes, bool& converged,
-                               hipStream_t s)
+// Face-adjacency labels (smallest tet id of the component, -1 if inactive)
+// into label; the number of components into *host (pinned) once s is done.
+// own, f, least: n_tets ints each; count: one word.
+static hipError_t run_face_components(const DevView& v, const int2* pairs, int64_t n_pairs, const int64_t* start,
+                                      int* own, int* f, int* least, uint32_t* count, uint32_t* host, int32_t* label,
+                                      hipStream_t s)
 {
-    hipError_t e = hipMemcpyAsync(host, flag, sizeof(uint32_t) * kFlagWords, hipMemcpyDeviceToHost, s);
+    const dim3 windows(std::max(1, (v.n_tets + kWindow - 1) / kWindow)), tets(std::max(1u, blocks(v.n_tets)));
+    hipLaunchKernelGGL(k_ccf_windows, windows, dim3(kWindow), 0, s, v.n_tets, v.mask, pairs, start, own, f, least,
+                       count);
+    if (n_pairs > 0)
+        hipLaunchKernelGGL(k_ccf_cross, dim3((unsigned)((n_pairs + kCross - 1) / kCross)), dim3(kBlock), 0, s, pairs,
+                           n_pairs, own, f);
+    hipLaunchKernelGGL(k_cc_roots, tets, dim3(kBlock), 0, s, v.n_tets, own, f, least, count);
+    hipLaunchKernelGGL(k_ccf_label, tets, dim3(kBlock), 0, s, v.n_tets, own, least, label, count, host);
+    return hipGetLastError();
+}
+
+// Component labels into label (device, n_tets); *host and count as above; own,
+// f, least: n_nodes ints each.
+static hipError_t run_components(const DevView& v, int* own, int* f, int* least, uint32_t* count, uint32_t* host,
+                                 int32_t* label, hipStream_t s)
+{
+    const dim3 nodes(std::max(1u, blocks(v.n_nodes)));
+    hipLaunchKernelGGL(k_cc_init, nodes, dim3(kBlock), 0, s, v.n_nodes, f, least, own, count);
+    if (v.n_tets > 0)
+        hipLaunchKernelGGL(k_cc_windows, dim3((v.n_tets + kWindow - 1) / kWindow), dim3(kWindow), 0, s, v, f, own,
+                           least);
+    hipLaunchKernelGGL(k_cc_roots, nodes, dim3(kBlock), 0, s, v.n_nodes, own, f, least, count);
+    hipLaunchKernelGGL(k_cc_label, dim3(std::max(1u, blocks(v.n_tets))), dim3(kBlock), 0, s, v, own, least, label, count,
+                       host);
+    return hipGetLastError();
+}
+
+// Waits for s; the count that the labels' kernel left in pinned memory.
+static sta_status read_count(sta_ctx* ctx, hipError_t e, const char* what, int64_t* n_components, hipStream_t s)
+{
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
-        return e;
-    int ran = 1;
-    for (int p = 0; p + 1 < batch; ++p)
-        ran += host[p] != 0u;
-    *passes += ran;
-    converged = host[batch - 1] == 0u && host[kTruncWord] == 0u;
-    return hipSuccess;
-}
-
-// Face-adjacency labels (smallest tet id of the component, -1 if inactive)
-// into label; *n_components on the host.  f: n_tets ints; flag: kFlagWords
-// words; host_flag: kFlagWords pinned words.  Synchronises s.
-hipError_t run_face_components(const DevView& v, const int2* pairs, int64_t n_pairs, int* f, uint32_t* flag,
-                               uint32_t* host_flag, int32_t* label, int64_t* n_components, int* passes,
-                               hipStream_t s)
-{
-    const unsigned gt = v.n_tets > 0 ? blocks(v.n_tets) : 1u;
-    const unsigned gp = n_pairs > 0 ? (unsigned)((n_pairs + kBlock - 1) / kBlock) : 1u;
-    // init also clears the first batch's flags
-    hipLaunchKernelGGL(k_ccf_init, dim3(gt), dim3(kBlock), 0, s, v.n_tets, f, flag);
-    if (n_pairs > 0)
-        hipLaunchKernelGGL(k_ccf_seed, dim3(gp), dim3(kBlock), 0, s, v.mask, pairs, n_pairs, f);
-    hipError_t e = hipGetLastError();
-    *passes = 0;
-    // batches of hooking passes until one changes nothing (bounded: every pass
-    // that does not end the loop lowers some pointer; the bound is far above
-    // what a correct pass sequence needs), then the labels, in the same batch
-    for (bool converged = false; e == hipSuccess && !converged;) {
-        if (*passes > v.n_tets + 2)
-            return hipErrorUnknown;
-        if (*passes > 0)
-            e = hipMemsetAsync(flag, 0, sizeof(uint32_t) * kFlagWords, s);
-        for (int p = 0; p < kFaceBatch && e == hipSuccess; ++p) {
-            const uint32_t* gate = p == 0 ? nullptr : flag + p - 1;
-            if (n_pairs > 0)
-                hipLaunchKernelGGL(k_ccf_hook, dim3(gp), dim3(kBlock), 0, s, v.mask, pairs, n_pairs, f, gate,
-                                   flag + p);
-            if (v.n_tets > 0)
-                hipLaunchKernelGGL(k_cc_shortcut, dim3(gt), dim3(kBlock), 0, s, v.n_tets, f, gate);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess && v.n_tets > 0) {
-            hipLaunchKernelGGL(k_ccf_label, dim3(gt), dim3(kBlock), 0, s, v.n_tets, v.mask, f, label,
-                               flag + kCountWord, flag + kTruncWord);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess)
-            e = finish_batch(flag, host_flag, kFaceBatch, passes, converged, s);
+    if (e != hipSuccess) {
+        ctx->errmsg = std::string(what) + hipGetErrorString(e);
+        return STA_EHIP;
     }
-    if (e == hipSuccess)
-        *n_components = host_flag[kCountWord];
-    return e;
-}
-
-// Component labels into label (device, n_tets); *n_components on the host.
-// flag: kFlagWords words; host_flag: kFlagWords pinned words.  Synchronises
-// s.  Returns hipErrorUnknown if the iteration bound is hit.
-hipError_t run_components(const DevView& v, const int32_t* dinc, int* f, uint32_t* mark, uint32_t* flag,
-                          uint32_t* host_flag, int32_t* label, int64_t* n_components, int* passes, hipStream_t s)
-{
-    const unsigned gn = v.n_nodes > 0 ? blocks(v.n_nodes) : 1u;
-    const unsigned gt = v.n_tets > 0 ? blocks(v.n_tets) : 1u;
-    const unsigned gf = blocks(std::max(v.n_tets, v.n_nodes) > 0 ? std::max(v.n_tets, v.n_nodes) : 1);
-    // the seed also marks the vertices of active tets and clears the first batch's flags
-    hipLaunchKernelGGL(k_cc_seed, dim3(gn), dim3(kBlock), 0, s, v, dinc, f, mark, flag);
-    // one shortcut before the first hooking pass: every vertex climbs its seed
-    // chain once, so that the tets' climbs in that pass are short (180 -> 122
-    // us per rebuild; the face seeds' chains are short already, and there the
-    // extra pass costs more than it saves)
-    if (v.n_nodes > 0)
-        hipLaunchKernelGGL(k_cc_shortcut, dim3(gn), dim3(kBlock), 0, s, v.n_nodes, f, nullptr);
-    hipError_t e = hipGetLastError();
-    *passes = 0;
-    // batches of hooking passes, each followed by a shortcut, until one
-    // changes nothing (then its reads were exact, so every active tet's
-    // vertices share one root); then labels and count in the same batch.
-    // Bounded as in the face variant.
-    for (bool converged = false; e == hipSuccess && !converged;) {
-        if (*passes > v.n_nodes + 2)
-            return hipErrorUnknown;
-        if (*passes > 0)
-            e = hipMemsetAsync(flag, 0, sizeof(uint32_t) * kFlagWords, s);
-        for (int p = 0; p < kVertexBatch && e == hipSuccess; ++p) {
-            const uint32_t* gate = p == 0 ? nullptr : flag + p - 1;
-            if (v.n_tets > 0)
-                hipLaunchKernelGGL(k_cc_hook, dim3(gt), dim3(kBlock), 0, s, v, f, gate, flag + p);
-            if (v.n_nodes > 0)
-                hipLaunchKernelGGL(k_cc_shortcut, dim3(gn), dim3(kBlock), 0, s, v.n_nodes, f, gate);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_cc_finish, dim3(gf), dim3(kBlock), 0, s, v, f, mark, label, flag + kCountWord,
-                               flag + kTruncWord);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess)
-            e = finish_batch(flag, host_flag, kVertexBatch, passes, converged, s);
-    }
-    if (e == hipSuccess)
-        *n_components = host_flag[kCountWord];
-    return e;
+    if (n_components)
+        *n_components = *ctx->cc_host;
+    return STA_OK;
 }
 
 }  // namespace sta
@@ -439,7 +460,7 @@ extern "C" sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t*
     hipError_t e = hipSuccess;
     if (!ctx->cc_ws) {
         void* q = nullptr;
-        e = hipMalloc(&q, sizeof(int32_t) * (2 * n + kFlagWords));  // parent and mark per vertex, the flags
+        e = hipMalloc(&q, sizeof(int32_t) * (3 * n + 1));  // the count, three words per vertex
         if (e != hipSuccess) {
             ctx->errmsg = std::string("connectivity workspace: ") + hipGetErrorString(e);
             return STA_ENOMEM;
@@ -448,29 +469,17 @@ extern "C" sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t*
         ctx->cc_ws = static_cast<int32_t*>(q);
     }
     if (!ctx->cc_host) {
-        e = hipHostMalloc((void**)&ctx->cc_host, sizeof(uint32_t) * kFlagWords, hipHostMallocDefault);
+        e = hipHostMalloc((void**)&ctx->cc_host, sizeof(uint32_t), hipHostMallocDefault);
         if (e != hipSuccess) {
             ctx->cc_host = nullptr;
             ctx->errmsg = std::string("connectivity host flag: ") + hipGetErrorString(e);
             return STA_ENOMEM;
         }
     }
-    int* f = ctx->cc_ws;
-    uint32_t* mark = reinterpret_cast<uint32_t*>(ctx->cc_ws + n);
-    uint32_t* flag = mark + n;
-    int64_t k = 0;
-    e = run_components(ctx->v, ctx->dinc, f, mark, flag, ctx->cc_host, labels_dev, &k, &ctx->cc_passes, s);
-    if (e == hipErrorUnknown) {
-        ctx->errmsg = "connectivity: pass bound exceeded (labels invalid)";
-        return STA_EHIP;
-    }
-    if (e != hipSuccess) {
-        ctx->errmsg = std::string("connectivity: ") + hipGetErrorString(e);
-        return STA_EHIP;
-    }
-    if (n_components)
-        *n_components = k;
-    return STA_OK;
+    uint32_t* count = reinterpret_cast<uint32_t*>(ctx->cc_ws);
+    int* own = ctx->cc_ws + 1;
+    e = run_components(ctx->v, own, own + n, own + 2 * n, count, ctx->cc_host, labels_dev, s);
+    return read_count(ctx, e, "connectivity: ", n_components, s);
 }
 
 extern "C" sta_status sta_face_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_components, void* stream)
@@ -489,48 +498,49 @@ extern "C" sta_status sta_face_components(sta_ctx* ctx, int32_t* labels_dev, int
             return STA_EHIP;
         }
         const std::vector<int2> pairs = host_face_pairs(T);
+        const int64_t windows = std::max<int64_t>(1, (ctx->n_tets + kWindow - 1) / kWindow);
+        std::vector<int64_t> start((size_t)windows + 1);
+        for (int64_t w = 0, k = 0; w <= windows; ++w) {
+            while (k < (int64_t)pairs.size() && pairs[k].x < w * kWindow)
+                ++k;
+            start[w] = k;
+        }
+        // the count, the pairs, each window's first pair, three words per tet
         void* q = nullptr;
-        const size_t bytes = sizeof(int32_t) * ((size_t)ctx->n_tets + kFlagWords) + sizeof(int2) * (pairs.size() + 1);
+        const size_t bytes = sizeof(int2) + sizeof(int2) * pairs.size() +
+                             sizeof(int64_t) * start.size() + 3 * sizeof(int32_t) * (size_t)ctx->n_tets;
         e = hipMalloc(&q, bytes);
         if (e != hipSuccess) {
             ctx->errmsg = std::string("face connectivity workspace: ") + hipGetErrorString(e);
             return STA_ENOMEM;
         }
         ctx->owned.push_back(q);
-        int32_t* base = static_cast<int32_t*>(q);
-        int2* pd = reinterpret_cast<int2*>(base + ((ctx->n_tets + kFlagWords + 1) / 2) * 2);  // 8-byte aligned after f and flags
+        int2* pd = static_cast<int2*>(q) + 1;
+        int64_t* sd = reinterpret_cast<int64_t*>(pd + pairs.size());
         if (!pairs.empty())
             e = hipMemcpy(pd, pairs.data(), sizeof(int2) * pairs.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            e = hipMemcpy(sd, start.data(), sizeof(int64_t) * start.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             ctx->errmsg = std::string("face pairs upload: ") + hipGetErrorString(e);
             return STA_EHIP;
         }
-        ctx->ccf_ws = base;
+        ctx->ccf_ws = static_cast<int32_t*>(q);
         ctx->ccf_pairs = pd;
+        ctx->ccf_start = sd;
+        ctx->ccf_root = reinterpret_cast<int32_t*>(sd + start.size());
         ctx->ccf_npairs = (int64_t)pairs.size();
     }
     if (!ctx->cc_host) {
-        e = hipHostMalloc((void**)&ctx->cc_host, sizeof(uint32_t) * kFlagWords, hipHostMallocDefault);
+        e = hipHostMalloc((void**)&ctx->cc_host, sizeof(uint32_t), hipHostMallocDefault);
         if (e != hipSuccess) {
             ctx->cc_host = nullptr;
             ctx->errmsg = std::string("connectivity host flag: ") + hipGetErrorString(e);
             return STA_ENOMEM;
         }
     }
-    int* f = ctx->ccf_ws;
-    uint32_t* flag = reinterpret_cast<uint32_t*>(ctx->ccf_ws + ctx->n_tets);
-    int64_t k = 0;
-    e = run_face_components(ctx->v, ctx->ccf_pairs, ctx->ccf_npairs, f, flag, ctx->cc_host, labels_dev, &k,
-                            &ctx->cc_passes, s);
-    if (e == hipErrorUnknown) {
-        ctx->errmsg = "face connectivity: pass bound exceeded (labels invalid)";
-        return STA_EHIP;
-    }
-    if (e != hipSuccess) {
-        ctx->errmsg = std::string("face connectivity: ") + hipGetErrorString(e);
-        return STA_EHIP;
-    }
-    if (n_components)
-        *n_components = k;
-    return STA_OK;
+    e = run_face_components(ctx->v, ctx->ccf_pairs, ctx->ccf_npairs, ctx->ccf_start, ctx->ccf_root,
+                            ctx->ccf_root + ctx->n_tets, ctx->ccf_root + 2 * ctx->n_tets, reinterpret_cast<uint32_t*>(ctx->ccf_ws),
+                            ctx->cc_host, labels_dev, s);
+    return read_count(ctx, e, "face connectivity: ", n_components, s);
 }

@@ -249,3 +249,49 @@ def test_all_inactive_and_all_active():
     lab, k = check_face(asm, w, np.ones(w.n_tets, np.uint8), pairs, "all active (face)")
     assert k == 1 and np.all(lab == 0)
     asm.close()
+
+
+def apart(m):
+    """m tets without a common vertex: every window of tets holds the most vertices it can."""
+    g = np.random.default_rng(m)
+    x = g.uniform(0.0, 1.0, size=(4 * m, 3))
+    tets = g.permutation(4 * m).astype(np.int32).reshape(m, 4)
+    return W.Workload("apart", x, tets, W.lognormal_E(m, g), np.ones(m, np.uint8))
+
+
+def chain(m, seed):
+    """m tets, each sharing a face with the next, ids scattered over the windows."""
+    g = np.random.default_rng(seed)
+    p = g.permutation(m)
+    tets = (np.arange(m)[:, None] + np.arange(4)[None, :]).astype(np.int32)[p]
+    return W.Workload("chain", g.uniform(0.0, 1.0, size=(m + 3, 3)), tets, W.lognormal_E(m, g), np.ones(m, np.uint8))
+
+
+def shuffled(n):
+    w = W.make_fracture(seed=5, n=n, counts=[50])
+    g = np.random.default_rng(n)
+    p, q = g.permutation(w.n_tets), g.permutation(w.n_nodes).astype(np.int32)
+    x = np.empty_like(w.x)
+    x[q] = w.x
+    return W.Workload("shuffled", x, np.ascontiguousarray(q[w.tets[p]]), w.E[p], w.mask0[p])
+
+
+@pytest.mark.parametrize("mesh", [lambda: apart(1), lambda: apart(1023), lambda: apart(1024), lambda: apart(1025),
+                                  lambda: apart(2049), lambda: chain(1024, 1), lambda: chain(5000, 2),
+                                  lambda: shuffled(9)])
+def test_windows(mesh):
+    """Windows of 1,024 tets, full and with a remainder, with no common vertex at all, one long
+    chain, and scattered ids (nearly every tet the root of its window): both adjacencies, all
+    active, then random masks of decreasing density and none."""
+    Sm = S()
+    w = mesh()
+    pairs = C.face_pairs(w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    g = np.random.default_rng(7)
+    every = np.arange(w.n_tets, dtype=np.int32)
+    for density in (1.0, 0.9, 0.5, 0.1, 0.0):
+        mask = (g.uniform(size=w.n_tets) < density).astype(np.uint8)
+        asm.apply_edits(*Sm.upload_frame(every, mask))
+        check(asm, w, mask, f"{w.name} {w.n_tets} {density} (vertex)")
+        check_face(asm, w, mask, pairs, f"{w.name} {w.n_tets} {density}")
+    asm.close()
