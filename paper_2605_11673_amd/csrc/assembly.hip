@@ -17,6 +17,7 @@
 // |.| are used.
 #include <hip/hip_runtime.h>
 
+#include "edit_table.h"
 #include "sta_internal.h"
 
 #pragma clang fp contract(off)
@@ -357,7 +358,6 @@ constexpr int kTetDoubles = 2 * kDiagUnitDoubles + kUnitDoubles;
 
 // The state of a tet is its mask byte unless the frame's own edits say
 // otherwise: listed gives 0 or 1 for an edited tet, kUnlisted for any other.
-constexpr uint32_t kUnlisted = 2u;
 struct MaskState {
     __device__ __forceinline__ uint32_t listed(uint32_t) const { return kUnlisted; }
 };
@@ -982,26 +982,6 @@ __global__ __launch_bounds__(kBlock) void k_frame(DevView v, const int32_t* __re
     }
 }
 
-// The frame's edits as a chained hash table in LDS: head[h] is the last edit
-// of bucket h (-1: none) and edit[i] = (tet << 1 | requested state, the next
-// edit of its bucket).
-struct EditTable {
-    const int32_t* head;
-    const int2* edit;
-    int log2;
-    __device__ __forceinline__ uint32_t bucket(uint32_t e) const { return (e * 2654435761u) >> (32 - log2); }
-    __device__ __forceinline__ uint32_t listed(uint32_t e) const
-    {
-        uint32_t l = kUnlisted;
-        for (int i = head[bucket(e)]; i >= 0;) {
-            const int2 t = edit[i];
-            l = (uint32_t)t.x >> 1 == e ? (uint32_t)t.x & 1u : l;
-            i = t.y;
-        }
-        return l;
-    }
-};
-
 // A whole frame in one launch without a grid barrier, for edit lists that fit
 // a table in LDS.  Every workgroup reads the whole list into its own table
 // (validating it, so that all agree on the frame's error before anything is
@@ -1017,19 +997,17 @@ struct EditTable {
 // kEdits: edits per workgroup; kShare: edits of the list per lane (n_host <=
 // 64 kUnits kEdits kShare).
 constexpr int kOnceMax = 2304;  // edits of the largest variant
-constexpr int kOnceSpare = 64;  // heads past the buckets, for lanes without an edit
 template <int kEdits, int kShare>
 __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const int32_t* __restrict__ ids,
                                                                const uint8_t* __restrict__ states, int32_t n_host,
                                                                const int32_t* __restrict__ n_dev, int log2)
 {
     constexpr int kThreads = 64 * kUnits * kEdits;
-    // heads (1 << log2, then kOnceSpare), then kShare kThreads edits
+    // the table's heads, then its edits
     extern __shared__ int4 s_dynamic[];
     __shared__ double s_val[kEdits][kTetDoubles];
     __shared__ int s_bits, s_change[kEdits];
     int32_t* head = reinterpret_cast<int32_t*>(s_dynamic);
-    int2* edit = reinterpret_cast<int2*>(head + (1 << log2) + kOnceSpare);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int unit = wave % kUnits, own = wave / kUnits, i = blockIdx.x * kEdits + own;
     // the wave's own edit, and this lane's share of the list
@@ -1039,15 +1017,9 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
         id = ids[min(i, n_host - 1)];
         st = states[min(i, n_host - 1)];
     }
-    int lid[kShare];
-    uint8_t lst[kShare];
-#pragma unroll
-    for (int k = 0; k < kShare; ++k) {
-        lid[k] = *(n_host > 0 ? ids + min(tid + k * kThreads, n_host - 1) : &kNoTet);
-        lst[k] = *(n_host > 0 ? states + min(tid + k * kThreads, n_host - 1) : &kNoState);
-    }
-    for (int h = tid; h < 1 << (log2 - 2); h += kThreads)
-        s_dynamic[h] = make_int4(-1, -1, -1, -1);
+    EditShare<kThreads, kShare> share;
+    share.load(ids, states, n_host, &kNoTet, &kNoState);
+    share.clear(s_dynamic, log2);
     if (tid == 0)
         s_bits = 0;
     bool bad_n;
@@ -1066,22 +1038,8 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
     }
     __syncthreads();
     int bits = bad_n ? ERR_RANGE : 0;
-    const EditTable table{head, edit, log2};
-    int next[kShare];
-    bool valid[kShare];
-#pragma unroll
-    for (int k = 0; k < kShare; ++k) {
-        const bool in = tid + k * kThreads < n;
-        valid[k] = in && (uint32_t)lid[k] < (uint32_t)v.n_tets && lst[k] <= 1;
-        bits |= in && !valid[k] ? ERR_RANGE : 0;
-        next[k] = atomicExch(head + (valid[k] ? table.bucket((uint32_t)lid[k]) : (1u << log2) + (uint32_t)lane),
-                             tid + k * kThreads);
-    }
-#pragma unroll
-    for (int k = 0; k < kShare; ++k) {
-        next[k] = valid[k] ? next[k] : -1;
-        edit[tid + k * kThreads] = make_int2((int)((uint32_t)lid[k] << 1 | (lst[k] & 1u)), next[k]);
-    }
+    const EditTable table{head, reinterpret_cast<int2*>(head + (1 << log2) + kTableSpare), log2};
+    bits |= share.insert(table, n, v.n_tets);
     __syncthreads();
     // in flight while duplicates are looked for
     UnitTerms<true> bdiag{};
@@ -1096,25 +1054,7 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
             u = load_incidence<false>(v, boff, 0);
         }
     }
-    // a duplicate finds its twin further down its own chain
-    bool more = false;
-#pragma unroll
-    for (int k = 0; k < kShare; ++k)
-        more |= next[k] >= 0;
-    while (more) {
-        int2 t[kShare];
-#pragma unroll
-        for (int k = 0; k < kShare; ++k)
-            t[k] = edit[next[k] >= 0 ? next[k] : 0];
-        more = false;
-#pragma unroll
-        for (int k = 0; k < kShare; ++k)
-            if (next[k] >= 0) {
-                bits |= (uint32_t)t[k].x >> 1 == (uint32_t)lid[k] ? ERR_DUP : 0;
-                next[k] = t[k].y;
-                more |= next[k] >= 0;
-            }
-    }
+    bits |= share.duplicates(table);
     if (bits)
         atomicOr(&s_bits, bits);
     if (unit == 0 && lane == 0)
@@ -1284,14 +1224,11 @@ bool frame_fits_once(int32_t n_host)
 hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                        const int32_t* n_dev, hipStream_t s)
 {
-    int log2 = 8;  // buckets: at least the edits, up to 2048
-    while ((1 << log2) < n_host && log2 < 11)
-        ++log2;
+    const int log2 = table_log2(n_host);
 #define ONCE(E, S)                                                                                           \
     if (n_host <= 64 * kUnits * E * S) {                                                                     \
         launch_kernel(&k_once<E, S>, dim3(n_host > 0 ? (n_host + E - 1) / E : 1), dim3(64 * kUnits * E),     \
-                      (uint32_t)(sizeof(int32_t) * ((1 << log2) + kOnceSpare) +                              \
-                                 sizeof(int2) * 64 * kUnits * E * S),                                        \
+                      table_bytes(log2, 64 * kUnits * E, S),                                                 \
                       s, v, ids, states, n_host, n_dev, log2);                                               \
         return hipGetLastError();                                                                            \
     }

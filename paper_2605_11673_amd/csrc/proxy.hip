@@ -10,7 +10,12 @@
 // integer atomics and stays exactly equal to a rebuild, whatever order the
 // atomics land in.
 //
-// A frame is two launches.  Phase 1, eight lanes per edit: validate, detect
+// A frame of up to kOnceMax edits is one launch: every changed tet's six edges
+// are counted again over their incidence, and its four vertices' active edges
+// over the tets around them, with the frame's own edits taken from a table
+// (k_proxy_once).  Integers again, so the state is the same.
+//
+// A larger frame is two launches.  Phase 1, eight lanes per edit: validate, detect
 // duplicates (a per-tet stamp), flip the mask, add +1 or -1 to the six edge
 // counts, and on a 0 <-> >0 transition add the same to both endpoint degrees.
 // Phase 2, after every count of the frame has landed: rewrite the six edge
@@ -25,13 +30,14 @@
 #include <string>
 #include <vector>
 
+#include "edit_table.h"
 #include "sta_internal.h"
 
 struct ProxyCtl {
     int32_t err;         // sticky error bits until sta_proxy_status_sync
     int32_t frame_err;   // error bits of the last frame
     int32_t last_n;      // edit count of the last frame
-    int32_t pad;
+    int32_t once;        // the last frame was one launch (its statistics: k_proxy_stats)
     uint32_t trans;      // 0 <-> >0 transitions counted by the running frame's phase 1
     uint32_t last_trans; // transitions of the last frame (0 if it was rolled back)
     uint32_t changed;    // edits that changed a tet's state, running frame
@@ -55,6 +61,11 @@ struct ProxyView {
     uint32_t* estamp;       // per tet, nonzero while an edit of this frame holds it
     uint8_t* undo;          // per edit: previous mask value, 0xFF = nothing to undo
     uint8_t* wg_err;        // phase 1: error bits per workgroup
+    // for the frame in one launch
+    int4* erec;             // 6 per tet: of each edge the incidence begin and count, and its two CSR indices
+    int4* vrec;             // 4 per tet: of each vertex the incidence begin and count, ndpos, the vertex
+    int4* vinc;             // per vertex its tets: tet, CSR column of its three edges there in the vertex's row
+    int32_t* ids;           // kOnceMax: the last frame's list
     ProxyCtl* ctl;
     double eps;
 };
@@ -264,6 +275,7 @@ __global__ __launch_bounds__(kBlock) void k_proxy_touched(ProxyView v, const int
         const uint32_t c = atomicExch(&v.ctl->changed, 0u);
         v.ctl->last_trans = fe ? 0u : t;
         v.ctl->last_changed = fe ? 0u : c;
+        v.ctl->once = 0;
         v.ctl->frame_err = fe;
         v.ctl->last_n = n;
         if (fe)
@@ -293,6 +305,220 @@ __global__ __launch_bounds__(kBlock) void k_proxy_touched(ProxyView v, const int
     }
     if (r == 0)
         v.estamp[id] = 0u;
+}
+
+__device__ int32_t kNoTet = -1;
+__device__ uint8_t kNoState = 0;
+
+// The state of a tet after the frame.
+__device__ __forceinline__ bool is_active(const EditTable& table, uint32_t tet, uint8_t mask)
+{
+    const uint32_t l = table.listed(tet);
+    return l == kUnlisted ? mask != 0 : l != 0u;
+}
+
+// A whole frame in one launch: two waves per edit, one for the tet's edges
+// (eight lanes each), one for its vertices (16 lanes each).  Nothing that a
+// workgroup reads is written by another one but the mask bytes of edited tets,
+// whose states come from the table, so there is no order to keep; edits that
+// share an edge or a vertex write the same.  What remains is a chain of four
+// dependent round trips: edit, record, incidences, masks: 4.6 us at 30 to 256
+// edits, 5.2 at 1,000, where the two launches of a larger frame take 4.7 + 3.9
+// and the gap between them.  Ten frames undone and redone and a rebuild at the
+// fracture mesh of resolution 31: 101 us (186 before).
+//
+// kEdits: edits per workgroup; kShare: edits of the list per thread.
+// The largest list: every workgroup reads all of it, so the time grows with its
+// length.  In a graph, one launch against two: 3.1 / 5.4 us at 1 edit, 4.5 / 6.8
+// at 256, 5.3 / 7.6 at 1,024, 6.7 / 7.8 at 1,600, 7.5 / 7.7 at 2,304.
+constexpr int kOnceMax = 2304;
+template <int kEdits, int kShare>
+__global__ __launch_bounds__(128 * kEdits) void k_proxy_once(ProxyView v, const int32_t* __restrict__ ids,
+                                                             const uint8_t* __restrict__ states, int32_t n_host,
+                                                             const int32_t* __restrict__ n_dev, int log2)
+{
+    constexpr int kThreads = 128 * kEdits;
+    extern __shared__ int4 s_dynamic[];  // the table's heads, then its edits
+    __shared__ int s_bits, s_change[kEdits];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int own = wave / 2, i = blockIdx.x * kEdits + own;
+    const bool edges = wave % 2 == 0;
+    const int id = *(n_host > 0 ? ids + min(i, n_host - 1) : &kNoTet);
+    const unsigned st = *(n_host > 0 ? states + min(i, n_host - 1) : &kNoState);
+    EditShare<kThreads, kShare> share;
+    share.load(ids, states, n_host, &kNoTet, &kNoState);
+    share.clear(s_dynamic, log2);
+    if (tid == 0)
+        s_bits = 0;
+    bool bad_n;
+    const int n = edit_count(n_host, n_dev, bad_n);
+    const bool mine = i < n && id >= 0 && id < v.n_tets;
+    // lanes of one edge or vertex; those of the last two edge groups have none
+    const int lanes = edges ? 8 : 16, q = lane / lanes, sub = lane % lanes;
+    const bool has = mine && (!edges || q < 6);
+    int4 rec = make_int4(0, 0, 0, 0);
+    int edge = 0;
+    uint8_t prev = 0;
+    if (has) {  // in flight while the table is built
+        rec = *(edges ? v.erec + 6 * (size_t)id + q : v.vrec + 4 * (size_t)id + q);
+        if (edges) {
+            edge = v.t2e[6 * (size_t)id + q];
+            prev = v.mask[id];
+        }
+    }
+    __syncthreads();
+    int32_t* head = reinterpret_cast<int32_t*>(s_dynamic);
+    const EditTable table{head, reinterpret_cast<int2*>(head + (1 << log2) + kTableSpare), log2};
+    int bits = bad_n ? ERR_RANGE : 0;
+    bits |= share.insert(table, n, v.n_tets);
+    __syncthreads();
+    // in flight while duplicates are looked for: the first two incidences of each lane
+    int4 t0 = make_int4(0, 0, 0, 0), t1 = t0;
+    if (has && rec.y > 0) {
+        const int k0 = rec.x + min(sub, rec.y - 1), k1 = rec.x + min(sub + lanes, rec.y - 1);
+        if (edges) {
+            t0.x = v.einc[k0];
+            t1.x = v.einc[k1];
+        } else {
+            t0 = v.vinc[k0];
+            t1 = v.vinc[k1];
+        }
+    }
+    bits |= share.duplicates(table);
+    if (bits)
+        atomicOr(&s_bits, bits);
+    if (edges && lane == 0)
+        s_change[own] = prev != st;
+    __syncthreads();
+    const int fe = s_bits;
+    if (blockIdx.x == 0 && tid == 0) {
+        v.ctl->once = 1;
+        v.ctl->frame_err = fe;
+        v.ctl->last_n = n;
+        if (fe)
+            atomicOr(&v.ctl->err, fe);
+    }
+    if (fe || !mine)
+        return;
+    const bool change = s_change[own] != 0;
+    if (edges && lane == 0) {
+        v.ids[i] = id;
+        v.undo[i] = change ? prev : (uint8_t)0xFF;
+        if (change)
+            v.mask[id] = (uint8_t)st;
+    }
+    if (!change)
+        return;
+    const uint8_t m0 = v.mask[t0.x], m1 = v.mask[t1.x];
+    if (edges) {
+        int c = has && sub < rec.y && is_active(table, t0.x, m0) ? 1 : 0;
+        c += has && sub + 8 < rec.y && is_active(table, t1.x, m1) ? 1 : 0;
+        for (int k = sub + 16; k < rec.y; k += 8) {
+            const int t = v.einc[rec.x + k];
+            c += is_active(table, t, v.mask[t]) ? 1 : 0;
+        }
+#pragma unroll
+        for (int d = 4; d > 0; d >>= 1)
+            c += __shfl_xor(c, d, 64);
+        if (has && sub == 0) {
+            const double x = off_value(c);
+            v.c[edge] = c;
+            v.values[rec.z] = x;
+            v.values[rec.w] = x;
+        }
+        return;
+    }
+    // the vertex's active edges, 64 columns of its row at a time
+    int degree = 0;
+    for (int base = 0, last = 63; base <= last; base += 64) {
+        unsigned long long on = 0ull;
+        auto add = [&](int4 t, bool active) {
+            last = max(last, max(t.y, max(t.z, t.w)));
+            auto bit = [&](int c) {
+                return active && (c & ~63) == base ? 1ull << (c & 63) : 0ull;
+            };
+            on |= bit(t.y) | bit(t.z) | bit(t.w);
+        };
+        if (sub < rec.y)
+            add(t0, is_active(table, t0.x, m0));
+        if (sub + 16 < rec.y)
+            add(t1, is_active(table, t1.x, m1));
+        for (int k = sub + 32; k < rec.y; k += 16) {
+            const int4 t = v.vinc[rec.x + k];
+            add(t, is_active(table, t.x, v.mask[t.x]));
+        }
+#pragma unroll
+        for (int d = 8; d > 0; d >>= 1)
+            on |= __shfl_xor(on, d, 64);
+        if (__any(last > 63))  // all four vertices go round as often
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1)
+                last = max(last, __shfl_xor(last, d, 64));
+        degree += __popcll(on);
+    }
+    if (sub == 0) {
+        v.deg[rec.w] = degree;
+        v.values[rec.z] = (double)degree + v.eps;
+    }
+}
+
+// Records for k_proxy_once, 10 threads per tet: its edges, then its vertices.
+// e2p: place of the tet among each vertex's tets; dseg: where those begin.
+__global__ __launch_bounds__(kBlock) void k_proxy_records(ProxyView v, const int32_t* __restrict__ e2p,
+                                                          const int32_t* __restrict__ ndiag,
+                                                          const int32_t* __restrict__ dseg)
+{
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int e = (int)(t / 10), q = (int)(t % 10);
+    if (e >= v.n_tets)
+        return;
+    if (q < 6) {
+        const int ek = v.t2e[6 * (size_t)e + q], k0 = v.eseg[ek];
+        v.erec[6 * (size_t)e + q] = make_int4(k0, v.eseg[ek + 1] - k0, v.epos[2 * ek], v.epos[2 * ek + 1]);
+        return;
+    }
+    const int a = q - 6, u = tet_vertex(v.T[e], a), d = ndiag[u], k0 = dseg[d];
+    v.vrec[4 * (size_t)e + a] = make_int4(k0, dseg[d + 1] - k0, v.ndpos[u], u);
+    int column[3];
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+        const int b = w < a ? w : w + 1, lo = min(a, b), hi = max(a, b);
+        const int ek = v.t2e[6 * (size_t)e + (lo == 0 ? hi - 1 : lo + hi)];  // pairs 01 02 03 12 13 23
+        column[w] = v.epos[2 * ek + (v.enode[2 * ek] == u ? 0 : 1)] - v.rowptr[u];
+    }
+    v.vinc[e2p[4 * (size_t)e + a]] = make_int4(e, column[0], column[1], column[2]);
+}
+
+// Statistics of a frame of k_proxy_once, in three steps over its edits: mark
+// the changed tets with their state before; count them, and for each the edges
+// whose activity changed and whose first changed tet it is; take the marks off.
+__global__ __launch_bounds__(kBlock) void k_proxy_stats(ProxyView v, int n, int step)
+{
+    const int t = blockIdx.x * kBlock + threadIdx.x, i = t / kLanes, r = t % kLanes;
+    if (i >= n || v.undo[i] == 0xFF)
+        return;
+    const int id = v.ids[i];
+    if (step != 1) {
+        if (r == 0)
+            v.estamp[id] = step == 0 ? 2u | v.undo[i] : 0u;
+        return;
+    }
+    if (r == 0)
+        atomicAdd(&v.ctl->changed, 1u);
+    if (r >= 6)
+        return;
+    const int4 rec = v.erec[6 * (size_t)id + r];
+    int before = 0, after = 0, first = -1;
+    for (int k = rec.x; k < rec.x + rec.y; ++k) {
+        const int x = v.einc[k];
+        const uint32_t mark = v.estamp[x];
+        before += mark ? (int)(mark & 1u) : v.mask[x];
+        after += v.mask[x];
+        if (first < 0 && mark)
+            first = x;
+    }
+    if (first == id && (before > 0) != (after > 0))
+        atomicAdd(&v.ctl->trans, 1u);
 }
 
 unsigned blocks(int64_t threads)
@@ -352,6 +578,18 @@ hipError_t launch_rebuild(const ProxyView& v, hipStream_t s)
 hipError_t launch_frame(const ProxyView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                         const int32_t* n_dev, hipStream_t s)
 {
+    const int log2 = table_log2(n_host);
+#define ONCE(E, S)                                                                                            \
+    if (n_host <= 128 * E * S) {                                                                              \
+        hipLaunchKernelGGL((k_proxy_once<E, S>), dim3(n_host > 0 ? (n_host + E - 1) / E : 1), dim3(128 * E),  \
+                           table_bytes(log2, 128 * E, S), s, v, ids, states, n_host, n_dev, log2);            \
+        return hipGetLastError();                                                                             \
+    }
+    ONCE(2, 1)
+    ONCE(4, 2)
+    ONCE(6, 3)
+#undef ONCE
+    static_assert(kOnceMax == 128 * 6 * 3, "the largest variant covers the largest list");
     const unsigned g = n_host > 0 ? blocks((int64_t)n_host * kLanes) : 1u;
     hipLaunchKernelGGL(k_proxy_edits, dim3(g), dim3(kBlock), 0, s, v, ids, states, n_host, n_dev);
     hipError_t e = hipGetLastError();
@@ -419,6 +657,11 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
     v.n_edges = (int32_t)P.no;
     v.eps = eps;
     int4* T = nullptr;
+    std::vector<int32_t> e2p((size_t)n_tets * 4);
+    for (int64_t e = 0; e < n_tets; ++e)
+        for (int a = 0; a < 4; ++a)
+            e2p[4 * e + a] = P.e2p[10 * e + a];
+    int32_t *e2p_d = nullptr, *ndiag_d = nullptr, *dseg_d = nullptr;  // for the records only, freed below
     int32_t *t2e_d = nullptr, *eseg = nullptr, *einc = nullptr, *epos_d = nullptr, *enode = nullptr,
             *rowptr = nullptr, *ndpos_d = nullptr;
     const int64_t wg = n_tets > 0 ? blocks(n_tets * kLanes) : 1;
@@ -443,6 +686,14 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
     PALLOC(v.undo, n_tets)
     PALLOC(v.wg_err, wg)
     PALLOC(v.ctl, 1)
+    PALLOC(v.erec, n_tets * 6)
+    PALLOC(v.vrec, n_tets * 4)
+    PALLOC(v.vinc, n_tets * 4)
+    PALLOC(v.ids, kOnceMax)
+    const size_t kept = p->owned.size();
+    PALLOC(e2p_d, n_tets * 4)
+    PALLOC(ndiag_d, n_nodes)
+    PALLOC(dseg_d, P.dseg.size())
 #undef PALLOC
     if (e == hipSuccess) e = put(T, reinterpret_cast<const int4*>(tets), (size_t)n_tets, s);
     if (e == hipSuccess) e = put(v.mask, mask0, (size_t)n_tets, s);
@@ -466,10 +717,19 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
     v.enode = enode;
     v.rowptr = rowptr;
     v.ndpos = ndpos_d;
+    if (e == hipSuccess) e = put(e2p_d, e2p.data(), e2p.size(), s);
+    if (e == hipSuccess) e = put(ndiag_d, P.ndiag.data(), P.ndiag.size(), s);
+    if (e == hipSuccess) e = put(dseg_d, P.dseg.data(), P.dseg.size(), s);
+    if (e == hipSuccess && n_tets > 0) {
+        hipLaunchKernelGGL(k_proxy_records, dim3(blocks(n_tets * 10)), dim3(kBlock), 0, s, v, e2p_d, ndiag_d, dseg_d);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess)
         e = launch_rebuild(v, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
+    for (; e == hipSuccess && p->owned.size() > kept; p->owned.pop_back())
+        e = hipFree(p->owned.back());
     if (e != hipSuccess) {
         const std::string msg = std::string("proxy build: ") + hipGetErrorString(e);
         release(p);
@@ -594,6 +854,23 @@ extern "C" sta_status sta_proxy_last_frame_stats(sta_proxy* p, void* stream, int
         e = hipMemcpy(&h, p->v.ctl, sizeof h, hipMemcpyDeviceToHost);
     if (e != hipSuccess)
         return pfail(p, STA_EHIP, std::string("proxy stats: ") + hipGetErrorString(e));
+    if (h.once) {
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        uint32_t sums[2] = {0u, 0u};
+        const int n = h.frame_err ? 0 : h.last_n;
+        for (int step = 0; step < 3 && n > 0 && e == hipSuccess; ++step) {
+            hipLaunchKernelGGL(k_proxy_stats, dim3(blocks((int64_t)n * kLanes)), dim3(kBlock), 0, s, p->v, n, step);
+            e = hipGetLastError();
+        }
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = hipMemcpy(&h, p->v.ctl, sizeof h, hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipMemcpy(&p->v.ctl->trans, &sums[0], sizeof(uint32_t), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(&p->v.ctl->changed, &sums[1], sizeof(uint32_t), hipMemcpyHostToDevice);
+        if (e != hipSuccess)
+            return pfail(p, STA_EHIP, std::string("proxy stats: ") + hipGetErrorString(e));
+        h.last_trans = h.trans;
+        h.last_changed = h.changed;
+    }
     out3[0] = h.last_n;
     out3[1] = h.last_changed;
     out3[2] = h.last_trans;

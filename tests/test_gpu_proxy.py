@@ -211,3 +211,69 @@ def test_maximum_size_frames():
         assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
     assert px.status_sync() == Sm.STA_OK
     px.close()
+
+
+def hub(m):
+    """m tets around one edge and m around one vertex: rows of several hundred columns."""
+    g = np.random.default_rng(m)
+    ring = 2 + np.arange(m)
+    around_edge = np.stack([np.zeros(m, int), np.ones(m, int), ring, 2 + (np.arange(m) + 1) % m], 1)
+    fan = 2 + m + np.arange(3 * m).reshape(m, 3)
+    around_vertex = np.concatenate([np.zeros((m, 1), int), fan], 1)
+    tets = np.concatenate([around_edge, around_vertex]).astype(np.int32)
+    x = g.uniform(0.0, 1.0, size=(2 + 4 * m, 3))
+    return W.Workload("hub", x, tets, np.ones(2 * m), g.integers(0, 2, size=2 * m).astype(np.uint8))
+
+
+@pytest.mark.parametrize("size", [0, 1, 255, 256, 257, 1024, 1025, 2304, 2305])
+def test_frame_sizes_with_mixed_edits(size):
+    """Lists at the edges of the one-launch variants and just past the largest: random states on
+    random tets (counts of one edge go down and up in one frame), then a duplicate at the end of
+    the list, which changes nothing."""
+    Sm = S()
+    w = W.make_fracture(seed=6, n=8, counts=[10])
+    assert w.n_tets > 2305
+    g = np.random.default_rng(size)
+    pat = P.proxy_pattern(w.n_nodes, w.tets)
+    px = Sm.Proxy.from_workload(w, EPS)
+    mask = w.mask0.copy()
+    oc = check(px, w, mask, pat, "build")
+    for t in range(3):
+        ids = g.choice(w.n_tets, size=size, replace=False).astype(np.int32)
+        st = g.integers(0, 2, size=size).astype(np.uint8)
+        px.apply_edits(*Sm.upload_frame(ids, st))
+        changed = int(np.sum(mask[ids] != st))
+        mask[ids] = st
+        before, oc = oc, check(px, w, mask, pat, f"{size} edits, frame {t}")
+        if size <= 2304:
+            flips = int(np.sum((oc > 0) != (before > 0)))
+            assert px.last_frame_stats() == {"edits": size, "changed": changed, "transitions": flips}
+        if size > 1:
+            ids[-1] = ids[0]
+            px.apply_edits(*Sm.upload_frame(ids, (1 - mask[ids]).astype(np.uint8)))
+            assert px.status_sync() == Sm.STA_EDUP
+            assert px.last_frame_stats() == {"edits": size, "changed": 0, "transitions": 0}
+            check(px, w, mask, pat, f"{size} edits, rolled back")
+    assert px.status_sync() == Sm.STA_OK
+    px.close()
+
+
+@pytest.mark.parametrize("m", [12, 15, 16, 200])
+def test_long_rows(m):
+    """An edge of m tets and rows of 4 m + 2 columns: just below and past 64, and several times 64."""
+    Sm = S()
+    w = hub(m)
+    g = np.random.default_rng(m)
+    pat = P.proxy_pattern(w.n_nodes, w.tets)
+    px = Sm.Proxy.from_workload(w, EPS)
+    mask = w.mask0.copy()
+    check(px, w, mask, pat, "hub build")
+    for t in range(6):
+        size = int(g.integers(1, w.n_tets + 1))
+        ids = g.choice(w.n_tets, size=size, replace=False).astype(np.int32)
+        st = g.integers(0, 2, size=size).astype(np.uint8)
+        px.apply_edits(*Sm.upload_frame(ids, st))
+        mask[ids] = st
+        check(px, w, mask, pat, f"hub {m} frame {t}")
+    assert px.status_sync() == Sm.STA_OK
+    px.close()
