@@ -617,6 +617,9 @@ sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, in
     return STA_OK;
 }
 
+// Iterations of a small solve's launch: some milliseconds at most.
+constexpr int kCgSmallIters = 1024;
+
 // Iterations to launch before the next look at the residual: what is left at
 // the mean rate of the `launched` iterations so far, at least 4 and at most
 // twice as many as have run (the rate changes on the way).
@@ -1175,12 +1178,26 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
     c.dinv = c.q + n;
     c.part = c.dinv + n;
     c.s = ctx->cg_s;
-    e = launch_cg_init(c, b_dev, rtol, s);
+    const bool small = cg_is_small(n);
+    if (small) {
+        // one launch, or one per kCgSmallIters iterations of a long solve
+        ctx->cg_host->done = 0;
+        for (int64_t k0 = 0; e == hipSuccess && !ctx->cg_host->done; k0 += kCgSmallIters) {
+            const int k1 = (int)std::min<int64_t>(k0 + kCgSmallIters, INT32_MAX);
+            e = timed(ctx, STA_KERNEL_SOLVE, s, [&] {
+                return launch_cg_small(c, b_dev, x_dev, ctx->cg_host, rtol, (int)k0, k1, max_iter, s);
+            });
+            if (e == hipSuccess)
+                e = hipStreamSynchronize(s);
+        }
+    } else {
+        e = launch_cg_init(c, b_dev, rtol, s);
+    }
     // iterations k = 0 .. max_iter (the last one only records the residual),
     // cg_chunk of them between host checks (a check costs about 18 us of idle GPU, a launch
     // pair past convergence about 3)
     int next = 0, chunk = 16;
-    while (e == hipSuccess) {
+    while (e == hipSuccess && !small) {
         const int count = max_iter + 1 - next < chunk ? max_iter + 1 - next : chunk;
         if (count > 0)
             e = timed(ctx, STA_KERNEL_SOLVE, s, [&] { return launch_cg_iterations(c, next, count, max_iter, s); });
@@ -1193,7 +1210,7 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
             break;
         chunk = cg_chunk(*ctx->cg_host, next);
     }
-    if (e == hipSuccess)
+    if (e == hipSuccess && !small)
         e = launch_cg_output(c, x_dev, s);
     if (e != hipSuccess)
         return hip_fail(ctx, e, "cg");

@@ -62,6 +62,16 @@ __device__ __forceinline__ double add_dpp(double x)
     return x + __longlong_as_double((long long)hi << 32 | (unsigned)lo);
 }
 
+// The same for the rows of 16 lanes that kRows names; others add 0.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ double add_dpp_rows(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, kCtrl, kRows, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, kRows, 0xf, false);
+    return x + __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+
 // Sum over each aligned group of 16 lanes, the same bits in all of them: lanes
 // 1 and 2 apart (quad permutations), then the mirrored half row and row (all
 // lanes of a quad, then of a half row, hold the same sum by then).
@@ -366,6 +376,247 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(CgView c, int k, int cur)
     }
 }
 
+// A whole solve of a small system in one workgroup.  Rows t, t + kSmallBlock,
+// ... of x, r and the preconditioner stay in thread t's registers, p and q in
+// LDS, and so does the matrix: the blocks of the first kSmallHeld rounds of
+// nodes (16 lanes per node as above) in registers, those of up to kSmallLds
+// more in LDS.  Barriers take the place of launches: three per iteration.  The
+// steps and the stopping rules are those of the launches above.
+//
+// Bound by its one compute unit: per iteration a chain of some 2 us (two
+// divisions, three barriers, the sums over waves), and 0.3 us a round.  Whole
+// solves, these launches / those above: 9 iterations of 24 rows 34 / 126 us, 27
+// of 375 rows 83 / 237, 31 of 648 rows 120 / 293, 37 of 1,029 rows 190 / 349.
+// Past the rounds that fit in registers and LDS the blocks would be read again
+// in each iteration, at 1.6 us a round: 42 iterations of 1,536 rows took 442 us
+// that way, 345 by the launches above, so there the rule draws its line.
+//
+// Iterations k0 .. k1 - 1; a solve that is not done by then is kept in the
+// workspace for the next launch, so that no launch runs for long.
+constexpr int kSmallBlock = 512, kSmallWaves = kSmallBlock / 64, kSmallGroups = kSmallBlock / kNodeLanes;
+constexpr int kSmallHeld = 8, kSmallLds = 3, kSmallNodes = (kSmallHeld + kSmallLds) * kSmallGroups;
+constexpr int kSmallRows = 3 * kSmallNodes, kSmallMine = (kSmallRows + kSmallBlock - 1) / kSmallBlock;
+
+__device__ __forceinline__ double sum_waves(const double* sh)
+{
+    return ((sh[0] + sh[1]) + (sh[2] + sh[3])) + ((sh[4] + sh[5]) + (sh[6] + sh[7]));
+}
+static_assert(kSmallWaves == 8, "sum_waves");
+
+// Sum over the wave, in lane 63 only.
+__device__ __forceinline__ double sum_wave(double x)
+{
+    x = sum16(x);
+    x = add_dpp_rows<0x142, 0xa>(x);     // row_bcast 15 into rows 1 and 3
+    return add_dpp_rows<0x143, 0xc>(x);  // row_bcast 31 into rows 2 and 3
+}
+
+// Sums of three values over each aligned group of 16 lanes: x's in its lane 0,
+// y's in lane 1, z's in lane 2 (after a step each, lanes keep one value only).
+__device__ __forceinline__ double sum16_three(double x, double y, double z, int lane)
+{
+    x = add_dpp<0xB1>(x);  // quad_perm 1 0 3 2
+    y = add_dpp<0xB1>(y);
+    z = add_dpp<0xB1>(z);
+    x = lane & 1 ? y : x;
+    x = add_dpp<0x4E>(x);  // quad_perm 2 3 0 1
+    z = add_dpp<0x4E>(z);
+    x = lane & 2 ? z : x;
+    x = add_dpp<0x124>(x);  // row_ror 4
+    return add_dpp<0x128>(x);  // row_ror 8
+}
+
+__global__ __launch_bounds__(kSmallBlock) void k_cg_small(CgView c, const double* b, double* x_out, CgScalars* host,
+                                                          double rtol, int k0, int k1, int max_iter)
+{
+    extern __shared__ double s_v[];  // per LDS round nine planes of kSmallBlock
+    __shared__ double s_p[kSmallRows + 3], s_q[kSmallRows + 1];  // past the rows: 0, for lanes without a neighbour or node
+    __shared__ double sh1[kSmallWaves], sh2[2 * kSmallWaves];
+    const int t = threadIdx.x, wave = t >> 6, nn = c.n / 3, group = t / kNodeLanes, l = t & (kNodeLanes - 1);
+    const int rounds = (nn + kSmallGroups - 1) / kSmallGroups;
+    double x[kSmallMine], r[kSmallMine], di[kSmallMine];
+    double rz = 0.0, rr = 0.0, rz_old = 0.0, bb = 0.0;
+#pragma unroll
+    for (int u = 0; u < kSmallMine; ++u) {
+        const int i = t + u * kSmallBlock, ii = i < c.n ? i : 0, pos = c.dpos[ii];
+        const double d = i < c.n && pos >= 0 ? c.vals[pos >= 0 ? pos : 0] : 0.0;
+        di[u] = d != 0.0 ? 1.0 / d : 0.0;
+        if (k0 == 0) {
+            x[u] = 0.0;
+            r[u] = d != 0.0 ? b[ii] : 0.0;
+        } else {
+            x[u] = c.x[ii];
+            r[u] = i < c.n ? c.r[ii] : 0.0;
+        }
+        if (i < kSmallRows)
+            s_p[i] = k0 == 0 ? 0.0 : c.zp[6 * (size_t)(ii / 3) + 3 + ii % 3];
+        const double z = r[u] * di[u];
+        rz = rz + r[u] * z;
+        rr = rr + r[u] * r[u];
+    }
+    if (t < 3)
+        s_p[kSmallRows + t] = 0.0;
+    // of each round the place in s_p of this lane's neighbour, the block, and whether the node has more neighbours
+    double v[kSmallHeld][9];
+    int j[kSmallHeld + kSmallLds];
+    unsigned more = 0u, live = 0u;
+    auto load = [&](int w, double (&m)[9]) {
+        const int i = w * kSmallGroups + group, ii = i < nn ? i : 0;
+        const int base = c.rowptr[3 * ii], rl = c.rowptr[3 * ii + 1] - base, a = c.adj[kNodeLanes * (size_t)ii + l];
+        const bool on = i < nn && a >= 0;
+        j[w] = on ? 3 * a : kSmallRows;
+        more |= i < nn && rl > 3 * kNodeLanes ? 1u << w : 0u;
+        const int row = 3 * ii + (l < 3 ? l : 0), pos = c.dpos[row];
+        live |= i < nn && l < 3 && pos >= 0 && c.vals[pos >= 0 ? pos : 0] != 0.0 ? 1u << w : 0u;
+        const double* q = c.vals + (on ? base + 3 * l : 0);
+#pragma unroll
+        for (int k = 0; k < 9; ++k)
+            m[k] = on ? q[(k / 3) * rl + k % 3] : 0.0;
+    };
+#pragma unroll
+    for (int w = 0; w < kSmallHeld; ++w)
+        load(w, v[w]);
+#pragma unroll
+    for (int w = 0; w < kSmallLds; ++w) {
+        j[kSmallHeld + w] = kSmallRows;
+        if (kSmallHeld + w < rounds) {
+            double m[9];
+            load(kSmallHeld + w, m);
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+                s_v[(9 * w + k) * kSmallBlock + t] = m[k];
+        }
+    }
+    if (k0 == 0) {
+        const double wz = sum_wave(rz), wr = sum_wave(rr);
+        if ((t & 63) == 63) {
+            sh2[wave] = wz;
+            sh2[kSmallWaves + wave] = wr;
+        }
+        __syncthreads();
+        rz = sum_waves(sh2);
+        bb = rr = sum_waves(sh2 + kSmallWaves);
+    } else {
+        rz = c.s->rzk[0];
+        rz_old = c.s->rzk[1];
+        rr = c.s->rr;
+        bb = c.s->bnorm2;
+    }
+    const double tol2 = (rtol * rtol) * bb;
+    bool done = k0 == 0 && bb == 0.0;
+    int k = k0;
+    while (!done) {
+        if ((k > 0 && rr <= tol2) || k >= max_iter) {
+            done = true;
+            break;
+        }
+        if (k == k1)
+            break;
+        const double beta = k > 0 ? rz / rz_old : 0.0;
+#pragma unroll
+        for (int u = 0; u < kSmallMine; ++u) {
+            const int i = t + u * kSmallBlock;
+            if (i < kSmallRows)
+                s_p[i] = (r[u] * di[u]) + beta * s_p[i];
+        }
+        __syncthreads();
+        double pq = 0.0;
+        auto node = [&](int w, const double (&m)[9]) {
+            const double* pj = s_p + j[w];
+            const int i = w * kSmallGroups + group, row = i < nn ? 3 * i + (l < 3 ? l : 0) : kSmallRows;
+            const double pr = s_p[row];
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                s0 = s0 + m[q] * pj[q];
+                s1 = s1 + m[3 + q] * pj[q];
+                s2 = s2 + m[6 + q] * pj[q];
+            }
+            if (more >> w & 1u) {
+                const int base = c.rowptr[3 * i], rl = c.rowptr[3 * i + 1] - base;
+                for (int kk = l + kNodeLanes; 3 * kk < rl; kk += kNodeLanes) {  // past the first 16 neighbours
+                    const double* e = s_p + c.colidx[base + 3 * kk];
+                    const double* g = c.vals + base + 3 * kk;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        s0 = s0 + g[q] * e[q];
+                        s1 = s1 + g[rl + q] * e[q];
+                        s2 = s2 + g[2 * rl + q] * e[q];
+                    }
+                }
+            }
+            const double acc = sum16_three(s0, s1, s2, t);
+            const double q = live >> w & 1u ? acc : 0.0;
+            if (l < 3)
+                s_q[row] = q;
+            pq = pq + pr * q;
+        };
+#pragma unroll
+        for (int w = 0; w < kSmallHeld; ++w)
+            if (w < rounds)
+                node(w, v[w]);
+#pragma unroll
+        for (int w = 0; w < kSmallLds; ++w)
+            if (kSmallHeld + w < rounds) {
+                double m[9];
+#pragma unroll
+                for (int q = 0; q < 9; ++q)
+                    m[q] = s_v[(9 * w + q) * kSmallBlock + t];
+                node(kSmallHeld + w, m);
+            }
+        pq = sum_wave(pq);
+        if ((t & 63) == 63)
+            sh1[wave] = pq;
+        __syncthreads();
+        const double alpha = rz / sum_waves(sh1);
+        double wz = 0.0, wr = 0.0;
+#pragma unroll
+        for (int u = 0; u < kSmallMine; ++u) {
+            const int i = t + u * kSmallBlock;
+            if (i < c.n) {
+                x[u] = x[u] + alpha * s_p[i];
+                r[u] = r[u] - alpha * s_q[i];
+                wz = wz + r[u] * (r[u] * di[u]);
+                wr = wr + r[u] * r[u];
+            }
+        }
+        wz = sum_wave(wz);
+        wr = sum_wave(wr);
+        if ((t & 63) == 63) {
+            sh2[wave] = wz;
+            sh2[kSmallWaves + wave] = wr;
+        }
+        __syncthreads();
+        rz_old = rz;
+        rz = sum_waves(sh2);
+        rr = sum_waves(sh2 + kSmallWaves);
+        ++k;
+    }
+#pragma unroll
+    for (int u = 0; u < kSmallMine; ++u) {
+        const int i = t + u * kSmallBlock;
+        if (i >= c.n)
+            continue;
+        if (done) {
+            x_out[i] = x[u];
+        } else {
+            c.x[i] = x[u];
+            c.r[i] = r[u];
+            c.zp[6 * (size_t)(i / 3) + 3 + i % 3] = s_p[i];
+        }
+    }
+    if (t == 0) {
+        c.s->rzk[0] = rz;
+        c.s->rzk[1] = rz_old;
+        c.s->rr = rr;
+        c.s->bnorm2 = bb;
+        host->rr = rr;
+        host->bnorm2 = bb;
+        host->iters = k;
+        host->done = done ? 1 : 0;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_cg_output(CgView c, double* __restrict__ x)
 {
     const int i = blockIdx.x * kBlock + threadIdx.x;
@@ -460,6 +711,23 @@ hipError_t launch_cg_iterations(const CgView& c, int first, int count, int max_i
         hipLaunchKernelGGL(k_cg_spmv, dim3(c.nparts_s), dim3(kBlock), 0, s, c, k, cur, max_iter);
         hipLaunchKernelGGL(k_cg_update, dim3(c.nparts_u), dim3(kBlock), 0, s, c, k, cur);
     }
+    return hipGetLastError();
+}
+
+bool cg_is_small(int n)
+{
+    return n <= kSmallRows;
+}
+
+// Iterations k0 .. k1 - 1 of a small solve, or its end; host: pinned.
+hipError_t launch_cg_small(const CgView& c, const double* b, double* x, CgScalars* host, double rtol, int k0, int k1,
+                           int max_iter, hipStream_t s)
+{
+    if (!cg_is_small(c.n))
+        return hipErrorInvalidValue;
+    const int rounds = (c.n / 3 + kSmallGroups - 1) / kSmallGroups;
+    const size_t lds = rounds > kSmallHeld ? sizeof(double) * 9 * kSmallBlock * (rounds - kSmallHeld) : 0;
+    hipLaunchKernelGGL(k_cg_small, dim3(1), dim3(kSmallBlock), lds, s, c, b, x, host, rtol, k0, k1, max_iter);
     return hipGetLastError();
 }
 

@@ -425,6 +425,9 @@ int update_grid(int n);
 hipError_t launch_cg_init(const CgView& c, const double* b, double rtol, hipStream_t s);
 // Iterations first .. first+count-1 (the iteration index picks the copy of p).
 hipError_t launch_cg_iterations(const CgView& c, int first, int count, int max_iter, hipStream_t s);
+bool cg_is_small(int n);
+hipError_t launch_cg_small(const CgView& c, const double* b, double* x, CgScalars* host, double rtol, int k0, int k1,
+                           int max_iter, hipStream_t s);
 hipError_t launch_cg_output(const CgView& c, double* x, hipStream_t s);
 
 // Lumped mass and implicit Euler (euler.hip).

@@ -73,3 +73,70 @@ def test_solution_and_limits(name):
         assert itk < it or torch.equal(xk, x)
     assert asm.cg_solve(torch.zeros_like(bd))[1] == 0
     asm.close()
+
+
+def bar(layers, stiff):
+    """Stiff cells in a row, with their moduli far apart: 1,760 iterations at 70 layers and 1e9."""
+    x1, t1 = W.grid_nodes(1), W.kuhn_tets(1)
+    x = np.concatenate([x1[:4] + [i, 0, 0] if x1[3, 0] == 0 else x1[:4] + [0, 0, i] for i in range(layers + 1)])
+    tets = np.concatenate([t1 + 4 * i for i in range(layers)]).astype(np.int32)
+    E = stiff * 10.0 ** np.random.default_rng(layers).uniform(-2, 2, size=len(tets))
+    return W.Workload("bar", x, tets, E, np.ones(len(tets), np.uint8))
+
+
+def padded(nodes):
+    """The largest fracture mesh of at most this many nodes, its nodes scattered among unused ones."""
+    n = int(round(nodes ** (1 / 3) + 0.5))
+    while (n + 1) ** 3 > nodes:
+        n -= 1
+    w = W.make_fracture(seed=8, n=n, counts=[1])
+    g = np.random.default_rng(nodes)
+    at = g.permutation(nodes)[:w.n_nodes]
+    x = g.uniform(size=(nodes, 3))
+    x[at] = w.x
+    return W.Workload("padded", x, at[w.tets].astype(np.int32), w.E, w.mask0)
+
+
+@pytest.mark.parametrize("nodes", [8, 32, 33, 256, 257, 288, 289, 343, 352, 353])
+def test_small_systems(nodes):
+    """Node counts where a small system's rounds, its blocks in LDS and the one launch itself
+    begin and end, with unused nodes between the others."""
+    Sm = S()
+    w = padded(nodes)
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    vals = asm.values()
+    v = vals.cpu().numpy()
+    g = np.random.default_rng(3)
+    live = np.diff(pat[0]) > 0
+    b = g.standard_normal(asm.n_rows)
+    x, it, rr = asm.cg_solve(torch.from_numpy(b).cuda(), rtol=1e-12)
+    bl = np.where(live, b, 0.0)
+    res, size = true_residual(pat, v, x.cpu().numpy(), bl)
+    nb = np.linalg.norm(bl)
+    assert rr <= 1e-12 and np.all(x.cpu().numpy()[~live] == 0.0)
+    assert res <= 1e-12 * nb + 8 * U * it * (size + nb), (res / nb, it)
+    for k in (0, 1, it - 1, it, it + 1):
+        xk, itk, rk = asm.cg_solve(torch.from_numpy(b).cuda(), rtol=1e-12, max_iter=k)
+        assert itk == min(k, it) and (itk < it or torch.equal(xk, x))
+    asm.close()
+
+
+def test_small_system_long_solve():
+    """More iterations than one launch takes: the solve goes on where it stopped, and ends at the
+    limit or at the tolerance as a shorter one does."""
+    Sm = S()
+    w = bar(70, 1e9)
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    vals = asm.values()
+    b = np.random.default_rng(5).standard_normal(asm.n_rows)
+    bl = np.where(np.diff(pat[0]) > 0, b, 0.0)
+    nb = np.linalg.norm(bl)
+    free = asm.cg_solve(torch.from_numpy(b).cuda(), rtol=1e-12)[1]
+    assert free > 1100
+    for k in (1023, 1024, 1025, 1100):
+        x, it, rr = asm.cg_solve(torch.from_numpy(b).cuda(), rtol=1e-12, max_iter=k)
+        res, size = true_residual(pat, vals.cpu().numpy(), x.cpu().numpy(), bl)
+        assert it == k and abs(res - rr * nb) <= 8 * U * it * (size + nb), (k, it, res / nb, rr)
+    asm.close()
