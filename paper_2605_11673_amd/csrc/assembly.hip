@@ -208,9 +208,12 @@ __global__ __launch_bounds__(kBlock) void k_geometry(DevView v)
 //
 // Loads past a tile's end take its last element (in range), so that no branch
 // or wait separates the loads of a round (with one: 116 us instead of 50 on the
-// 384,000-tet cube; summing stored contributions from HBM took 88 to 91).
+// 384,000-tet cube; summing stored contributions from HBM took 88 to 91).  The
+// phases of one workgroup wait for each other, so it takes several on a compute
+// unit to keep it busy: with 31,920 bytes of LDS five fit, and it takes 46 us
+// (of which 24 are arithmetic); with 34,032, four, 50.
 constexpr int kRowThreads = 192;
-constexpr int kRowStride = 15;              // doubles per staged record (odd: neighbouring records differ in bank)
+constexpr int kRowStride = 13;              // doubles per staged record (odd: neighbouring records differ in bank)
 constexpr int kDiagStride = kTilePairs + 1;  // diagonal values: value vi of pair p at vi * kDiagStride + p
 constexpr int kRowOut = 6 * kDiagStride > 9 * kTileBlocks ? 6 * kDiagStride : 9 * kTileBlocks;
 static_assert(kRowThreads == kTileBlocks + 64 && kTileNodes * 6 <= 64, "one wave of diagonal lanes");
@@ -218,10 +221,10 @@ static_assert(kTilePairs == kRowThreads, "one lane per pair");
 template <bool NT>
 __global__ __launch_bounds__(kRowThreads) void k_rows(DevView v)
 {
-    __shared__ double s_geo[kTilePairs * kRowStride];
+    __shared__ double s_geo[kTilePairs * kRowStride];  // g, lamV
+    __shared__ double s_mu[kTilePairs];                // muV
     __shared__ double s_out[kRowOut];  // the diagonal values, then the rows
     __shared__ uint16_t s_term[kTileTerms];
-    __shared__ uint8_t s_vertex[kTilePairs];  // the row node's local vertex in each pair's tet
     const RowTile tile = v.tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const int tid = threadIdx.x;
     constexpr int kRounds = kTilePairs * 8 / kRowThreads;
@@ -236,6 +239,7 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(DevView v)
 #pragma unroll
     for (int k = 0; k < kTermRounds; ++k)
         term[k] = v.terms[tile.term0 + min(k * kRowThreads + tid, tile.terms - 1)];
+    const uint32_t own = v.di[tile.pair0 + min(tid, tile.pairs - 1)];  // this lane's pair
     // row block or row node of this lane
     const int dl = tid - kTileBlocks;  // diagonal lane: node dl / 6, value dl % 6
     const bool has_blk = tid < tile.blks, has_node = dl >= 0 && dl < 6 * tile.nodes;
@@ -254,20 +258,22 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(DevView v)
 #pragma unroll
     for (int k = 0; k < kRounds; ++k) {
         const int p = k * kPerRound + (tid >> 3);
-        s_geo[p * kRowStride + 2 * j] = on[k] ? q[k].x : 0.0;
-        if (j < 7)
-            s_geo[p * kRowStride + 2 * j + 1] = on[k] ? q[k].y : 0.0;
-        else
-            s_vertex[p] = (uint8_t)(u[k] & 3u);
+        const double x = on[k] ? q[k].x : 0.0, y = on[k] ? q[k].y : 0.0;
+        if (j < 7) {  // j = 6: lamV, muV
+            s_geo[p * kRowStride + 2 * j] = x;
+            *(j < 6 ? s_geo + p * kRowStride + 2 * j + 1 : s_mu + p) = y;
+        } else {
+            s_out[5 * kDiagStride + p] = x;  // ml, until its lane puts a diagonal value there
+        }
     }
     __syncthreads();
     {
         const double* r = s_geo + tid * kRowStride;
-        const double* pa = r + 3 * s_vertex[tid];
+        const double* pa = r + 3 * (own & 3u);
         Geo G;
         G.lamV = r[12];
-        G.muV = r[13];
-        G.ml = r[14];
+        G.muV = s_mu[tid];
+        G.ml = s_out[5 * kDiagStride + tid];
         const double g[3] = {pa[0], pa[1], pa[2]};
         const double s = dot3(g, g);
 #pragma unroll
@@ -288,7 +294,7 @@ __global__ __launch_bounds__(kRowThreads) void k_rows(DevView v)
             const double* pb = r + 3 * (t & 3u);
             Geo G;
             G.lamV = r[12];
-            G.muV = r[13];
+            G.muV = s_mu[t >> 4];
             const double ga[3] = {pa[0], pa[1], pa[2]}, gb[3] = {pb[0], pb[1], pb[2]};
             const double s = dot3(ga, gb);
 #pragma unroll

@@ -178,7 +178,7 @@ constexpr int kGeoDoubles = 16;  // doubles per record; the first 15 hold values
 // is), contiguous in di; its row blocks are the nodes' (node, neighbour)
 // blocks, contiguous in rowblk; its terms list, for each off-diagonal row
 // block in ascending tet id, the pair and the two local vertices.
-constexpr int kTilePairs = 192, kTileBlocks = 128, kTileNodes = 10, kTileTerms = 768;
+constexpr int kTilePairs = 192, kTileBlocks = 128, kTileNodes = 10, kTileTerms = 3 * kTilePairs;
 struct RowTile {
     int32_t pair0, pairs;  // range of di
     int32_t blk0, blks;    // range of rowblk
