@@ -76,6 +76,194 @@ __device__ __forceinline__ void geometry(const DevView& v, int4 t, Geo& G)
     G.V = fabs(det) / 6.0;
 }
 
+// Gather the 3x3 cotangent block Abar_ab (rows: vertex a dofs, columns: vertex b dofs).
+__device__ __forceinline__ void gather_block(const DevView& v, const double* __restrict__ gA, const int* id, int a,
+                                             int b, int blk, double out[3][3])
+{
+    const BlockDesc d = v.desc[blk];
+    if (a == b) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                out[i][j] = gA[d.up + i * d.rl + j];
+    } else if (id[a] < id[b]) {  // row node of the stored block is vertex a
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                out[i][j] = gA[d.up + i * d.rl + j];
+    } else {  // row node is vertex b: entry (3a+i, 3b+j) is the mirror part
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                out[i][j] = gA[d.lo + i * d.rlj + j];
+    }
+}
+
+// Every tet gathers its 144 cotangents: for meshes of few bricks (below), which
+// would leave most of the chip idle.  Workgroups of one wave, so that the waves
+// are spread over the compute units: 16.4 us at 48,000 tets, 22.6 at 82,944,
+// where workgroups of four took 17.2 and 26.2.
+constexpr int kDirect = 64;
+__global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int32_t* __restrict__ order,
+                                                            int32_t n_chunks, const double* __restrict__ gA,
+                                                            double* __restrict__ g_logE,
+                                                            double* __restrict__ xbar)
+{
+    // each XCD takes one contiguous share of the chunk order, chunks that are
+    // near in space: neighbouring tets share node blocks, so their cotangent
+    // rows stay in one L2
+    constexpr int kPer = kDirect / kAdjointChunk;
+    const int slot = xcd_remap(blockIdx.x, gridDim.x) * kPer + threadIdx.x / kAdjointChunk;
+    if (slot >= n_chunks)
+        return;
+    const int e = order[slot] * kAdjointChunk + (threadIdx.x % kAdjointChunk);
+    if (e >= v.n_tets)
+        return;
+    const int* pos = v.e2p + 10 * (size_t)e;
+    if (!v.mask[e]) {
+        g_logE[e] = 0.0;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            double* dst = xbar + 3 * (size_t)pos[a];
+            dst[0] = 0.0;
+            dst[1] = 0.0;
+            dst[2] = 0.0;
+        }
+        return;
+    }
+    const int4 t = v.T[e];
+    const int id[4] = {t.x, t.y, t.z, t.w};
+    const int* eb = v.e2b + 10 * (size_t)e;
+    Geo G;
+    geometry(v, t, G);
+    const double E = v.E[e];
+    const double lam_dt = (E * v.mat.clam) * v.mat.cdt;  // lambda dt^2
+    const double mu_dt = (E * v.mat.cmu) * v.mat.cdt;    // mu dt^2
+    const double lamV = lam_dt * G.V, muV = mu_dt * G.V;
+
+    double Plam = 0.0, Pmu = 0.0, Pm = 0.0;
+    double gbar[4][3];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            gbar[a][i] = 0.0;
+
+    // pairs (a, b) with a <= b; B_ab = Abar_ab + Abar_ba^T, B_ba = B_ab^T
+    constexpr int PA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2};
+    constexpr int PB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        const int a = PA[q], b = PB[q];
+        double Aab[3][3], Aba[3][3];
+        gather_block(v, gA, id, a, b, eb[q], Aab);
+        if (a == b) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    Aba[i][j] = Aab[i][j];
+        } else {
+            gather_block(v, gA, id, b, a, eb[q], Aba);
+        }
+        // P terms over (a,b) and, for a != b, (b,a)
+        const double* ga = G.g[a];
+        const double* gb = G.g[b];
+        const double sab = (ga[0] * gb[0] + ga[1] * gb[1]) + ga[2] * gb[2];
+        double t_ab = 0.0, t_ba = 0.0, plam = 0.0, pmu = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                plam += ga[i] * Aab[i][j] * gb[j];
+                pmu += gb[i] * Aab[i][j] * ga[j];
+                if (a != b) {
+                    plam += gb[i] * Aba[i][j] * ga[j];
+                    pmu += ga[i] * Aba[i][j] * gb[j];
+                }
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            t_ab += Aab[i][i];
+            t_ba += Aba[i][i];
+        }
+        if (a == b) {
+            Plam += plam;
+            Pmu += pmu + t_ab * sab;
+            Pm += t_ab;
+        } else {
+            Plam += plam;
+            Pmu += pmu + (t_ab + t_ba) * sab;
+        }
+        // gbar: B_ab = Aab + Aba^T drives gbar_a (with g_b); B_ba = B_ab^T drives gbar_b (with g_a)
+        double B[3][3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                B[i][j] = Aab[i][j] + Aba[j][i];
+        const double trB = (B[0][0] + B[1][1]) + B[2][2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            double ua = 0.0, ub = 0.0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                ua += (lamV * B[i][j] + muV * B[j][i]) * gb[j];
+                if (a != b)
+                    ub += (lamV * B[j][i] + muV * B[i][j]) * ga[j];
+            }
+            gbar[a][i] += ua + muV * trB * gb[i];
+            if (a != b)
+                gbar[b][i] += ub + muV * trB * ga[i];
+        }
+    }
+    g_logE[e] = lamV * Plam + muV * Pmu;
+
+    const double Vbar = lam_dt * Plam + mu_dt * Pmu + 0.25 * v.mat.rho * Pm;
+    const double detbar = Vbar * (G.det < 0.0 ? -1.0 : 1.0) / 6.0;
+    // Gbar columns k = 1..3: gbar_k - gbar_0 ; G columns g_k
+    double Gm[3][3], Gb[3][3];  // [row i][col k-1]
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            Gm[i][k] = G.g[k + 1][i];
+            Gb[i][k] = gbar[k + 1][i] - gbar[0][i];
+        }
+    // Dbar = -G Gbar^T G + detbar det G
+    double T1[3][3];  // Gbar^T G
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            T1[i][j] = (Gb[0][i] * Gm[0][j] + Gb[1][i] * Gm[1][j]) + Gb[2][i] * Gm[2][j];
+    double Db[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            Db[i][j] = -((Gm[i][0] * T1[0][j] + Gm[i][1] * T1[1][j]) + Gm[i][2] * T1[2][j]) +
+                       detbar * G.det * Gm[i][j];
+    double xb[4][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        xb[1][i] = Db[i][0];
+        xb[2][i] = Db[i][1];
+        xb[3][i] = Db[i][2];
+        xb[0][i] = -((Db[i][0] + Db[i][1]) + Db[i][2]);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        double* dst = xbar + 3 * (size_t)pos[a];
+        dst[0] = xb[a][0];
+        dst[1] = xb[a][1];
+        dst[2] = xb[a][2];
+    }
+}
+
 // Everything above depends on the cotangents through B_ab = Abar_ab + Abar_ba^T
 // alone: P_lam = sum_{a<b} g_a^T B_ab g_b + 1/2 sum_a g_a^T B_aa g_a,
 // P_mu = sum_{a<b} (g_b^T B_ab g_a + tr(B_ab) g_a.g_b) + 1/2 sum_a (...),
@@ -93,6 +281,10 @@ __device__ __forceinline__ void geometry(const DevView& v, int4 t, Geo& G)
 // every line of the rows twice: 78 instead of 72 us a call.)
 constexpr int kBrickChunks = kAdjointBrick / kAdjointChunk;
 constexpr int kBrickBlocks = 10 * kAdjointBrick, kBrickReads = 2 * kBrickBlocks;  // most a brick can have
+// Fewer bricks (4 a compute unit) and every tet gathers for itself: the whole
+// adjoint, gathered / by bricks, 11.7 / 15.0 us at 1,296 tets, 16.4 / 21.0 at
+// 48,000, 27.5 / 28.6 at 105,456, 35.0 / 33.8 at 131,712, 56.4 / 52.4 at 235,824.
+constexpr int kMinBricks = 1024;
 constexpr int kBrickTable = 4096;  // hash slots while a brick's blocks are found
 constexpr int kEntryWords = 3;
 constexpr int kMirror = 1 << 15, kDiagonal = 1 << 14;
@@ -473,9 +665,11 @@ __global__ __launch_bounds__(kBlock) void k_slot_outer(int n_rows, const int32_t
 
 }  // namespace
 
+// 0: the mesh is too small for bricks.
 int adjoint_bricks(int n_chunks)
 {
-    return (n_chunks + kBrickChunks - 1) / kBrickChunks;
+    const int bricks = (n_chunks + kBrickChunks - 1) / kBrickChunks;
+    return bricks < kMinBricks ? 0 : bricks;
 }
 
 hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
@@ -494,7 +688,10 @@ hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n
 hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
                           const double* gA, double* g_logE, double* g_x, double* xbar, hipStream_t s)
 {
-    if (v.n_tets > 0)
+    if (v.n_tets > 0 && !plan.entries)
+        hipLaunchKernelGGL(k_adjoint_direct, dim3((n_chunks * kAdjointChunk + kDirect - 1) / kDirect), dim3(kDirect), 0, s,
+                           v, order, n_chunks, gA, g_logE, xbar);
+    else if (v.n_tets > 0)
         hipLaunchKernelGGL(k_adjoint_element, dim3(adjoint_bricks(n_chunks)), dim3(kAdjointBrick),
                            9 * sizeof(double) * plan.most, s, v, order, n_chunks, plan, gA, g_logE, xbar);
     hipError_t e = hipGetLastError();

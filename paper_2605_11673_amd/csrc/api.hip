@@ -486,11 +486,12 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.ctl = ctl;
 
     // the adjoint's bricks: count, running sums, fill
-    if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, false, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e == hipSuccess && bricks > 0) {
+        e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, false, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
         std::vector<int32_t> starts((size_t)bricks + 1), blocks((size_t)bricks);
-        e = hipMemcpy(starts.data(), c->adj_plan.starts, sizeof(int32_t) * bricks, hipMemcpyDeviceToHost);
+        if (e == hipSuccess)
+            e = hipMemcpy(starts.data(), c->adj_plan.starts, sizeof(int32_t) * bricks, hipMemcpyDeviceToHost);
         if (e == hipSuccess)
             e = hipMemcpy2D(blocks.data(), sizeof(int32_t), c->adj_plan.refs, 20 * kAdjointBrick, sizeof(int32_t),
                             (size_t)bricks, hipMemcpyDeviceToHost);

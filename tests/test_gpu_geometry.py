@@ -189,3 +189,26 @@ def test_adjoint_bricks(mesh):
     assert np.all(np.abs(gl - ol) <= tl) and np.all(np.abs(gx - ox) <= tx)
     assert np.all(gl[w.mask0 == 0] == 0.0)
     asm.close()
+
+
+@pytest.mark.parametrize("m", [130944, 130945, 131072, 140001])
+def test_adjoint_many_tets(m):
+    """Tet counts where bricks begin (1,024 of 128 tets) and the last one is short; scattered nodes, so
+    that bricks hold many different blocks: every tet and coordinate within its rounding bound."""
+    from tests.bounds import adjoint_tolerances
+    Sm = S()
+    g = np.random.default_rng(m)
+    n = 300
+    tets = (np.cumsum(g.integers(1, n // 4, size=(m, 4)), axis=1) - 1).astype(np.int32)
+    w = W.Workload("many", g.uniform(0.0, 1.0, size=(n, 3)), tets, W.lognormal_E(m, g),
+                   g.integers(0, 2, size=m).astype(np.uint8))
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    gA = g.standard_normal(asm.nnz)
+    gl, gx = (t.cpu().numpy() for t in asm.adjoint(torch.from_numpy(gA).cuda()))
+    args = (w.x, w.tets, w.E, w.nu, w.rho, w.dt, w.mask0, *pat, gA)
+    ol, ox = oracle.adjoint(*args)
+    tl, tx = adjoint_tolerances(w, w.mask0, pat[0], pat[1], gA)
+    assert np.all(np.abs(gl - ol) <= tl) and np.all(np.abs(gx - ox) <= tx)
+    assert np.all(gl[w.mask0 == 0] == 0.0)
+    asm.close()
