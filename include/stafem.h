@@ -442,9 +442,11 @@ void sta_destroy(sta_ctx* ctx);
  * vertex in some candidate tet (other rows are empty).  The pattern never
  * changes: an inactive edge's two entries hold +0.0, an active one's -1.0;
  * a diagonal holds float64(degree) + eps.  Edges are numbered in ascending
- * (u, v), u < v.  Counts and degrees are maintained as int32 with the +1/-1
- * deltas of eq. (7); values are rewritten from them, so every frame leaves
- * the state exactly equal to sta_proxy_full_rebuild on the same mask.
+ * (u, v), u < v.  Counts and degrees are int32, so the +1/-1 deltas of
+ * eq. (7) and counting a changed tet's edges again give the same; values are
+ * rewritten from them, and every frame leaves the state exactly equal to
+ * sta_proxy_full_rebuild on the same mask.  A frame of up to 2,304 edits is
+ * one launch, a larger one two.
  * Stream, error and threading rules as above.
  * ------------------------------------------------------------------------ */
 typedef struct sta_proxy sta_proxy;

@@ -116,9 +116,6 @@ __device__ __forceinline__ double entry(const double* ga, const double* gb, doub
     return v;
 }
 
-constexpr int PA[6] = {0, 0, 0, 1, 1, 2};
-constexpr int PB[6] = {1, 2, 3, 2, 3, 3};
-
 __device__ __constant__ int kDiagP[6] = {0, 0, 0, 1, 1, 2};
 __device__ __constant__ int kDiagQ[6] = {0, 1, 2, 1, 2, 2};
 
