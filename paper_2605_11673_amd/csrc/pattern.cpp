@@ -173,22 +173,17 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
 void build_row_plan(int64_t n, const int32_t* tets, int64_t m, const HostPattern& P,
                     const std::vector<int64_t>& node_off, RowPlan& R)
 {
-    auto local = [&](int64_t e, int32_t node) {
-        for (int a = 0; a < 4; ++a)
-            if (tets[4 * e + a] == node)
-                return (uint32_t)a;
-        return 0u;
-    };
     // incidences with their local vertices
     R.di.resize((size_t)m * 4);
     R.oi.resize((size_t)m * 6);
     for (int64_t e = 0; e < m; ++e)
         for (int a = 0; a < 4; ++a)
             R.di[P.e2p[10 * e + a]] = (uint32_t)e << 2 | (uint32_t)a;
-    for (int64_t o = 0; o < P.no; ++o)
-        for (int32_t k = P.oseg[o]; k < P.oseg[o + 1]; ++k) {
-            const int64_t e = P.oinc[k];
-            R.oi[k] = (uint32_t)e << 4 | local(e, P.opair[2 * o]) << 2 | local(e, P.opair[2 * o + 1]);
+    for (int64_t e = 0; e < m; ++e)
+        for (int p = 0; p < 6; ++p) {  // the pair's smaller node first, as in opair
+            const uint32_t a = kPairA[p], b = kPairB[p];
+            const bool up = tets[4 * e + a] < tets[4 * e + b];
+            R.oi[P.e2p[10 * e + 4 + p]] = (uint32_t)e << 4 | (up ? a << 2 | b : b << 2 | a);
         }
     // per row block (9 CSR values each) its off-diagonal block and whether the row is its upper node
     const int64_t nb = P.nnz / 9;
@@ -199,6 +194,8 @@ void build_row_plan(int64_t n, const int32_t* tets, int64_t m, const HostPattern
         row_off[P.rowptr[3 * j] / 9 + (P.ometa[4 * o + 2] - P.rowptr[3 * j]) / 3] = (int32_t)(2 * o + 1);
     }
     R.rowblk.assign((size_t)nb, make_uint2(0, 0));
+    R.terms.reserve((size_t)m * 12);
+    R.rownode.reserve((size_t)P.nd);
     std::vector<uint8_t> big_off((size_t)P.no, 0);
     size_t mesh = 0;
     bool open = false;
