@@ -57,34 +57,38 @@ __global__ __launch_bounds__(kBlock) void k_tet_mass(DevView v, double* __restri
 
 // One thread per node: its diagonal block's incidence segment in ascending
 // tet id, active terms only.  Tet ids, mask bytes and masses are loaded
-// kChunk at a time and then added in order (a few memory round trips per
-// segment instead of two per term).
-__global__ __launch_bounds__(kBlock) void k_lumped_mass(DevView v, const int32_t* __restrict__ dinc,
-                                                        const double* __restrict__ ml, double* __restrict__ m)
+// kChunk at a time and then added in order: two memory round trips for the 24
+// tets of an inner node.  The gathers are bound by the address units, so that
+// workgroups of one wave spread a small mesh over as many of them as there
+// are: 7.0 -> 3.6 us at 1,728 nodes, 9.2 -> 7.8 at 68,921 (8 tets at a time,
+// workgroups of four waves before).
+constexpr int kMassBlock = 64;
+__global__ __launch_bounds__(kMassBlock) void k_lumped_mass(DevView v, const int32_t* __restrict__ dinc,
+                                                            const double* __restrict__ ml, double* __restrict__ m)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    const int i = blockIdx.x * kMassBlock + threadIdx.x;
     if (i >= v.n_nodes)
         return;
     double acc = 0.0;
     const int b = v.ndiag[i];
     if (b >= 0) {
         const BlockDesc d = v.desc[b];
-        constexpr int kChunk = 8;
+        constexpr int kChunk = 24;
         for (int k0 = d.k0; k0 < d.k1; k0 += kChunk) {
             int e[kChunk];
 #pragma unroll
             for (int j = 0; j < kChunk; ++j)
-                e[j] = k0 + j < d.k1 ? dinc[k0 + j] : -1;
-            bool on[kChunk];
+                e[j] = dinc[min(k0 + j, d.k1 - 1)];  // past the end: its last tet, not added
+            uint8_t on[kChunk];
             double w[kChunk];
 #pragma unroll
             for (int j = 0; j < kChunk; ++j) {
-                on[j] = e[j] >= 0 && v.mask[e[j]];
-                w[j] = e[j] >= 0 ? ml[e[j]] : 0.0;
+                on[j] = v.mask[e[j]];
+                w[j] = ml[e[j]];
             }
 #pragma unroll
             for (int j = 0; j < kChunk; ++j)
-                if (on[j])
+                if (k0 + j < d.k1 && on[j])
                     acc = acc + w[j];
         }
     }
@@ -127,7 +131,8 @@ hipError_t launch_lumped_mass(const DevView& v, const int32_t* dinc, const doubl
 {
     if (v.n_nodes == 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_lumped_mass, dim3(blocks(v.n_nodes)), dim3(kBlock), 0, s, v, dinc, tet_ml, m);
+    hipLaunchKernelGGL(k_lumped_mass, dim3((v.n_nodes + kMassBlock - 1) / kMassBlock), dim3(kMassBlock), 0, s, v, dinc,
+                       tet_ml, m);
     return hipGetLastError();
 }
 

@@ -152,3 +152,21 @@ def test_euler_steps_match_oracle_per_dof(iters, n_frames):
     print(f"[euler] {iters} iterations per step: worst error / bound {worst:.3e}", flush=True)
     assert asm.status_sync() == Sm.STA_OK
     asm.close()
+
+
+@pytest.mark.parametrize("spokes", [1, 23, 24, 25, 48, 49, 130])
+def test_lumped_mass_of_a_hub(spokes):
+    """A node of as many tets as are loaded at a time, one fewer and more, and an unused node."""
+    Sm = S()
+    g = np.random.default_rng(spokes)
+    tets = np.concatenate([np.zeros((spokes, 1), int), 1 + np.arange(3 * spokes).reshape(spokes, 3)], 1)
+    x = g.uniform(0.0, 1.0, size=(3 * spokes + 2, 3))
+    w = W.Workload("fan", x, tets.astype(np.int32), W.lognormal_E(spokes, g), np.ones(spokes, np.uint8))
+    asm = Sm.Assembler.from_workload(w)
+    for density in (1.0, 0.6, 0.0):
+        mask = (g.uniform(size=spokes) < density).astype(np.uint8)
+        asm.apply_edits(*Sm.upload_frame(np.arange(spokes, dtype=np.int32), mask))
+        m = asm.lumped_mass()
+        torch.cuda.synchronize()
+        assert np.array_equal(bits(m.cpu().numpy()), bits(oracle.lumped_mass(w.x, w.tets, w.rho, mask)))
+    asm.close()
