@@ -5,12 +5,12 @@
 //   A[3a+i][3b+j] = lamV g_ai g_bj + muV g_aj g_bi + [i=j] muV (g_a.g_b) + [a=b][i=j] m,
 // lamV = lambda V dt^2, muV = mu V dt^2, m = rho V / 4, V = |det D| / 6,
 // g_k = column k of G = D^-T (k = 1..3), g_0 = -(g_1 + g_2 + g_3), D = [x1-x0, x2-x0, x3-x0]:
-// with Abar the 12x12 gather of gA over the tet's slots and B_ab = Abar_ab + Abar_ba^T,
-//   P_lam = sum_ab g_a^T Abar_ab g_b,  P_mu = sum_ab (g_b^T Abar_ab g_a + tr(Abar_ab) g_a.g_b),
-//   P_m = sum_a tr(Abar_aa),
-//   dL/dlogE = lamV P_lam + muV P_mu        (lambda, mu proportional to E = exp(logE)),
-//   gbar_a = sum_b (lamV B_ab + muV B_ab^T + muV tr(B_ab) I) g_b,
-//   Vbar = (lambda dt^2) P_lam + (mu dt^2) P_mu + (rho/4) P_m,
+// with Abar the 12x12 gather of gA over the tet's slots, B_ab = Abar_ab + Abar_ba^T (B_ba = B_ab^T) and
+// C_ab = lambda dt^2 B_ab + mu dt^2 (B_ab^T + tr(B_ab) I):
+//   u_ab = C_ab g_b,  P = sum_{a<b} g_a . u_ab + 1/2 sum_a g_a . u_aa,  P_m = 1/2 sum_a tr(B_aa),
+//   dL/dlogE = V P                          (lambda, mu proportional to E = exp(logE)),
+//   gbar_a = V sum_b u_ab,
+//   Vbar = P + (rho/4) P_m,
 //   Dbar = -G Gbar^T G + (Vbar sign(det) / 6) det G,  Gbar columns gbar_k - gbar_0,
 //   xbar_k = column k of Dbar (k = 1..3), xbar_0 = -(xbar_1 + xbar_2 + xbar_3).
 // Inactive tets contribute nothing.  Per-vertex xbar are stored at the tet's
@@ -76,153 +76,52 @@ __device__ __forceinline__ void geometry(const DevView& v, int4 t, Geo& G)
     G.V = fabs(det) / 6.0;
 }
 
-// Gather the 3x3 cotangent block Abar_ab (rows: vertex a dofs, columns: vertex b dofs).
-__device__ __forceinline__ void gather_block(const DevView& v, const double* __restrict__ gA, const int* id, int a,
-                                             int b, int blk, double out[3][3])
+// The tet's sums over its blocks: both kernels below form the same B_ab and add
+// them in the order of the block slots through here, so that a tet's results
+// are the same bits whichever of them it falls to (a mesh alone and in a batch
+// may differ in that).
+struct TetSums {
+    double P = 0.0, Pm = 0.0;
+    double u[4][3] = {};
+};
+constexpr int kSlotA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2}, kSlotB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
+
+__device__ __forceinline__ void add_block(TetSums& s, const Geo& G, int a, int b, const double (&B)[3][3],
+                                          double lam_dt, double mu_dt)
 {
-    const BlockDesc d = v.desc[blk];
+    const double* ga = G.g[a];
+    const double* gb = G.g[b];
+    const double tr = (B[0][0] + B[1][1]) + B[2][2], t = mu_dt * tr;
+    double C[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            C[i][j] = lam_dt * B[i][j] + mu_dt * B[j][i];
+    double ua[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        ua[i] = ((C[i][0] * gb[0] + C[i][1] * gb[1]) + C[i][2] * gb[2]) + t * gb[i];
+        s.u[a][i] += ua[i];
+    }
+    const double p = (ga[0] * ua[0] + ga[1] * ua[1]) + ga[2] * ua[2];
     if (a == b) {
+        s.P += 0.5 * p;
+        s.Pm += 0.5 * tr;
+    } else {
+        s.P += p;
 #pragma unroll
         for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.up + i * d.rl + j];
-    } else if (id[a] < id[b]) {  // row node of the stored block is vertex a
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.up + i * d.rl + j];
-    } else {  // row node is vertex b: entry (3a+i, 3b+j) is the mirror part
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                out[i][j] = gA[d.lo + i * d.rlj + j];
+            s.u[b][i] += ((C[0][i] * ga[0] + C[1][i] * ga[1]) + C[2][i] * ga[2]) + t * ga[i];
     }
 }
 
-// Every tet gathers its 144 cotangents: for meshes of few bricks (below), which
-// would leave most of the chip idle.  Workgroups of one wave, so that the waves
-// are spread over the compute units: 16.4 us at 48,000 tets, 22.6 at 82,944,
-// where workgroups of four took 17.2 and 26.2.
-constexpr int kDirect = 64;
-__global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int32_t* __restrict__ order,
-                                                            int32_t n_chunks, const double* __restrict__ gA,
-                                                            double* __restrict__ g_logE,
-                                                            double* __restrict__ xbar)
+// dL/dlogE of the tet and its vertices' xbar from its sums.
+__device__ __forceinline__ void store_tet(const DevView& v, const TetSums& s, const Geo& G, double* g_logE,
+                                          double* xbar, const int* pos)
 {
-    // each XCD takes one contiguous share of the chunk order, chunks that are
-    // near in space: neighbouring tets share node blocks, so their cotangent
-    // rows stay in one L2
-    constexpr int kPer = kDirect / kAdjointChunk;
-    const int slot = xcd_remap(blockIdx.x, gridDim.x) * kPer + threadIdx.x / kAdjointChunk;
-    if (slot >= n_chunks)
-        return;
-    const int e = order[slot] * kAdjointChunk + (threadIdx.x % kAdjointChunk);
-    if (e >= v.n_tets)
-        return;
-    const int* pos = v.e2p + 10 * (size_t)e;
-    if (!v.mask[e]) {
-        g_logE[e] = 0.0;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            double* dst = xbar + 3 * (size_t)pos[a];
-            dst[0] = 0.0;
-            dst[1] = 0.0;
-            dst[2] = 0.0;
-        }
-        return;
-    }
-    const int4 t = v.T[e];
-    const int id[4] = {t.x, t.y, t.z, t.w};
-    const int* eb = v.e2b + 10 * (size_t)e;
-    Geo G;
-    geometry(v, t, G);
-    const double E = v.E[e];
-    const double lam_dt = (E * v.mat.clam) * v.mat.cdt;  // lambda dt^2
-    const double mu_dt = (E * v.mat.cmu) * v.mat.cdt;    // mu dt^2
-    const double lamV = lam_dt * G.V, muV = mu_dt * G.V;
-
-    double Plam = 0.0, Pmu = 0.0, Pm = 0.0;
-    double gbar[4][3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            gbar[a][i] = 0.0;
-
-    // pairs (a, b) with a <= b; B_ab = Abar_ab + Abar_ba^T, B_ba = B_ab^T
-    constexpr int PA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2};
-    constexpr int PB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
-#pragma unroll
-    for (int q = 0; q < 10; ++q) {
-        const int a = PA[q], b = PB[q];
-        double Aab[3][3], Aba[3][3];
-        gather_block(v, gA, id, a, b, eb[q], Aab);
-        if (a == b) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    Aba[i][j] = Aab[i][j];
-        } else {
-            gather_block(v, gA, id, b, a, eb[q], Aba);
-        }
-        // P terms over (a,b) and, for a != b, (b,a)
-        const double* ga = G.g[a];
-        const double* gb = G.g[b];
-        const double sab = (ga[0] * gb[0] + ga[1] * gb[1]) + ga[2] * gb[2];
-        double t_ab = 0.0, t_ba = 0.0, plam = 0.0, pmu = 0.0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                plam += ga[i] * Aab[i][j] * gb[j];
-                pmu += gb[i] * Aab[i][j] * ga[j];
-                if (a != b) {
-                    plam += gb[i] * Aba[i][j] * ga[j];
-                    pmu += ga[i] * Aba[i][j] * gb[j];
-                }
-            }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            t_ab += Aab[i][i];
-            t_ba += Aba[i][i];
-        }
-        if (a == b) {
-            Plam += plam;
-            Pmu += pmu + t_ab * sab;
-            Pm += t_ab;
-        } else {
-            Plam += plam;
-            Pmu += pmu + (t_ab + t_ba) * sab;
-        }
-        // gbar: B_ab = Aab + Aba^T drives gbar_a (with g_b); B_ba = B_ab^T drives gbar_b (with g_a)
-        double B[3][3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j)
-                B[i][j] = Aab[i][j] + Aba[j][i];
-        const double trB = (B[0][0] + B[1][1]) + B[2][2];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            double ua = 0.0, ub = 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                ua += (lamV * B[i][j] + muV * B[j][i]) * gb[j];
-                if (a != b)
-                    ub += (lamV * B[j][i] + muV * B[i][j]) * ga[j];
-            }
-            gbar[a][i] += ua + muV * trB * gb[i];
-            if (a != b)
-                gbar[b][i] += ub + muV * trB * ga[i];
-        }
-    }
-    g_logE[e] = lamV * Plam + muV * Pmu;
-
-    const double Vbar = lam_dt * Plam + mu_dt * Pmu + 0.25 * v.mat.rho * Pm;
+    *g_logE = G.V * s.P;
+    const double Vbar = s.P + 0.25 * v.mat.rho * s.Pm;
     const double detbar = Vbar * (G.det < 0.0 ? -1.0 : 1.0) / 6.0;
     // Gbar columns k = 1..3: gbar_k - gbar_0 ; G columns g_k
     double Gm[3][3], Gb[3][3];  // [row i][col k-1]
@@ -231,7 +130,7 @@ __global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             Gm[i][k] = G.g[k + 1][i];
-            Gb[i][k] = gbar[k + 1][i] - gbar[0][i];
+            Gb[i][k] = G.V * s.u[k + 1][i] - G.V * s.u[0][i];
         }
     // Dbar = -G Gbar^T G + detbar det G
     double T1[3][3];  // Gbar^T G
@@ -264,11 +163,85 @@ __global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int
     }
 }
 
-// Everything above depends on the cotangents through B_ab = Abar_ab + Abar_ba^T
-// alone: P_lam = sum_{a<b} g_a^T B_ab g_b + 1/2 sum_a g_a^T B_aa g_a,
-// P_mu = sum_{a<b} (g_b^T B_ab g_a + tr(B_ab) g_a.g_b) + 1/2 sum_a (...),
-// P_m = 1/2 sum_a tr(B_aa).  A brick of kAdjointBrick tets that are near in space
-// (kBrickChunks chunks of the Morton order) shares most of its blocks: 128
+// Zeros of an inactive tet.
+__device__ __forceinline__ void store_inactive(double* g_logE, double* xbar, const int* pos)
+{
+    *g_logE = 0.0;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        double* dst = xbar + 3 * (size_t)pos[a];
+        dst[0] = 0.0;
+        dst[1] = 0.0;
+        dst[2] = 0.0;
+    }
+}
+
+// The tet's sums from its 144 cotangents.
+__device__ __forceinline__ void gather_sums(TetSums& s, const DevView& v, const double* __restrict__ gA, int e, int4 T,
+                                            const Geo& G, double lam_dt, double mu_dt)
+{
+    const int id[4] = {T.x, T.y, T.z, T.w};
+    const int* eb = v.e2b + 10 * (size_t)e;
+#pragma unroll
+    for (int q = 0; q < 10; ++q) {
+        // Abar_ab stands in the upper copy if vertex a is the smaller node, in the mirror otherwise
+        const BlockDesc d = v.desc[eb[q]];
+        const int a = kSlotA[q], b = kSlotB[q];
+        const bool swap = id[a] > id[b];
+        const int pa = swap ? d.lo : d.up, la = swap ? d.rlj : d.rl, pb = swap ? d.up : d.lo, lb = swap ? d.rl : d.rlj;
+        double Aab[3][3], Aba[3][3], B[3][3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                Aab[i][j] = gA[pa + i * la + j];
+                Aba[i][j] = a == b ? Aab[i][j] : gA[pb + i * lb + j];
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                B[i][j] = Aab[i][j] + Aba[j][i];
+        add_block(s, G, a, b, B, lam_dt, mu_dt);
+    }
+}
+
+// Every tet gathers its 144 cotangents: for meshes of few bricks (below), which
+// would leave most of the chip idle.  Workgroups of one wave, so that the waves
+// are spread over the compute units: 16.4 us at 48,000 tets, 22.6 at 82,944,
+// where workgroups of four took 17.2 and 26.2.
+constexpr int kDirect = 64;
+__global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int32_t* __restrict__ order,
+                                                            int32_t n_chunks, const double* __restrict__ gA,
+                                                            double* __restrict__ g_logE,
+                                                            double* __restrict__ xbar)
+{
+    // each XCD takes one contiguous share of the chunk order, chunks that are
+    // near in space: neighbouring tets share node blocks, so their cotangent
+    // rows stay in one L2
+    constexpr int kPer = kDirect / kAdjointChunk;
+    const int slot = xcd_remap(blockIdx.x, gridDim.x) * kPer + threadIdx.x / kAdjointChunk;
+    if (slot >= n_chunks)
+        return;
+    const int e = order[slot] * kAdjointChunk + (threadIdx.x % kAdjointChunk);
+    if (e >= v.n_tets)
+        return;
+    const int* pos = v.e2p + 10 * (size_t)e;
+    if (!v.mask[e]) {
+        store_inactive(g_logE + e, xbar, pos);
+        return;
+    }
+    const int4 t = v.T[e];
+    Geo G;
+    geometry(v, t, G);
+    const double E = v.E[e];
+    TetSums s;
+    gather_sums(s, v, gA, e, t, G, (E * v.mat.clam) * v.mat.cdt, (E * v.mat.cmu) * v.mat.cdt);
+    store_tet(v, s, G, g_logE + e, xbar, pos);
+}
+
+// A brick of kAdjointBrick tets that are near in space (kBrickChunks chunks of
+// the Morton order) shares most of its blocks: 128
 // tets name 1,280 blocks, about 330 of them different.  So the brick's
 // different blocks are formed once, in LDS, and each tet reads its ten from
 // there.
@@ -414,8 +387,7 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const
     const int id[4] = {T.x, T.y, T.z, T.w};
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
-        constexpr int A[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2}, B[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
-        const unsigned swap = id[A[q]] > id[B[q]] ? 1u << 15 : 0u;
+        const unsigned swap = id[kSlotA[q]] > id[kSlotB[q]] ? 1u << 15 : 0u;
         plan.refs[((size_t)brick * 10 + q) * kAdjointBrick + t] =
             e >= 0 ? (uint16_t)(s_rank[s_at[slot[q]]] | swap) : (uint16_t)0;
     }
@@ -515,108 +487,22 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_element(DevView v, co
     if (e < 0)
         return;
     if (!active) {
-        g_logE[e] = 0.0;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            double* dst = xbar + 3 * (size_t)pos[a];
-            dst[0] = 0.0;
-            dst[1] = 0.0;
-            dst[2] = 0.0;
-        }
+        store_inactive(g_logE + e, xbar, pos);
         return;
     }
     const double lam_dt = (E * v.mat.clam) * v.mat.cdt;  // lambda dt^2
     const double mu_dt = (E * v.mat.cmu) * v.mat.cdt;    // mu dt^2
-    const double lamV = lam_dt * G.V, muV = mu_dt * G.V;
-
-    // gbar_a = lamV U_a + muV W_a, U_a = sum_b B_ab g_b, W_a = sum_b (B_ab^T + tr(B_ab) I) g_b
-    double Plam = 0.0, Pmu = 0.0, Pm = 0.0;
-    double U[4][3] = {}, W[4][3] = {};
+    TetSums s;
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
-        constexpr int PA[10] = {0, 1, 2, 3, 0, 0, 0, 1, 1, 2}, PB[10] = {0, 1, 2, 3, 1, 2, 3, 2, 3, 3};
-        const int a = PA[q], b = PB[q];
         const double* r = s_blocks + 9 * (ref[q] & 0x7fffu);
         const int x = ref[q] >> 15 ? 2 : 0;  // transposed: entries 1 3, 2 6 and 5 7 change places
         const double B[3][3] = {{r[0], r[1 + x], r[2 + 2 * x]},
                                 {r[3 - x], r[4], r[5 + x]},
                                 {r[6 - 2 * x], r[7 - x], r[8]}};
-        const double* ga = G.g[a];
-        const double* gb = G.g[b];
-        const double tr = (B[0][0] + B[1][1]) + B[2][2];
-        const double sab = (ga[0] * gb[0] + ga[1] * gb[1]) + ga[2] * gb[2];
-        double Bg[3], Btg[3];  // B g_b, B^T g_b
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            Bg[i] = (B[i][0] * gb[0] + B[i][1] * gb[1]) + B[i][2] * gb[2];
-            Btg[i] = (B[0][i] * gb[0] + B[1][i] * gb[1]) + B[2][i] * gb[2];
-            U[a][i] += Bg[i];
-            W[a][i] += Btg[i] + tr * gb[i];
-        }
-        const double plam = (ga[0] * Bg[0] + ga[1] * Bg[1]) + ga[2] * Bg[2];
-        const double pmu = ((ga[0] * Btg[0] + ga[1] * Btg[1]) + ga[2] * Btg[2]) + tr * sab;
-        if (a == b) {
-            Plam += 0.5 * plam;
-            Pmu += 0.5 * pmu;
-            Pm += 0.5 * tr;
-        } else {
-            Plam += plam;
-            Pmu += pmu;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {  // B_ba = B_ab^T
-                U[b][i] += (B[0][i] * ga[0] + B[1][i] * ga[1]) + B[2][i] * ga[2];
-                W[b][i] += ((B[i][0] * ga[0] + B[i][1] * ga[1]) + B[i][2] * ga[2]) + tr * ga[i];
-            }
-        }
+        add_block(s, G, kSlotA[q], kSlotB[q], B, lam_dt, mu_dt);
     }
-    g_logE[e] = lamV * Plam + muV * Pmu;
-    double gbar[4][3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            gbar[a][i] = lamV * U[a][i] + muV * W[a][i];
-
-    const double Vbar = lam_dt * Plam + mu_dt * Pmu + 0.25 * v.mat.rho * Pm;
-    const double detbar = Vbar * (G.det < 0.0 ? -1.0 : 1.0) / 6.0;
-    // Gbar columns k = 1..3: gbar_k - gbar_0 ; G columns g_k
-    double Gm[3][3], Gb[3][3];  // [row i][col k-1]
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            Gm[i][k] = G.g[k + 1][i];
-            Gb[i][k] = gbar[k + 1][i] - gbar[0][i];
-        }
-    // Dbar = -G Gbar^T G + detbar det G
-    double T1[3][3];  // Gbar^T G
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            T1[i][j] = (Gb[0][i] * Gm[0][j] + Gb[1][i] * Gm[1][j]) + Gb[2][i] * Gm[2][j];
-    double Db[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-            Db[i][j] = -((Gm[i][0] * T1[0][j] + Gm[i][1] * T1[1][j]) + Gm[i][2] * T1[2][j]) +
-                       detbar * G.det * Gm[i][j];
-    double xb[4][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        xb[1][i] = Db[i][0];
-        xb[2][i] = Db[i][1];
-        xb[3][i] = Db[i][2];
-        xb[0][i] = -((Db[i][0] + Db[i][1]) + Db[i][2]);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        double* dst = xbar + 3 * (size_t)pos[a];
-        dst[0] = xb[a][0];
-        dst[1] = xb[a][1];
-        dst[2] = xb[a][2];
-    }
+    store_tet(v, s, G, g_logE + e, xbar, pos);
 }
 
 // dL/dx of node i, component c: its diagonal segment's xbar in ascending tet id.
