@@ -208,7 +208,7 @@ __device__ __forceinline__ void gather_sums(TetSums& s, const DevView& v, const 
 
 // Every tet gathers its 144 cotangents: for meshes of few bricks (below), which
 // would leave most of the chip idle.  Workgroups of one wave, so that the waves
-// are spread over the compute units: 16.4 us at 48,000 tets, 22.6 at 82,944,
+// are spread over the compute units: 16.1 us at 48,000 tets, 23.5 at 82,944,
 // where workgroups of four took 17.2 and 26.2.
 constexpr int kDirect = 64;
 __global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int32_t* __restrict__ order,
@@ -252,26 +252,27 @@ __global__ __launch_bounds__(kDirect) void k_adjoint_direct(DevView v, const int
 // kind), the blocks numbered in ascending id; and per tet slot ten references,
 // block number | transpose << 15.  (Two lists, upper copies and mirrors, read
 // every line of the rows twice: 78 instead of 72 us a call.)
-constexpr int kBrickChunks = kAdjointBrick / kAdjointChunk;
 constexpr int kBrickBlocks = 10 * kAdjointBrick, kBrickReads = 2 * kBrickBlocks;  // most a brick can have
 // Fewer bricks (4 a compute unit) and every tet gathers for itself: the whole
-// adjoint, gathered / by bricks, 11.7 / 15.0 us at 1,296 tets, 16.4 / 21.0 at
-// 48,000, 27.5 / 28.6 at 105,456, 35.0 / 33.8 at 131,712, 56.4 / 52.4 at 235,824.
+// adjoint, gathered / by bricks, 12.0 / 15.6 us at 1,296 tets, 16.1 / 21.8 at
+// 48,000, 28.3 / 31.5 at 105,456, 35.1 / 34.7 at 131,712, 39.6 / 42.4 at 162,000,
+// 56.3 / 53.8 at 235,824 (this depends on how the cells' rows fall into chunks).
 constexpr int kMinBricks = 1024;
+// Fewer active tets of a brick gather for themselves (in a refinement superset
+// most candidates are inactive): 384,000 tets of which 5, 10, 25, 50 per cent are
+// active, at random, by bricks 60 us each, gathered 46, 47, 55, 67.
+constexpr int kFewActive = 40;
 constexpr int kBrickTable = 4096;  // hash slots while a brick's blocks are found
 constexpr int kEntryWords = 3;
 constexpr int kMirror = 1 << 15, kDiagonal = 1 << 14;
 static_assert(kBrickBlocks < kBrickTable && kBrickBlocks < kDiagonal, "every block finds a place and a number");
 
 // Tet of slot t of a brick, or -1.
-__device__ __forceinline__ int brick_tet(const DevView& v, const int32_t* __restrict__ order, int n_chunks, int brick,
-                                         int t)
+__device__ __forceinline__ int brick_tet(const DevView& v, const int32_t* __restrict__ order, int brick, int t)
 {
-    const int c = brick * kBrickChunks + t / kAdjointChunk;
-    if (c >= n_chunks)
-        return -1;
-    const int e = order[c] * kAdjointChunk + t % kAdjointChunk;
-    return e < v.n_tets ? e : -1;
+    const int c = order[brick * kBrickChunks + t / kAdjointChunk];
+    const int e = c * kAdjointChunk + t % kAdjointChunk;
+    return c >= 0 && e < v.n_tets ? e : -1;
 }
 
 // Ranks of kMine values per thread among the n different values of list.
@@ -290,11 +291,11 @@ __device__ __forceinline__ void rank_among(const int* list, int n, const int (&v
 }
 
 // Plan of one brick per workgroup.  fill = false: only how many row blocks it
-// reads, into starts, and how many blocks it has, into refs (as a word); true:
-// its entries, starts being the running sum by then, and its references.
+// reads, into starts, and how many blocks it has, into entries; true: its
+// entries, starts being the running sum by then, and its references.
 template <bool kFill>
 __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const int32_t* __restrict__ order,
-                                                                int32_t n_chunks, AdjointPlan plan)
+                                                                AdjointPlan plan)
 {
     __shared__ int s_key[kBrickTable];      // block of each hash slot, -1: free
     __shared__ uint16_t s_at[kBrickTable];  // its place in s_list
@@ -308,7 +309,7 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const
     if (t == 0)
         s_n = s_m = 0;
     __syncthreads();
-    const int e = brick_tet(v, order, n_chunks, brick, t);
+    const int e = brick_tet(v, order, brick, t);
     int slot[10];
 #pragma unroll
     for (int q = 0; q < 10; ++q) {
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const
     if (!kFill) {
         if (t == 0) {
             plan.starts[brick] = m;
-            *reinterpret_cast<int32_t*>(plan.refs + (size_t)brick * 10 * kAdjointBrick) = n;
+            plan.entries[brick] = n;
         }
         return;
     }
@@ -401,15 +402,16 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_plan(DevView v, const
 // 144 cotangents), the whole adjoint 72 (97).  Bricks of 64 tets, 8 rounds in
 // flight, whole rows per lane and atomic adds in LDS measured 71 to 82.
 __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_element(DevView v, const int32_t* __restrict__ order,
-                                                                   int32_t n_chunks, AdjointPlan plan,
+                                                                   AdjointPlan plan,
                                                                    const double* __restrict__ gA,
                                                                    double* __restrict__ g_logE,
                                                                    double* __restrict__ xbar)
 {
     extern __shared__ double s_blocks[];
+    __shared__ int s_active[kAdjointBrick / 64];
     // each XCD takes one contiguous share of the bricks: neighbouring bricks share rows in its L2
     const int brick = xcd_remap(blockIdx.x, gridDim.x), t = threadIdx.x;
-    const int e = brick_tet(v, order, n_chunks, brick, t);
+    const int e = brick_tet(v, order, brick, t);
     const int start = plan.starts[brick], m = plan.starts[brick + 1] - start;
     const int32_t* __restrict__ entries = plan.entries + (size_t)kEntryWords * start;
     // the tet's own data, in flight while the blocks are formed
@@ -432,22 +434,23 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_element(DevView v, co
     constexpr int kWaveBlocks = 21, kRound = kAdjointBrick / 64 * kWaveBlocks, kAhead = 15, kBatch = kAhead * kRound;
     const int j = (t & 63) % 3, first = (t & 63) < 63 ? (t >> 6) * kWaveBlocks + (t & 63) / 3 : 1 << 20;
     double x[kAhead][3];
-    int what[kAhead];
-    auto load_rows = [&](int b0) {
-        int pos[kAhead], rl[kAhead];
+    int what[kAhead], at[kAhead], rl[kAhead];
+    auto load_entries = [&](int b0) {
 #pragma unroll
         for (int w = 0; w < kAhead; ++w) {
             const int k = b0 + first + w * kRound;
             const int32_t* o = entries + kEntryWords * min(k, m - 1);
-            pos[w] = o[0];
+            at[w] = o[0];
             rl[w] = o[1];
             what[w] = o[2] | ((m - 1 - k) >> 31);  // -1 past the end
         }
+    };
+    auto load_rows = [&]() {
 #pragma unroll
         for (int w = 0; w < kAhead; ++w)
 #pragma unroll
             for (int i = 0; i < 3; ++i)
-                x[w][i] = gA[pos[w] + i * rl[w] + j];
+                x[w][i] = gA[at[w] + i * rl[w] + j];
     };
     auto store_uppers = [&]() {
 #pragma unroll
@@ -469,16 +472,38 @@ __global__ __launch_bounds__(kAdjointBrick) void k_adjoint_element(DevView v, co
                     dst[i] = dst[i] + x[w][i];
             }
     };
+    load_entries(0);
+    // few active tets gather for themselves
+    const int mine = __popcll(__ballot(e >= 0 && active));
+    if ((t & 63) == 0)
+        s_active[t >> 6] = mine;
+    __syncthreads();
+    if (s_active[0] + s_active[1] < kFewActive) {
+        if (e >= 0 && active) {
+            Geo G;
+            geometry(v, T, G);
+            TetSums s;
+            gather_sums(s, v, gA, e, T, G, (E * v.mat.clam) * v.mat.cdt, (E * v.mat.cmu) * v.mat.cdt);
+            store_tet(v, s, G, g_logE + e, xbar, pos);
+        } else if (e >= 0) {
+            store_inactive(g_logE + e, xbar, pos);
+        }
+        return;
+    }
     for (int b0 = kBatch; b0 < m; b0 += kBatch) {  // rows past the first batch are read twice
-        load_rows(b0);
+        load_entries(b0);
+        load_rows();
         store_uppers();
     }
-    load_rows(0);
+    if (m > kBatch)
+        load_entries(0);
+    load_rows();
     store_uppers();
     __syncthreads();
     add_mirrors();
     for (int b0 = kBatch; b0 < m; b0 += kBatch) {
-        load_rows(b0);
+        load_entries(b0);
+        load_rows();
         add_mirrors();
     }
     Geo G;
@@ -558,28 +583,26 @@ int adjoint_bricks(int n_chunks)
     return bricks < kMinBricks ? 0 : bricks;
 }
 
-hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
-                               bool fill, hipStream_t s)
+hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, const AdjointPlan& plan, bool fill, hipStream_t s)
 {
-    if (n_chunks == 0)
+    if (plan.bricks == 0)
         return hipSuccess;
-    const dim3 grid(adjoint_bricks(n_chunks));
     if (fill)
-        hipLaunchKernelGGL(k_adjoint_plan<true>, grid, dim3(kAdjointBrick), 0, s, v, order, n_chunks, plan);
+        hipLaunchKernelGGL(k_adjoint_plan<true>, dim3(plan.bricks), dim3(kAdjointBrick), 0, s, v, order, plan);
     else
-        hipLaunchKernelGGL(k_adjoint_plan<false>, grid, dim3(kAdjointBrick), 0, s, v, order, n_chunks, plan);
+        hipLaunchKernelGGL(k_adjoint_plan<false>, dim3(plan.bricks), dim3(kAdjointBrick), 0, s, v, order, plan);
     return hipGetLastError();
 }
 
 hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
                           const double* gA, double* g_logE, double* g_x, double* xbar, hipStream_t s)
 {
-    if (v.n_tets > 0 && !plan.entries)
+    if (v.n_tets > 0 && plan.bricks == 0)
         hipLaunchKernelGGL(k_adjoint_direct, dim3((n_chunks * kAdjointChunk + kDirect - 1) / kDirect), dim3(kDirect), 0, s,
                            v, order, n_chunks, gA, g_logE, xbar);
     else if (v.n_tets > 0)
-        hipLaunchKernelGGL(k_adjoint_element, dim3(adjoint_bricks(n_chunks)), dim3(kAdjointBrick),
-                           9 * sizeof(double) * plan.most, s, v, order, n_chunks, plan, gA, g_logE, xbar);
+        hipLaunchKernelGGL(k_adjoint_element, dim3(plan.bricks), dim3(kAdjointBrick), 9 * sizeof(double) * plan.most, s,
+                           v, order, plan, gA, g_logE, xbar);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || v.n_nodes == 0)
         return e;

@@ -384,10 +384,10 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     TetRecord* trec = nullptr;
     ALLOC(trec, n_tets);
     const int64_t n_chunks = (n_tets + kAdjointChunk - 1) / kAdjointChunk;
-    ALLOC(c->adj_order, n_chunks);
-    const int64_t bricks = adjoint_bricks((int)n_chunks);
-    ALLOC(c->adj_plan.refs, bricks * 10 * kAdjointBrick);
-    ALLOC(c->adj_plan.starts, bricks + 1);
+    // a brick has one chunk at least: room for as many bricks as chunks while they are found
+    const bool bricks = adjoint_bricks((int)n_chunks) > 0;
+    ALLOC(c->adj_order, bricks ? n_chunks * kBrickChunks : n_chunks);
+    ALLOC(c->adj_plan.starts, bricks ? n_chunks + 1 : 0);
 #undef ALLOC
     if (e != hipSuccess) {
         free_all(c);
@@ -427,7 +427,9 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     if (e == hipSuccess) e = upload(e2b, he2b.data(), he2b.size(), s);
     if (e == hipSuccess) e = upload(e2p, P.e2p.data(), P.e2p.size(), s);
     if (e == hipSuccess) e = upload(c->dinc, P.dinc.data(), P.dinc.size(), s);
-    const std::vector<int32_t> order = adjoint_chunk_order(x, hT, node_off, tet_off);
+    std::vector<int32_t> order = adjoint_chunk_order(x, hT, node_off, tet_off);
+    if (bricks)
+        order.resize((size_t)adjoint_bricks((int)n_chunks) * kBrickChunks, -1);
     if (e == hipSuccess) e = upload(c->adj_order, order.data(), order.size(), s);
     c->adj_chunks = (int32_t)n_chunks;
     if (e == hipSuccess) e = upload(di, R.di.data(), R.di.size(), s);
@@ -485,28 +487,40 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.wg_err = wg_err;
     v.ctl = ctl;
 
-    // the adjoint's bricks: count, running sums, fill
-    if (e == hipSuccess && bricks > 0) {
-        e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, false, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        std::vector<int32_t> starts((size_t)bricks + 1), blocks((size_t)bricks);
-        if (e == hipSuccess)
-            e = hipMemcpy(starts.data(), c->adj_plan.starts, sizeof(int32_t) * bricks, hipMemcpyDeviceToHost);
-        if (e == hipSuccess)
-            e = hipMemcpy2D(blocks.data(), sizeof(int32_t), c->adj_plan.refs, 20 * kAdjointBrick, sizeof(int32_t),
-                            (size_t)bricks, hipMemcpyDeviceToHost);
+    // the adjoint's bricks: count, halve those that are too large, running sums, fill
+    if (e == hipSuccess && bricks) {
+        AdjointPlan& plan = c->adj_plan;
+        int32_t* blocks_d = nullptr;
+        e = hipMalloc((void**)&blocks_d, sizeof(int32_t) * n_chunks);
+        std::vector<int32_t> starts, blocks;
+        do {
+            plan.bricks = (int32_t)(order.size() / kBrickChunks);
+            starts.resize((size_t)plan.bricks + 1);
+            blocks.resize((size_t)plan.bricks);
+            if (e == hipSuccess) e = hipMemcpy(c->adj_order, order.data(), sizeof(int32_t) * order.size(), hipMemcpyHostToDevice);
+            plan.entries = blocks_d;
+            if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, plan, false, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e == hipSuccess)
+                e = hipMemcpy(starts.data(), plan.starts, sizeof(int32_t) * plan.bricks, hipMemcpyDeviceToHost);
+            if (e == hipSuccess)
+                e = hipMemcpy(blocks.data(), blocks_d, sizeof(int32_t) * plan.bricks, hipMemcpyDeviceToHost);
+        } while (e == hipSuccess && halve_large_bricks(order, blocks));
+        plan.entries = nullptr;
+        (void)hipFree(blocks_d);
         int32_t sum = 0;  // at most 16 per tet slot: a tet reads 4 + 2 * 6 row blocks
-        for (int64_t k = 0; k < bricks; ++k) {
+        for (int32_t k = 0; e == hipSuccess && k < plan.bricks; ++k) {
             const int32_t m = starts[k];
             starts[k] = sum;
             sum += m;
-            c->adj_plan.most = std::max(c->adj_plan.most, blocks[k]);
+            plan.most = std::max(plan.most, blocks[k]);
         }
-        starts[bricks] = sum;
-        if (e == hipSuccess) e = dalloc(c, &c->adj_plan.entries, (size_t)3 * sum);
+        starts[plan.bricks] = sum;
+        if (e == hipSuccess) e = dalloc(c, &plan.entries, (size_t)3 * sum);
+        if (e == hipSuccess) e = dalloc(c, &plan.refs, (size_t)plan.bricks * 10 * kAdjointBrick);
         if (e == hipSuccess)
-            e = hipMemcpy(c->adj_plan.starts, starts.data(), sizeof(int32_t) * (bricks + 1), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, c->adj_chunks, c->adj_plan, true, s);
+            e = hipMemcpy(plan.starts, starts.data(), sizeof(int32_t) * starts.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = launch_adjoint_plan(v, c->adj_order, plan, true, s);
     }
     if (e == hipSuccess) e = launch_geometry(v, s);
     if (e == hipSuccess) e = launch_rows(v, false, s);

@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "adjoint_plan.h"
 #include "stafem.h"
 #include <hip/hip_ext.h>
 
@@ -248,11 +249,11 @@ struct DevView {
 // The adjoint's bricks (adjoint.hip): three words for each row block that each
 // reads, where each brick's begin (one past the last at the end), and 10
 // references per tet slot.
-constexpr int kAdjointChunk = 16, kAdjointBrick = 128;
 struct AdjointPlan {
     int32_t* entries = nullptr;
     int32_t* starts = nullptr;
     uint16_t* refs = nullptr;
+    int32_t bricks = 0;
     int32_t most = 0;  // blocks of the brick that has most
 };
 
@@ -310,7 +311,8 @@ struct sta_ctx {
     sta::CgScalars* cg_s = nullptr;
     sta::CgScalars* cg_host = nullptr;  // pinned
     double* adj_xbar = nullptr;     // 3 doubles per diagonal incidence
-    int32_t* adj_order = nullptr;   // adjoint visiting order of the kAdjointChunk-tet chunks
+    int32_t* adj_order = nullptr;   // adjoint visiting order of the kAdjointChunk-tet chunks, brick by brick
+                                    // where there are bricks (-1: none)
     int32_t adj_chunks = 0;
     sta::AdjointPlan adj_plan;
     int32_t* dinc = nullptr;        // per diagonal incidence: its tet (segments in ascending tet id)
@@ -405,12 +407,12 @@ hipError_t launch_set_params(const DevView& v, const double* x_aos, const double
 // The adjoint visits the tets in chunks of kAdjointChunk consecutive ids, in
 // an order fixed at context build (each mesh's chunks by the Morton code of
 // their centroid), bricks of kAdjointBrick tets at a time.  Any order gives
-// the same bits.  The plan is found on the device at context build.
-// fill = false: the bricks' numbers of row blocks into starts, and of blocks as
-// the first word of each brick's references; then, with starts their running
-// sum and entries allocated, fill = true.
-hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
-                               bool fill, hipStream_t s);
+// the same bits, and so does either of its two kernels.  The plan is found on
+// the device at context build.
+// fill = false: the bricks' numbers of row blocks into starts, and of blocks into
+// entries; then, with starts their running sum, entries and refs allocated, fill
+// = true.
+hipError_t launch_adjoint_plan(const DevView& v, const int32_t* order, const AdjointPlan& plan, bool fill, hipStream_t s);
 int adjoint_bricks(int n_chunks);
 hipError_t launch_adjoint(const DevView& v, const int32_t* order, int32_t n_chunks, const AdjointPlan& plan,
                           const double* gA, double* g_logE, double* g_x, double* xbar, hipStream_t s);
