@@ -10,7 +10,8 @@
 // integer atomics and stays exactly equal to a rebuild, whatever order the
 // atomics land in.
 //
-// A frame of up to kOnceMax edits is one launch: every changed tet's six edges
+// A frame of up to kOnceMax edits is one launch, on a mesh whose vertices and
+// edges have few tets (frame_rules.h): every changed tet's six edges
 // are counted again over their incidence, and its four vertices' active edges
 // over the tets around them, with the frame's own edits taken from a table
 // (k_proxy_once).  Integers again, so the state is the same.
@@ -31,6 +32,7 @@
 #include <vector>
 
 #include "edit_table.h"
+#include "frame_rules.h"
 #include "sta_internal.h"
 
 struct ProxyCtl {
@@ -73,6 +75,7 @@ struct ProxyView {
 struct sta_proxy {
     int device = 0;
     int64_t n_nodes = 0, n_tets = 0, n_edges = 0, nnz = 0;
+    bool once = true;  // frames of one launch (of up to kOnceMax edits)
     ProxyView v{};
     int32_t* colidx = nullptr;
     std::vector<void*> owned;
@@ -575,12 +578,12 @@ hipError_t launch_rebuild(const ProxyView& v, hipStream_t s)
     return e;
 }
 
-hipError_t launch_frame(const ProxyView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
+hipError_t launch_frame(const ProxyView& v, bool once, const int32_t* ids, const uint8_t* states, int32_t n_host,
                         const int32_t* n_dev, hipStream_t s)
 {
     const int log2 = table_log2(n_host);
 #define ONCE(E, S)                                                                                            \
-    if (n_host <= 128 * E * S) {                                                                              \
+    if (once && n_host <= 128 * E * S) {                                                                      \
         hipLaunchKernelGGL((k_proxy_once<E, S>), dim3(n_host > 0 ? (n_host + E - 1) / E : 1), dim3(128 * E),  \
                            table_bytes(log2, 128 * E, S), s, v, ids, states, n_host, n_dev, log2);            \
         return hipGetLastError();                                                                             \
@@ -648,9 +651,16 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
         epos[2 * b] = P.ometa[4 * b + 0];
         epos[2 * b + 1] = P.ometa[4 * b + 2];
     }
+    int64_t rounds = 0;
     for (int64_t u = 0; u < n_nodes; ++u)
-        if (P.ndiag[u] >= 0)
-            ndpos[u] = P.dmeta[2 * (size_t)P.ndiag[u]];
+        if (P.ndiag[u] >= 0) {
+            const size_t d = (size_t)P.ndiag[u];
+            ndpos[u] = P.dmeta[2 * d];
+            rounds = std::max(rounds, proxy_vertex_rounds(P.dseg[d + 1] - P.dseg[d], P.dmeta[2 * d + 1]));
+        }
+    for (int64_t b = 0; b < P.no; ++b)
+        rounds = std::max(rounds, proxy_edge_rounds(P.oseg[b + 1] - P.oseg[b]));
+    p->once = rounds <= kProxyOnceRounds;
     ProxyView& v = p->v;
     v.n_nodes = (int32_t)n_nodes;
     v.n_tets = (int32_t)n_tets;
@@ -758,7 +768,7 @@ extern "C" sta_status sta_proxy_apply_edits(sta_proxy* p, const int32_t* ids_dev
     if (n_edits > 0 && (!ids_dev || !states_dev))
         return pfail(p, STA_EINVAL, "NULL edit arrays");
     const hipError_t e =
-        launch_frame(p->v, ids_dev, states_dev, (int32_t)n_edits, nullptr, static_cast<hipStream_t>(stream));
+        launch_frame(p->v, p->once, ids_dev, states_dev, (int32_t)n_edits, nullptr, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? STA_OK : pfail(p, STA_EHIP, std::string("proxy frame: ") + hipGetErrorString(e));
 }
 
@@ -770,7 +780,7 @@ extern "C" sta_status sta_proxy_apply_edits_dev(sta_proxy* p, const int32_t* ids
     if (capacity < 1 || capacity > p->n_tets || !ids_dev || !states_dev || !n_dev)
         return pfail(p, STA_EINVAL, "capacity must be in [1, n_tets] and the device arrays non-NULL");
     const hipError_t e =
-        launch_frame(p->v, ids_dev, states_dev, (int32_t)capacity, n_dev, static_cast<hipStream_t>(stream));
+        launch_frame(p->v, p->once, ids_dev, states_dev, (int32_t)capacity, n_dev, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? STA_OK : pfail(p, STA_EHIP, std::string("proxy frame: ") + hipGetErrorString(e));
 }
 

@@ -1,0 +1,62 @@
+"""Meshes with vertices and edges of very many tets: the state is the oracle's, and a frame
+does not take a time that grows with the square of what is around it."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_11673_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def S():
+    from paper_2605_11673_amd import stafem
+    return stafem
+
+
+def cone(n):
+    """2 n^2 tets from the triangles of a square to one apex."""
+    i, j = np.meshgrid(np.arange(n + 1), np.arange(n + 1), indexing="ij")
+    x = np.concatenate([np.stack([0 * i, i / n, j / n], -1).reshape(-1, 3), [[1.0, 0.4, 0.6]]])
+    ids = np.arange((n + 1) ** 2).reshape(n + 1, n + 1)
+    tri = np.concatenate([np.stack([ids[:-1, :-1], ids[1:, :-1], ids[1:, 1:]], -1).reshape(-1, 3),
+                          np.stack([ids[:-1, :-1], ids[:-1, 1:], ids[1:, 1:]], -1).reshape(-1, 3)])
+    tets = np.concatenate([np.full((len(tri), 1), (n + 1) ** 2), tri], 1).astype(np.int32)
+    return W.Workload("cone", x, tets, W.lognormal_E(len(tets), np.random.default_rng(n)),
+                      np.ones(len(tets), np.uint8))
+
+
+def seconds(f, reps=5):
+    best = np.inf
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("n", [4, 7, 50])
+def test_proxy_frames_at_an_apex(n):
+    """32 tets (one launch), 98 and 5,000 (two launches; in one, 7 and 13 ms a frame at 5,000)."""
+    from oracle import proxy as P
+    Sm = S()
+    w = cone(n)
+    pat = P.proxy_pattern(w.n_nodes, w.tets)
+    px = Sm.Proxy.from_workload(w, W.PROXY_EPS)
+    g = np.random.default_rng(n)
+    mask = w.mask0.copy()
+    for k in (1, 30, min(2304, w.n_tets)):
+        ids = g.permutation(w.n_tets)[:k].astype(np.int32)
+        frames = [Sm.upload_frame(ids, 1 - mask[ids]), Sm.upload_frame(ids, mask[ids])]
+        px.apply_edits(*frames[0])
+        mask[ids] = 1 - mask[ids]
+        v, c, d = (t.cpu().numpy() for t in px.state())
+        ov, oc, od = P.proxy_rebuild(w.n_nodes, w.tets, mask, W.PROXY_EPS, pat)
+        assert np.array_equal(c, oc) and np.array_equal(d, od) and np.array_equal(v.view(np.uint64), ov.view(np.uint64))
+        assert seconds(lambda: [px.apply_edits(*f) for f in (frames[1], frames[0])]) < 2e-3, k
+    assert px.status_sync() == Sm.STA_OK
+    px.close()
