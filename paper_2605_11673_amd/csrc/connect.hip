@@ -9,7 +9,7 @@
 // triple are found once on the host and kept on the device.
 //
 // Both are a union-find over parent pointers f.  Each workgroup first merges
-// one window of consecutive tets in LDS and keeps one root per set it finds.
+// one window of tets, consecutive or near each other, in LDS and keeps one root per set it finds.
 // Vertex: every vertex of the window then takes its set's root as its own,
 // exchanging it for that of another window that holds the vertex: those two
 // roots are to be united.  Face: the pairs that cross windows name two roots
@@ -148,19 +148,36 @@ __global__ __launch_bounds__(kBlock) void k_cc_init(int n, int* __restrict__ f, 
     }
 }
 
+// The slot of vertex x in a window's hash table.
+__device__ __forceinline__ int find_slot(int* key, int x, bool* added = nullptr)
+{
+    unsigned h = priority(x) >> (32 - 13);
+    for (;; h = (h + 1) & (kSlots - 1)) {  // ends: there are more slots than vertices
+        const int old = atomicCAS(key + h, -1, x);
+        if (added)
+            *added = old == -1;
+        if (old == -1 || old == x)
+            return (int)h;
+    }
+}
+
 // One window of tets: the vertices of its active tets in a hash table, merged
 // there; then its roots with those of other windows.  Bound by latency: chains
 // of LDS atomics, then of pointers to global roots.  22 us at 196,608 tets,
 // where seeding every vertex from its tets and two to four hooking passes, each
-// with a shortcut pass, took 13 + 62; the whole call 54 us at 384,000 tets, all
-// active or half of them (54, 464 before), 366 with scattered ids (5,554).
-__global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, int* f, int* __restrict__ own, int* least)
+// with a shortcut pass, took 13 + 62; the whole call 52 us at 384,000 tets, all
+// active or half of them (62, 250 to 500 before).
+//
+// kOrdered: windows of the tets in the order given (below).
+template <bool kOrdered>
+__global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, const int* __restrict__ order, int* f,
+                                                        int* __restrict__ own, int* least)
 {
     __shared__ int s_key[kSlots], s_f[kSlots], s_least[kSlots];
     __shared__ unsigned long long s_pair[kPairSlots];
-    const int e = blockIdx.x * kWindow + threadIdx.x;
-    const int4 t = v.T[min(e, v.n_tets - 1)];
-    const bool on = e < v.n_tets && v.mask[min(e, v.n_tets - 1)];
+    const int i = blockIdx.x * kWindow + threadIdx.x, ii = min(i, v.n_tets - 1), e = kOrdered ? order[ii] : ii;
+    const int4 t = v.T[e];
+    const bool on = i < v.n_tets && v.mask[e];
     for (int h = threadIdx.x; h < kSlots; h += kWindow) {
         s_key[h] = -1;
         s_f[h] = h;
@@ -173,15 +190,8 @@ __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, int* f, int* 
         const int x[4] = {t.x, t.y, t.z, t.w};
         int slot[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            unsigned h = priority(x[k]) >> (32 - 13);
-            for (;; h = (h + 1) & (kSlots - 1)) {  // ends: there are more slots than vertices
-                const int old = atomicCAS(&s_key[h], -1, x[k]);
-                if (old == -1 || old == x[k])
-                    break;
-            }
-            slot[k] = (int)h;
-        }
+        for (int k = 0; k < 4; ++k)
+            slot[k] = find_slot(s_key, x[k]);
 #pragma unroll
         for (int k = 1; k < 4; ++k)
             unite_lds(s_f, slot[0], slot[k]);
@@ -211,6 +221,86 @@ __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, int* f, int* 
     for (int k = 0; k < kMine; ++k)
         if (other[k] >= 0 && other[k] != root[k] && new_pair(s_pair, root[k], other[k]))
             unite(f, root[k], other[k]);
+}
+
+// Windows of tets that are near each other leave few roots to unite; of tets in
+// no order, nearly every vertex of each is one, and a call on 384,000 tets took
+// 940 us.  By their smallest vertex the tets are near each other again if the
+// vertices' ids are: 58 us, as in order (71 by the hooking passes); and share at
+// least that vertex if not: 140 (by id 350; 3,290).  The first call looks at some
+// windows and keeps that order if it halves their vertices, for 0.1 ms.  Any
+// order gives the same labels.
+//
+// Vertices of the candidates of every step-th window, into sum.
+constexpr int kSpreadWindows = 64, kSpreadFrom = 16 * kWindow, kSpreadVertices = 1024;
+template <bool kOrdered>
+__global__ __launch_bounds__(kWindow) void k_cc_spread(DevView v, const int* __restrict__ order, int step, uint32_t* sum)
+{
+    __shared__ int s_key[kSlots];
+    __shared__ uint32_t s_count;
+    const int i = blockIdx.x * step * kWindow + threadIdx.x, ii = min(i, v.n_tets - 1);
+    const int4 t = v.T[kOrdered ? order[ii] : ii];
+    for (int h = threadIdx.x; h < kSlots; h += kWindow)
+        s_key[h] = -1;
+    if (threadIdx.x == 0)
+        s_count = 0u;
+    __syncthreads();
+    if (i < v.n_tets) {
+        const int x[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            bool added;
+            (void)find_slot(s_key, x[k], &added);
+            if (added)
+                atomicAdd(&s_count, 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        atomicAdd(sum, s_count);
+}
+
+// Order by smallest vertex: counts per vertex, their running sums, places.
+__global__ __launch_bounds__(kBlock) void k_cc_zero(int n, uint32_t* __restrict__ at)
+{
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n)
+        at[i] = 0u;
+}
+
+__global__ __launch_bounds__(kBlock) void k_cc_place(DevView v, uint32_t* at, int* __restrict__ order)
+{
+    const int e = blockIdx.x * kBlock + threadIdx.x;
+    if (e >= v.n_tets)
+        return;
+    const int4 t = v.T[e];
+    const uint32_t p = atomicAdd(at + min(min(t.x, t.y), min(t.z, t.w)), 1u);
+    if (order)
+        order[p] = e;
+}
+
+__global__ __launch_bounds__(kWindow) void k_cc_sums(int n, uint32_t* __restrict__ at)
+{
+    __shared__ uint32_t s_sum[kWindow];
+    const int t = threadIdx.x, per = (n + kWindow - 1) / kWindow;
+    const int i0 = min(n, t * per), i1 = min(n, i0 + per);
+    uint32_t mine = 0u;
+    for (int i = i0; i < i1; ++i)
+        mine += at[i];
+    s_sum[t] = mine;
+    __syncthreads();
+    for (int d = 1; d < kWindow; d *= 2) {
+        const uint32_t x = t >= d ? s_sum[t - d] : 0u;
+        __syncthreads();
+        s_sum[t] += x;
+        __syncthreads();
+    }
+    uint32_t sum = s_sum[t] - mine;
+    for (int i = i0; i < i1; ++i) {
+        const uint32_t c = at[i];
+        at[i] = sum;
+        sum += c;
+    }
 }
 
 // After the unions: of every id i the root, into own[i] (a root of i's window
@@ -417,16 +507,54 @@ static hipError_t run_face_components(const DevView& v, const int2* pairs, int64
     return hipGetLastError();
 }
 
+// The order of the tets for the windows, into *order (NULL: by id), once per
+// context; word: a device word, at: n_nodes words of scratch.  Waits for s.
+static hipError_t order_tets(const DevView& v, uint32_t* word, uint32_t* at, int** order, hipStream_t s)
+{
+    *order = nullptr;
+    if (v.n_tets < kSpreadFrom)
+        return hipSuccess;
+    const int windows = (v.n_tets + kWindow - 1) / kWindow, looked = std::min(windows, kSpreadWindows);
+    auto spread = [&](const int* by, uint32_t* sum) {
+        hipLaunchKernelGGL(k_cc_zero, dim3(1), dim3(kBlock), 0, s, 1, word);
+        hipLaunchKernelGGL((by ? k_cc_spread<true> : k_cc_spread<false>), dim3(looked), dim3(kWindow), 0, s, v, by,
+                           windows / looked, word);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(sum, word, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+    };
+    uint32_t by_id = 0u, by_vertex = 0u;
+    hipError_t e = spread(nullptr, &by_id);
+    if (e != hipSuccess || by_id <= (uint32_t)(looked * kSpreadVertices))
+        return e;
+    int* q = nullptr;
+    if ((e = hipMalloc((void**)&q, sizeof(int) * (size_t)v.n_tets)) != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(k_cc_zero, dim3(blocks(v.n_nodes)), dim3(kBlock), 0, s, v.n_nodes, at);
+    hipLaunchKernelGGL(k_cc_place, dim3(blocks(v.n_tets)), dim3(kBlock), 0, s, v, at, (int*)nullptr);
+    hipLaunchKernelGGL(k_cc_sums, dim3(1), dim3(kWindow), 0, s, v.n_nodes, at);
+    hipLaunchKernelGGL(k_cc_place, dim3(blocks(v.n_tets)), dim3(kBlock), 0, s, v, at, q);
+    e = hipGetLastError();
+    if (e == hipSuccess)
+        e = spread(q, &by_vertex);
+    if (e == hipSuccess && by_vertex <= by_id / 2)
+        *order = q;
+    else
+        (void)hipFree(q);
+    return e;
+}
+
 // Component labels into label (device, n_tets); *host and count as above; own,
 // f, least: n_nodes ints each.
-static hipError_t run_components(const DevView& v, int* own, int* f, int* least, uint32_t* count, uint32_t* host,
-                                 int32_t* label, hipStream_t s)
+static hipError_t run_components(const DevView& v, const int* order, int* own, int* f, int* least, uint32_t* count,
+                                 uint32_t* host, int32_t* label, hipStream_t s)
 {
     const dim3 nodes(std::max(1u, blocks(v.n_nodes)));
     hipLaunchKernelGGL(k_cc_init, nodes, dim3(kBlock), 0, s, v.n_nodes, f, least, own, count);
     if (v.n_tets > 0)
-        hipLaunchKernelGGL(k_cc_windows, dim3((v.n_tets + kWindow - 1) / kWindow), dim3(kWindow), 0, s, v, f, own,
-                           least);
+        hipLaunchKernelGGL((order ? k_cc_windows<true> : k_cc_windows<false>), dim3((v.n_tets + kWindow - 1) / kWindow),
+                           dim3(kWindow), 0, s, v, order, f, own, least);
     hipLaunchKernelGGL(k_cc_roots, nodes, dim3(kBlock), 0, s, v.n_nodes, own, f, least, count);
     hipLaunchKernelGGL(k_cc_label, dim3(std::max(1u, blocks(v.n_tets))), dim3(kBlock), 0, s, v, own, least, label, count,
                        host);
@@ -478,7 +606,18 @@ extern "C" sta_status sta_components(sta_ctx* ctx, int32_t* labels_dev, int64_t*
     }
     uint32_t* count = reinterpret_cast<uint32_t*>(ctx->cc_ws);
     int* own = ctx->cc_ws + 1;
-    e = run_components(ctx->v, own, own + n, own + 2 * n, count, ctx->cc_host, labels_dev, s);
+    if (!ctx->cc_ordered) {
+        e = order_tets(ctx->v, count, reinterpret_cast<uint32_t*>(own), &ctx->cc_order, s);
+        if (e == hipErrorOutOfMemory) {
+            ctx->errmsg = std::string("connectivity order: ") + hipGetErrorString(e);
+            return STA_ENOMEM;
+        }
+        if (ctx->cc_order)
+            ctx->owned.push_back(ctx->cc_order);
+        ctx->cc_ordered = e == hipSuccess;
+    }
+    if (e == hipSuccess)
+        e = run_components(ctx->v, ctx->cc_order, own, own + n, own + 2 * n, count, ctx->cc_host, labels_dev, s);
     return read_count(ctx, e, "connectivity: ", n_components, s);
 }
 

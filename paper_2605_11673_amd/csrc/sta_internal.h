@@ -322,6 +322,8 @@ struct sta_ctx {
     double* audit_ws = nullptr;     // audit: nnz re-summed values, then 2 counters
     int32_t* cc_ws = nullptr;       // connectivity: the count, then root, parent and smallest id per node
     uint32_t* cc_host = nullptr;    // pinned: number of components
+    int32_t* cc_order = nullptr;    // order of the tets that the vertex adjacency's windows take (NULL: by id)
+    bool cc_ordered = false;        // cc_order is found
     int32_t* ccf_ws = nullptr;      // face connectivity: the count, then what follows
     int2* ccf_pairs = nullptr;      // candidate tet pairs with a common face
     int64_t* ccf_start = nullptr;   // first pair of each window of tets
