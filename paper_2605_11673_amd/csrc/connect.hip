@@ -165,15 +165,20 @@ __device__ __forceinline__ int find_slot(int* key, int x, bool* added = nullptr)
 // there; then its roots with those of other windows.  Bound by latency: chains
 // of LDS atomics, then of pointers to global roots.  22 us at 196,608 tets,
 // where seeding every vertex from its tets and two to four hooking passes, each
-// with a shortcut pass, took 13 + 62; the whole call 52 us at 384,000 tets, all
+// with a shortcut pass, took 13 + 62; the whole call 45 us at 384,000 tets, all
 // active or half of them (62, 250 to 500 before).
 //
-// kOrdered: windows of the tets in the order given (below).
-template <bool kOrdered>
+// kOrdered: windows of the tets in the order given (below).  kMany: the roots'
+// smallest ids are found where the pointers were, so that two workgroups fit on a
+// compute unit, at the price of two more barriers (1 us); for more windows than
+// compute units: 375 windows 52.6 -> 44.5 us a call, the 1,388 of a batch of 64
+// meshes 104.7 -> 82.0 (93 by the hooking passes); one window 28.1, else 29.3.
+constexpr int kManyWindows = 256;
+template <bool kOrdered, bool kMany>
 __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, const int* __restrict__ order, int* f,
                                                         int* __restrict__ own, int* least)
 {
-    __shared__ int s_key[kSlots], s_f[kSlots], s_least[kSlots];
+    __shared__ int s_key[kSlots], s_f[kSlots], s_least[kMany ? 1 : kSlots];
     __shared__ unsigned long long s_pair[kPairSlots];
     const int i = blockIdx.x * kWindow + threadIdx.x, ii = min(i, v.n_tets - 1), e = kOrdered ? order[ii] : ii;
     const int4 t = v.T[e];
@@ -181,7 +186,8 @@ __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, const int* __
     for (int h = threadIdx.x; h < kSlots; h += kWindow) {
         s_key[h] = -1;
         s_f[h] = h;
-        s_least[h] = INT32_MAX;
+        if (!kMany)
+            s_least[h] = INT32_MAX;
     }
     for (int h = threadIdx.x; h < kPairSlots; h += kWindow)
         s_pair[h] = ~0ull;
@@ -198,24 +204,37 @@ __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, const int* __
     }
     __syncthreads();
     constexpr int kMine = kSlots / kWindow;
-    int root[kMine], other[kMine];
+    int at[kMine], root[kMine], other[kMine];
 #pragma unroll
     for (int k = 0; k < kMine; ++k) {
         const int h = threadIdx.x + k * kWindow, x = s_key[h];
-        root[k] = other[k] = -1;
+        at[k] = root[k] = other[k] = -1;
         if (x >= 0) {
-            const int r = climb_lds(s_f, h);
-            atomicMin(s_least + r, x);
-            root[k] = s_key[r];
+            at[k] = climb_lds(s_f, h);
+            if (!kMany)
+                atomicMin(s_least + at[k], x);
+            root[k] = s_key[at[k]];
             other[k] = atomicExch(own + x, root[k]);
         }
     }
     __syncthreads();
+    if (kMany) {  // no pointer is followed any more
+#pragma unroll
+        for (int k = 0; k < kMine; ++k)
+            if (at[k] == (int)threadIdx.x + k * kWindow)  // a root
+                s_f[at[k]] = root[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kMine; ++k)
+            if (at[k] >= 0 && at[k] != (int)threadIdx.x + k * kWindow)
+                atomicMin(s_f + at[k], s_key[threadIdx.x + k * kWindow]);
+        __syncthreads();
+    }
 #pragma unroll
     for (int k = 0; k < kMine; ++k) {
         const int h = threadIdx.x + k * kWindow;
-        if (s_least[h] != INT32_MAX)  // h is a root
-            atomicMin(least + s_key[h], s_least[h]);
+        if (kMany ? at[k] == h : s_least[h] != INT32_MAX)  // h is a root
+            atomicMin(least + s_key[h], kMany ? s_f[h] : s_least[h]);
     }
 #pragma unroll
     for (int k = 0; k < kMine; ++k)
@@ -226,8 +245,8 @@ __global__ __launch_bounds__(kWindow) void k_cc_windows(DevView v, const int* __
 // Windows of tets that are near each other leave few roots to unite; of tets in
 // no order, nearly every vertex of each is one, and a call on 384,000 tets took
 // 940 us.  By their smallest vertex the tets are near each other again if the
-// vertices' ids are: 58 us, as in order (71 by the hooking passes); and share at
-// least that vertex if not: 140 (by id 350; 3,290).  The first call looks at some
+// vertices' ids are: 49 us, 45 in order (71 by the hooking passes); and share at
+// least that vertex if not: 200 (by id 350; 3,290).  The first call looks at some
 // windows and keeps that order if it halves their vertices, for 0.1 ms.  Any
 // order gives the same labels.
 //
@@ -552,9 +571,11 @@ static hipError_t run_components(const DevView& v, const int* order, int* own, i
 {
     const dim3 nodes(std::max(1u, blocks(v.n_nodes)));
     hipLaunchKernelGGL(k_cc_init, nodes, dim3(kBlock), 0, s, v.n_nodes, f, least, own, count);
-    if (v.n_tets > 0)
-        hipLaunchKernelGGL((order ? k_cc_windows<true> : k_cc_windows<false>), dim3((v.n_tets + kWindow - 1) / kWindow),
-                           dim3(kWindow), 0, s, v, order, f, own, least);
+    const int windows = (v.n_tets + kWindow - 1) / kWindow;
+    auto merge = windows > kManyWindows ? (order ? k_cc_windows<true, true> : k_cc_windows<false, true>)
+                                        : (order ? k_cc_windows<true, false> : k_cc_windows<false, false>);
+    if (windows > 0)
+        hipLaunchKernelGGL(merge, dim3(windows), dim3(kWindow), 0, s, v, order, f, own, least);
     hipLaunchKernelGGL(k_cc_roots, nodes, dim3(kBlock), 0, s, v.n_nodes, own, f, least, count);
     hipLaunchKernelGGL(k_cc_label, dim3(std::max(1u, blocks(v.n_tets))), dim3(kBlock), 0, s, v, own, least, label, count,
                        host);
