@@ -256,8 +256,10 @@ sta_status sta_slot_outer(sta_ctx* ctx, const double* a_dev, const double* b_dev
  * context's own values).  Rows with a zero diagonal (nodes with no active
  * tet) are held at x = 0 and their b is ignored.  Stops when
  * ||r|| <= rtol ||b|| or after max_iter iterations.  b_dev, x_dev: device,
- * n_rows.  Synchronises `stream` (convergence is checked every 16
- * iterations).  *iters_out / *relres_out (may be NULL) report the result. */
+ * n_rows.  Synchronises `stream` (the host looks at the residual after 16
+ * iterations, then where its rate so far says that the solve should end; a
+ * small system's solve ends on the device).  *iters_out / *relres_out (may be
+ * NULL) report the result. */
 sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_dev, double* x_dev, double rtol,
                         int max_iter, void* stream, int* iters_out, double* relres_out);
 

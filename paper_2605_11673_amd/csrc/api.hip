@@ -11,6 +11,7 @@
 #include <utility>
 #include <vector>
 
+#include "solve_rules.h"
 #include "sta_internal.h"
 
 using namespace sta;
@@ -635,19 +636,6 @@ sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, in
 // Iterations of a small solve's launch: some milliseconds at most.
 constexpr int kCgSmallIters = 1024;
 
-// Iterations to launch before the next look at the residual: what is left at
-// the mean rate of the `launched` iterations so far, at least 4 and at most
-// twice as many as have run (the rate changes on the way).
-int cg_chunk(const CgScalars& h, int launched)
-{
-    const double rate = std::log(h.rr / h.bnorm2) / launched;  // per iteration, negative
-    const double left = std::log(h.tol2 / h.rr) / rate;
-    const int most = 2 * launched < 256 ? 2 * launched : 256;
-    if (!(left < most))  // not a number, infinite or growing residual included
-        return rate < 0.0 ? most : 16;
-    return left > 4.0 ? (int)std::ceil(left) : 4;
-}
-
 bool valid_map(int qd, int qo)
 {
     return (qd == 1 || qd == 4 || qd == 16) && (qo == 1 || qo == 4);
@@ -1209,8 +1197,7 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
         e = launch_cg_init(c, b_dev, rtol, s);
     }
     // iterations k = 0 .. max_iter (the last one only records the residual),
-    // cg_chunk of them between host checks (a check costs about 18 us of idle GPU, a launch
-    // pair past convergence about 3)
+    // cg_chunk of them between host checks
     int next = 0, chunk = 16;
     while (e == hipSuccess && !small) {
         const int count = max_iter + 1 - next < chunk ? max_iter + 1 - next : chunk;
@@ -1223,7 +1210,7 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
             e = hipStreamSynchronize(s);
         if (e != hipSuccess || ctx->cg_host->done || next > max_iter)
             break;
-        chunk = cg_chunk(*ctx->cg_host, next);
+        chunk = cg_chunk(ctx->cg_host->rr, ctx->cg_host->bnorm2, ctx->cg_host->tol2, next);
     }
     if (e == hipSuccess && !small)
         e = launch_cg_output(c, x_dev, s);
