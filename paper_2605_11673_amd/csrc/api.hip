@@ -11,7 +11,6 @@
 #include <utility>
 #include <vector>
 
-#include "solve_rules.h"
 #include "sta_internal.h"
 
 using namespace sta;
@@ -335,6 +334,7 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     v.no = (int32_t)P.no;
     v.mat = material(nu, rho, dt);
 
+    c->cg_small = cg_small_pays(n_nodes, P.rowptr.data());
     const int64_t nb = P.nd + P.no;
     double *xs, *E_d, *geo, *values;
     int4* T;
@@ -1181,7 +1181,7 @@ sta_status sta_cg_solve(sta_ctx* ctx, const double* values_dev, const double* b_
     c.dinv = c.q + n;
     c.part = c.dinv + n;
     c.s = ctx->cg_s;
-    const bool small = cg_is_small(n);
+    const bool small = ctx->cg_small;
     if (small) {
         // one launch, or one per kCgSmallIters iterations of a long solve
         ctx->cg_host->done = 0;

@@ -389,12 +389,14 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(CgView c, int k, int cur)
 // of 375 rows 83 / 237, 31 of 648 rows 120 / 293, 37 of 1,029 rows 190 / 349.
 // Past the rounds that fit in registers and LDS the blocks would be read again
 // in each iteration, at 1.6 us a round: 42 iterations of 1,536 rows took 442 us
-// that way, 345 by the launches above, so there the rule draws its line.
+// that way, 345 by the launches above, so there the rule draws its line; and
+// where many nodes have many neighbours (cg_small_pays).
 //
 // Iterations k0 .. k1 - 1; a solve that is not done by then is kept in the
 // workspace for the next launch, so that no launch runs for long.
 constexpr int kSmallBlock = 512, kSmallWaves = kSmallBlock / 64, kSmallGroups = kSmallBlock / kNodeLanes;
 constexpr int kSmallHeld = 8, kSmallLds = 3, kSmallNodes = (kSmallHeld + kSmallLds) * kSmallGroups;
+static_assert(kSmallGroups == kCgSmallRound && kSmallHeld + kSmallLds == kCgSmallRounds, "cg_small_pays");
 constexpr int kSmallRows = 3 * kSmallNodes, kSmallMine = (kSmallRows + kSmallBlock - 1) / kSmallBlock;
 
 __device__ __forceinline__ double sum_waves(const double* sh)
@@ -714,16 +716,11 @@ hipError_t launch_cg_iterations(const CgView& c, int first, int count, int max_i
     return hipGetLastError();
 }
 
-bool cg_is_small(int n)
-{
-    return n <= kSmallRows;
-}
-
 // Iterations k0 .. k1 - 1 of a small solve, or its end; host: pinned.
 hipError_t launch_cg_small(const CgView& c, const double* b, double* x, CgScalars* host, double rtol, int k0, int k1,
                            int max_iter, hipStream_t s)
 {
-    if (!cg_is_small(c.n))
+    if (c.n > kSmallRows)
         return hipErrorInvalidValue;
     const int rounds = (c.n / 3 + kSmallGroups - 1) / kSmallGroups;
     const size_t lds = rounds > kSmallHeld ? sizeof(double) * 9 * kSmallBlock * (rounds - kSmallHeld) : 0;

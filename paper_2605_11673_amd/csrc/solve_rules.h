@@ -1,9 +1,41 @@
 // How a solve is launched (host only).
 #pragma once
 
+#include <algorithm>
 #include <cmath>
+#include <cstdint>
 
 namespace sta {
+
+constexpr int kCgNeighbours = 16;   // of a node, held at a fixed place; the others are read again in each iteration
+constexpr int kCgSmallRound = 32;   // nodes that the one workgroup of a small solve takes at a time
+constexpr int kCgSmallRounds = 11;  // of which it holds the blocks
+
+// Whether a system's solve is one launch of one workgroup.  rowptr: of its
+// 3 `nodes` rows.  An iteration there takes some 2 us, 0.3 for each round of nodes
+// and 0.45 for each trip over further neighbours, of all rounds one after the
+// other; by two launches 8.5 to 9.5, and 0.4 a trip, all rounds side by side.
+// Whole solves, one workgroup / launches, in us: fracture meshes and refinement
+// supersets of up to 343 nodes 185 / 341 and 175 / 204, a vertex of 325
+// neighbours 1,060 / 1,605; 100 nodes of 40 to 60 674 / 945, of all 918 / 743; 200 and
+// 350 of 150 to 200 1,830 / 835 and 22,500 / 2,170.
+inline bool cg_small_pays(int64_t nodes, const int32_t* rowptr)
+{
+    const int64_t rounds = (nodes + kCgSmallRound - 1) / kCgSmallRound;
+    if (rounds > kCgSmallRounds)
+        return false;
+    int64_t trips = 0, most = 0;
+    for (int64_t w = 0; w < rounds; ++w) {
+        int64_t round = 0;
+        for (int64_t i = w * kCgSmallRound; i < std::min(nodes, (w + 1) * kCgSmallRound); ++i) {
+            const int64_t further = (rowptr[3 * i + 1] - rowptr[3 * i]) / 3 - kCgNeighbours;
+            round = std::max(round, (further + kCgNeighbours - 1) / kCgNeighbours);
+        }
+        trips += round;
+        most = std::max(most, round);
+    }
+    return 9 * trips + 6 * rounds <= 150 + 8 * most;
+}
 
 // Iterations to launch before the next look at the residual (rr = |r|^2), after
 // `launched` of them: what is left at the mean rate so far, at least 4 and at most

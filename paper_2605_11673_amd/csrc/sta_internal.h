@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "adjoint_plan.h"
+#include "solve_rules.h"
 #include "stafem.h"
 #include <hip/hip_ext.h>
 
@@ -264,7 +265,6 @@ struct CgScalars {
     double rzk[2];  // r_k . z_k by iteration parity (the product of iteration k reads k-1's, writes k's)
 };
 
-constexpr int kCgNeighbours = 16;
 struct CgView {
     int32_t n;        // rows
     int32_t nparts;   // partial sums of the start kernels (one per 256 rows)
@@ -310,6 +310,7 @@ struct sta_ctx {
     int32_t* cg_adj = nullptr;
     sta::CgScalars* cg_s = nullptr;
     sta::CgScalars* cg_host = nullptr;  // pinned
+    bool cg_small = false;          // a solve is one launch of one workgroup
     double* adj_xbar = nullptr;     // 3 doubles per diagonal incidence
     int32_t* adj_order = nullptr;   // adjoint visiting order of the kAdjointChunk-tet chunks, brick by brick
                                     // where there are bricks (-1: none)
@@ -429,7 +430,6 @@ int update_grid(int n);
 hipError_t launch_cg_init(const CgView& c, const double* b, double rtol, hipStream_t s);
 // Iterations first .. first+count-1 (the iteration index picks the copy of p).
 hipError_t launch_cg_iterations(const CgView& c, int first, int count, int max_iter, hipStream_t s);
-bool cg_is_small(int n);
 hipError_t launch_cg_small(const CgView& c, const double* b, double* x, CgScalars* host, double rtol, int k0, int k1,
                            int max_iter, hipStream_t s);
 hipError_t launch_cg_output(const CgView& c, double* x, hipStream_t s);

@@ -60,3 +60,24 @@ def test_proxy_frames_at_an_apex(n):
         assert seconds(lambda: [px.apply_edits(*f) for f in (frames[1], frames[0])]) < 2e-3, k
     assert px.status_sync() == Sm.STA_OK
     px.close()
+
+
+@pytest.mark.parametrize("n,m", [(40, 1000), (100, 400), (100, 2000), (350, 10000)])
+def test_small_solves_with_many_neighbours(n, m):
+    """Solved by one workgroup (the first two) and by launches: residuals within the bound of
+    tests/test_gpu_cg.py."""
+    import oracle
+    from tests.test_gpu_cg import U, true_residual
+    Sm = S()
+    g = np.random.default_rng(n + m)
+    tets = np.argsort(g.uniform(size=(m, n)), axis=1)[:, :4].astype(np.int32)
+    w = W.Workload("dense", g.uniform(size=(n, 3)), tets, W.lognormal_E(m, g), np.ones(m, np.uint8))
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    live = np.diff(pat[0]) > 0
+    b = np.where(live, g.standard_normal(asm.n_rows), 0.0)
+    x, it, rr = asm.cg_solve(torch.from_numpy(b).cuda(), rtol=1e-12)
+    res, size = true_residual(pat, asm.values().cpu().numpy(), x.cpu().numpy(), b)
+    nb = np.linalg.norm(b)
+    assert rr <= 1e-12 and res <= 1e-12 * nb + 8 * U * it * (size + nb), (res / nb, it)
+    asm.close()

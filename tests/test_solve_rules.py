@@ -1,23 +1,31 @@
-"""How many iterations of a solve run between two looks at its residual."""
+"""How a solve is launched: the iterations between two looks at its residual, and which
+systems one workgroup solves."""
 import ctypes
 import math
 
 import numpy as np
 import pytest
 
+import oracle
+from paper_2605_11673_amd import workloads as W
 from tests.hostcode import compiled
 
 SOURCE = r"""
 #include "solve_rules.h"
 extern "C" int chunk(double rr, double bb, double tol2, int launched) { return sta::cg_chunk(rr, bb, tol2, launched); }
+extern "C" int small_pays(long long nodes, const int32_t* rowptr) { return sta::cg_small_pays(nodes, rowptr); }
 """
 
 
 @pytest.fixture(scope="module")
-def chunk(tmp_path_factory):
-    f = compiled(tmp_path_factory.mktemp("rules"), SOURCE).chunk
-    f.argtypes = [ctypes.c_double, ctypes.c_double, ctypes.c_double, ctypes.c_int]
-    return f
+def rules(tmp_path_factory):
+    return compiled(tmp_path_factory.mktemp("rules"), SOURCE)
+
+
+@pytest.fixture(scope="module")
+def chunk(rules):
+    rules.chunk.argtypes = [ctypes.c_double, ctypes.c_double, ctypes.c_double, ctypes.c_int]
+    return rules.chunk
 
 
 @pytest.mark.parametrize("ratio", [1.0, 1.5, 30.0, 1e8, math.inf, math.nan])
@@ -52,3 +60,21 @@ def test_looks_of_a_solve(chunk, rise):
             break
         n = chunk(math.exp(log_rr[launched]), 1.0, 1e-24, launched)
     assert looks <= math.ceil(len(log_rr) / 16) and launched - len(log_rr) <= 256
+
+
+def small_pays(rules, degrees):
+    """degrees: neighbours of each node, itself included."""
+    rowptr = np.concatenate([[0], np.cumsum(np.repeat(3 * np.asarray(degrees), 3))]).astype(np.int32)
+    return bool(rules.small_pays(ctypes.c_longlong(len(degrees)), rowptr.ctypes.data_as(ctypes.c_void_p)))
+
+
+def test_one_workgroup_for_a_small_system(rules):
+    for w in (W.make_cube(0, 4), W.make_fracture(0, 6, counts=[1]), W.make_refinement(0, 3, 1)):
+        rowptr = oracle.pattern(w.n_nodes, w.tets)[0]
+        assert rules.small_pays(ctypes.c_longlong(w.n_nodes), rowptr.ctypes.data_as(ctypes.c_void_p)), w.name
+    assert small_pays(rules, [15] * 352) and not small_pays(rules, [15] * 353)
+    assert small_pays(rules, [0] * 10) and small_pays(rules, [])
+    assert small_pays(rules, [12] * 300 + [320])  # one vertex with many neighbours
+    for n in (100, 200, 350):  # nearly all of them neighbours of each other
+        assert not small_pays(rules, [min(n, 170)] * n), n
+    assert small_pays(rules, [40] * 40)
