@@ -306,8 +306,9 @@ sta_status sta_face_components(sta_ctx* ctx, int32_t* labels_dev, int64_t* n_com
 
 /* Execution configuration.
  *   fused       A frame whose list (capacity) holds at most 2,304 edits is one
- *               launch.  Above, 0: two launches (edit phase, touched phase);
- *               1: one persistent launch (both phases, grid barrier between).
+ *               launch, on a mesh of which no vertex has more than 1,024 tets.
+ *               Any other, 0: two launches (edit phase, touched phase); 1: one
+ *               persistent launch (both phases, grid barrier between).
  *               With fused 1 and a spin limit set (sta_set_barrier_spin_limit)
  *               every frame is the persistent launch.
  *   rebuild_qd / rebuild_qo, stream_qd / stream_qo: slot mapping (diagonal

@@ -319,8 +319,10 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
     c->nnz = P.nnz;
     c->nd = P.nd;
     c->no = P.no;
-    for (int64_t b = 0; b < P.nd; ++b)
+    for (int64_t b = 0; b < P.nd; ++b) {
         c->bucket_blocks[diag_bucket(P.dseg[b + 1] - P.dseg[b])]++;
+        c->longest = std::max<int64_t>(c->longest, P.dseg[b + 1] - P.dseg[b]);
+    }
     for (int64_t o = 0; o < P.no; ++o)
         c->bucket_blocks[kDiagBuckets + off_bucket(P.oseg[o + 1] - P.oseg[o])]++;
     c->nu = nu;
@@ -591,19 +593,21 @@ void trace_call(sta_ctx* ctx, const char* call, int64_t n, bool n_is_capacity, h
     std::fflush(ctx->trace);
 }
 
-// One frame.  A list that fits k_once's table takes one launch without a grid
-// barrier whatever the mode (5.9 us a frame on the 384k-tet stream, against
-// 8.4 for two launches and 15 to 23 for one with a barrier); a longer one two
-// launches, or with fused set one persistent launch with a barrier.  A spin
-// limit set by the caller asks for the barrier it limits.
+// The launches of a frame of so many edits (or such a capacity).
+FrameRoute route_of(const sta_ctx* ctx, int64_t n)
+{
+    return frame_route(n, ctx->longest, ctx->fused != 0, ctx->barrier_spin != kBarrierSpinDefault);
+}
+
 sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, int32_t n_host, const int32_t* n_dev,
                      hipStream_t s)
 {
     hipError_t e = hipSuccess;
-    if (frame_fits_once(n_host) && !(ctx->fused && ctx->barrier_spin != kBarrierSpinDefault)) {
+    const FrameRoute route = route_of(ctx, n_host);
+    if (route == FrameRoute::once) {
         e = timed(
             ctx, STA_KERNEL_FRAME, s, [&] { return launch_once(ctx->v, ids, states, n_host, n_dev, s); }, true);
-    } else if (ctx->fused) {
+    } else if (route == FrameRoute::barrier) {
         if (ctx->frame_max_grid <= 0) {
             e = frame_max_grid(ctx->device, &ctx->frame_max_grid);
             if (e != hipSuccess)

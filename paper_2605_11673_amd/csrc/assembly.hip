@@ -404,12 +404,43 @@ __device__ __forceinline__ uint32_t load_incidence(const DevView& v, const UnitT
     return (kDiag ? v.di : v.oi)[t < b.total() ? k : 0];
 }
 
+// What one lane needs to form one term's entries.
+struct Term {
+    uint32_t tet;
+    double ga[3], gb[3], lamV, muV, ml;
+    uint8_t active;
+};
+
+template <bool kDiag>
+__device__ __forceinline__ void load_term(const DevView& v, uint32_t u, Term& t)
+{
+    t.tet = kDiag ? u >> 2 : u >> 4;
+    const double* r = v.geo + (size_t)kGeoDoubles * t.tet;
+    const double* pa = r + 3 * (kDiag ? u & 3u : (u >> 2) & 3u);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        t.ga[i] = pa[i];
+    t.lamV = r[12];
+    t.muV = r[13];
+    if (kDiag) {
+        t.ml = r[14];
+    } else {
+        const double* pb = r + 3 * (u & 3u);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            t.gb[i] = pb[i];
+    }
+    t.active = v.mask[t.tet];
+}
+
 // Sum the wave's blocks and write their CSR values; u: the incidences of the
 // first kUnitTerms terms.  Each lane forms the entries of one term at a time
 // from its tet's record into val (LDS, kUnitDoubles per wave); then one lane
 // per block value adds its block's entries in ascending order.  Any segment
-// length works.
-template <bool kDiag, class State>
+// length works: a round's incidences are loaded a round ahead, and with kAhead its
+// records too (rows of nodes of 20,000 and 5,000 tets 470 -> 397 and 123 -> 109 us;
+// in the frames the 20 registers cost a third of the waves).
+template <bool kDiag, bool kAhead, class State>
 __device__ __forceinline__ void sum_unit(const DevView& v, const BlockDesc& d, const UnitTerms<kDiag>& b, uint32_t u,
                                          double* val, const State& state)
 {
@@ -421,33 +452,29 @@ __device__ __forceinline__ void sum_unit(const DevView& v, const BlockDesc& d, c
     const int r0 = has ? lane / U::kValues : 0, e0 = has ? lane % U::kValues : 0;
     const int lo = __shfl(b.own, r0, 64), hi = has ? lo + __shfl(b.cnt, r0, 64) : lo;
     double acc = 0.0;
+    Term t, next;
+    if (kAhead) {
+        load_term<kDiag>(v, u, next);
+        if (kUnitTerms < total)
+            u = load_incidence<kDiag>(v, b, kUnitTerms);
+    }
     for (int base = 0; base < total; base += kUnitTerms) {
-        if (base > 0)
-            u = load_incidence<kDiag>(v, b, base);
-        const uint32_t e = kDiag ? u >> 2 : u >> 4;
-        const double* r = v.geo + (size_t)kGeoDoubles * e;
-        const double* pa = r + 3 * (kDiag ? u & 3u : (u >> 2) & 3u);
-        double ga[3], gb[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            ga[i] = pa[i];
+        constexpr int kLead = (kAhead ? 2 : 1) * kUnitTerms;
+        if (kAhead)
+            t = next;
+        if (!kAhead || base + kUnitTerms < total)
+            load_term<kDiag>(v, u, kAhead ? next : t);
+        if (base + kLead < total)
+            u = load_incidence<kDiag>(v, b, base + kLead);
         Geo G;
-        G.lamV = r[12];
-        G.muV = r[13];
-        if (kDiag) {
-            G.ml = r[14];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                gb[i] = ga[i];
-        } else {
-            const double* pb = r + 3 * (u & 3u);
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                gb[i] = pb[i];
-        }
-        const uint8_t active = v.mask[e];
-        const uint32_t listed = state.listed(e);  // while the record is in flight
-        const bool on = listed == kUnlisted ? active != 0 : listed != 0u;
+        G.lamV = t.lamV;
+        G.muV = t.muV;
+        if (kDiag)
+            G.ml = t.ml;
+        const double* ga = t.ga;
+        const double* gb = kDiag ? t.ga : t.gb;
+        const uint32_t listed = state.listed(t.tet);  // while the record is in flight
+        const bool on = listed == kUnlisted ? t.active != 0 : listed != 0u;
         // LDS accesses of one wave complete in issue order; the fences only
         // keep the compiler from moving them
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -467,13 +494,13 @@ __device__ __forceinline__ void sum_unit(const DevView& v, const BlockDesc& d, c
         const int z = min(hi - base, kUnitTerms);
         for (int k = max(lo - base, 0); k < z; k += 8) {
             const double* p = val + k * U::kStride + e0;
-            double t[8];
+            double x[8];
 #pragma unroll
             for (int w = 0; w < 8; ++w)
-                t[w] = p[w * U::kStride];
+                x[w] = p[w * U::kStride];
 #pragma unroll
             for (int w = 0; w < 8; ++w)
-                acc = acc + (k + w < z ? t[w] : 0.0);
+                acc = acc + (k + w < z ? x[w] : 0.0);
         }
     }
     const int up = __shfl(d.up, r0, 64), rl = __shfl(d.rl, r0, 64);
@@ -489,12 +516,12 @@ __device__ __forceinline__ void sum_unit(const DevView& v, const BlockDesc& d, c
 }
 
 // The same from the start, with the states in the mask.
-template <bool kDiag>
+template <bool kDiag, bool kAhead>
 __device__ __forceinline__ void sum_unit_masked(const DevView& v, const BlockDesc& d, double* val)
 {
     const UnitTerms<kDiag> b = unit_terms<kDiag>(d);
     if (b.total() > 0)
-        sum_unit<kDiag>(v, d, b, load_incidence<kDiag>(v, b, 0), val, MaskState{});
+        sum_unit<kDiag, kAhead>(v, d, b, load_incidence<kDiag>(v, b, 0), val, MaskState{});
 }
 
 // Rows of nodes too large for a tile: waves of two of their diagonal blocks,
@@ -512,12 +539,12 @@ __global__ __launch_bounds__(kBlock) void k_rows_big(DevView v)
         const int k = w * Unit<true>::kBlocks + lane;
         if (lane < Unit<true>::kBlocks && k < v.n_bigd)
             d = load_desc(v.desc + v.bigd[k]);
-        sum_unit_masked<true>(v, d, s_val[threadIdx.x >> 6]);
+        sum_unit_masked<true, true>(v, d, s_val[threadIdx.x >> 6]);
     } else {
         const int k = (w - wd) * Unit<false>::kBlocks + lane;
         if (lane < Unit<false>::kBlocks && k < v.n_bigo)
             d = load_desc(v.desc + v.bigo[k]);
-        sum_unit_masked<false>(v, d, s_val[threadIdx.x >> 6]);
+        sum_unit_masked<false, true>(v, d, s_val[threadIdx.x >> 6]);
     }
 }
 
@@ -616,9 +643,10 @@ __device__ __forceinline__ int edit_lane(const DevView& v, int id, unsigned st, 
 // time) and kOW for its off-diagonal ones (six at a time), each going on while
 // records are left; then one lane per edit (stamp release, rollback).  A region
 // fills from its start and mostly holds 4 to 6 diagonal and 10 to 15
-// off-diagonal claims, so three and three waves take one pass (twelve, one for
-// every possible record, left most of them to find nothing); a persistent
-// grid, which cannot have them all resident, takes fewer.
+// off-diagonal claims, so four and two waves take one pass or two (of 4 + 2, 4 +
+// 4, 5 + 3, 8 + 2 and 8 + 4 waves the first is the fastest for refinement frames of
+// 5,778 and 7,344 edits, 12.5 and 14.7 us against 13.2 to 14.9 and 15.7 to 18.0);
+// a persistent grid, which cannot have them all resident, takes fewer.
 template <int kDW, int kOW>
 struct RegionWaves {
     static constexpr int kWaves = kDW + kOW;
@@ -655,9 +683,9 @@ struct RegionWaves {
         while (k < count) {
             if (!fe) {
                 if (diag)
-                    sum_unit_masked<true>(v, d, val);
+                    sum_unit_masked<true, false>(v, d, val);
                 else
-                    sum_unit_masked<false>(v, d, val);
+                    sum_unit_masked<false, false>(v, d, val);
             }
             if ((int)(threadIdx.x & 63) < blocks && d.kind >= 0)
                 v.bstamp[d.block] = 0u;
@@ -999,7 +1027,6 @@ __global__ __launch_bounds__(kBlock) void k_frame(DevView v, const int32_t* __re
 //
 // kEdits: edits per workgroup; kShare: edits of the list per lane (n_host <=
 // 64 kUnits kEdits kShare).
-constexpr int kOnceMax = 2304;  // edits of the largest variant
 template <int kEdits, int kShare>
 __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const int32_t* __restrict__ ids,
                                                                const uint8_t* __restrict__ states, int32_t n_host,
@@ -1080,9 +1107,9 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
     if (!change)
         return;
     if (unit < 2)
-        sum_unit<true>(v, bd, bdiag, u, s_val[own] + unit * kDiagUnitDoubles, table);
+        sum_unit<true, false>(v, bd, bdiag, u, s_val[own] + unit * kDiagUnitDoubles, table);
     else
-        sum_unit<false>(v, bd, boff, u, s_val[own] + 2 * kDiagUnitDoubles, table);
+        sum_unit<false, false>(v, bd, boff, u, s_val[own] + 2 * kDiagUnitDoubles, table);
 }
 
 // Statistics of a frame of k_once: the distinct blocks of its changed tets
@@ -1219,11 +1246,6 @@ hipError_t launch_delta_frame(const DevView& v, const int32_t* ids, const uint8_
     return hipGetLastError();
 }
 
-bool frame_fits_once(int32_t n_host)
-{
-    return n_host <= kOnceMax;
-}
-
 hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                        const int32_t* n_dev, hipStream_t s)
 {
@@ -1241,7 +1263,7 @@ hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* stat
 #undef ONCE
     return hipErrorInvalidValue;
 }
-static_assert(kOnceMax == 64 * kUnits * 4 * 3, "the largest variant covers the largest list");
+static_assert(kFrameOnceEdits == 64 * kUnits * 4 * 3, "the largest variant covers the largest list");
 
 hipError_t launch_once_stats(const DevView& v, int32_t n, unsigned long long* counts4, hipStream_t s)
 {
@@ -1268,6 +1290,11 @@ hipError_t launch_touched_phase(const DevView& v, const int32_t* ids, int32_t n_
     return hipGetLastError();
 }
 
+// The query counts seven workgroups of k_frame on a compute unit, by its 72
+// VGPRs and 104 scalar ones, and a grid of so many was not all resident: its
+// barrier gave up.  The scalar registers that each wave holds besides its own are
+// not in that count, so it takes no more than five, which leave a third of them.
+constexpr int kFramePerCu = 5;
 hipError_t frame_max_grid(int device, int* max_grid)
 {
     int cus = 0, per_cu = 0;
@@ -1275,7 +1302,7 @@ hipError_t frame_max_grid(int device, int* max_grid)
     if (e == hipSuccess)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&k_frame, kBlock, 0);
     if (e == hipSuccess)
-        *max_grid = per_cu * cus;
+        *max_grid = (per_cu < kFramePerCu ? per_cu : kFramePerCu) * cus;
     return e;
 }
 

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "adjoint_plan.h"
+#include "frame_rules.h"
 #include "solve_rules.h"
 #include "stafem.h"
 #include <hip/hip_ext.h>
@@ -294,6 +295,7 @@ struct sta_ctx {
     // execution configuration (sta_set_config / sta_autotune)
     sta::MapConfig rebuild_map, stream_map;
     int64_t bucket_blocks[sta::kDiagBuckets + sta::kOffBuckets] = {};  // blocks per incidence-length bucket
+    int64_t longest = 0;    // most candidate tets of a vertex
     int fused = 0;          // 1: one persistent launch per frame
     int frame_grid_cap = 0; // 0: occupancy limit only
     int frame_max_grid = 0; // co-resident workgroups for the fused kernel
@@ -377,8 +379,7 @@ hipError_t launch_rows(const DevView& v, bool nt, hipStream_t s);
 hipError_t launch_rows_big(const DevView& v, bool always, hipStream_t s);
 // Streaming.  n_dev (device int32, may be NULL) overrides n_host, which
 // then only sizes the grid (an upper bound on the edit count).
-// One launch for a list that fits its table (frame_fits_once), else two phases.
-bool frame_fits_once(int32_t n_host);
+// One launch (frame_rules.h), or two phases.
 hipError_t launch_once(const DevView& v, const int32_t* ids, const uint8_t* states, int32_t n_host,
                        const int32_t* n_dev, hipStream_t s);
 // Blocks and incidences (diagonal, off-diagonal) touched by the last frame of launch_once.

@@ -10,6 +10,10 @@ from tests.hostcode import compiled
 SOURCE = r"""
 #include "frame_rules.h"
 using namespace sta;
+extern "C" int route(long long edits, long long longest, int fused, int limited)
+{
+    return (int)frame_route(edits, longest, fused != 0, limited != 0);
+}
 extern "C" long long proxy_most() { return kProxyOnceRounds; }
 extern "C" long long edge_rounds(long long t) { return proxy_edge_rounds(t); }
 extern "C" long long vertex_rounds(long long t, long long c) { return proxy_vertex_rounds(t, c); }
@@ -43,3 +47,15 @@ def test_proxy_frames_of_one_launch(rules):
     for tets, columns in ((200, 122), (5000, 2602), (160, 65), (1, 641)):
         assert rules.vertex_rounds(ll(tets), ll(columns)) > rules.proxy_most(), tets
     assert rules.edge_rounds(ll(100)) > rules.proxy_most()
+
+
+ONCE, TWO, BARRIER = 0, 1, 2
+
+
+@pytest.mark.parametrize("edits,longest,fused,limited,want", [
+    (0, 24, 0, 0, ONCE), (2304, 48, 0, 0, ONCE), (2305, 48, 0, 0, TWO), (2305, 48, 1, 0, BARRIER), (2304, 48, 1, 0, ONCE),
+    (1, 1024, 0, 0, ONCE), (1, 1025, 0, 0, TWO), (2304, 5000, 0, 0, TWO), (10, 5000, 1, 0, BARRIER),
+    (10, 24, 1, 1, BARRIER), (10, 24, 0, 1, ONCE), (5000, 24, 0, 1, TWO)])
+def test_frame_route(rules, edits, longest, fused, limited, want):
+    ll = ctypes.c_longlong
+    assert rules.route(ll(edits), ll(longest), fused, limited) == want

@@ -81,3 +81,32 @@ def test_small_solves_with_many_neighbours(n, m):
     nb = np.linalg.norm(b)
     assert rr <= 1e-12 and res <= 1e-12 * nb + 8 * U * it * (size + nb), (res / nb, it)
     asm.close()
+
+
+@pytest.mark.parametrize("n,one", [(22, True), (23, False), (50, False)])
+def test_frames_at_an_apex(n, one):
+    """968 tets of a vertex (one launch, which sums a block once for each edit), 1,058 and 5,000 (two,
+    which sum it once; at 5,000 and 2,304 edits 257 us in one launch, 133 in two)."""
+    import oracle
+    Sm = S()
+    w = cone(n)
+    pat = oracle.pattern(w.n_nodes, w.tets)
+    asm = Sm.Assembler.from_workload(w)
+    asm.enable_kernel_timing(True)
+    asm.kernel_times()
+    g = np.random.default_rng(n)
+    mask = w.mask0.copy()
+    sizes = (1, 64, 65, min(2304, w.n_tets))
+    for k in sizes:
+        ids = g.permutation(w.n_tets)[:k].astype(np.int32)
+        asm.apply_edits(*Sm.upload_frame(ids, 1 - mask[ids]))
+        mask[ids] = 1 - mask[ids]
+        got = asm.values().cpu().numpy()
+        assert np.array_equal(got.view(np.uint64), oracle.rebuild_workload(w, mask, pat).view(np.uint64)), k
+    times = asm.kernel_times()
+    launches = tuple(times[k][0] if k in times else 0 for k in ("frame", "edits", "touched"))
+    assert launches == ((4, 0, 0) if one else (0, 4, 4)), times
+    asm.full_rebuild()
+    assert np.array_equal(asm.values().cpu().numpy().view(np.uint64), got.view(np.uint64))
+    assert asm.audit() == {"values_differing": 0, "tets_differing": 0} and asm.status_sync() == Sm.STA_OK
+    asm.close()
