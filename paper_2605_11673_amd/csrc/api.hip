@@ -568,13 +568,27 @@ sta_status build_context(const double* x, int64_t n_nodes, const int32_t* tets, 
 
 namespace {
 
+// The launches of a frame of so many edits (or such a capacity).
+FrameRoute route_of(const sta_ctx* ctx, int64_t n)
+{
+    return frame_route(n, ctx->longest, ctx->fused != 0, ctx->barrier_spin != kBarrierSpinDefault);
+}
+
 // One JSON line per traced call (after the call's launches are queued).  With
 // trace_stats the stream is synchronised and the frame's statistics added.
 void trace_call(sta_ctx* ctx, const char* call, int64_t n, bool n_is_capacity, hipStream_t s)
 {
     if (!ctx->trace)
         return;
+    // how the frame ran; of a rebuild, how frames are asked to
     const char* mode = ctx->fused ? "one launch" : "two launches";
+    if (std::strncmp(call, "apply_edits", 11) == 0) {
+        const FrameRoute route = route_of(ctx, n);
+        const bool delta = std::strcmp(call, "apply_edits_delta") == 0;
+        mode = delta || route == FrameRoute::two ? "two launches"
+               : route == FrameRoute::once       ? "one launch"
+                                                 : "one launch with a grid barrier";
+    }
     std::fprintf(ctx->trace, "{\"seq\": %lld, \"call\": \"%s\", \"%s\": %lld, \"frame_mode\": \"%s\", "
                  "\"host_us\": %.1f",
                  (long long)ctx->trace_seq++, call, n_is_capacity ? "capacity" : "edits", (long long)n, mode,
@@ -591,12 +605,6 @@ void trace_call(sta_ctx* ctx, const char* call, int64_t n, bool n_is_capacity, h
     }
     std::fprintf(ctx->trace, "}\n");
     std::fflush(ctx->trace);
-}
-
-// The launches of a frame of so many edits (or such a capacity).
-FrameRoute route_of(const sta_ctx* ctx, int64_t n)
-{
-    return frame_route(n, ctx->longest, ctx->fused != 0, ctx->barrier_spin != kBarrierSpinDefault);
 }
 
 sta_status run_frame(sta_ctx* ctx, const int32_t* ids, const uint8_t* states, int32_t n_host, const int32_t* n_dev,
