@@ -362,8 +362,9 @@ sta_status sta_get_bucket_map(const sta_ctx* ctx, int which, int* qd3, int* qo2,
 /* Autotuner: times the full rebuild with and without rebuild_nt, and one
  * streaming frame (ids_dev / states_dev, device, n_edits; each timed
  * application is undone before the next) with fused 0 and with fused 1 under
- * grid caps, keeps the fastest of each and returns a text report in report
- * (may be NULL).  If the environment variable STA_TUNE_CACHE names a
+ * grid caps, keeps the fastest of each (by 1% at least) and returns a text
+ * report in report (may be NULL).  A frame that is one launch in either mode is
+ * timed once and fused and grid_cap stay as they are, also from the file.  If the environment variable STA_TUNE_CACHE names a
  * file, a previous result for the same mesh sizes and frame size is reused
  * from it and new results are appended.  Synchronises `stream`. */
 sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* states_dev, int64_t n_edits,

@@ -231,7 +231,17 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
         }
         return st;
     };
+    const Cfg saved = current(ctx);
+    // A list that takes the same launches in either mode says nothing about the modes: they stay as they
+    // are set (a choice among equals would be noise, and longer lists would run by it).
+    const bool limited = ctx->barrier_spin != kBarrierSpinDefault;
+    const bool modes_differ = frame_route(n_edits, ctx->longest, false, limited) !=
+                              frame_route(n_edits, ctx->longest, true, limited);
     if (cache && cache_lookup(cache, key, best)) {
+        if (!modes_differ) {
+            best.fused = saved.fused;
+            best.cap = saved.cap;
+        }
         const sta_status st = apply(ctx, best);
         std::snprintf(line, sizeof line, "cached %s: %s\n", cache, describe(best).c_str());
         rep += line;
@@ -278,7 +288,6 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
         cleanup();
         return tune_fail(ctx, STA_ENOMEM, "autotune workspace");
     }
-    const Cfg saved = current(ctx);
     const int saved_timing = ctx->timing;
     ctx->timing = false;
     sta_status st = STA_OK;
@@ -330,6 +339,9 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
         rep += line;
     }
 
+    // A setting is taken over the one before it only if it is at least 1% faster.
+    constexpr double kMargin = 0.99;
+
     // 1. rebuild: cached or non-temporal stores
     double best_t = 1e30;
     for (int nt = 0; nt <= 1 && st == STA_OK; ++nt) {
@@ -338,16 +350,22 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
         const double med = time_rebuild(c);
         std::snprintf(line, sizeof line, "rebuild  nt %d: %9.2f us\n", nt, med);
         rep += line;
-        if (med < best_t) {
+        if (med < kMargin * best_t) {
             best_t = med;
             best.nt = nt;
         }
     }
 
-    // 2. streaming frame: the library's choice for the size, or one launch with a grid barrier
+    // 2. streaming frame: two launches (fused 0), or one with a grid barrier
+    if (!modes_differ && st == STA_OK) {
+        const double med = time_frame(best);
+        std::snprintf(line, sizeof line, "frame    %9.2f us, the same launches in either mode: fused %d cap %d kept\n",
+                      med, best.fused, best.cap);
+        rep += line;
+    }
     best_t = 1e30;
     const int caps[3] = {0, 256, 1024};
-    for (int fused = 0; fused <= 1 && st == STA_OK; ++fused)
+    for (int fused = 0; fused <= 1 && modes_differ && st == STA_OK; ++fused)
         for (int ci = 0; ci < (fused ? 3 : 1) && st == STA_OK; ++ci) {
             Cfg c = best;
             c.fused = fused, c.cap = caps[ci];
@@ -355,7 +373,7 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
             std::snprintf(line, sizeof line, "frame    %s cap %4d: %9.2f us\n", fused ? "fused" : "default", caps[ci],
                           med);
             rep += line;
-            if (med < best_t) {
+            if (med < kMargin * best_t) {
                 best_t = med;
                 best.fused = fused;
                 best.cap = caps[ci];

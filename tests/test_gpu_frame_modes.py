@@ -91,3 +91,39 @@ def test_barrier_frame_errors_roll_back(k):
     got = asm.values().cpu().numpy()
     assert np.array_equal(got.view(np.uint64), oracle.rebuild_workload(w, mask, pat).view(np.uint64))
     asm.close()
+
+
+@pytest.mark.parametrize("cached", [False, True])
+def test_autotune_keeps_the_mode_that_it_cannot_tell(tmp_path, monkeypatch, cached):
+    """A frame of one launch in either mode leaves fused and the grid cap as they are, with a tuning file
+    that an earlier choice left or without."""
+    Sm = S()
+    w = W.make_fracture(seed=3, n=12, counts=[300, 50])
+    asm = Sm.Assembler.from_workload(w)
+    frame = Sm.upload_frame(*w.frames[0])
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("STA_TUNE_CACHE", str(path))
+    if cached:  # a file in which fused is 1 with the cap 256
+        first = asm.autotune(*frame, reps=2)
+        assert "chosen" in first
+        key, values = path.read_text().splitlines()[0].split("|")
+        v = values.split()
+        v[0], v[5] = "1", "256"
+        path.write_text(f"{key}| {' '.join(v)}\n")
+    for fused, cap in ((0, 0), (1, 77)):
+        asm.set_config(fused=fused, grid_cap=cap)
+        rep = asm.autotune(*frame, reps=2)
+        assert rep.startswith("cached") == (cached or (fused, cap) != (0, 0)), rep
+        cfg = asm.get_config()
+        assert (cfg["fused"], cfg["grid_cap"]) == (fused, cap), rep
+    asm.close()
+
+
+def test_autotune_tells_the_modes_of_a_long_list():
+    """2,305 edits: two launches and the grid barrier under its caps are timed, each by itself."""
+    Sm = S()
+    w = W.make_fracture(seed=3, n=12, counts=[10])
+    asm = Sm.Assembler.from_workload(w)
+    rep = asm.autotune(*Sm.upload_frame(np.arange(2305, dtype=np.int32), np.zeros(2305, np.uint8)), reps=2)
+    assert sum(l.startswith("frame ") for l in rep.splitlines()) == 4, rep
+    asm.close()
