@@ -1114,19 +1114,28 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
 
 // Statistics of a frame of k_once: the distinct blocks of its changed tets
 // (claimed through their stamps) and their incidences, diagonal and
-// off-diagonal, into count[0..3]; then the stamps are released.
+// off-diagonal, into count[0..3]; then the stamps are released.  Summed per
+// workgroup first: an atomic for each block on the four words took 400 us of the
+// call after 2,000 edits (515 -> 101 us).
 __global__ __launch_bounds__(kBlock) void k_once_stats(DevView v, int n, unsigned long long* count, int release)
 {
+    __shared__ unsigned long long s_count[4];
+    if (threadIdx.x < 4)
+        s_count[threadIdx.x] = 0ull;
+    __syncthreads();
     const int t = blockIdx.x * kBlock + threadIdx.x, i = t / kEditLanes, r = t % kEditLanes;
-    if (i >= n || r >= 10 || v.undo[i] == 0xFF)
-        return;
-    const BlockDesc d = load_desc(v.trec[reinterpret_cast<const int32_t*>(v.rec)[i]].desc + r);
-    if (release) {
-        v.bstamp[d.block] = 0u;
-    } else if (atomicExch(&v.bstamp[d.block], 1u) == 0u) {
-        atomicAdd(count + (d.kind == 0 ? 0 : 1), 1ull);
-        atomicAdd(count + (d.kind == 0 ? 2 : 3), (unsigned long long)(d.k1 - d.k0));
+    if (i < n && r < 10 && v.undo[i] != 0xFF) {
+        const BlockDesc d = load_desc(v.trec[reinterpret_cast<const int32_t*>(v.rec)[i]].desc + r);
+        if (release) {
+            v.bstamp[d.block] = 0u;
+        } else if (atomicExch(&v.bstamp[d.block], 1u) == 0u) {
+            atomicAdd(s_count + (d.kind == 0 ? 0 : 1), 1ull);
+            atomicAdd(s_count + (d.kind == 0 ? 2 : 3), (unsigned long long)(d.k1 - d.k0));
+        }
     }
+    __syncthreads();
+    if (threadIdx.x < 4 && s_count[threadIdx.x])
+        atomicAdd(count + threadIdx.x, s_count[threadIdx.x]);
 }
 
 // Audit: 1 if tet e's stored geometry differs in any bit from what the
