@@ -44,6 +44,7 @@ struct ProxyCtl {
     uint32_t last_trans; // transitions of the last frame (0 if it was rolled back)
     uint32_t changed;    // edits that changed a tet's state, running frame
     uint32_t last_changed;
+    uint32_t once_trans, once_changed;  // the same two of a frame of one launch, counted when asked for
 };
 
 struct ProxyView {
@@ -76,6 +77,7 @@ struct sta_proxy {
     int device = 0;
     int64_t n_nodes = 0, n_tets = 0, n_edges = 0, nnz = 0;
     bool once = true;  // frames of one launch (of up to kOnceMax edits)
+    bool once_used = false;  // one was launched or captured
     ProxyView v{};
     int32_t* colidx = nullptr;
     std::vector<void*> owned;
@@ -492,13 +494,17 @@ __global__ __launch_bounds__(kBlock) void k_proxy_records(ProxyView v, const int
     v.vinc[e2p[4 * (size_t)e + a]] = make_int4(e, column[0], column[1], column[2]);
 }
 
-// Statistics of a frame of k_proxy_once, in three steps over its edits: mark
-// the changed tets with their state before; count them, and for each the edges
-// whose activity changed and whose first changed tet it is; take the marks off.
-__global__ __launch_bounds__(kBlock) void k_proxy_stats(ProxyView v, int n, int step)
+// Statistics of the last frame, if it was k_proxy_once's, in three steps over its
+// edits: mark the changed tets with their state before; count them, and for each
+// the edges whose activity changed and whose first changed tet it is; take the
+// marks off.  The host reads the control words once, after all of it (31 us a call,
+// 71 with the frame's kind read first and the counters cleared by copies).
+__global__ __launch_bounds__(kBlock) void k_proxy_stats(ProxyView v, int step)
 {
     const int t = blockIdx.x * kBlock + threadIdx.x, i = t / kLanes, r = t % kLanes;
-    if (i >= n || v.undo[i] == 0xFF)
+    if (step == 0 && t == 0)
+        v.ctl->once_trans = v.ctl->once_changed = 0u;
+    if (!v.ctl->once || v.ctl->frame_err || i >= v.ctl->last_n || v.undo[i] == 0xFF)
         return;
     const int id = v.ids[i];
     if (step != 1) {
@@ -507,7 +513,7 @@ __global__ __launch_bounds__(kBlock) void k_proxy_stats(ProxyView v, int n, int 
         return;
     }
     if (r == 0)
-        atomicAdd(&v.ctl->changed, 1u);
+        atomicAdd(&v.ctl->once_changed, 1u);
     if (r >= 6)
         return;
     const int4 rec = v.erec[6 * (size_t)id + r];
@@ -521,7 +527,7 @@ __global__ __launch_bounds__(kBlock) void k_proxy_stats(ProxyView v, int n, int 
             first = x;
     }
     if (first == id && (before > 0) != (after > 0))
-        atomicAdd(&v.ctl->trans, 1u);
+        atomicAdd(&v.ctl->once_trans, 1u);
 }
 
 unsigned blocks(int64_t threads)
@@ -578,9 +584,12 @@ hipError_t launch_rebuild(const ProxyView& v, hipStream_t s)
     return e;
 }
 
-hipError_t launch_frame(const ProxyView& v, bool once, const int32_t* ids, const uint8_t* states, int32_t n_host,
-                        const int32_t* n_dev, hipStream_t s)
+hipError_t launch_frame(sta_proxy* p, const int32_t* ids, const uint8_t* states, int32_t n_host, const int32_t* n_dev,
+                        hipStream_t s)
 {
+    const ProxyView& v = p->v;
+    const bool once = p->once && n_host <= kOnceMax;
+    p->once_used |= once;
     const int log2 = table_log2(n_host);
 #define ONCE(E, S)                                                                                            \
     if (once && n_host <= 128 * E * S) {                                                                      \
@@ -768,7 +777,7 @@ extern "C" sta_status sta_proxy_apply_edits(sta_proxy* p, const int32_t* ids_dev
     if (n_edits > 0 && (!ids_dev || !states_dev))
         return pfail(p, STA_EINVAL, "NULL edit arrays");
     const hipError_t e =
-        launch_frame(p->v, p->once, ids_dev, states_dev, (int32_t)n_edits, nullptr, static_cast<hipStream_t>(stream));
+        launch_frame(p, ids_dev, states_dev, (int32_t)n_edits, nullptr, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? STA_OK : pfail(p, STA_EHIP, std::string("proxy frame: ") + hipGetErrorString(e));
 }
 
@@ -780,7 +789,7 @@ extern "C" sta_status sta_proxy_apply_edits_dev(sta_proxy* p, const int32_t* ids
     if (capacity < 1 || capacity > p->n_tets || !ids_dev || !states_dev || !n_dev)
         return pfail(p, STA_EINVAL, "capacity must be in [1, n_tets] and the device arrays non-NULL");
     const hipError_t e =
-        launch_frame(p->v, p->once, ids_dev, states_dev, (int32_t)capacity, n_dev, static_cast<hipStream_t>(stream));
+        launch_frame(p, ids_dev, states_dev, (int32_t)capacity, n_dev, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? STA_OK : pfail(p, STA_EHIP, std::string("proxy frame: ") + hipGetErrorString(e));
 }
 
@@ -858,28 +867,22 @@ extern "C" sta_status sta_proxy_last_frame_stats(sta_proxy* p, void* stream, int
 {
     if (!p || !out3)
         return STA_EINVAL;
-    hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    hipError_t e = hipSuccess;
+    for (int step = 0; step < 3 && p->once_used && e == hipSuccess; ++step) {
+        hipLaunchKernelGGL(k_proxy_stats, dim3(blocks((int64_t)kOnceMax * kLanes)), dim3(kBlock), 0, s, p->v, step);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
     ProxyCtl h{};
     if (e == hipSuccess)
         e = hipMemcpy(&h, p->v.ctl, sizeof h, hipMemcpyDeviceToHost);
     if (e != hipSuccess)
         return pfail(p, STA_EHIP, std::string("proxy stats: ") + hipGetErrorString(e));
     if (h.once) {
-        hipStream_t s = static_cast<hipStream_t>(stream);
-        uint32_t sums[2] = {0u, 0u};
-        const int n = h.frame_err ? 0 : h.last_n;
-        for (int step = 0; step < 3 && n > 0 && e == hipSuccess; ++step) {
-            hipLaunchKernelGGL(k_proxy_stats, dim3(blocks((int64_t)n * kLanes)), dim3(kBlock), 0, s, p->v, n, step);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e == hipSuccess) e = hipMemcpy(&h, p->v.ctl, sizeof h, hipMemcpyDeviceToHost);
-        if (e == hipSuccess) e = hipMemcpy(&p->v.ctl->trans, &sums[0], sizeof(uint32_t), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(&p->v.ctl->changed, &sums[1], sizeof(uint32_t), hipMemcpyHostToDevice);
-        if (e != hipSuccess)
-            return pfail(p, STA_EHIP, std::string("proxy stats: ") + hipGetErrorString(e));
-        h.last_trans = h.trans;
-        h.last_changed = h.changed;
+        h.last_trans = h.once_trans;
+        h.last_changed = h.once_changed;
     }
     out3[0] = h.last_n;
     out3[1] = h.last_changed;
