@@ -203,7 +203,7 @@ sta_status sta_last_frame_stats(sta_ctx* ctx, void* stream, int64_t* out, int n_
 /* A batch whose geometry records exceed 100 MB is rebuilt in groups of
  * consecutive meshes: each group counts one STA_KERNEL_ELEMENT launch and two
  * STA_KERNEL_REDUCE launches (the tiles of rows, then the rows of nodes too
- * large for a tile). */
+ * large for a tile; without any, the second runs only while kernels are timed). */
 #define STA_KERNEL_EDITS 2     /* two-launch frame, phase 1: validate, flip, claim */
 #define STA_KERNEL_TOUCHED 3   /* two-launch frame, phase 2: re-sum claimed blocks */
 #define STA_KERNEL_ADJOINT 4

@@ -705,10 +705,10 @@ sta_status sta_full_rebuild(sta_ctx* ctx, void* stream)
             e = timed(ctx, STA_KERNEL_ELEMENT, s, [&] { return launch_geometry(vt, s); }, true);
         if (e == hipSuccess)
             e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows(vr, nt, s); }, true);
-        // launched for every group, with or without large nodes, so that each group's row passes are
-        // the same two in the kernel times
+        // while kernels are timed it is launched with nothing to do too, so that each group's row passes
+        // are the same two in the times
         if (e == hipSuccess)
-            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows_big(vr, true, s); }, true);
+            e = timed(ctx, STA_KERNEL_REDUCE, s, [&] { return launch_rows_big(vr, ctx->timing, s); }, true);
     }
     if (e != hipSuccess)
         return hip_fail(ctx, e, "full_rebuild launch");

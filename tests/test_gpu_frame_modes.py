@@ -1,5 +1,6 @@
 """Which launches frames take, as the kernel times and the trace tell it, and the frame with a grid
 barrier where it is asked for: its errors undo what the first phase wrote."""
+import ctypes
 import json
 import os
 
@@ -127,3 +128,28 @@ def test_autotune_tells_the_modes_of_a_long_list():
     rep = asm.autotune(*Sm.upload_frame(np.arange(2305, dtype=np.int32), np.zeros(2305, np.uint8)), reps=2)
     assert sum(l.startswith("frame ") for l in rep.splitlines()) == 4, rep
     asm.close()
+
+
+def test_grouped_rebuild_launches_what_it_needs():
+    """A batch rebuilt in groups and without large nodes: two launches a group, three while timed."""
+    Sm = S()
+    ws = W.make_batch(seed=0)
+    b = Sm.Batch.from_workloads(ws)
+    b.enable_kernel_timing(True)
+    b.kernel_times()
+    b.full_rebuild()
+    times = b.kernel_times()
+    b.enable_kernel_timing(False)
+    groups = times["element"][0]
+    assert groups > 1 and times["reduce"][0] == 2 * groups
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    side = torch.cuda.Stream()
+    handle, graph, nodes = ctypes.c_void_p(side.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(handle, 2) == 0
+    b.full_rebuild(stream=side)
+    assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    assert nodes.value == 2 * groups, (nodes.value, groups)
+    b.close()
