@@ -1184,6 +1184,17 @@ __global__ __launch_bounds__(kBlock) void k_clear_stamps(DevView v)
         v.bstamp[i] = 0u;
 }
 
+// Every tet's block descriptors, 16 bytes a thread, once per context (filling them
+// in on the host and copying took 30 of the 228 ms that the building of 384,000 tets
+// took).
+__global__ __launch_bounds__(kBlock) void k_records(DevView v, int4* __restrict__ out)
+{
+    static_assert(sizeof(BlockDesc) == 32 && sizeof(TetRecord) == 320, "20 times 16 bytes");
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < 20 * (int64_t)v.n_tets)
+        out[i] = reinterpret_cast<const int4*>(v.desc + v.e2b[i / 2])[i % 2];
+}
+
 __global__ __launch_bounds__(kBlock) void k_set_params(int n_nodes, int n_tets, const double* __restrict__ x_aos,
                                                        const double* __restrict__ Ein, double* xs, double* ys,
                                                        double* zs, double* Eout)
@@ -1204,6 +1215,15 @@ inline unsigned blocks_for(int64_t threads)
 }
 
 }  // namespace
+
+hipError_t launch_records(const DevView& v, TetRecord* trec, hipStream_t s)
+{
+    if (v.n_tets == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_records, dim3(blocks_for(20 * (int64_t)v.n_tets)), dim3(kBlock), 0, s, v,
+                       reinterpret_cast<int4*>(trec));
+    return hipGetLastError();
+}
 
 hipError_t launch_geometry(const DevView& v, hipStream_t s)
 {

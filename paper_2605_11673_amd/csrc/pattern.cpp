@@ -39,18 +39,34 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
         if (did[i] == 0)
             did[i] = (int32_t)nd++;
 
-    // off-diagonal blocks: sorted unique (min, max) node pairs
-    std::vector<uint64_t> keys((size_t)m * 6);
+    // off-diagonal blocks: unique (min, max) node pairs in ascending order, the larger nodes of each
+    // smaller one sorted by themselves (one sort of all pairs took three times as long)
+    std::vector<int64_t> first((size_t)n + 1, 0);
+    auto smaller = [&](int64_t e, int p) { return std::min(tets[4 * e + kPairA[p]], tets[4 * e + kPairB[p]]); };
+    auto larger = [&](int64_t e, int p) { return std::max(tets[4 * e + kPairA[p]], tets[4 * e + kPairB[p]]); };
     for (int64_t e = 0; e < m; ++e)
-        for (int p = 0; p < 6; ++p) {
-            uint64_t a = (uint32_t)tets[4 * e + kPairA[p]], b = (uint32_t)tets[4 * e + kPairB[p]];
-            uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-            keys[6 * e + p] = (lo << 32) | hi;
-        }
-    std::vector<uint64_t> okeys(keys);
-    std::sort(okeys.begin(), okeys.end());
-    okeys.erase(std::unique(okeys.begin(), okeys.end()), okeys.end());
-    const int64_t no = (int64_t)okeys.size();
+        for (int p = 0; p < 6; ++p)
+            first[smaller(e, p) + 1]++;
+    for (int64_t i = 0; i < n; ++i)
+        first[i + 1] += first[i];
+    std::vector<int32_t> partner((size_t)m * 6);
+    {
+        std::vector<int64_t> fill(first.begin(), first.end() - 1);
+        for (int64_t e = 0; e < m; ++e)
+            for (int p = 0; p < 6; ++p)
+                partner[fill[smaller(e, p)]++] = larger(e, p);
+    }
+    int64_t no = 0;
+    for (int64_t i = 0; i < n; ++i) {  // unique ones to the front; first[i] becomes their begin
+        const auto b = partner.begin() + first[i], e = partner.begin() + first[i + 1];
+        std::sort(b, e);
+        const auto u = std::unique(b, e);
+        std::copy(b, u, partner.begin() + no);
+        first[i] = no;
+        no += u - b;
+    }
+    first[n] = no;
+    partner.resize((size_t)no);
     if (nd > INT32_MAX || no > INT32_MAX || 6 * m > INT32_MAX)
         return "mesh too large for 32-bit block indices";
 
@@ -64,7 +80,9 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
             dcount[b + 1]++;
         }
         for (int p = 0; p < 6; ++p) {
-            int32_t b = (int32_t)(std::lower_bound(okeys.begin(), okeys.end(), keys[6 * e + p]) - okeys.begin());
+            const int32_t i = smaller(e, p);
+            const int32_t b = (int32_t)(std::lower_bound(partner.begin() + first[i], partner.begin() + first[i + 1],
+                                                         larger(e, p)) - partner.begin());
             P.e2b[10 * e + 4 + p] = b;
             ocount[b + 1]++;
         }
@@ -100,10 +118,11 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
     std::vector<int64_t> deg(n + 1, 0);
     for (int64_t i = 0; i < n; ++i)
         deg[i + 1] = did[i] >= 0 ? 1 : 0;
-    for (uint64_t k : okeys) {
-        deg[(k >> 32) + 1]++;
-        deg[(k & 0xffffffffu) + 1]++;
-    }
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t b = first[i]; b < first[i + 1]; ++b) {
+            deg[i + 1]++;
+            deg[partner[b] + 1]++;
+        }
     std::vector<int64_t> aoff(n + 1, 0);
     for (int64_t i = 0; i < n; ++i)
         aoff[i + 1] = aoff[i] + deg[i + 1];
@@ -112,11 +131,11 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
     for (int64_t i = 0; i < n; ++i)
         if (did[i] >= 0)
             adj[afill[i]++] = (int32_t)i;
-    for (uint64_t k : okeys) {
-        int64_t i = (int64_t)(k >> 32), j = (int64_t)(k & 0xffffffffu);
-        adj[afill[i]++] = (int32_t)j;
-        adj[afill[j]++] = (int32_t)i;
-    }
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t b = first[i]; b < first[i + 1]; ++b) {
+            adj[afill[i]++] = partner[b];
+            adj[afill[partner[b]]++] = (int32_t)i;
+        }
     for (int64_t i = 0; i < n; ++i)
         std::sort(adj.begin() + aoff[i], adj.begin() + aoff[i + 1]);
 
@@ -155,8 +174,10 @@ std::string build_host_pattern(int64_t n, const int32_t* tets, int64_t m, HostPa
     }
     P.ometa.assign((size_t)no * 4, 0);
     P.opair.assign((size_t)no * 2, 0);
-    for (int64_t b = 0; b < no; ++b) {
-        const int64_t i = (int64_t)(okeys[b] >> 32), j = (int64_t)(okeys[b] & 0xffffffffu);
+    for (int64_t b = 0, i = 0; b < no; ++b) {
+        while (b >= first[i + 1])
+            ++i;
+        const int64_t j = partner[b];
         P.opair[2 * b + 0] = (int32_t)i;
         P.opair[2 * b + 1] = (int32_t)j;
         P.ometa[4 * b + 0] = (int32_t)(P.rowptr[bs * i] + bs * pos(i, j));

@@ -680,7 +680,7 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
     for (int64_t e = 0; e < n_tets; ++e)
         for (int a = 0; a < 4; ++a)
             e2p[4 * e + a] = P.e2p[10 * e + a];
-    int32_t *e2p_d = nullptr, *ndiag_d = nullptr, *dseg_d = nullptr;  // for the records only, freed below
+    int32_t *e2p_d = nullptr, *ndiag_d = nullptr, *dseg_d = nullptr;  // for the records only
     int32_t *t2e_d = nullptr, *eseg = nullptr, *einc = nullptr, *epos_d = nullptr, *enode = nullptr,
             *rowptr = nullptr, *ndpos_d = nullptr;
     const int64_t wg = n_tets > 0 ? blocks(n_tets * kLanes) : 1;
@@ -705,14 +705,15 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
     PALLOC(v.undo, n_tets)
     PALLOC(v.wg_err, wg)
     PALLOC(v.ctl, 1)
-    PALLOC(v.erec, n_tets * 6)
-    PALLOC(v.vrec, n_tets * 4)
-    PALLOC(v.vinc, n_tets * 4)
-    PALLOC(v.ids, kOnceMax)
-    const size_t kept = p->owned.size();
-    PALLOC(e2p_d, n_tets * 4)
-    PALLOC(ndiag_d, n_nodes)
-    PALLOC(dseg_d, P.dseg.size())
+    // what a frame of one launch needs, and what only the records do, in an allocation each; the second
+    // goes back unless it is small (a free took 15 of the 130 us of an eight-node mesh)
+    PALLOC(v.erec, n_tets * 14 + kOnceMax / 4)
+    v.vrec = v.erec + n_tets * 6;
+    v.vinc = v.vrec + n_tets * 4;
+    v.ids = reinterpret_cast<int32_t*>(v.vinc + n_tets * 4);
+    PALLOC(e2p_d, n_tets * 4 + n_nodes + (int64_t)P.dseg.size())
+    ndiag_d = e2p_d + n_tets * 4;
+    dseg_d = ndiag_d + n_nodes;
 #undef PALLOC
     if (e == hipSuccess) e = put(T, reinterpret_cast<const int4*>(tets), (size_t)n_tets, s);
     if (e == hipSuccess) e = put(v.mask, mask0, (size_t)n_tets, s);
@@ -747,8 +748,10 @@ extern "C" sta_status sta_proxy_build(const int32_t* tets, int64_t n_nodes, int6
         e = launch_rebuild(v, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    for (; e == hipSuccess && p->owned.size() > kept; p->owned.pop_back())
+    if (e == hipSuccess && n_tets > 65536) {
         e = hipFree(p->owned.back());
+        p->owned.pop_back();
+    }
     if (e != hipSuccess) {
         const std::string msg = std::string("proxy build: ") + hipGetErrorString(e);
         release(p);

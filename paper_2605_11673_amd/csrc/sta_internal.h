@@ -373,6 +373,7 @@ inline void launch_kernel(void (*k)(KArgs...), dim3 grid, dim3 block, uint32_t s
 }
 
 // Kernel launchers (assembly.hip).
+hipError_t launch_records(const DevView& v, TetRecord* trec, hipStream_t s);
 hipError_t launch_geometry(const DevView& v, hipStream_t s);
 hipError_t launch_rows(const DevView& v, bool nt, hipStream_t s);
 // The blocks of nodes too large for a tile; nothing to do: launched only if always is set.
