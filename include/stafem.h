@@ -450,7 +450,7 @@ void sta_destroy(sta_ctx* ctx);
  * eq. (7) and counting a changed tet's edges again give the same; values are
  * rewritten from them, and every frame leaves the state exactly equal to
  * sta_proxy_full_rebuild on the same mask.  A frame of up to 2,304 edits is
- * one launch if no vertex or edge of the mesh has many tets (about 80), any
+ * one launch if no vertex or edge of the mesh has many tets (about 100), any
  * other two.
  * Stream, error and threading rules as above.
  * ------------------------------------------------------------------------ */

@@ -33,11 +33,11 @@ inline FrameRoute frame_route(int64_t edits, int64_t longest, bool fused, bool p
 // over their tets, eight lanes each, and its vertices' active edges over theirs,
 // 16 lanes each, 64 columns of the row at a time: so many rounds, each a chain of
 // two round trips.  Two launches change counts and degrees by atomics whatever
-// there is around.  Meshes of more rounds than this take them for every frame:
-// two frames of 30 to 1,000 edits took, by one launch, 10 to 11 us at 2 to 5
-// rounds, 13 at 10, 16 to 20 at 12 to 14, 24 at 18, 34 at 27, and 13 ms at the
-// 12,000 of a vertex of 5,000 tets; by two, 13 to 16 us at any.
-constexpr int64_t kProxyOnceRounds = 10;
+// there is around.  Meshes of more rounds than this take them for every frame: two
+// frames of 30 to 1,000 edits took, by one launch / two, 10 to 11 / 16 us at 2 to 5
+// rounds, 16 to 20 / 16 to 24 at 12 to 14, 24 / 22 at 18, 34 / 22 at 27, and 13,000 / 21
+// at the 12,000 of a vertex of 5,000 tets.
+constexpr int64_t kProxyOnceRounds = 14;
 
 inline int64_t proxy_edge_rounds(int64_t tets)
 {

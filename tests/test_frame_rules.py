@@ -44,9 +44,9 @@ def test_proxy_frames_of_one_launch(rules):
         of_vertex, of_edge, columns = incidence(w)
         assert rules.vertex_rounds(ll(of_vertex), ll(columns)) <= rules.proxy_most()
         assert rules.edge_rounds(ll(of_edge)) <= rules.proxy_most()
-    for tets, columns in ((200, 122), (5000, 2602), (160, 65), (1, 641)):
+    for tets, columns in ((200, 122), (5000, 2602), (160, 65), (1, 1025)):
         assert rules.vertex_rounds(ll(tets), ll(columns)) > rules.proxy_most(), tets
-    assert rules.edge_rounds(ll(100)) > rules.proxy_most()
+    assert rules.edge_rounds(ll(121)) > rules.proxy_most()
 
 
 ONCE, TWO, BARRIER = 0, 1, 2

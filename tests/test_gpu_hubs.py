@@ -39,9 +39,9 @@ def seconds(f, reps=5):
     return best
 
 
-@pytest.mark.parametrize("n", [4, 7, 50])
+@pytest.mark.parametrize("n", [4, 7, 8, 50])
 def test_proxy_frames_at_an_apex(n):
-    """32 tets (one launch), 98 and 5,000 (two launches; in one, 7 and 13 ms a frame at 5,000)."""
+    """32 and 98 tets (one launch), 128 and 5,000 (two launches; in one, 7 and 13 ms a frame at 5,000)."""
     from oracle import proxy as P
     Sm = S()
     w = cone(n)
