@@ -200,7 +200,7 @@ sta_status sta_last_frame_stats(sta_ctx* ctx, void* stream, int64_t* out, int n_
  * file that cannot be opened for appending fails the build with STA_EINVAL. */
 #define STA_KERNEL_ELEMENT 0   /* element geometry (rebuild) */
 #define STA_KERNEL_REDUCE 1    /* sums of every row (rebuild) */
-/* A batch whose geometry records exceed 100 MB is rebuilt in groups of
+/* A batch whose geometry records exceed 170 MB is rebuilt in groups of
  * consecutive meshes: each group counts one STA_KERNEL_ELEMENT launch and two
  * STA_KERNEL_REDUCE launches (the tiles of rows, then the rows of nodes too
  * large for a tile; without any, the second runs only while kernels are timed). */
@@ -375,7 +375,7 @@ sta_status sta_autotune(sta_ctx* ctx, const int32_t* ids_dev, const uint8_t* sta
  * tet t is global tet tet_off[j] + t).  Arguments as for sta_build_pattern,
  * per mesh (arrays of k host pointers and sizes); nu, rho, dt shared.  A
  * frame over all meshes is one sta_apply_edits / sta_apply_edits_dev call
- * with global tet ids; with fused = 1 it is one launch, and with
+ * with global tet ids (its launches as sta_set_config says), and with
  * sta_apply_edits_dev it can be captured once into a HIP graph. */
 sta_status sta_batch_build(int k, const double* const* x, const int64_t* n_nodes, const int32_t* const* tets,
                            const int64_t* n_tets, const double* const* E, double nu, double rho, double dt,
@@ -392,8 +392,8 @@ sta_status sta_batch_offsets(const sta_ctx* ctx, int* k, int64_t* node_off, int6
  * kernel launched back to back on one stream, out4[1] = nanoseconds per
  * dependent global load over a 256 MB working set, out4[2] = the same over
  * an L2-resident 1 MB set, out4[3] = nanoseconds per dependent returning
- * device-scope atomic.  A streaming frame is two launches with a few
- * dependent round trips each, so these numbers bound its latency. */
+ * device-scope atomic.  A streaming frame is one launch or two, each a few
+ * dependent round trips, so these numbers bound its latency. */
 sta_status sta_latency_probe(void* stream, double* out4);
 
 /* Measured streaming bandwidth of this GPU's HBM, in GB/s (1e9 B/s), on
