@@ -7,9 +7,9 @@ Headline workload: jittered Kuhn cube 40^3 x 6 (384,000 candidate tets,
 dt 1e-2.  One step = the 24-frame Voronoi fracture stream (50..2000
 deletions per frame) followed by the 24 frames that reinsert the deleted
 tets in reverse order (merge), so every step starts and ends at the
-initial mask.  Edit lists are resident in HBM before timing.  The slot
-mapping and frame mode are chosen by the library's autotuner on the peak
-frame before timing.  The timed region replays the whole step captured as
+initial mask.  Edit lists are resident in HBM before timing.  The rebuild's
+stores (and the mode of frames of more edits than one launch takes) are chosen
+by the library's autotuner on the peak frame before timing.  The timed region replays the whole step captured as
 one HIP graph.
 
 Printed: one compact JSON line on stdout (the last line, a few KB): touched
