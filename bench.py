@@ -9,8 +9,8 @@ deletions per frame) followed by the 24 frames that reinsert the deleted
 tets in reverse order (merge), so every step starts and ends at the
 initial mask.  Edit lists are resident in HBM before timing.  The rebuild's
 stores (and the mode of frames of more edits than one launch takes) are chosen
-by the library's autotuner on the peak frame before timing.  The timed region replays the whole step captured as
-one HIP graph.
+by the library's autotuner on the peak frame before timing.  The timed region
+replays the whole step captured as one HIP graph.
 
 Printed: one compact JSON line on stdout (the last line, a few KB): touched
 slots/s over the timed steps, per-frame streaming and rebuild times (both
@@ -390,8 +390,9 @@ class Stream:
         eb = bytes_element(self.n_tets, self.n_nodes)
         n_e, ms_e = kt.get("element", (0, 0.0))
         n_r, ms_r = kt.get("reduce", (0, 0.0))
-        # a batch too large for the Infinity Cache is rebuilt in mesh groups (one element and two
-        # reduce launches per group): rates and counted bytes are per rebuild, all groups together
+        # a large batch is rebuilt in mesh groups, a geometry and a row launch each (and, while
+        # kernels are timed, one for large nodes, also with none): rates and counted bytes are
+        # per rebuild, all groups together
         rebuilds = len(self.frames_host) * reps
         per_e, per_r = n_e / max(rebuilds, 1), n_r / max(rebuilds, 1)
         te = load_traffic(self.workload, ["k_geometry"])
@@ -399,7 +400,7 @@ class Stream:
         el = roofline("k_geometry", eb * rebuilds, ms_e * 1e-3, rebuilds,
                       traffic=None if te is None else round(te * per_e, 1))
         re = roofline("k_rows", rb * rebuilds, ms_r * 1e-3, rebuilds,
-                      traffic=None if tr is None else round(tr * per_r, 1))
+                      traffic=None if tr is None else round(tr * per_e, 1))
         el["launches_per_rebuild"], re["launches_per_rebuild"] = per_e, per_r
         return {"element": el, "reduce": re,
                 "rebuild_us_mean": round((ms_e + ms_r) * 1e3 / max(rebuilds, 1), 3),
@@ -1050,8 +1051,8 @@ def connectivity_section(torch, stafem, w, frames, args):
         if adj == "vertex" or n_pairs:
             nb = bytes_connectivity_pass(w.n_tets, w.n_nodes, n_pairs if adj == "face" else 0)
             # the first kernel runs once per rebuild: the unit of the counted bytes
-            ks = (["k_cc_seed", "k_cc_shortcut", "k_cc_hook", "k_cc_finish"] if adj == "vertex"
-                  else ["k_ccf_init", "k_ccf_seed", "k_ccf_hook", "k_cc_shortcut", "k_ccf_label"])
+            ks = (["k_cc_init", "k_cc_windows", "k_cc_roots", "k_cc_label"] if adj == "vertex"
+                  else ["k_ccf_windows", "k_ccf_cross", "k_cc_roots", "k_ccf_label"])
             out[adj]["roofline"] = roofline(f"connectivity ({adj}), one-pass lower bound", nb, med * 1e-6, 1,
                                             traffic=load_traffic(f"connectivity_{adj}", ks, per=ks[0]))
         if adj in oracle_s:
