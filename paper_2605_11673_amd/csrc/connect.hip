@@ -9,7 +9,8 @@
 // triple are found once on the host and kept on the device.
 //
 // Both are a union-find over parent pointers f.  Each workgroup first merges
-// one window of tets, consecutive or near each other, in LDS and keeps one root per set it finds.
+// one window of tets, consecutive or near each other, in LDS and keeps one root
+// per set it finds.
 // Vertex: every vertex of the window then takes its set's root as its own,
 // exchanging it for that of another window that holds the vertex: those two
 // roots are to be united.  Face: the pairs that cross windows name two roots

@@ -8,13 +8,14 @@ namespace sta {
 
 // A frame of the elasticity operator.  One launch re-sums the ten blocks of every
 // edited tet, each as often as edits share it, from lists of up to kFrameOnceEdits
-// (one launch / two at 1, 300, 1,700, 2,304 random edits of 384,000 tets: 3.7 / 6.1, 5.0 /
-// 8.9, 8.9 / 12.0, 13.1 / 13.3 us).  Two launches sum every block once, which counts
-// where a vertex has many tets: 5,000 of them, 64, 768, 2,304 edits 115 / 108, 152 / 116,
-// 257 / 133 us; 2,450, 768 77 / 65; but 968, 768 33 / 35; 512, 300 17 / 21.  So meshes whose longest list of a vertex's tets is past kFrameOnceTets take
-// two.  A grid barrier between two phases of one launch costs more than a launch
-// (15 to 23 us a frame) and is taken for longer lists if the caller asks for it, and for
-// any if they limit its polls.
+// (one launch / two at 1, 300, 1,700, 2,304 random edits of 384,000 tets: 3.7 / 6.1,
+// 5.0 / 8.9, 8.9 / 12.0, 13.1 / 13.3 us).  Two launches sum every block once, which
+// counts where a vertex has many tets: 5,000 of them, 64, 768, 2,304 edits 115 / 108,
+// 152 / 116, 257 / 133 us; 2,450, 768 77 / 65; but 968, 768 33 / 35; 512, 300 17 / 21.
+// So meshes whose longest list of a vertex's tets is past kFrameOnceTets take two.
+// A grid barrier between two phases of one launch costs more than a launch
+// (15 to 23 us a frame) and is taken for longer lists if the caller asks for it, and
+// for any if they limit its polls.
 constexpr int32_t kFrameOnceEdits = 2304;
 constexpr int64_t kFrameOnceTets = 1024;
 
