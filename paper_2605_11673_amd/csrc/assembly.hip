@@ -1116,7 +1116,7 @@ __global__ __launch_bounds__(64 * kUnits * kEdits) void k_once(DevView v, const 
 // (claimed through their stamps) and their incidences, diagonal and
 // off-diagonal, into count[0..3]; then the stamps are released.  Summed per
 // workgroup first: an atomic for each block on the four words took 400 us of the
-// call after 2,000 edits (515 -> 101 us).
+// call after 2,000 edits (515 -> 61 us).
 __global__ __launch_bounds__(kBlock) void k_once_stats(DevView v, int n, unsigned long long* count, int release)
 {
     __shared__ unsigned long long s_count[4];
